@@ -81,9 +81,7 @@ enum {
                                 neighbours (0 and 360 degrees are one direction,
                                 Sec. 3.1 spectrum grid); a Gaussian acts at each
                                 pixel through the image of its mean (shifted by a
-                                whole number of grid widths) nearest to it. Lists
-                                are built by binning when a query's tiles form one
-                                segment (at most 256), else by key sorting         */
+                                whole number of grid widths) nearest to it          */
     SWF_DETERMINISTIC = 1 << 7 /* swf_render_backward: gradients summed in a fixed
                                 order (bitwise the same from run to run) instead of
                                 by atomic adds; takes 128 bytes per list entry of
@@ -428,9 +426,9 @@ swf_status swf_last_device_status(swf_ctx *ctx, swf_device_status *out);
  * summed milliseconds and the number of launches since the last reset:
  * stage 0 tx features, 1 MLP+deform+preprocess, 2 scan, 3 emit keys,
  * 4 radix sort, 5 tile ranges, 6 blend. Without SWF_FULL_SORT the lists are
- * built by binning instead: stage 2 is then the per-block tile histograms and
- * their scan, stage 3 is empty and stage 4 the stable placement of the pair
- * indices (same lists as the sort). swf_render_backward adds stage 7 blend
+ * built by binning instead: stage 2 is then the per-block tile counts and
+ * their prefixes, stage 4 the stable placement of the pair indices with the tile
+ * ranges (same lists as the sort), and stages 3 and 5 are empty. swf_render_backward adds stage 7 blend
  * backward, 8 preprocess backward and 9 MLP backward (layer GEMMs, masks,
  * column sums, the positional-encoding chain), besides the forward stages of
  * the forward pass it repeats.

@@ -63,7 +63,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     uint16_t* wb = (uint16_t*)(tmp + n_cs);      // BF16 weights: hidden layers 1.., output, then dy
     float* wt = (float*)(((uintptr_t)(tmp + n_cs + n_wb) + 15) & ~(uintptr_t)15);  // FP32 W^T, 16-byte aligned
     float* fmean = (float*)w.fmean.ptr, *ftx = (float*)w.ftx.ptr, *qs = (float*)w.qs.ptr;
-    launch_tx_features(d, tx, B, qs, st, ftx);
+    launch_tx_features(d, tx, B, qs, nullptr, st, ftx);
     launch_mean_features_f32(d, fmean, st);
     uint16_t* wl[8] = {};
     uint16_t* dyb = nullptr;

@@ -132,22 +132,23 @@ __device__ __forceinline__ int mix_find(const MixQuery* qs, int B, int v, F fiel
 }
 
 // mixed.hip
-void launch_mix_tx_features(const MixBatch& m, const float* tx, float* qs, hipStream_t st);
+// status (may be null; also of the other TX launches): kStatusWords words set to zero
+constexpr int kStatusWords = 8;
+void launch_mix_tx_features(const MixBatch& m, const float* tx, float* qs, uint32_t* status, hipStream_t st);
 void launch_mix_static(const MixBatch& m, int64_t pair_cap, const Grid& tile, const Records& r, hipStream_t st);
 void launch_mix_clear_tail(const MixBatch& m, int64_t pair_cap, const Records& r, hipStream_t st);
 // Lists of a mixed batch by binning (sort.hip), with the geometry of its largest query (max_n pairs, max_tiles
 // tiles) for every query; ranges over its global tiles.
+struct BinCount;
 bool mix_bin_fits(int B, int max_tiles);
-size_t mix_bin_hist_entries(int B, int max_n, int max_tiles);
-size_t mix_bin_scan_entries(int B, int max_n, int max_tiles);
+size_t mix_bin_entries(int B, int max_n, int max_tiles);
 void launch_mix_bin_hist(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
                          unsigned long long* cull, hipStream_t st);
-void launch_mix_bin_offsets(const MixBatch& m, int max_n, int max_tiles, uint32_t* bins, void* scan_scratch,
-                            uint64_t* total, hipStream_t st);
-void launch_mix_bin_scatter(const MixBatch& m, int max_n, int max_tiles, const Records& r, const uint32_t* bins,
-                            const uint64_t* n_dev, uint32_t* vals, hipStream_t st);
-void launch_mix_bin_ranges(const MixBatch& m, int max_n, int max_tiles, const uint32_t* bins, const uint64_t* total,
-                           const uint64_t* n_dev, int64_t tile_cap, uint2* ranges, hipStream_t st);
+void launch_mix_bin_offsets(const MixBatch& m, int max_n, int max_tiles, uint32_t* bins, const BinCount& c,
+                            hipStream_t st);
+void launch_mix_bin_place(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
+                          const uint64_t* total, const uint64_t* n_dev, uint32_t* vals, uint2* ranges,
+                          hipStream_t st);
 void launch_mix_emit_keys(const MixBatch& m, const Records& r, const uint32_t* offsets, int64_t pair_cap,
                           uint64_t capacity, uint32_t* keys, uint32_t* vals, uint32_t* status,
                           unsigned long long* cull, hipStream_t st);
@@ -165,7 +166,7 @@ void launch_mix_mlp_fp32(const MixBatch& m, const float* qs, const Records& r, i
 
 // paper.hip
 void launch_paper_centers(const DevScene& d, hipStream_t st);
-void launch_paper_tx(const DevScene& d, const float* tx, int B, float* txf, hipStream_t st);
+void launch_paper_tx(const DevScene& d, const float* tx, int B, float* txf, uint32_t* status, hipStream_t st);
 void launch_paper_static(const DevScene& d, int B, const Grid& g, const Records& r, hipStream_t st);
 void launch_paper_mlp(const DevScene& d, const float* txf, int B, const Grid& g, const Records& r, float* delta_out,
                       hipStream_t st);
@@ -174,7 +175,7 @@ void launch_gmm_blend(const uint2* ranges, const uint32_t* vals, const Records& 
                       float* chan, hipStream_t st);
 
 // pe_mlp.hip
-void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, hipStream_t st,
+void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, uint32_t* status, hipStream_t st,
                         float* feat_out = nullptr);
 // FP32 backward of a 256 x 256 layer on the FP32 matrix cores: wt = W^T packed fragment-major (65536 floats, from
 // W [256][256] row-major); out [P][256] = (dz [P][256] W) masked by act [P][256] > 0; with bpart (non-null,
@@ -223,23 +224,26 @@ void launch_tile_ranges(const void* keys, int key_bytes, int64_t n, int64_t n_gt
 void launch_clear_u32(uint32_t* p, int n, hipStream_t st);
 // n_eff = total if total <= cap else 0; *status (if not null) is set to 1 if total > cap, else to 0
 void launch_effective_count(const uint64_t* total, uint64_t cap, uint64_t* n_eff, uint32_t* status, hipStream_t st);
-// Binning path: per-block histograms of each tile segment of a query, their
-// column prefixes and the scanned tile totals (`bins` holds both), then the
-// stable placement of pair indices into per-tile lists and the tile ranges.
-bool bin_fits(int B, int N, const Grid& g);  // the segment grid fits one launch
-size_t bin_hist_entries(int B, int N, const Grid& g);  // uint32 entries of `bins`
-size_t bin_scan_entries(int B, int N, const Grid& g);  // entries the tile-total scan runs over
+// Binning path: per-block tile counts of a query, their prefixes and the tiles'
+// list positions (`bins` holds both), then the stable placement of pair indices
+// into per-tile lists and the tile ranges.
+bool bin_fits(int B, int N, const Grid& g);  // the tile grid and batch fit the binning path
+size_t bin_entries(int B, int N, const Grid& g);  // uint32 entries of `bins`
 // cull (may be null): two device counters that receive the number of culled
 // pairs, non-finite / degenerate and off the grid (also launch_emit_keys)
 void launch_bin_hist(const Records& r, int B, int N, const Grid& g, uint32_t* bins, unsigned long long* cull,
                      hipStream_t st);
-// column prefixes in place, tile starts, and the number of list entries in *total
-void launch_bin_offsets(int B, int N, const Grid& g, uint32_t* bins, void* scan_scratch, uint64_t* total,
-                        hipStream_t st);
-void launch_bin_scatter(const Records& r, int B, int N, const Grid& g, const uint32_t* bins,
-                        const uint64_t* n_dev, uint32_t* vals, hipStream_t st);
-void launch_bin_ranges(const uint32_t* bins, int B, int N, const Grid& g, const uint64_t* total,
-                       const uint64_t* n_dev, uint2* ranges, hipStream_t st);
+struct BinCount {  // where the number of list entries goes
+    uint64_t* total;   // device
+    uint64_t cap;      // 0, or the lists' fixed capacity: then n_eff and status are set
+    uint64_t* n_eff;   // total if it fits cap, else 0
+    uint32_t* status;  // 1 if total > cap, else 0
+    uint32_t* done;    // zero at launch
+    uint64_t* host;    // pinned host copy of the total (may be null)
+};
+void launch_bin_offsets(int B, int N, const Grid& g, uint32_t* bins, const BinCount& c, hipStream_t st);
+void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* bins, const uint64_t* total,
+                      const uint64_t* n_dev, uint32_t* vals, uint2* ranges, hipStream_t st);
 
 // backward.hip
 // det_part (may be null): per (list entry, wave) sums, 32 floats per entry of the lists, zeroed by the caller;

@@ -21,10 +21,11 @@ namespace {
 constexpr int kThreads = 256;
 
 __global__ __launch_bounds__(256) void mix_tx_kernel(MixBatch m, const float* __restrict__ tx,
-                                                     float* __restrict__ qs) {
+                                                     float* __restrict__ qs, uint32_t* __restrict__ status) {
     __shared__ float feat[kTxFeat];
     const int b = blockIdx.x;
     const int t = threadIdx.x;
+    if (status && b == 0 && t < kStatusWords) status[t] = 0u;
     const MixScene& s = m.scenes[m.queries[b].scene];
     if (t < 3 * (kTxBands + 1)) {
         const int d = t % 3;
@@ -152,8 +153,8 @@ void launch_mix_clear_tail(const MixBatch& m, int64_t pair_cap, const Records& r
     if (pair_cap > 0) mix_clear_tail_kernel<<<(unsigned)((pair_cap + 255) / 256), 256, 0, st>>>(m, pair_cap, r);
 }
 
-void launch_mix_tx_features(const MixBatch& m, const float* tx, float* qs, hipStream_t st) {
-    if (m.B > 0) mix_tx_kernel<<<m.B, 256, 0, st>>>(m, tx, qs);
+void launch_mix_tx_features(const MixBatch& m, const float* tx, float* qs, uint32_t* status, hipStream_t st) {
+    if (m.B > 0) mix_tx_kernel<<<m.B, 256, 0, st>>>(m, tx, qs, status);
 }
 
 void launch_mix_static(const MixBatch& m, int64_t pair_cap, const Grid& g, const Records& r, hipStream_t st) {

@@ -136,9 +136,11 @@ __global__ __launch_bounds__(256) void paper_centers_kernel(const float* __restr
 
 // gamma(s_hat) with 6 bands per query: 39 features, padded to 48.
 __global__ __launch_bounds__(64) void paper_tx_kernel(const float* __restrict__ tx, float lox, float loy, float loz,
-                                                      float rx, float ry, float rz, float* __restrict__ out) {
+                                                      float rx, float ry, float rz, float* __restrict__ out,
+                                                      uint32_t* __restrict__ status) {
     const int b = blockIdx.x;
     const int t = threadIdx.x;
+    if (status && b == 0 && t < kStatusWords) status[t] = 0u;
     float* o = out + (size_t)b * kPaperFeatStride;
     if (t < 3 * (kPaperTxBands + 1)) {
         const int dd = t % 3;
@@ -384,9 +386,9 @@ void launch_paper_centers(const DevScene& d, hipStream_t st) {
         paper_centers_kernel<<<(d.n + 255) / 256, 256, 0, st>>>(d.pcx, d.pcy, d.n, d.W, d.H, d.pcen, d.pfeat);
 }
 
-void launch_paper_tx(const DevScene& d, const float* tx, int B, float* txf, hipStream_t st) {
+void launch_paper_tx(const DevScene& d, const float* tx, int B, float* txf, uint32_t* status, hipStream_t st) {
     paper_tx_kernel<<<B, 64, 0, st>>>(tx, d.room_lo[0], d.room_lo[1], d.room_lo[2], d.room_hi[0] - d.room_lo[0],
-                                      d.room_hi[1] - d.room_lo[1], d.room_hi[2] - d.room_lo[2], txf);
+                                      d.room_hi[1] - d.room_lo[1], d.room_hi[2] - d.room_lo[2], txf, status);
 }
 
 static PaperArgs paper_args(const DevScene& d, int B, const Grid& g, const Records& r) {

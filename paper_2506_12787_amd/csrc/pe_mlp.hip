@@ -20,10 +20,12 @@ __global__ __launch_bounds__(256) void tx_features_kernel(const float* __restric
                                                           const float* __restrict__ b1, int hidden, int in_dim,
                                                           float lox, float loy, float loz, float rx, float ry,
                                                           float rz, float* __restrict__ qs,
-                                                          float* __restrict__ feat_out) {
+                                                          float* __restrict__ feat_out,
+                                                          uint32_t* __restrict__ status) {
     __shared__ float feat[kTxFeat];
     const int b = blockIdx.x;
     const int t = threadIdx.x;
+    if (status && b == 0 && t < kStatusWords) status[t] = 0u;
     if (t < 3 * (kTxBands + 1)) {
         const int d = t % 3;
         const int k = t / 3;  // 0: identity, 1..L: band k-1
@@ -339,10 +341,11 @@ void launch_gather_params(float* const* src, const uint32_t* perm, int n, float*
     if (n > 0) gather_params_kernel<<<(n + 255) / 256, 256, 0, st>>>(p, perm, n);
 }
 
-void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, hipStream_t st, float* feat_out) {
+void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, uint32_t* status, hipStream_t st,
+                        float* feat_out) {
     const float rx = s.room_hi[0] - s.room_lo[0], ry = s.room_hi[1] - s.room_lo[1], rz = s.room_hi[2] - s.room_lo[2];
     tx_features_kernel<<<B, 256, 0, st>>>(tx, s.w[0], s.b[0], s.hidden, s.in_dim, s.room_lo[0], s.room_lo[1],
-                                          s.room_lo[2], rx, ry, rz, qs, feat_out);
+                                          s.room_lo[2], rx, ry, rz, qs, feat_out, status);
 }
 
 void launch_mlp_fp32(const DevScene& s, const float* qs, int B, const Grid& g, bool paper_mask, const Records& r,

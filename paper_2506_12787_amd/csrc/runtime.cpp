@@ -562,9 +562,9 @@ swf_status Ctx::release_scene(int id) {
     return SWF_OK;
 }
 
-// Enqueue preprocess (+ MLP) for B queries into the workspace records.
-swf_status Ctx::enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int B, int flags, const Grid& g, float* delta_sorted,
-                                   hipStream_t st) {
+// Enqueue preprocess (+ MLP) for B queries into the workspace records; status (may be null): status words to clear.
+swf_status Ctx::enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int B, int flags, const Grid& g,
+                                   float* delta_sorted, uint32_t* status, hipStream_t st) {
     ++w.seq;  // the records (and the lists built from them) are about to change
     const DevScene& d = sc->d;
     const bool deform = !(flags & SWF_NO_DEFORM);
@@ -591,8 +591,9 @@ swf_status Ctx::enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int
             if ((s = w.qs.reserve(this, (size_t)B * kPaperFeatStride * sizeof(float), st))) return s;
         }
         stage_begin(SWF_STAGE_MLP, st);
+        if (!deform && status) launch_clear_u32(status, kStatusWords, st);
         if (deform) {
-            launch_paper_tx(d, tx, B, (float*)w.qs.ptr, st);
+            launch_paper_tx(d, tx, B, (float*)w.qs.ptr, status, st);
             launch_paper_mlp(d, (const float*)w.qs.ptr, B, g, w.rec, delta_sorted, st);
         } else {
             launch_paper_static(d, B, g, w.rec, st);
@@ -605,7 +606,7 @@ swf_status Ctx::enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int
         if (!tx) return fail(SWF_E_INVALID, "tx is NULL");
         if ((s = w.qs.reserve(this, (size_t)B * d.hidden * sizeof(float), st))) return s;
         stage_begin(SWF_STAGE_TX, st);
-        launch_tx_features(d, tx, B, (float*)w.qs.ptr, st);
+        launch_tx_features(d, tx, B, (float*)w.qs.ptr, status, st);
         stage_end(st);
         stage_begin(SWF_STAGE_MLP, st);
         if (flags & SWF_MLP_BF16)
@@ -621,6 +622,7 @@ swf_status Ctx::enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int
         stage_end(st);
     } else {
         stage_begin(SWF_STAGE_MLP, st);
+        if (status) launch_clear_u32(status, kStatusWords, st);
         launch_preprocess_static(d, B, g, w.rec, st);
         stage_end(st);
     }
@@ -646,15 +648,13 @@ swf_status Ctx::forward_lists(Workspace& w, int sid, const float* tx, int B, int
     if ((uint64_t)B * g.tiles >= (1ull << 31)) return fail(SWF_E_INVALID, "batch * tiles too large");
     w.last.valid = false;
     w.last.stream = st;
-    // the status word and the culled-pair counters start at zero for every render
-    launch_clear_u32(w.status_dev, 8, st);
-    swf_status s = enqueue_preprocess(w, sc, tx, B, flags, g, nullptr, st);
+    // the status words and the culled-pair counters start at zero for every render
+    swf_status s = enqueue_preprocess(w, sc, tx, B, flags, g, nullptr, w.status_dev, st);
     if (s) return s;
     const bool full = (flags & SWF_FULL_SORT) != 0;
     const int64_t n_gt = (int64_t)B * g.tiles;
     if ((s = w.ranges.reserve(this, (size_t)n_gt * sizeof(uint2), st))) return s;
-    // binning unless the full 64-bit sort is asked for (or the segment grid would exceed the launch limit, or a
-    // periodic azimuth spans more than one segment: the multi-segment placement enumerates unwrapped rectangles)
+    // binning unless the full 64-bit sort is asked for or the grid has more tiles than a placement block holds
     if (!full && bin_fits(B, d.n, g)) {
         const bool spec = key_cap == 0 && spec_cap > 0 && spec_used;
         s = lists_binned(w, d, B, g, st, spec ? spec_cap : key_cap, spec);
@@ -674,11 +674,13 @@ swf_status Ctx::forward_lists(Workspace& w, int sid, const float* tx, int B, int
     return hip(hipGetLastError(), "forward launch");
 }
 
+static const char kTooManyEntries[] =
+    "more list entries than one launch sequence takes (max_list_entries, at most 2^32 - 1)";
+
 // Key count after an exclusive scan whose 64-bit total is in w.total_dev:
 // read back (key_cap == 0), or kept on the device as the effective count
 // (total if it fits key_cap, else 0 with the overflow bit set).
-swf_status Ctx::key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64_t& nk, const uint64_t*& n_dev,
-                          bool readback) {
+swf_status Ctx::key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64_t& nk, const uint64_t*& n_dev) {
     nk = key_cap;
     n_dev = nullptr;
     if (key_cap == 0) {
@@ -692,42 +694,55 @@ swf_status Ctx::key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64
         uint64_t* n_eff = w.total_dev + 1;  // the word after the scan total
         launch_effective_count(w.total_dev, key_cap, n_eff, w.status_dev, st);  // also sets the status word
         n_dev = n_eff;
-        if (readback) {
-            swf_status s;
-            if ((s = hip(hipMemcpyAsync(w.total_host, w.total_dev, sizeof(uint64_t), hipMemcpyDeviceToHost, st),
-                         "total D2H")))
-                return s;
-            if ((s = hip(hipEventRecord(w.total_ev, st), "total event"))) return s;
-        }
     }
-    if (nk > max_list_entries)
-        return fail(SWF_E_OVERFLOW, "more list entries than one launch sequence takes (max_list_entries, at most "
-                                    "2^32 - 1)");
-    return SWF_OK;
+    return nk > max_list_entries ? fail(SWF_E_OVERFLOW, kTooManyEntries) : SWF_OK;
 }
 
-// Lists by binning (per tile segment of a query): tile histograms per block of
-// pairs, their scan, stable placement, ranges. Same lists as the full sort.
+// Count targets of a binned list build and the key count after it: read back (key_cap == 0: one wait), or kept on the
+// device as the effective count; with `readback` the host copy is complete once total_ev has passed.
+BinCount Ctx::bin_count(Workspace& w, uint64_t key_cap, bool readback) {
+    BinCount c;
+    c.total = w.total_dev;
+    c.cap = key_cap;
+    c.n_eff = w.total_dev + 1;
+    c.status = w.status_dev;
+    c.done = w.status_dev + 1;
+    c.host = key_cap == 0 || readback ? w.total_host : nullptr;
+    return c;
+}
+
+swf_status Ctx::bin_key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64_t& nk, const uint64_t*& n_dev,
+                              bool readback) {
+    swf_status s = hip(hipGetLastError(), "list offsets");
+    if (s) return s;
+    nk = key_cap;
+    n_dev = key_cap ? w.total_dev + 1 : nullptr;
+    if (key_cap == 0) {
+        if ((s = hip(hipStreamSynchronize(st), "stream sync"))) return s;
+        nk = *w.total_host;
+    } else if (readback) {
+        if ((s = hip(hipEventRecord(w.total_ev, st), "total event"))) return s;
+    }
+    return nk > max_list_entries ? fail(SWF_E_OVERFLOW, kTooManyEntries) : SWF_OK;
+}
+
+// Lists by binning (per query): tile counts per block of pairs, their prefixes and the tiles' positions, stable
+// placement with the tile ranges. Same lists as the full sort.
 swf_status Ctx::lists_binned(Workspace& w, const DevScene& d, int B, const Grid& g, hipStream_t st,
                              uint64_t key_cap, bool readback) {
     swf_status s;
-    const int64_t nh = (int64_t)bin_hist_entries(B, d.n, g);
-    if ((s = w.bins.reserve(this, (size_t)nh * sizeof(uint32_t) + 16, st))) return s;
-    if ((s = w.scan.reserve(this, scan_scratch_bytes((int64_t)bin_scan_entries(B, d.n, g)) + 64, st))) return s;
+    if ((s = w.bins.reserve(this, bin_entries(B, d.n, g) * sizeof(uint32_t) + 16, st))) return s;
     uint32_t* bins = (uint32_t*)w.bins.ptr;
     stage_begin(SWF_STAGE_SCAN, st);
     launch_bin_hist(w.rec, B, d.n, g, bins, w.cull_dev, st);
-    launch_bin_offsets(B, d.n, g, bins, w.scan.ptr, w.total_dev, st);
+    launch_bin_offsets(B, d.n, g, bins, bin_count(w, key_cap, readback), st);
     stage_end(st);
     uint64_t nk;
     const uint64_t* n_dev;
-    if ((s = key_count(w, st, key_cap, nk, n_dev, readback))) return s;
+    if ((s = bin_key_count(w, st, key_cap, nk, n_dev, readback))) return s;
     if ((s = w.vals.reserve(this, nk * 4 + 16, st))) return s;
     stage_begin(SWF_STAGE_SORT, st);
-    launch_bin_scatter(w.rec, B, d.n, g, bins, n_dev, (uint32_t*)w.vals.ptr, st);
-    stage_end(st);
-    stage_begin(SWF_STAGE_RANGES, st);
-    launch_bin_ranges(bins, B, d.n, g, w.total_dev, n_dev, (uint2*)w.ranges.ptr, st);
+    launch_bin_place(w.rec, B, d.n, g, bins, w.total_dev, n_dev, (uint32_t*)w.vals.ptr, (uint2*)w.ranges.ptr, st);
     stage_end(st);
     w.last.n_keys = nk;
     w.last.full = false;
@@ -1006,11 +1021,11 @@ swf_status Ctx::enqueue_mixed(Workspace& w, const MixPlan& p, const float* tx, i
     w.rec.count = (uint32_t*)w.count.ptr;
     w.last.valid = false;
     w.last.stream = st;
-    launch_clear_u32(w.status_dev, 8, st);
     stage_begin(SWF_STAGE_MLP, st);
+    if (!deform) launch_clear_u32(w.status_dev, kStatusWords, st);
     if (deform) {
         if ((s = w.qs.reserve(this, (size_t)p.B_cap * 256 * sizeof(float), st))) return s;
-        launch_mix_tx_features(mb, tx, (float*)w.qs.ptr, st);
+        launch_mix_tx_features(mb, tx, (float*)w.qs.ptr, w.status_dev, st);
         if (flags & SWF_MLP_BF16)
             launch_mix_mlp_bf16(mb, (const float*)w.qs.ptr, w.rec, st, (flags & SWF_PAPER_DEFORM) != 0, false);
         else
@@ -1028,24 +1043,19 @@ swf_status Ctx::enqueue_mixed(Workspace& w, const MixPlan& p, const float* tx, i
     uint32_t* svals = nullptr;
     if ((s = w.ranges.reserve(this, (size_t)tile_cap * sizeof(uint2) + 16, st))) return s;
     if (binned) {
-        // tile histograms per block of pairs of each query, their scan, stable placement, ranges
-        const int64_t nh = (int64_t)mix_bin_hist_entries(k.B_cap, k.bin_n, k.bin_tiles);
-        const int64_t ns = (int64_t)mix_bin_scan_entries(k.B_cap, k.bin_n, k.bin_tiles);
-        if ((s = w.bins.reserve(this, (size_t)nh * sizeof(uint32_t) + 16, st))) return s;
-        if ((s = w.scan.reserve(this, scan_scratch_bytes(ns) + 64, st))) return s;
+        // tile counts per block of pairs of each query, their prefixes, stable placement and ranges
+        if ((s = w.bins.reserve(this, mix_bin_entries(k.B_cap, k.bin_n, k.bin_tiles) * sizeof(uint32_t) + 16, st)))
+            return s;
         uint32_t* bins = (uint32_t*)w.bins.ptr;
         stage_begin(SWF_STAGE_SCAN, st);
         launch_mix_bin_hist(mb, k.bin_n, k.bin_tiles, w.rec, bins, w.cull_dev, st);
-        launch_mix_bin_offsets(mb, k.bin_n, k.bin_tiles, bins, w.scan.ptr, w.total_dev, st);
+        launch_mix_bin_offsets(mb, k.bin_n, k.bin_tiles, bins, bin_count(w, k.key_cap, false), st);
         stage_end(st);
-        if ((s = key_count(w, st, k.key_cap, nk, n_dev))) return s;
+        if ((s = bin_key_count(w, st, k.key_cap, nk, n_dev, false))) return s;
         if ((s = w.vals.reserve(this, nk * 4 + 16, st))) return s;
         stage_begin(SWF_STAGE_SORT, st);
-        launch_mix_bin_scatter(mb, k.bin_n, k.bin_tiles, w.rec, bins, n_dev, (uint32_t*)w.vals.ptr, st);
-        stage_end(st);
-        stage_begin(SWF_STAGE_RANGES, st);
-        launch_mix_bin_ranges(mb, k.bin_n, k.bin_tiles, bins, w.total_dev, n_dev, tile_cap, (uint2*)w.ranges.ptr,
-                              st);
+        launch_mix_bin_place(mb, k.bin_n, k.bin_tiles, w.rec, bins, w.total_dev, n_dev, (uint32_t*)w.vals.ptr,
+                             (uint2*)w.ranges.ptr, st);
         stage_end(st);
         svals = (uint32_t*)w.vals.ptr;
     } else {
@@ -1283,7 +1293,7 @@ swf_status swf_debug_deform(swf_ctx* h, int32_t scene_id, const float* tx, int32
     if (d.kind == 1) {
         // paper-model scene: 5 residuals per pair, already in id order
         const Grid g = make_grid(d.H, d.W, 16);
-        swf_status s = c->enqueue_preprocess(c->ws, sc, tx, batch, flags, g, delta, st);
+        swf_status s = c->enqueue_preprocess(c->ws, sc, tx, batch, flags, g, delta, nullptr, st);
         c->ws.last.valid = false;
         return s ? s : c->hip(hipGetLastError(), "debug deform");
     }
@@ -1291,7 +1301,7 @@ swf_status swf_debug_deform(swf_ctx* h, int32_t scene_id, const float* tx, int32
     swf_status s = c->ws.delta.reserve(c, cnt * sizeof(float) + 16, st);
     if (s) return s;
     const Grid g = make_grid(d.H, d.W, (flags & SWF_TILE8) ? 8 : 16);
-    s = c->enqueue_preprocess(c->ws, sc, tx, batch, flags, g, (float*)c->ws.delta.ptr, st);
+    s = c->enqueue_preprocess(c->ws, sc, tx, batch, flags, g, (float*)c->ws.delta.ptr, nullptr, st);
     if (s) return s;
     launch_permute_delta((const float*)c->ws.delta.ptr, d.perm, batch, d.n, delta, st);
     c->ws.last.valid = false;

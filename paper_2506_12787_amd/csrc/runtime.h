@@ -161,7 +161,7 @@ struct Ctx {
     swf_status pack_mlp(Scene* s, const swf_mlp* mlp, bool dev, bool alloc);
     swf_status update_scene(int id, const swf_gaussians* g, const swf_mlp* mlp, bool dev, hipStream_t st);
     swf_status enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int B, int flags, const Grid& g,
-                                  float* delta_sorted, hipStream_t st);
+                                  float* delta_sorted, uint32_t* status, hipStream_t st);
     // key_cap == 0: size the key buffers from the scan total (one 8-byte
     // device-to-host read and a stream wait). key_cap > 0: fixed capacity, no
     // host synchronisation (graph-capturable); overflow sets the status word.
@@ -171,8 +171,10 @@ struct Ctx {
     swf_status forward_lists(Workspace& w, int sid, const float* tx, int B, int flags, hipStream_t st,
                              uint64_t key_cap = 0, uint64_t spec_cap = 0, bool* spec_used = nullptr, int rH = 0,
                              int rW = 0);
-    swf_status key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64_t& nk, const uint64_t*& n_dev,
-                         bool readback = false);
+    swf_status key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64_t& nk, const uint64_t*& n_dev);
+    BinCount bin_count(Workspace& w, uint64_t key_cap, bool readback);
+    swf_status bin_key_count(Workspace& w, hipStream_t st, uint64_t key_cap, uint64_t& nk, const uint64_t*& n_dev,
+                             bool readback);
     swf_status lists_binned(Workspace& w, const DevScene& d, int B, const Grid& g, hipStream_t st, uint64_t key_cap,
                             bool readback = false);
     swf_status lists_sorted(Workspace& w, const DevScene& d, int B, const Grid& g, bool full, hipStream_t st,

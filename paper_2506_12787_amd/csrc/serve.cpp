@@ -159,7 +159,7 @@ int64_t round_cap(int64_t x, int64_t lo) {
 uint64_t estimate_mixed_bytes(const MixCaps& k) {
     const uint64_t raw = (uint64_t)k.pair_cap * 56 + k.key_cap * 16 + (uint64_t)k.tile_cap * 8 +
                          (uint64_t)k.outs * 4 + (uint64_t)k.B_cap * (256 * 4 + 1024) + (uint64_t)k.pair_cap / 64 +
-                         mix_bin_hist_entries(k.B_cap, k.bin_n, k.bin_tiles) * 4 + (1u << 20);
+                         mix_bin_entries(k.B_cap, k.bin_n, k.bin_tiles) * 4 + (1u << 20);
     return raw + raw / 4 + 64 * 256;
 }
 
@@ -172,7 +172,7 @@ uint64_t estimate_bytes(const DevScene& d, int bucket, uint64_t key_cap) {
     const uint64_t pairs = (uint64_t)bucket * d.n;
     const uint64_t tiles = (uint64_t)bucket * ((d.W + 15) / 16) * ((d.H + 15) / 16);
     // binning histogram bounded with the finer (8-pixel) tiling
-    const uint64_t bins = bin_hist_entries(bucket, d.n, make_grid(d.H, d.W, 8)) * 4;
+    const uint64_t bins = bin_entries(bucket, d.n, make_grid(d.H, d.W, 8)) * 4;
     const uint64_t raw = pairs * 56 + key_cap * 16 + tiles * 8 + (uint64_t)bucket * ((uint64_t)d.H * d.W * 4 + 1024) +
                          (uint64_t)bucket * 256 * 4 + bins + (1u << 20);
     return raw + raw / 4 + 64 * 256;

@@ -365,79 +365,81 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(const K* __rest
 
 // ---- binning: per-query stable counting sort by tile -----------------------
 // Pairs are stored in (query, depth) order and a pair covers a tile at most
-// once, so the list of a tile is the pairs covering it in pair order. A query's
-// tiles are split into S segments of 2^db tiles (db = 8 with at most 256 tiles
-// per query, one segment; else 9); every query is binned by a stable counting
-// pass per segment, which gives exactly the order of the full (tile, depth)
-// sort without materialising keys in memory.
-//   bin_hist:    block (j, q) histograms the tiles covered by pairs
-//                [j * pb, (j + 1) * pb) of query q, for every segment s, into
-//                its own row: hist[((q * S + s) * nbq + j) * 2^db + tile - 2^db s]
-//   bin_colscan: per column (q, s, tile) the exclusive prefix over the blocks,
-//                in place, and the column total; an exclusive scan of the totals
-//                in (query, tile) order gives every tile's first list position
-//                (`starts`, stored after the histogram) and the entry count. A
-//                block's first position in a tile's list is the tile's start
-//                plus the block's column prefix.
-//   bin_place:   (one segment) the block places its pairs batch by batch: each
-//                key sets its pair's bit in a per-tile mask of the batch, and
-//                its rank in the tile's list is the number of the batch's pairs
-//                below its own in that mask
-//   bin_scatter: (several segments) the block, segment by segment, ranks its
-//                keys stably with wave64 ballots over the db digit bits
-//   bin_ranges:  tile (q, t) spans [start(q, t), start(q, t + 1))
-// A periodic azimuth (wrapped rectangles, tx1 < tx0: columns tx0 .. TW - 1,
-// then 0 .. tx1) is binned when a query has one segment.
+// once, so the list of a tile is the pairs covering it in pair order: the order
+// of the full (tile, depth) sort, without keys in memory.
+//   bin_hist:    block (j, q) counts, for every tile, the pairs
+//                [j * pb, (j + 1) * pb) of query q that cover it, into its own
+//                row: hist[(q * nbq + j) * stride + tile]
+//   bin_offsets: per tile the exclusive prefix over the blocks, in place, the
+//                tiles' first list positions and the entry count
+//   bin_place:   block (j, q) writes its pairs into the tiles' lists; block
+//                (0, q) also the tile ranges of query q
+// A periodic azimuth has wrapped rectangles (tx1 < tx0: columns tx0 .. TW - 1,
+// then 0 .. tx1).
 struct BinGeom {
-    int N, TW, tiles, db, S, pb, nbq;  // pairs per query, tile grid, digit bits, segments, pairs/block, blocks/query
+    int N, TW, TH, tiles;  // pairs per query and its tile grid (mixed batches: of the largest query; TW, TH unused)
+    int stride;            // tiles per query rounded up to whole waves
+    int pb, nbq;           // pairs per block, blocks per query
+    int cap;               // most pairs in a placement wave's row list and segment list
 };
 
-constexpr int kWideDb = 9;       // digit bits when a query has more than 256 tiles (segments of 512)
-constexpr int kMaxTiles = 4096;           // tiles per query the binning path takes
+constexpr int kMaxTiles = 4096;   // tiles per query the binning path takes
+constexpr int kColChunk = 256;    // (query, tile) columns per workgroup of bin_offsets
+constexpr int kPlaceWaves = 12;   // most waves of a placement block
+constexpr int kSegCols = 8;       // tiles per column segment of the placement
 
-BinGeom bin_geom(int N, const Grid& g) {
+// Blocks of 1024 pairs and lists of 640 up to 256 tiles (a row of a 90 x 360 grid meets ~430 of the 1024), of 2048
+// and 512 beyond. Measured for the placement, us: 6.4M pairs at 90 x 360: 1024 / 640 109, 1024 / 512 118, 2048 158,
+// 512 127; 32M pairs at 360 x 1440: 2048 / 512 1613, 4096 1899, 1024 2365, 2048 / 640 2629. What decides is how many
+// waves the lists leave room for in LDS (24 per CU at the values taken), then how full the segment lists are.
+// Halved (to 256 at least) while the batch has fewer than two blocks per compute unit: one query of 100k pairs is
+// placed in 98 blocks at 1024 pairs, in 391 at 256.
+BinGeom bin_geom(int64_t B, int N, int TW, int TH, int tiles) {
     BinGeom b;
     b.N = N;
-    b.TW = g.TW;
-    b.tiles = g.tiles;
-    b.db = g.tiles <= 256 ? 8 : kWideDb;
-    b.S = std::max(1, (g.tiles + (1 << b.db) - 1) >> b.db);
-    b.pb = b.S == 1 ? 1024 : 8192;  // larger blocks keep the (S x 256 x blocks) histogram small
+    b.TW = TW;
+    b.TH = TH;
+    b.tiles = tiles;
+    b.stride = std::max(64, (tiles + 63) & ~63);
+    b.pb = tiles <= 256 ? 1024 : 2048;
+    while (b.pb > 256 && B * ((N + b.pb - 1) / b.pb) < 512) b.pb /= 2;
     b.nbq = std::max(1, (N + b.pb - 1) / b.pb);
+    b.cap = std::min(b.pb, tiles <= 256 ? 640 : 512);
     return b;
 }
 
-// Every tile of a pair's rectangle (rows top to bottom, columns from tx0, a
-// wrapped rectangle continuing at column 0): calls f(tile).
-template <typename F>
-__device__ __forceinline__ void for_rect_tiles(uint2 r, int TW, F&& f) {
-    const int tx0 = r.x & 0xffff, tx1 = r.x >> 16, ty0 = r.y & 0xffff, ty1 = r.y >> 16;
-    const int w = tx1 >= tx0 ? tx1 - tx0 + 1 : TW - tx0 + tx1 + 1;
-    for (int ty = ty0; ty <= ty1; ++ty)
-        for (int k = 0; k < w; ++k) {
-            const int col = tx0 + k < TW ? tx0 + k : tx0 + k - TW;
-            f((uint32_t)(ty * TW + col));
-        }
+// The bins buffer. Column e = q * stride + tile; chunk e / 256.
+struct BinBufs {
+    unsigned long long* ctot;  // list entries of a chunk of columns
+    uint32_t* cbase;           // first list position of the chunk
+    uint32_t* lstart;          // [B][stride] first list position of a column relative to its chunk
+    uint32_t* hist;            // [B][nbq][stride]
+};
+
+int64_t bin_chunks(int64_t B, const BinGeom& G) { return (B * G.stride + kColChunk - 1) / kColChunk; }
+
+size_t bin_words(int64_t B, const BinGeom& G) {
+    const size_t ch = ((size_t)bin_chunks(B, G) + 1) & ~(size_t)1;
+    return 3 * ch + (size_t)B * G.stride * (1 + (size_t)G.nbq);
 }
 
-__device__ __forceinline__ uint32_t seg_count(uint2 r, int TW, int t0, int seg) {
-    const int tx0 = r.x & 0xffff, tx1 = r.x >> 16, ty0 = r.y & 0xffff, ty1 = r.y >> 16;
-    if (ty1 * TW + tx1 < t0 || ty0 * TW + tx0 >= t0 + seg) return 0;
-    uint32_t c = 0;
-    for (int ty = ty0; ty <= ty1; ++ty) {
-        const int a = max(ty * TW + tx0, t0), b = min(ty * TW + tx1, t0 + seg - 1);
-        c += b >= a ? (uint32_t)(b - a + 1) : 0u;
-    }
-    return c;
+BinBufs bin_bufs(uint32_t* bins, int64_t B, const BinGeom& G) {
+    const size_t ch = ((size_t)bin_chunks(B, G) + 1) & ~(size_t)1;
+    BinBufs b;
+    b.ctot = reinterpret_cast<unsigned long long*>(bins);
+    b.cbase = bins + 2 * ch;
+    b.lstart = bins + 3 * ch;
+    b.hist = b.lstart + (size_t)B * G.stride;
+    return b;
 }
 
 // A query's pairs and tile grid for the binning kernels: uniform over a
 // single-scene batch (G), from the batch's tables for a mixed one, whose
-// geometry G (segments, block size, blocks per query) covers its largest
-// query: a smaller query leaves its extra blocks and segments empty.
+// geometry G (row stride, block size, blocks per query) covers its largest
+// query: a smaller query leaves its extra blocks and tiles empty.
 struct BinQuery {
-    int N, TW, tiles, S;
-    size_t row0;
+    int N, TW, TH, tiles;
+    size_t row0, tile0;  // first pair record, first global tile
 };
 
 template <bool kMix>
@@ -449,453 +451,358 @@ __device__ __forceinline__ BinQuery bin_query(const BinGeom& G, const MixBatch& 
         b.N = e.pair_base - a.pair_base;  // 0 for the padding queries of a capacity-sized batch
         b.tiles = e.tile_base - a.tile_base;
         b.TW = mix.scenes[a.scene].TW;
-        b.S = (b.tiles + (1 << G.db) - 1) >> G.db;
+        b.TH = b.tiles ? mix.scenes[a.scene].TH : 0;
         b.row0 = (size_t)a.pair_base;
+        b.tile0 = (size_t)a.tile_base;
     } else {
         b.N = G.N;
         b.tiles = G.tiles;
         b.TW = G.TW;
-        b.S = G.S;
+        b.TH = G.TH;
         b.row0 = (size_t)q * G.N;
+        b.tile0 = (size_t)q * G.tiles;
     }
     return b;
 }
 
-// Tile histogram of one block of pairs of one query, for every tile segment, in
-// the block's own row: hist[((q * S + segment) * nbq + block) * 2^db + tile % 2^db].
-// With one segment the counts are kept per wave (less atomic contention).
-template <bool kMix = false>
+// Tile counts of one block of pairs of one query. A rectangle adds one to every
+// tile it covers, which is the two-dimensional running sum of +1 / -1 at its
+// four corners: four LDS atomics per pair (eight for a wrapped rectangle)
+// whatever its size, then one pass down the columns and a wave scan along each
+// row. An atomic per covered tile instead (7 tiles per pair at 90 x 360, 20 at
+// 180 x 720, every wave as long as its largest rectangle) took 44 us for 6.4M
+// pairs at 90 x 360 and 140 us for 0.8M pairs at 180 x 720.
+constexpr int kHistCells = kMaxTiles + 600;  // (TH + 1) (TW + 1) for TH TW <= kMaxTiles and TH, TW <= 512
+
+template <bool kMix>
 __global__ __launch_bounds__(kThreads) void bin_hist_kernel(const uint2* __restrict__ rect,
                                                             const uint32_t* __restrict__ count, BinGeom G,
                                                             uint32_t* __restrict__ hist,
-                                                            unsigned long long* __restrict__ cull,
-                                                            MixBatch mix = MixBatch{}) {
-    __shared__ uint32_t h[kMaxTiles + 1024];  // S segments of 2^db tiles: at most kMaxTiles + 2^db - 1
+                                                            unsigned long long* __restrict__ cull, MixBatch mix) {
+    __shared__ int h[kHistCells];
     __shared__ uint32_t nculled[2];
-    const int kSegTiles = 1 << G.db;
-    const bool one = G.S == 1;
-    const int n = one ? kWaves * kSegTiles : G.S * kSegTiles;
-    for (int i = threadIdx.x; i < n; i += kThreads) h[i] = 0;
-    if (threadIdx.x < 2) nculled[threadIdx.x] = 0;
-    __syncthreads();
-    uint32_t* hw = one ? h + (threadIdx.x >> 6) * kSegTiles : h;
     const int j = blockIdx.x, q = blockIdx.y;
     const BinQuery Q = bin_query<kMix>(G, mix, q);
+    const int pitch = Q.TW + 1;
+    for (int i = threadIdx.x; i < (Q.TH + 1) * pitch; i += kThreads) h[i] = 0;
+    if (threadIdx.x < 2) nculled[threadIdx.x] = 0;
+    __syncthreads();
     const int p_beg = j * G.pb, p_end = min(p_beg + G.pb, Q.N);
-    const size_t row0 = Q.row0;
     uint32_t nf = 0, og = 0;  // culled pairs seen by this thread, by reason
     for (int p = p_beg + (int)threadIdx.x; p < p_end; p += kThreads) {
-        const uint2 r = rect[row0 + p];
-        if (count[row0 + p] == 0) {
+        const uint2 r = rect[Q.row0 + p];
+        if (count[Q.row0 + p] == 0) {
             nf += r.y == kCullNonFinite;
             og += r.y == kCullOffGrid;
             continue;
         }
-        for_rect_tiles(r, Q.TW, [&](uint32_t t) { atomicAdd(&hw[t], 1u); });
+        const int tx0 = r.x & 0xffff, tx1 = r.x >> 16;
+        int* top = h + (int)(r.y & 0xffff) * pitch;
+        int* bot = h + ((int)(r.y >> 16) + 1) * pitch;
+        atomicAdd(&top[tx0], 1);
+        atomicAdd(&bot[tx0], -1);
+        atomicAdd(&top[tx1 + 1], -1);
+        atomicAdd(&bot[tx1 + 1], 1);
+        if (tx1 < tx0) {  // wrapped: [0, tx1] and [tx0, TW)
+            atomicAdd(&top[0], 1);
+            atomicAdd(&bot[0], -1);
+        }
     }
     if (nf) atomicAdd(&nculled[0], nf);
     if (og) atomicAdd(&nculled[1], og);
     __syncthreads();
     if (cull && threadIdx.x < 2 && nculled[threadIdx.x]) atomicAdd(&cull[threadIdx.x], (unsigned long long)nculled[threadIdx.x]);
-    for (int i = threadIdx.x; i < G.S * kSegTiles; i += kThreads) {
-        uint32_t v = h[i];
-        if (one)
-#pragma unroll
-            for (int k = 1; k < kWaves; ++k) v += h[k * kSegTiles + i];
-        const int sg = i / kSegTiles, d = i - sg * kSegTiles;
-        hist[(((size_t)(q * G.S + sg) * G.nbq + j) << G.db) + d] = v;
+    for (int c = threadIdx.x; c < Q.TW; c += kThreads) {
+        int run = 0;
+        for (int y = 0; y < Q.TH; ++y) {
+            run += h[y * pitch + c];
+            h[y * pitch + c] = run;
+        }
     }
+    __syncthreads();
+    uint32_t* row = hist + ((size_t)q * G.nbq + j) * G.stride;
+    for (int y = threadIdx.x >> 6; y < Q.TH; y += kWaves) {
+        int carry = 0;
+        for (int c0 = 0; c0 < Q.TW; c0 += 64) {
+            const int c = c0 + (int)lane_id();
+            const int v = wave_inclusive_scan<int>(c < Q.TW ? h[y * pitch + c] : 0) + carry;
+            if (c < Q.TW) row[y * Q.TW + c] = (uint32_t)v;
+            carry = __shfl(v, 63, 64);
+        }
+    }
+    for (int t = Q.tiles + (int)threadIdx.x; t < G.stride; t += kThreads) row[t] = 0u;
 }
 
-// Column (query-segment, tile) i of the histogram: the exclusive prefix over
-// its nbq blocks, in place, and the column total. Consecutive threads take
-// consecutive tiles, so every access is coalesced.
-__global__ __launch_bounds__(kThreads) void bin_colscan_kernel(uint32_t* __restrict__ hist, int64_t cols, int nbq,
-                                                               int db, uint32_t* __restrict__ totals) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= cols) return;
-    const int64_t qs = i >> db, d = i & ((1 << db) - 1);
-    uint32_t* col = hist + ((qs * nbq) << db) + d;
-    const size_t stride = (size_t)1 << db;
-    uint32_t run = 0;
-    int j = 0;
-    for (; j + 8 <= nbq; j += 8) {
-        uint32_t v[8];
+// Block c: the columns [256 c, 256 c + 256) of the (query, tile) pairs. Per
+// column the exclusive prefix over the query's nbq blocks, in place (the rows
+// are cut into blockDim / 256 groups, summed, then rewritten; up to kHeldRows
+// rows of a group stay in registers between), the columns' starts within the
+// chunk and the chunk's total. The last block to finish (a counter the caller
+// zeroed) scans the chunk totals into the chunks' first positions and writes
+// the entry count, the count usable at a fixed capacity (total if it fits, else
+// 0 with the overflow bit of the status word), and the count to the host. One
+// launch; column prefixes, scan and count in five took 27 us per call at any
+// size below 16k tiles.
+struct BinTotals {
+    unsigned long long* total;  // entries of all lists
+    uint64_t cap;               // 0: the host sizes the lists from the count
+    unsigned long long* n_eff;
+    uint32_t* status;
+    uint32_t* done;             // zero at launch
+    unsigned long long* host;   // pinned host copy of the total, or null
+};
+
+constexpr int kHeldRows = 32;
+
+__global__ __launch_bounds__(1024) void bin_offsets_kernel(BinBufs bb, BinGeom G, int64_t cols, BinTotals T) {
+    __shared__ uint32_t part[4][kColChunk];
+    __shared__ uint64_t wsum[16];
+    __shared__ int last;
+    const int groups = (int)blockDim.x / kColChunk;
+    const int col = (int)threadIdx.x & (kColChunk - 1), grp = (int)threadIdx.x / kColChunk;
+    const int w = (int)threadIdx.x >> 6, W = (int)blockDim.x >> 6;
+    const int64_t e = (int64_t)blockIdx.x * kColChunk + col;
+    const bool in = e < cols;
+    const int q = (int)((uint32_t)min(e, cols - 1) / (uint32_t)G.stride);
+    const int R = (G.nbq + groups - 1) / groups;
+    const int r0 = grp * R, r1 = in ? min(r0 + R, G.nbq) : r0;
+    const size_t ld = (size_t)G.stride;
+    uint32_t* h = bb.hist + (size_t)q * G.nbq * ld + (size_t)(e - (int64_t)q * G.stride);
+    const bool held = R <= kHeldRows;
+    uint32_t v[kHeldRows];
+    uint32_t sum = 0;
+    if (held) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = col[(size_t)(j + k) * stride];
+        for (int k = 0; k < kHeldRows; ++k) v[k] = r0 + k < r1 ? h[(size_t)(r0 + k) * ld] : 0u;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            col[(size_t)(j + k) * stride] = run;
+        for (int k = 0; k < kHeldRows; ++k) sum += v[k];
+    } else {
+        for (int r = r0; r < r1; r += kHeldRows) {
+#pragma unroll
+            for (int k = 0; k < kHeldRows; ++k) v[k] = r + k < r1 ? h[(size_t)(r + k) * ld] : 0u;
+#pragma unroll
+            for (int k = 0; k < kHeldRows; ++k) sum += v[k];
+        }
+    }
+    part[grp][col] = sum;
+    __syncthreads();
+    uint32_t run = 0, tot = 0;
+    for (int g = 0; g < groups; ++g) {
+        if (g < grp) run += part[g][col];
+        tot += part[g][col];
+    }
+    for (int r = r0; r < r1; r += kHeldRows) {
+        if (!held)
+#pragma unroll
+            for (int k = 0; k < kHeldRows; ++k) v[k] = r + k < r1 ? h[(size_t)(r + k) * ld] : 0u;
+#pragma unroll
+        for (int k = 0; k < kHeldRows; ++k) {
+            if (r + k < r1) h[(size_t)(r + k) * ld] = run;
             run += v[k];
         }
     }
-    for (; j < nbq; ++j) {
-        const uint32_t v = col[(size_t)j * stride];
-        col[(size_t)j * stride] = run;
-        run += v;
+    // the columns' starts within the chunk: the first 256 threads (4 waves) hold one column each
+    uint32_t inc = 0;
+    if (grp == 0) {
+        inc = wave_inclusive_scan<uint32_t>(tot);
+        if (lane_id() == 63) wsum[w] = inc;
     }
-    totals[i] = run;
+    __syncthreads();
+    if (grp == 0) {
+        uint32_t before = 0;
+        for (int k = 0; k < w; ++k) before += (uint32_t)wsum[k];
+        if (in) bb.lstart[e] = before + inc - tot;
+    }
+    if (threadIdx.x == 0) {
+        const unsigned long long ct = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        __hip_atomic_store(&bb.ctot[blockIdx.x], ct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        last = __hip_atomic_fetch_add(T.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    const int nblk = (int)gridDim.x;
+    uint64_t base = 0;
+    for (int i0 = 0; i0 < nblk; i0 += (int)blockDim.x) {
+        const int i = i0 + (int)threadIdx.x;
+        const uint64_t x = i < nblk ? __hip_atomic_load(&bb.ctot[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+        const uint64_t ix = wave_inclusive_scan<uint64_t>(x);
+        if (lane_id() == 63) wsum[w] = ix;
+        __syncthreads();
+        uint64_t before = 0, all = 0;
+        for (int k = 0; k < W; ++k) {
+            const uint64_t y = wsum[k];
+            before += k < w ? y : 0ull;
+            all += y;
+        }
+        if (i < nblk) bb.cbase[i] = (uint32_t)(base + before + ix - x);
+        base += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        *T.total = base;
+        if (T.cap) {
+            *T.n_eff = base <= T.cap ? base : 0ull;
+            *T.status = base > T.cap ? 1u : 0u;
+        }
+        if (T.host) __hip_atomic_store(T.host, (unsigned long long)base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
-// Placement for one segment (at most 256 tiles per query): one block of pairs
-// of one query, in batches of 256 pairs (one per thread). A batch's keys, in
-// pair order, are processed in chunks of kTile positions; every lane computes
-// the key at its position directly (the owning pair by binary search over the
-// batch's key offsets, the tile by enumerating the pair's rectangle row by row)
-// and sets the pair's bit in the tile's 256-bit mask. The key's rank in the
-// tile's list is then the tile's start for this block, plus the batch's earlier
-// pairs covering the tile (their keys all lie at earlier positions, so their
-// bits are set by then), plus the entries of the block's earlier batches.
-template <bool kMix = false>
-__global__ __launch_bounds__(kThreads) void bin_place_kernel(const uint2* __restrict__ rect,
-                                                             const uint32_t* __restrict__ count, BinGeom G,
-                                                             const uint32_t* __restrict__ hs,
-                                                             const uint32_t* __restrict__ starts,
-                                                             const uint64_t* __restrict__ n_dev,
-                                                             uint32_t* __restrict__ vals, MixBatch mix = MixBatch{}) {
-    constexpr int kSeg = 256;
-    constexpr int kBatch = kThreads;
-    constexpr int kWords = kBatch / 64;
-    static_assert(kSeg == kThreads, "one tile per thread in the per-tile steps");
-    // fixed-capacity run that overflowed: nothing is placed (block-uniform)
-    if (n_dev && *n_dev == 0) return;
-    // word-major, so the tiles of consecutive keys (consecutive tiles) fall on consecutive banks
-    __shared__ unsigned long long mask[kWords][kSeg];  // bit p of word w: pair 64 w + p of the batch covers the tile
-    __shared__ uint32_t pre[kWords][kSeg];             // pairs covering the tile in the words before
-    __shared__ uint32_t base[kSeg];
-    __shared__ uint32_t lds[kWaves + 1];
-    __shared__ uint32_t s_o[kBatch], s_w[kBatch];
-    __shared__ int s_ty0[kBatch], s_tx0[kBatch];
-    __shared__ float s_rw[kBatch];
+// base + the set bits of m below this lane
+__device__ __forceinline__ uint32_t rank_below(uint64_t m, uint32_t base) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+
+// A pair of a placement block: first column (10 bits), last column (10 bits; a
+// wrapped rectangle's runs past TW), index in the block (12 bits). kNoPair
+// covers no column.
+__device__ __forceinline__ uint32_t pack_pair(uint32_t c0, uint32_t c1, uint32_t id) {
+    return c0 | (c1 << 10) | (id << 20);
+}
+constexpr uint32_t kNoPair = 1023u | (1022u << 10);
+
+// Placement. The block's rectangles are staged in LDS; each wave takes tile
+// rows of its own (row r, r + nw, ...), so no barrier and no atomic orders the
+// writes. Per row it collects the pairs whose rectangle meets the row, in pair
+// order (ballot compaction into its own LDS list); per segment of 8 columns the
+// pairs of that list that meet the segment; then per 64 of those and per tile
+// one ballot gives the covering lanes, which write their pair indices to
+// consecutive list positions (the tile's next position is a scalar of the
+// wave). Vector work per (64 candidates, tile): two instructions for the test,
+// three for the rank and the store; a segment's candidates cover a given tile
+// of it with probability ~1/4 on 1-12 px Gaussians, against ~1/20 without the
+// two compactions. Finding each key's owner by binary search, ranking it by
+// masks and storing it to a scattered 4-byte address (the earlier scheme; with
+// several 512-tile segments, ranking by digit ballots) took 192 us for the 44M
+// entries of 6.4M pairs at 90 x 360, 594 us for 16M entries at 180 x 720 and
+// 2,923 us for 345M entries at 360 x 1440; this takes 109, 44 and 1,613 us,
+// bound by instruction issue (at 360 x 1440 the vector unit is busy 61% of the
+// cycles, the scalar unit 51%; HBM writes are twice the lists' bytes, 1.4 TB/s).
+template <bool kMix, bool kWrap>
+__global__ __launch_bounds__(64 * kPlaceWaves) void bin_place_kernel(const uint2* __restrict__ rect,
+                                                                     const uint32_t* __restrict__ count, BinGeom G,
+                                                                     BinBufs bb,
+                                                                     const unsigned long long* __restrict__ total,
+                                                                     const unsigned long long* __restrict__ n_dev,
+                                                                     uint32_t* __restrict__ vals,
+                                                                     uint2* __restrict__ ranges, MixBatch mix) {
+    extern __shared__ uint32_t s_dyn[];
+    uint2* s_p = reinterpret_cast<uint2*>(s_dyn);  // (first row | rows << 16, packed pair); 0 rows: no tiles
+    uint32_t* s_base = s_dyn + 2 * G.pb;           // next list position of every tile
+    const int cap = G.cap;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)lane_id(), nw = (int)blockDim.x >> 6;
+    uint32_t* s_row = s_base + G.stride + (size_t)wave * 2 * cap;  // the wave's lists of packed pairs
+    uint32_t* s_seg = s_row + cap;
     const int j = blockIdx.x, q = blockIdx.y;
-    const int t = threadIdx.x;
     const BinQuery Q = bin_query<kMix>(G, mix, q);
+    const bool over = n_dev && *n_dev == 0;  // a fixed-capacity run that overflowed places nothing
     const int p_beg = j * G.pb, p_end = min(p_beg + G.pb, Q.N);
-    const size_t row0 = Q.row0;
+    const int np = max(p_end - p_beg, 0);
+    const uint32_t e0 = (uint32_t)q * (uint32_t)G.stride;  // the query's first column
+    if (j == 0) {
+        const uint32_t all = gridDim.y * (uint32_t)G.stride;
+        for (int t = threadIdx.x; t < Q.tiles; t += (int)blockDim.x) {
+            const uint32_t e = e0 + (uint32_t)t, f = e + 1u;
+            const uint32_t a = bb.lstart[e] + bb.cbase[e / kColChunk];
+            const uint32_t z = f < all ? bb.lstart[f] + bb.cbase[f / kColChunk] : (uint32_t)*total;
+            ranges[Q.tile0 + t] = !over && a < z ? make_uint2(a, z) : make_uint2(0u, 0u);
+        }
+    }
+    if (over || np == 0) return;
+    const uint32_t* hrow = bb.hist + ((size_t)q * G.nbq + j) * G.stride;
+    for (int t = threadIdx.x; t < Q.tiles; t += (int)blockDim.x)
+        s_base[t] = bb.lstart[e0 + t] + bb.cbase[(e0 + t) / kColChunk] + hrow[t];
+    const int nk = (np + 63) / 64;
     const int TW = Q.TW;
-    base[t] = hs[(((size_t)q * G.nbq + j) << 8) + t] + starts[((size_t)q << 8) + t];
-#pragma unroll
-    for (int k = 0; k < kWords; ++k) mask[k][t] = 0ull;
-    uint32_t c_next = 0u;
-    uint2 r_next = make_uint2(0u, 0u);
-    if (p_beg + t < p_end) {
-        c_next = count[row0 + p_beg + t];
-        r_next = rect[row0 + p_beg + t];
-    }
-    for (int s0 = p_beg; s0 < p_end; s0 += kBatch) {
-        const uint32_t c = c_next;
-        const uint2 r = r_next;
-        const int pn = s0 + kBatch + t;
-        c_next = pn < p_end ? count[row0 + pn] : 0u;
-        if (pn < p_end) r_next = rect[row0 + pn];
-        uint32_t K;
-        const uint32_t o = block_exclusive_scan<uint32_t>(c, lds, &K);  // synchronises
-        if (K == 0) continue;
-        s_o[t] = o;
-        if (c) {
-            const int tx0 = r.x & 0xffff, tx1 = r.x >> 16;
-            const uint32_t w = (uint32_t)(tx1 >= tx0 ? tx1 - tx0 + 1 : TW - tx0 + tx1 + 1);
-            s_ty0[t] = (int)(r.y & 0xffff);
-            s_tx0[t] = tx0;
-            s_w[t] = w;
-            s_rw[t] = 1.0f / (float)w;
+    for (int i = threadIdx.x; i < nk * 64; i += (int)blockDim.x) {
+        uint2 p = make_uint2(0u, kNoPair);
+        if (i < np && count[Q.row0 + p_beg + i]) {
+            const uint2 r = rect[Q.row0 + p_beg + i];
+            const uint32_t tx0 = r.x & 0xffff, tx1 = r.x >> 16, ty0 = r.y & 0xffff, ty1 = r.y >> 16;
+            p = make_uint2(ty0 | ((ty1 - ty0 + 1u) << 16),
+                           pack_pair(tx0, tx1 >= tx0 ? tx1 : tx1 + (uint32_t)TW, (uint32_t)i));
         }
-        for (uint32_t c0 = 0; c0 < K; c0 += kTile) {
-            __syncthreads();  // the batch's pair table is complete; the previous chunk's ranks are read
-            uint32_t dig[kItems], own[kItems];
+        s_p[i] = p;
+    }
+    __syncthreads();
+    const uint32_t v0 = (uint32_t)(Q.row0 + p_beg);
+    constexpr int kU = 4;  // chunks read together
+    for (int r = wave; r < Q.TH; r += nw) {
+        for (int k = 0; k < nk;) {
+            // the pairs of the next chunks that meet row r, at most a list's worth
+            int n = 0;
+            while (k < nk && n + 64 <= cap) {
+                uint2 p[kU];
 #pragma unroll
-            for (int i = 0; i < kItems; ++i) {
-                const uint32_t gp = c0 + (uint32_t)(i * kThreads + t);
-                own[i] = kBatch;  // no key at this position
-                dig[i] = 0u;
-                if (gp < K) {
-                    // last pair whose first key is at or before gp (s_o is non-decreasing; a pair without keys
-                    // shares its offset with the next pair, so the last one is the owner)
-                    int lo = 0;
+                for (int u = 0; u < kU; ++u) p[u] = s_p[min(k + u, nk - 1) * 64 + lane];
+                int u0 = 0;  // chunks taken
 #pragma unroll
-                    for (int step = kBatch / 2; step > 0; step >>= 1)
-                        if (s_o[lo + step] <= gp) lo += step;
-                    const uint32_t m = gp - s_o[lo], w = s_w[lo];
-                    // m < 256 keys, w <= 256 columns: the product is at most one below the quotient
-                    uint32_t qr = (uint32_t)((float)m * s_rw[lo]);
-                    uint32_t cc = m - qr * w;
-                    if (cc >= w) {
-                        ++qr;
-                        cc -= w;
+                for (int u = 0; u < kU; ++u) {
+                    if (k + u >= nk || n + 64 > cap) break;
+                    const bool f = (uint32_t)r - (p[u].x & 0xffffu) < (p[u].x >> 16);
+                    const uint64_t m = __ballot(f);
+                    if (f) s_row[rank_below(m, (uint32_t)n)] = p[u].y;
+                    n += __popcll(m);
+                    u0 = u + 1;
+                }
+                k += u0;
+            }
+            // whole 64-pair chunks (n + 64 may pass the list: its last chunk is full then)
+            if (n & 63) s_row[min(n + lane, n | 63)] = kNoPair;
+            __builtin_amdgcn_wave_barrier();
+            for (int c0 = 0; c0 < TW; c0 += kSegCols) {
+                int ns = 0;
+                for (int i = 0; i < n; i += 64 * kU) {
+                    uint32_t p[kU];
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) p[u] = i + 64 * u < n ? s_row[i + 64 * u + lane] : kNoPair;
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) {
+                        if (i + 64 * u >= n) break;
+                        const uint32_t a = p[u] & 1023u, z = (p[u] >> 10) & 1023u;
+                        bool f = a < (uint32_t)(c0 + kSegCols) && z >= (uint32_t)c0;
+                        // the image one period to the left
+                        if (kWrap) f = f || (z >= (uint32_t)(c0 + TW) && p[u] != kNoPair);
+                        const uint64_t m = __ballot(f);
+                        if (f) s_seg[rank_below(m, (uint32_t)ns)] = p[u];
+                        ns += __popcll(m);
                     }
-                    const int col = s_tx0[lo] + (int)cc;
-                    const uint32_t d = (uint32_t)((s_ty0[lo] + (int)qr) * TW + (col < TW ? col : col - TW));
-                    dig[i] = d;
-                    own[i] = (uint32_t)lo;
-                    atomicOr(&mask[lo >> 6][d], 1ull << (lo & 63));
                 }
-            }
-            __syncthreads();
-            {
-                uint32_t run = 0;
+                if (ns == 0) continue;
+                if (ns & 63) s_seg[min(ns + lane, ns | 63)] = kNoPair;
+                __builtin_amdgcn_wave_barrier();
+                const int nc = min(kSegCols, TW - c0);
+                uint32_t* sb = s_base + r * TW + c0;
+                uint32_t vb = lane < nc ? sb[lane] : 0u;
+                uint32_t b[kSegCols];
 #pragma unroll
-                for (int k = 0; k < kWords; ++k) {
-                    pre[k][t] = run;
-                    run += (uint32_t)__popcll(mask[k][t]);
-                }
-            }
-            __syncthreads();
+                for (int t = 0; t < kSegCols; ++t) b[t] = __builtin_amdgcn_readlane(vb, t);
+                uint32_t next = s_seg[lane];
+                for (int i = 0; i < ns; i += 64) {
+                    const uint32_t p = next;
+                    if (i + 64 < ns) next = s_seg[i + 64 + lane];
+                    const uint32_t a = p & 1023u, w = ((p >> 10) & 1023u) + 1u - a;
+                    const uint32_t d0 = (uint32_t)c0 - a;
+                    const uint32_t v = v0 + (p >> 20);
 #pragma unroll
-            for (int i = 0; i < kItems; ++i) {
-                if (own[i] < (uint32_t)kBatch) {
-                    const uint32_t d = dig[i], lo = own[i];
-                    const uint32_t rank = pre[lo >> 6][d] +
-                                          (uint32_t)__popcll(mask[lo >> 6][d] & ((1ull << (lo & 63)) - 1ull));
-                    vals[base[d] + rank] = (uint32_t)(row0 + s0 + lo);
-                }
-            }
-        }
-        __syncthreads();  // every rank of the batch is read
-        uint32_t tot = 0;
-#pragma unroll
-        for (int k = 0; k < kWords; ++k) {
-            tot += (uint32_t)__popcll(mask[k][t]);
-            mask[k][t] = 0ull;
-        }
-        base[t] += tot;  // the next batch's scan synchronises before anything reads base or the masks
-    }
-}
-
-// Lanes of the wave (among those with `ok`) whose DB-bit digit equals this
-// lane's: the AND over the digit's bits of the bit's ballot where this lane's
-// bit is 1 and of its complement where it is 0, written as ~(ballot ^ s) with s
-// the lane's bit sign-extended to a word. Returns (rank among them in lane
-// order, their number).
-template <int DB>
-__device__ __forceinline__ uint2 digit_match(uint32_t d, bool ok) {
-    const uint64_t v = __ballot(ok);
-    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-#pragma unroll
-    for (int b = 0; b < DB; ++b) {
-        const uint32_t sb = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // 0 or ~0
-        const uint64_t bal = __ballot(sb != 0u);
-        lo &= ~((uint32_t)bal ^ sb);
-        hi &= ~((uint32_t)(bal >> 32) ^ sb);
-    }
-    const uint64_t m = ((uint64_t)hi << 32) | lo;
-    return make_uint2((uint32_t)__popcll(m & lanemask_lt()), (uint32_t)__popcll(m));
-}
-
-// Enumeration of the keys a pair has in a tile segment [t0, t0 + seg), in the
-// row-major order of for_rect_tiles: the first intersecting row of the rectangle
-// (possibly clipped by the segment start) gives keys 0 .. n0 - 1 at tiles
-// a0 + m; the later rows are whole (only the last can be clipped by the segment
-// end, which the key count already excludes) and hold key n0 + q * w + c at
-// tile rb + q * TW + c. Tiles are relative to t0.
-struct SegRun {
-    int a0, rb;
-    uint32_t n0, w;
-    float rw;  // 1 / w
-};
-
-__device__ __forceinline__ SegRun seg_run(uint2 r, int TW, int t0, int seg) {
-    const int tx0 = r.x & 0xffff, tx1 = r.x >> 16, ty0 = r.y & 0xffff;
-    const int ya = ty0 * TW + tx1 >= t0 ? ty0 : (t0 - tx1 + TW - 1) / TW;
-    const int a = max(ya * TW + tx0, t0), e = min(ya * TW + tx1, t0 + seg - 1);
-    SegRun s;
-    s.a0 = a - t0;
-    s.n0 = (uint32_t)(e - a + 1);
-    s.rb = (ya + 1) * TW + tx0 - t0;
-    s.w = (uint32_t)(tx1 - tx0 + 1);
-    s.rw = 1.0f / (float)s.w;
-    return s;
-}
-
-// Tile (relative to t0) of key m < the pair's key count in the segment.
-__device__ __forceinline__ uint32_t seg_tile_at(int a0, int rb, uint32_t n0, uint32_t w, float rw, int TW,
-                                                uint32_t m) {
-    if (m < n0) return (uint32_t)(a0 + (int)m);
-    const uint32_t mm = m - n0;
-    uint32_t q = (uint32_t)((float)mm * rw);  // m < 2^24: exact operands, at most one below
-    uint32_t c = mm - q * w;
-    if (c >= w) {
-        ++q;
-        c -= w;
-    }
-    return (uint32_t)(rb + (int)q * TW + (int)c);
-}
-
-// Stable placement of one block of pairs of one query, segment by segment
-// (the block's output positions then lie in 256 tile lists at a time). Pairs
-// are taken in batches of 256 * PPT (PPT consecutive pairs per thread; several
-// when a query has several segments, so that a batch still holds many keys of
-// one segment); the batch's keys in the segment, in pair order, are processed
-// in chunks of kTile positions, split into whole 64-key items over the waves in
-// order. Every lane computes the key at its position directly (load-balanced:
-// the owning pair is found by binary search over the batch's key offsets),
-// ranks it among equal tiles with wave64 ballots, and the ranks are offset per
-// wave and per tile through LDS counters; base[] holds each tile's next output
-// position for this block.
-template <int PPT, int DB, bool kMix = false>
-__global__ __launch_bounds__(kThreads) void bin_scatter_kernel(const uint2* __restrict__ rect,
-                                                               const uint32_t* __restrict__ count, BinGeom G,
-                                                               const uint32_t* __restrict__ hs,
-                                                               const uint32_t* __restrict__ starts,
-                                                               const uint64_t* __restrict__ n_dev,
-                                                               uint32_t* __restrict__ vals,
-                                                               MixBatch mix = MixBatch{}) {
-    constexpr int kSeg = 1 << DB;
-    constexpr int kBatch = kThreads * PPT;
-    // fixed-capacity run that overflowed: nothing is placed (block-uniform)
-    if (n_dev && *n_dev == 0) return;
-    __shared__ uint32_t base[kSeg];
-    __shared__ uint32_t wcnt[kWaves][kSeg];
-    __shared__ uint32_t ttot[kSeg];
-    __shared__ uint32_t lds[kWaves + 1];
-    // per pair of the batch: first key offset and the enumeration of its keys
-    __shared__ uint32_t s_o[kBatch], s_n0[kBatch], s_w[kBatch];
-    __shared__ int s_a0[kBatch], s_rb[kBatch];
-    __shared__ float s_rw[kBatch];
-    const int w = threadIdx.x >> 6;
-    const int j = blockIdx.x, q = blockIdx.y;
-    const BinQuery Q = bin_query<kMix>(G, mix, q);
-    const int p_beg = j * G.pb, p_end = min(p_beg + G.pb, Q.N);
-    const size_t row0 = Q.row0;
-    // segments past the query's tiles hold no keys (their histogram entries are zero)
-    for (int sg = 0; sg < Q.S; ++sg) {
-        const int t0 = sg * kSeg;
-        __syncthreads();  // the previous segment is placed
-        for (int d = threadIdx.x; d < kSeg; d += kThreads)
-            base[d] = hs[(((size_t)(q * G.S + sg) * G.nbq + j) << DB) + d] + starts[((size_t)(q * G.S + sg) << DB) + d];
-        // the next batch's (count, rect) are loaded while this one is placed
-        uint32_t c_next[PPT];
-        uint2 r_next[PPT];
-#pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const int p = p_beg + (int)threadIdx.x * PPT + i;
-            c_next[i] = p < p_end ? count[row0 + p] : 0u;
-            r_next[i] = p < p_end ? rect[row0 + p] : make_uint2(0u, 0u);
-        }
-        for (int s0 = p_beg; s0 < p_end; s0 += kBatch) {
-            uint32_t c[PPT];
-            uint2 r[PPT];
-            uint32_t csum = 0;
-#pragma unroll
-            for (int i = 0; i < PPT; ++i) {
-                r[i] = r_next[i];
-                c[i] = !c_next[i] ? 0u : (Q.S == 1 ? c_next[i] : seg_count(r[i], Q.TW, t0, kSeg));
-                csum += c[i];
-                const int pn = s0 + kBatch + (int)threadIdx.x * PPT + i;
-                c_next[i] = pn < p_end ? count[row0 + pn] : 0u;
-                if (pn < p_end) r_next[i] = rect[row0 + pn];
-            }
-            uint32_t K;
-            uint32_t o = block_exclusive_scan<uint32_t>(csum, lds, &K);  // synchronises
-            if (K == 0) continue;
-#pragma unroll
-            for (int i = 0; i < PPT; ++i) {
-                const int e = (int)threadIdx.x * PPT + i;  // pair within the batch
-                s_o[e] = o;
-                if (c[i]) {
-                    const SegRun sr = seg_run(r[i], Q.TW, t0, kSeg);
-                    s_a0[e] = sr.a0;
-                    s_rb[e] = sr.rb;
-                    s_n0[e] = sr.n0;
-                    s_w[e] = sr.w;
-                    s_rw[e] = sr.rw;
-                }
-                o += c[i];
-            }
-            for (uint32_t c0 = 0; c0 < K; c0 += kTile) {
-                for (int i = threadIdx.x; i < kWaves * kSeg; i += kThreads) (&wcnt[0][0])[i] = 0;
-                __syncthreads();  // counters cleared; the batch's pair table is complete
-                const uint32_t n_here = min(K - c0, (uint32_t)kTile);
-                const uint32_t ipw = ((n_here + 63) / 64 + kWaves - 1) / kWaves;  // items per wave
-                uint32_t dig[kItems], lr[kItems], pl[kItems];
-                bool ok[kItems];
-#pragma unroll
-                for (int jj = 0; jj < kItems; ++jj) {
-                    const uint32_t idx0 = ((uint32_t)w * ipw + (uint32_t)jj) * 64;
-                    ok[jj] = false;
-                    dig[jj] = lr[jj] = pl[jj] = 0;
-                    if ((uint32_t)jj >= ipw || idx0 >= n_here) continue;  // wave-uniform
-                    const uint32_t idx = idx0 + lane_id();
-                    ok[jj] = idx < n_here;
-                    uint32_t d = 0, pr = 0;
-                    if (ok[jj]) {
-                        const uint32_t gp = c0 + idx;  // key position in the batch
-                        // last pair whose first key is at or before gp (s_o is
-                        // non-decreasing; a pair without keys shares its offset
-                        // with the next pair, so the last one is the owner)
-                        int lo = 0;
-#pragma unroll
-                        for (int step = kBatch / 2; step > 0; step >>= 1)
-                            if (s_o[lo + step] <= gp) lo += step;
-                        pr = (uint32_t)lo;
-                        d = seg_tile_at(s_a0[lo], s_rb[lo], s_n0[lo], s_w[lo], s_rw[lo], Q.TW, gp - s_o[lo]);
+                    for (int t = 0; t < kSegCols; ++t) {
+                        bool f = d0 + (uint32_t)t < w;
+                        if (kWrap) f = (f || d0 + (uint32_t)(t + TW) < w) && t < nc;
+                        const uint64_t m = __ballot(f);
+                        if (f) vals[rank_below(m, b[t])] = v;
+                        b[t] += (uint32_t)__popcll(m);
                     }
-                    dig[jj] = d;
-                    pl[jj] = pr;
-                    const uint2 rc = digit_match<DB>(d, ok[jj]);
-                    const uint32_t rank = rc.x, cnt = rc.y;
-                    uint32_t prev = 0;
-                    if (ok[jj]) prev = wcnt[w][d];
-                    lr[jj] = prev + rank;
-                    __builtin_amdgcn_wave_barrier();
-                    if (ok[jj] && rank == 0) wcnt[w][d] = prev + cnt;
-                    __builtin_amdgcn_wave_barrier();
                 }
-                __syncthreads();
-                for (int d = threadIdx.x; d < kSeg; d += kThreads) {
-                    uint32_t run = 0;
 #pragma unroll
-                    for (int k = 0; k < kWaves; ++k) {
-                        const uint32_t cc = wcnt[k][d];
-                        wcnt[k][d] = run;
-                        run += cc;
-                    }
-                    ttot[d] = run;
-                }
-                __syncthreads();
-#pragma unroll
-                for (int jj = 0; jj < kItems; ++jj)
-                    if (ok[jj]) vals[base[dig[jj]] + wcnt[w][dig[jj]] + lr[jj]] = (uint32_t)(row0 + s0 + pl[jj]);
-                __syncthreads();
-                for (int d = threadIdx.x; d < kSeg; d += kThreads) base[d] += ttot[d];
-                __syncthreads();
+                for (int t = 0; t < kSegCols; ++t) vb = lane == t ? b[t] : vb;
+                if (lane < nc) sb[lane] = vb;
+                __builtin_amdgcn_wave_barrier();
             }
         }
     }
-}
-
-// Ranges of a mixed batch's global tiles: tile t of query q starts at entry
-// (q, segment t >> db, t mod 2^db) of the scanned tile totals.
-__global__ void mix_bin_ranges_kernel(const uint32_t* __restrict__ starts, MixBatch mix, BinGeom G,
-                                      const uint64_t* __restrict__ total, const uint64_t* __restrict__ n_dev,
-                                      int64_t tile_cap, uint2* __restrict__ ranges) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= tile_cap || i >= mix.queries[mix.B].tile_base) return;  // the blend skips tiles past the batch
-    if (n_dev && *n_dev == 0) {
-        ranges[i] = make_uint2(0u, 0u);
-        return;
-    }
-    const int q = mix_find(mix.queries, mix.B, (int)i, [](const MixQuery& x) { return x.tile_base; });
-    const int64_t t = i - mix.queries[q].tile_base;
-    const size_t e = ((size_t)q * G.S << G.db) + t;
-    const uint32_t a = starts[e];
-    const uint32_t b = e + 1 < ((size_t)mix.B * G.S << G.db) ? starts[e + 1] : (uint32_t)*total;
-    ranges[i] = a < b ? make_uint2(a, b) : make_uint2(0u, 0u);
-}
-
-__global__ void bin_ranges_kernel(const uint32_t* __restrict__ starts, int B, BinGeom G,
-                                  const uint64_t* __restrict__ total, const uint64_t* __restrict__ n_dev,
-                                  uint2* __restrict__ ranges) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)B * G.tiles) return;
-    if (n_dev && *n_dev == 0) {
-        ranges[i] = make_uint2(0u, 0u);
-        return;
-    }
-    const int64_t q = i / G.tiles, t = i - q * G.tiles;
-    const size_t e = ((size_t)q * G.S << G.db) + t;  // segments of a query are consecutive
-    const uint32_t a = starts[e];
-    const uint32_t b = e + 1 < ((size_t)B * G.S << G.db) ? starts[e + 1] : (uint32_t)*total;
-    ranges[i] = a < b ? make_uint2(a, b) : make_uint2(0u, 0u);
 }
 
 // ---- tile ranges -----------------------------------------------------------
@@ -1047,132 +954,93 @@ void launch_tile_ranges(const void* keys, int key_bytes, int64_t n, int64_t n_gt
         tile_ranges_kernel<false><<<blocks, 256, 0, st>>>(keys, n, ranges, n_dev);
 }
 
-bool bin_fits(int B, int N, const Grid& g) {
-    // a periodic azimuth is binned with one segment
-    return B <= 65535 && g.tiles <= kMaxTiles && (!g.wrap || g.tiles <= 256);
-}
+bool bin_fits(int B, int N, const Grid& g) { return B <= 65535 && g.tiles <= kMaxTiles; }
 
-// The bins buffer: the histogram (B * S * nbq rows of 2^db), then the scanned
-// tile totals (B * S * 2^db).
-static size_t hist_entries(int B, const BinGeom& G) { return ((size_t)B * G.S * G.nbq) << G.db; }
-static size_t start_entries(int B, const BinGeom& G) { return ((size_t)B * G.S) << G.db; }
+static BinGeom geom_of(int B, int N, const Grid& g) { return bin_geom(B, N, g.TW, g.TH, g.tiles); }
+// Mixed batches: the geometry of the batch's largest query (max_n pairs, max_tiles tiles) for every query.
+static BinGeom mix_geom(int B, int max_n, int max_tiles) { return bin_geom(B, max_n, 0, 0, max_tiles); }
 
-size_t bin_hist_entries(int B, int N, const Grid& g) {
-    const BinGeom G = bin_geom(N, g);
-    return hist_entries(B, G) + start_entries(B, G);
-}
-
-size_t bin_scan_entries(int B, int N, const Grid& g) { return start_entries(B, bin_geom(N, g)); }
+size_t bin_entries(int B, int N, const Grid& g) { return bin_words(B, geom_of(B, N, g)); }
+size_t mix_bin_entries(int B, int max_n, int max_tiles) { return bin_words(B, mix_geom(B, max_n, max_tiles)); }
 
 static void hist_launch(const BinGeom& G, int B, const Records& r, uint32_t* bins, unsigned long long* cull,
                         hipStream_t st, const MixBatch* m) {
+    const BinBufs bb = bin_bufs(bins, B, G);
     if (m)
-        bin_hist_kernel<true><<<dim3(G.nbq, B), kThreads, 0, st>>>(r.rect, r.count, G, bins, cull, *m);
+        bin_hist_kernel<true><<<dim3(G.nbq, B), kThreads, 0, st>>>(r.rect, r.count, G, bb.hist, cull, *m);
     else
-        bin_hist_kernel<false><<<dim3(G.nbq, B), kThreads, 0, st>>>(r.rect, r.count, G, bins, cull);
+        bin_hist_kernel<false><<<dim3(G.nbq, B), kThreads, 0, st>>>(r.rect, r.count, G, bb.hist, cull, MixBatch{});
 }
 
-static void offsets_launch(const BinGeom& G, int B, uint32_t* bins, void* scratch, uint64_t* total, hipStream_t st) {
-    const int64_t cols = (int64_t)start_entries(B, G);
-    uint32_t* starts = bins + hist_entries(B, G);
-    bin_colscan_kernel<<<(unsigned)((cols + kThreads - 1) / kThreads), kThreads, 0, st>>>(bins, cols, G.nbq, G.db,
-                                                                                          starts);
-    launch_exclusive_scan(starts, starts, total, cols, scratch, st);
+static void offsets_launch(const BinGeom& G, int B, uint32_t* bins, const BinCount& c, hipStream_t st) {
+    BinTotals t;
+    t.total = reinterpret_cast<unsigned long long*>(c.total);
+    t.cap = c.cap;
+    t.n_eff = reinterpret_cast<unsigned long long*>(c.n_eff);
+    t.status = c.status;
+    t.done = c.done;
+    t.host = reinterpret_cast<unsigned long long*>(c.host);
+    // few rows per column: one row group (a quarter of the threads)
+    const int threads = G.nbq <= 8 ? kColChunk : 4 * kColChunk;
+    bin_offsets_kernel<<<(unsigned)bin_chunks(B, G), threads, 0, st>>>(bin_bufs(bins, B, G), G,
+                                                                       (int64_t)B * G.stride, t);
 }
 
-static void place_launch(const BinGeom& G, int B, const Records& r, const uint32_t* bins, const uint64_t* n_dev,
-                         uint32_t* vals, hipStream_t st, const MixBatch* m) {
-    const uint32_t* starts = bins + hist_entries(B, G);
+static void place_launch(const BinGeom& G, int B, int TH, bool wrap, const Records& r, uint32_t* bins,
+                         const uint64_t* total, const uint64_t* n_dev, uint32_t* vals, uint2* ranges, hipStream_t st,
+                         const MixBatch* m) {
+    // waves: the tile rows dealt evenly over at most 12 (6 rows: 6 waves of one; 23 rows: 12 of two)
+    const int rounds = (TH + kPlaceWaves - 1) / kPlaceWaves;
+    const int nw = std::max(1, rounds ? (TH + rounds - 1) / rounds : 1);
+    const size_t lds = 8 * (size_t)G.pb + 4 * (size_t)G.stride + (size_t)nw * 8 * G.cap;
     const dim3 grid(G.nbq, B);
-    if (G.S == 1 && G.db == 8) {
-        if (m)
-            bin_place_kernel<true><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bins, starts, n_dev, vals, *m);
-        else
-            bin_place_kernel<false><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bins, starts, n_dev, vals);
-    } else {
-        if (m)
-            bin_scatter_kernel<4, kWideDb, true><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bins, starts, n_dev,
-                                                                            vals, *m);
-        else
-            bin_scatter_kernel<4, kWideDb><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bins, starts, n_dev, vals);
-    }
+    const auto* tot = reinterpret_cast<const unsigned long long*>(total);
+    const auto* nd = reinterpret_cast<const unsigned long long*>(n_dev);
+    const BinBufs bb = bin_bufs(bins, B, G);
+    if (m)
+        bin_place_kernel<true, false><<<grid, 64 * nw, lds, st>>>(r.rect, r.count, G, bb, tot, nd, vals, ranges, *m);
+    else if (wrap)
+        bin_place_kernel<false, true><<<grid, 64 * nw, lds, st>>>(r.rect, r.count, G, bb, tot, nd, vals, ranges,
+                                                                  MixBatch{});
+    else
+        bin_place_kernel<false, false><<<grid, 64 * nw, lds, st>>>(r.rect, r.count, G, bb, tot, nd, vals, ranges,
+                                                                   MixBatch{});
 }
 
 void launch_bin_hist(const Records& r, int B, int N, const Grid& g, uint32_t* bins, unsigned long long* cull,
                      hipStream_t st) {
-    if (B <= 0) return;
-    const BinGeom G = bin_geom(N, g);
-    if (N <= 0) {
-        launch_clear_u32(bins, (int)hist_entries(B, G), st);
-        return;
-    }
-    hist_launch(G, B, r, bins, cull, st, nullptr);
+    hist_launch(geom_of(B, N, g), B, r, bins, cull, st, nullptr);
 }
 
-void launch_bin_offsets(int B, int N, const Grid& g, uint32_t* bins, void* scratch, uint64_t* total,
-                        hipStream_t st) {
-    if (B <= 0) {
-        launch_clear_u32(reinterpret_cast<uint32_t*>(total), 2, st);
-        return;
-    }
-    offsets_launch(bin_geom(N, g), B, bins, scratch, total, st);
+void launch_bin_offsets(int B, int N, const Grid& g, uint32_t* bins, const BinCount& c, hipStream_t st) {
+    offsets_launch(geom_of(B, N, g), B, bins, c, st);
 }
 
-void launch_bin_scatter(const Records& r, int B, int N, const Grid& g, const uint32_t* bins, const uint64_t* n_dev,
-                        uint32_t* vals, hipStream_t st) {
-    if (B <= 0 || N <= 0) return;
-    place_launch(bin_geom(N, g), B, r, bins, n_dev, vals, st, nullptr);
-}
-
-void launch_bin_ranges(const uint32_t* bins, int B, int N, const Grid& g, const uint64_t* total,
-                       const uint64_t* n_dev, uint2* ranges, hipStream_t st) {
-    const int64_t m = (int64_t)B * g.tiles;
-    if (m <= 0) return;
-    const BinGeom G = bin_geom(N, g);
-    bin_ranges_kernel<<<(unsigned)((m + 255) / 256), 256, 0, st>>>(bins + hist_entries(B, G), B, G, total, n_dev,
-                                                                    ranges);
-}
-
-// Mixed batches: the geometry of the batch's largest query (max_n pairs, max_tiles tiles) for every query.
-static BinGeom mix_geom(int max_n, int max_tiles) {
-    Grid g{};
-    g.tiles = max_tiles;
-    return bin_geom(max_n, g);
+void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* bins, const uint64_t* total,
+                      const uint64_t* n_dev, uint32_t* vals, uint2* ranges, hipStream_t st) {
+    place_launch(geom_of(B, N, g), B, g.TH, g.wrap != 0, r, bins, total, n_dev, vals, ranges, st, nullptr);
 }
 
 bool mix_bin_fits(int B, int max_tiles) { return B <= 65535 && max_tiles <= kMaxTiles; }
 
-size_t mix_bin_hist_entries(int B, int max_n, int max_tiles) {
-    const BinGeom G = mix_geom(max_n, max_tiles);
-    return hist_entries(B, G) + start_entries(B, G);
-}
-
-size_t mix_bin_scan_entries(int B, int max_n, int max_tiles) { return start_entries(B, mix_geom(max_n, max_tiles)); }
-
 void launch_mix_bin_hist(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
                          unsigned long long* cull, hipStream_t st) {
-    if (m.B <= 0) return;
-    hist_launch(mix_geom(max_n, max_tiles), m.B, r, bins, cull, st, &m);
+    if (m.B > 0) hist_launch(mix_geom(m.B, max_n, max_tiles), m.B, r, bins, cull, st, &m);
 }
 
-void launch_mix_bin_offsets(const MixBatch& m, int max_n, int max_tiles, uint32_t* bins, void* scratch,
-                            uint64_t* total, hipStream_t st) {
-    if (m.B <= 0) return;
-    offsets_launch(mix_geom(max_n, max_tiles), m.B, bins, scratch, total, st);
+void launch_mix_bin_offsets(const MixBatch& m, int max_n, int max_tiles, uint32_t* bins, const BinCount& c,
+                            hipStream_t st) {
+    if (m.B > 0) offsets_launch(mix_geom(m.B, max_n, max_tiles), m.B, bins, c, st);
 }
 
-void launch_mix_bin_scatter(const MixBatch& m, int max_n, int max_tiles, const Records& r, const uint32_t* bins,
-                            const uint64_t* n_dev, uint32_t* vals, hipStream_t st) {
-    if (m.B <= 0) return;
-    place_launch(mix_geom(max_n, max_tiles), m.B, r, bins, n_dev, vals, st, &m);
-}
-
-void launch_mix_bin_ranges(const MixBatch& m, int max_n, int max_tiles, const uint32_t* bins, const uint64_t* total,
-                           const uint64_t* n_dev, int64_t tile_cap, uint2* ranges, hipStream_t st) {
-    if (tile_cap <= 0 || m.B <= 0) return;
-    const BinGeom G = mix_geom(max_n, max_tiles);
-    mix_bin_ranges_kernel<<<(unsigned)((tile_cap + 255) / 256), 256, 0, st>>>(bins + hist_entries(m.B, G), m, G,
-                                                                               total, n_dev, tile_cap, ranges);
+void launch_mix_bin_place(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
+                          const uint64_t* total, const uint64_t* n_dev, uint32_t* vals, uint2* ranges,
+                          hipStream_t st) {
+    // the rows of the batch's grids are in its tables on the device: as many waves as a grid of max_tiles
+    // squarish tiles has rows, the waves of a flatter grid idle
+    if (m.B > 0)
+        place_launch(mix_geom(m.B, max_n, max_tiles), m.B, max_tiles <= 256 ? 6 : 12, false, r, bins, total, n_dev,
+                     vals, ranges, st, &m);
 }
 
 }  // namespace swf
