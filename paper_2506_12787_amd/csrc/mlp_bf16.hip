@@ -49,10 +49,7 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) {
 
 constexpr int kUnitU4 = 1024;  // uint4 per 16 KiB unit of the weight stream
 constexpr int kSlots = 3;
-#ifndef SWF_PF_DEPTH
-#define SWF_PF_DEPTH 2
-#endif
-constexpr int kDepth = SWF_PF_DEPTH;  // weight fragments read ahead of the MFMA using them (<= 8)
+constexpr int kQsPitch = 260;  // floats per query row of the layer-1 TX term in LDS (rows on different banks)
 
 struct Bf16Args {
     MlpArgs m;
@@ -62,7 +59,8 @@ struct Bf16Args {
     const float* bias_h[7];   // biases of hidden layers 1..n_hidden-1
     const float* bias_o;      // output bias
     int n_tiles;              // B * tiles_per_query
-    int tiles_per_query;      // ceil(N / pairs per block): tiles never straddle two queries
+    int tiles_per_query;      // ceil(N / pairs per block): tiles never straddle two queries (kPack: 0)
+    uint32_t rows;            // kPack: the tiles cut these flat (query, pair) rows
     uint16_t* act_out;        // kAct: hidden activations (bf16 bits) [n_hidden][B * N][256]
     int64_t act_stride;       // elements per activation layer: B * N * 256
     MixBatch mix;             // kMix: the batch's scene and query tables (per tile: query, scene, stream, biases)
@@ -127,12 +125,22 @@ __device__ __forceinline__ void vmem_wait_all() { __builtin_amdgcn_s_waitcnt(0x0
 // scene, pair count, weight stream and biases from the batch's tables); the
 // ring fetches each step from the stream of the tile it belongs to, and the
 // next tile's biases are copied into the other half of a double buffer.
-template <int NCB, int WAVES, int STEP, int WPE, bool kAct, bool kMix = false>
+//
+// kPack: the tiles cut the batch's flat rows whatever query they belong to (up
+// to NQ queries per tile, whose layer-1 TX terms are in LDS; a pair's
+// accumulators start from its own query's).
+//
+// DEPTH: weight fragments read ahead of the MFMA using them (<= 8). With 3
+// column blocks 2 are enough; with one column block a fragment is used up in 16
+// cycles, so the LDS latency needs 8 in flight.
+template <int NCB, int WAVES, int STEP, int WPE, bool kAct, bool kMix = false, int NQ = 1, int DEPTH = 2>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void
 mlp_bf16_kernel(Bf16Args a) {
     typedef __attribute__((address_space(3))) void* lds_ptr;
     constexpr int kPairsPerWave = 16 * NCB;
     constexpr int kPairsPerBlock = WAVES * kPairsPerWave;
+    constexpr bool kPack = NQ > 1;
+    constexpr int kDepth = DEPTH;
     static_assert(kPairsPerBlock % 64 == 0, "whole 64-pair groups per block");
     static_assert(STEP == 16 || STEP == 32, "ring steps of 16 or 32 fragments");
     constexpr int kStepU4 = STEP * 64;  // uint4 per ring slot
@@ -140,7 +148,7 @@ mlp_bf16_kernel(Bf16Args a) {
     __shared__ float outs[WAVES][kPairsPerWave][8];
     // Layer-1 TX term of the current and the next tile's query, hidden and
     // output biases: C operands read from LDS.
-    __shared__ __attribute__((aligned(16))) float qs_s[2][256];
+    __shared__ __attribute__((aligned(16))) float qs_s[2][NQ][kPack ? kQsPitch : 256];
     constexpr int kBiasBufs = kMix ? 2 : 1;
     __shared__ __attribute__((aligned(16))) float bias_s[kBiasBufs][7][256];
     __shared__ __attribute__((aligned(16))) float bias_o_s[kBiasBufs][16];
@@ -161,9 +169,13 @@ mlp_bf16_kernel(Bf16Args a) {
     const int my_tiles = n_tiles > (int)blockIdx.x ? (n_tiles - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
     if (my_tiles == 0) return;
     const int q_end = my_tiles * S;  // ring steps of this workgroup
-    // query of a tile (block-uniform)
+    // first flat row of a tile (kPack)
+    auto tile_row = [&](int t) { return (uint32_t)t * (uint32_t)kPairsPerBlock; };
+    // query of a tile (kPack: its first) (block-uniform)
     auto tile_query = [&](int t) {
-        if constexpr (kMix)
+        if constexpr (kPack)
+            return (int)(tile_row(t) / (uint32_t)a.m.N);
+        else if constexpr (kMix)
             return mix_find(a.mix.queries, a.mix.B, t, [](const MixQuery& x) { return x.mlp_tile_base; });
         else
             return t / a.tiles_per_query;
@@ -178,8 +190,22 @@ mlp_bf16_kernel(Bf16Args a) {
             for (int l = 0; l < n_mid; ++l) bias_s[0][l][tid] = a.bias_h[l][tid];
             if (tid < 16) bias_o_s[0][tid] = tid < kOut ? a.bias_o[tid] : 0.0f;
         }
-        qs_s[0][tid] = a.m.qs[(size_t)q0 * 256 + tid];
+        if constexpr (!kPack) qs_s[0][0][tid] = a.m.qs[(size_t)q0 * 256 + tid];
     }
+    // kPack: the TX terms of a tile's queries, one 1 KiB row per wave and piece, global -> LDS; awaited by the wait
+    // before the next barrier
+    auto fetch_qs = [&](int t, int buf) {
+        const uint32_t r0 = tile_row(t), r1 = min(r0 + (uint32_t)kPairsPerBlock, a.rows) - 1u;
+        const int qa = (int)(r0 / (uint32_t)a.m.N), nq = (int)(r1 / (uint32_t)a.m.N) - qa + 1;
+#pragma unroll
+        for (int i = 0; i < (NQ + WAVES - 1) / WAVES; ++i) {
+            const int k = i * WAVES + wave;
+            if (k < nq && k < NQ)
+                dma_b128(reinterpret_cast<const uint4*>(a.m.qs + (size_t)(qa + k) * 256) + lane,
+                         (uint32_t)(uintptr_t)(lds_ptr)&qs_s[buf][k][0]);
+        }
+    };
+    if constexpr (kPack) fetch_qs((int)blockIdx.x, 0);
     // weight stream of the tile the ring is fetching for (kMix: it changes with the tile's scene)
     int fetch_it = 0;
     const uint4* fstream = a.stream;
@@ -214,7 +240,7 @@ mlp_bf16_kernel(Bf16Args a) {
 #define SWF_FETCH_BM(tile_)                                                                              \
     do {                                                                                                 \
         const int t_ = (tile_);                                                                          \
-        const int qy_ = tile_query(t_);                                                                  \
+        const int qy_ = kPack ? 0 : tile_query(t_);                                                      \
         int tb_ = qy_ * a.tiles_per_query, nq_ = a.m.N;                                                  \
         const bf16x8* mf_ = a.mfeat;                                                                     \
         if (kMix) {                                                                                      \
@@ -225,7 +251,10 @@ mlp_bf16_kernel(Bf16Args a) {
         }                                                                                                \
         const int pp_ = (t_ - tb_) * kPairsPerBlock + wave * kPairsPerWave;                              \
         _Pragma("unroll") for (int cb = 0; cb < NCB; ++cb) {                                             \
-            const int p_ = min(pp_ + cb * 16 + n16, nq_ - 1);                                            \
+            int p_ = min(pp_ + cb * 16 + n16, nq_ - 1);                                                  \
+            if (kPack)                                                                                   \
+                p_ = (int)(min(tile_row(t_) + (uint32_t)(wave * kPairsPerWave + cb * 16 + n16),          \
+                               a.rows - 1u) % (uint32_t)a.m.N);                                       \
             dma_b128(reinterpret_cast<const uint4*>(mf_) + (size_t)p_ * 4 + g, bm_lds + cb * 1024);      \
         }                                                                                                \
     } while (0)
@@ -272,7 +301,7 @@ mlp_bf16_kernel(Bf16Args a) {
         dst_[cp_][cb_] = __builtin_bit_cast(bf16x8, u_);                              \
         if (kAct) {                                                                   \
             const int pa_ = p0 + (cb_) * 16 + n16;                                    \
-            if (pa_ < a.m.N) {                                                        \
+            if (pa_ < Nq) {                                                           \
                 uint2* d_ = reinterpret_cast<uint2*>(a.act_out + (size_t)(lay_) * a.act_stride + \
                                                      (row0 + pa_) * 256 + 32 * (cp_) + 4 * g);  \
                 d_[0] = make_uint2(u_.x, u_.y);                                       \
@@ -346,7 +375,12 @@ mlp_bf16_kernel(Bf16Args a) {
             tb = a.mix.queries[qry].mlp_tile_base;
             row0 = (size_t)a.mix.queries[qry].pair_base;
         }
-        const int p0 = (tile - tb) * kPairsPerBlock + wave * kPairsPerWave;
+        int p0 = (tile - tb) * kPairsPerBlock + wave * kPairsPerWave;
+        if constexpr (kPack) {  // rows count from the tile's first
+            row0 = (size_t)tile_row(tile);
+            Nq = (int)min((uint32_t)kPairsPerBlock, a.rows - tile_row(tile));
+            p0 = wave * kPairsPerWave;
+        }
         // ---- layer 1 (mean part, K = 32): B = bf16 gamma(mu_hat); C = TX term of the query ----
         bf16x8 bm[NCB];
 #pragma unroll
@@ -356,15 +390,28 @@ mlp_bf16_kernel(Bf16Args a) {
         }
         SWF_ADVANCE();
         {
-            const float* qrow = &qs_s[it & 1][4 * g];
+            const float* qrow[kPack ? NCB : 1];
+            if constexpr (kPack) {
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) {  // rows past the end take the last pair's query
+                    const uint32_t r = (uint32_t)row0 + (uint32_t)min(p0 + cb * 16 + n16, Nq - 1);
+                    qrow[cb] = &qs_s[it & 1][(int)(r / (uint32_t)a.m.N) - qry][4 * g];
+                }
+            } else {
+                qrow[0] = &qs_s[it & 1][0][4 * g];
+            }
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
-                const float4 b4 = *reinterpret_cast<const float4*>(qrow + 16 * t);
-                const f32x4 c0 = {b4.x, b4.y, b4.z, b4.w};
+                f32x4 c0[kPack ? NCB : 1];
+#pragma unroll
+                for (int k = 0; k < (kPack ? NCB : 1); ++k) {
+                    const float4 b4 = *reinterpret_cast<const float4*>(qrow[k] + 16 * t);
+                    c0[k] = f32x4{b4.x, b4.y, b4.z, b4.w};
+                }
                 bf16x8 w;
                 SWF_TAKE(w, t, 16);
 #pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) acc[t][cb] = mfma(w, bm[cb], c0);
+                for (int cb = 0; cb < NCB; ++cb) acc[t][cb] = mfma(w, bm[cb], c0[kPack ? cb : 0]);
                 // pairs 0..6 as 7 * NCB (pair, column block) units, NCB / 2 per
                 // fragment from t = 2 on; pair c' is final once t > 2c' + 1
                 if (t >= 2)
@@ -381,8 +428,11 @@ mlp_bf16_kernel(Bf16Args a) {
         // TX term of the next tile's query, stored to LDS before this tile's
         // last barrier (the other buffer is read by this tile's layer 1 only)
         const int next_tile = tile + (int)gridDim.x;
+        if constexpr (kPack) {
+            if (it + 1 < my_tiles) fetch_qs(next_tile, (it + 1) & 1);
+        }
         const float qs_next =
-            it + 1 < my_tiles && tid < 256 ? a.m.qs[(size_t)tile_query(next_tile) * 256 + tid] : 0.0f;
+            !kPack && it + 1 < my_tiles && tid < 256 ? a.m.qs[(size_t)tile_query(next_tile) * 256 + tid] : 0.0f;
         // ---- hidden layers, two per iteration so the act buffers alternate statically ----
         int l = 0;
         for (; l + 1 < n_mid; l += 2) {
@@ -395,7 +445,7 @@ mlp_bf16_kernel(Bf16Args a) {
         } else {
             SWF_OUTPUT(0);
         }
-        if (tid < 256) qs_s[(it + 1) & 1][tid] = qs_next;
+        if (!kPack && tid < 256) qs_s[(it + 1) & 1][0][tid] = qs_next;
         if constexpr (kMix) {
             // the next tile's biases into the other half of the double buffer (its previous reader, the tile
             // before this one, is done): hidden layers by wave, one 1 KiB piece each, global -> LDS, awaited
@@ -413,7 +463,10 @@ mlp_bf16_kernel(Bf16Args a) {
         if (lane < kPairsPerWave) {
             const int p = p0 + lane;
             if (p < Nq) {
-                if constexpr (kMix)
+                if constexpr (kPack)
+                    deform_epilogue(a.m, row0 + p, (int)(((uint32_t)row0 + (uint32_t)p) % (uint32_t)a.m.N),
+                                    outs[wave][lane]);
+                else if constexpr (kMix)
                     mix_epilogue(a.mix.scenes[a.mix.queries[qry].scene], a.m, row0 + p, p, outs[wave][lane]);
                 else
                     deform_epilogue(a.m, row0 + p, p, outs[wave][lane]);
@@ -460,25 +513,97 @@ void compute_mean_features_bf16(DevScene& s, hipStream_t st) {
                                                                       reinterpret_cast<__bf16*>(s.bf_mfeat));
 }
 
-// One kernel variant: NCB column blocks of 16 pairs per wave, WAVES waves per
-// workgroup, ring steps of STEP fragments, WPE waves per SIMD. The grid is
-// persistent: as many workgroups as fit on the CUs at once (registers and LDS
-// decide; launching more would only queue them).
-template <int NCB, int WAVES, int STEP, int WPE, bool kAct = false>
-void launch_variant(Bf16Args a, int n, int B, int n_hidden, hipStream_t st) {
-    constexpr int kPerBlock = 16 * NCB * WAVES;
+// One kernel variant over tiles [0, n_tiles): NCB column blocks of 16 pairs per wave, WAVES waves per workgroup, ring
+// steps of STEP fragments, WPE waves per SIMD. The grid is persistent: as many workgroups as fit on the CUs at once
+// (registers and LDS decide; launching more would only queue them).
+template <int NCB, int WAVES, int STEP, int WPE, bool kAct = false, int NQ = 1, int DEPTH = 2>
+void launch_tiles(Bf16Args& a, int n_tiles, int n_hidden, hipStream_t st) {
     static const int resident = [] {  // thread-safe one-time initialisation
         int r = 0;
-        const hipError_t e =
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, mlp_bf16_kernel<NCB, WAVES, STEP, WPE, kAct>, 64 * WAVES, 0);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &r, mlp_bf16_kernel<NCB, WAVES, STEP, WPE, kAct, false, NQ, DEPTH>, 64 * WAVES, 0);
         return (e == hipSuccess && r > 0) ? r : 1;
     }();
     a.n_steps = 2 + (128 / STEP) * (n_hidden - 1);
+    a.n_tiles = n_tiles;
+    if (!n_tiles) return;
+    const int blocks = std::min(n_tiles, n_compute_units() * resident);
+    mlp_bf16_kernel<NCB, WAVES, STEP, WPE, kAct, false, NQ, DEPTH><<<blocks, 64 * WAVES, 0, st>>>(a);
+}
+
+// The same over the batch's flat rows, tiles of any queries.
+template <int NCB, int WAVES, int WPE, bool kAct, int NQ, int DEPTH>
+void launch_rows(Bf16Args a, int64_t P, int n_hidden, hipStream_t st) {
+    constexpr int kPerBlock = 16 * NCB * WAVES;
+    a.rows = (uint32_t)P;
+    a.tiles_per_query = 0;
+    launch_tiles<NCB, WAVES, 32, WPE, kAct, NQ, DEPTH>(a, (int)((P + kPerBlock - 1) / kPerBlock), n_hidden, st);
+}
+
+// Tile shapes of the flat rows, largest first: pairs per tile, queries whose TX terms its LDS holds, and the measured
+// microseconds of the first and of every further round of tiles over the 256 compute units (four hidden layers). One
+// round lasts as long as the 416 KB weight stream takes through one CU and its waves through the MFMAs, so fewer
+// pairs per tile make a shorter round, but more pairs per tile a higher rate.
+struct RowTile {
+    int pairs, nq;
+    float first_us, more_us;
+};
+constexpr RowTile kRowTiles[4] = {
+    {384, 10, 34.0f, 26.5f}, {256, 15, 26.0f, 20.0f}, {128, 22, 18.0f, 16.0f}, {64, 24, 14.0f, 11.5f}};
+
+template <bool kAct>
+void launch_row_tiles(int shape, const Bf16Args& a, int64_t P, int n_hidden, hipStream_t st) {
+    switch (shape) {
+        case 0: launch_rows<3, 8, 2, kAct, kRowTiles[0].nq, 2>(a, P, n_hidden, st); break;
+        case 1: launch_rows<2, 8, 2, kAct, kRowTiles[1].nq, 4>(a, P, n_hidden, st); break;
+        case 2: launch_rows<1, 8, 2, kAct, kRowTiles[2].nq, 8>(a, P, n_hidden, st); break;
+        default: launch_rows<1, 4, 1, kAct, kRowTiles[3].nq, 8>(a, P, n_hidden, st); break;
+    }
+}
+
+// The tile shape that the table above makes cheapest for the batch. 100k pairs are 261 tiles of 384 (a second round
+// for five tiles) but two rounds of 256: 61 -> 50 us; 50 pairs take 16 us in a 64-pair tile, 29 in one of 384.
+// Queries of few Gaussians are cut as flat rows (1024 queries of 50 pairs: 200 tiles of 256 pairs in 29 us, 1024
+// tiles mostly of padding in 123); otherwise 384-pair tiles keep to one query, which saves the per-pair TX terms.
+// (Whole rounds of 384-pair tiles with the remainder in small tiles of a second launch measured no better at 800k
+// pairs: 278 us either way, the second launch costs what the unfilled round does.)
+template <bool kAct>
+void launch_batch(Bf16Args a, int n, int B, int n_hidden, hipStream_t st) {
+    const int64_t P = (int64_t)n * B, cus = n_compute_units();
+    if (P == 0) return;
+    // the queries of a tile within its LDS rows; row numbers in 32 bits up to the end of the last tile
+    auto fits = [&](int s) {
+        return (kRowTiles[s].pairs - 2) / n + 2 <= kRowTiles[s].nq && P <= (1ll << 32) - 1024;
+    };
+    auto rounds_us = [&](int s, int64_t tiles) {
+        return kRowTiles[s].first_us + (float)((tiles + cus - 1) / cus - 1) * kRowTiles[s].more_us;
+    };
+    const int tpq = (n + 383) / 384;
+    // 384-pair tiles of one query each where they pad less than 2%, of flat rows otherwise
+    const bool flat = (int64_t)tpq * 384 * B > P + P / 50 && fits(0);
+    int shape = 0;
+    float best = rounds_us(0, flat ? (P + 383) / 384 : (int64_t)tpq * B);
+    for (int s = 1; s < 4; ++s) {
+        const float us = rounds_us(s, (P + kRowTiles[s].pairs - 1) / kRowTiles[s].pairs);
+        if (fits(s) && us < best) {
+            best = us;
+            shape = s;
+        }
+    }
+    if (shape > 0 || flat) {
+        launch_row_tiles<kAct>(shape, a, P, n_hidden, st);
+    } else {
+        a.tiles_per_query = tpq;
+        launch_tiles<3, 8, 32, 2, kAct>(a, tpq * B, n_hidden, st);
+    }
+}
+
+// The tile shape the context asks for: tiles never straddle two queries.
+template <int NCB, int WAVES, int WPE>
+void launch_variant(Bf16Args a, int n, int B, int n_hidden, hipStream_t st) {
+    constexpr int kPerBlock = 16 * NCB * WAVES;
     a.tiles_per_query = (n + kPerBlock - 1) / kPerBlock;
-    a.n_tiles = a.tiles_per_query * B;
-    if (!a.n_tiles) return;
-    const int blocks = std::min(a.n_tiles, n_compute_units() * resident);
-    mlp_bf16_kernel<NCB, WAVES, STEP, WPE, kAct><<<blocks, 64 * WAVES, 0, st>>>(a);
+    launch_tiles<NCB, WAVES, 32, WPE>(a, a.tiles_per_query * B, n_hidden, st);
 }
 
 void launch_mix_mlp_bf16(const MixBatch& m, const float* qs, const Records& r, hipStream_t st, bool paper_mask,
@@ -512,16 +637,17 @@ void launch_mlp_bf16(const DevScene& s, const float* qs, int B, const Grid& g, b
     a.mfeat = reinterpret_cast<const bf16x8*>(s.bf_mfeat);
     for (int l = 0; l + 1 < s.n_hidden && l < 7; ++l) a.bias_h[l] = s.b[l + 1];
     a.bias_o = s.b[s.n_hidden];
-    if (act_out) {  // the default variant (every variant computes the same values)
+    // every variant computes the same values
+    if (act_out) {
         a.act_out = reinterpret_cast<uint16_t*>(act_out);
         a.act_stride = (int64_t)B * s.n * 256;
-        launch_variant<3, 8, 32, 2, true>(a, s.n, B, s.n_hidden, st);
+        launch_batch<true>(a, s.n, B, s.n_hidden, st);
     } else if (pairs_per_wave == 64)
-        launch_variant<4, 4, 32, 1>(a, s.n, B, s.n_hidden, st);  // 256 pairs, one wave per SIMD
+        launch_variant<4, 4, 1>(a, s.n, B, s.n_hidden, st);  // 256 pairs, one wave per SIMD
     else if (pairs_per_wave == 32)
-        launch_variant<2, 8, 32, 2>(a, s.n, B, s.n_hidden, st);  // 256 pairs, two waves per SIMD
+        launch_variant<2, 8, 2>(a, s.n, B, s.n_hidden, st);  // 256 pairs, two waves per SIMD
     else
-        launch_variant<3, 8, 32, 2>(a, s.n, B, s.n_hidden, st);  // default: 384 pairs, two waves per SIMD
+        launch_batch<false>(a, s.n, B, s.n_hidden, st);  // default
 }
 
 }  // namespace swf
