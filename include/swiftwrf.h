@@ -168,8 +168,8 @@ swf_status swf_scene_bytes(swf_ctx *ctx, int32_t scene_id, uint64_t *bytes);
  * SWF_NO_DEFORM, may be NULL then). out: device float32 [batch][H][W].
  * aux: device buffer of 8*batch*H*W bytes when SWF_KEEP_AUX, else NULL.
  * Enqueued on `stream`; the call returns after enqueueing, except that it waits
- * once for the total key count (an 8-byte device-to-host read after the key
- * scan). The first render of a context sizes the key buffers from that count
+ * once for the total key count (8 bytes written to the host after the key scan),
+ * unless the lists fit 2^18 entries whatever the count (batch * n * tiles). The first render of a context sizes the key buffers from that count
  * before enqueueing the rest; later ones enqueue the rest at the buffers'
  * capacity and wait for the count meanwhile, rendering again at the exact size
  * (the same call, still on `stream`) if it did not fit. A batch whose lists

@@ -209,6 +209,10 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
     if (flags & SWF_DETERMINISTIC) {
         // per (list entry, wave) sums, zero where a wave contributes nothing, stored per pair: a pair's entries
         // from its first slot on (the exclusive scan of the key counts), in the row-major order of its tiles
+        if (w.last.uncounted) {
+            if ((s = hip(hipStreamSynchronize(w.last.stream), "stream sync"))) return s;
+            w.count_last();
+        }
         const size_t db = (size_t)w.last.n_keys * 32 * sizeof(float);
         if ((s = w.det.reserve(this, db + 16, st))) return s;
         if (db && (s = hip(hipMemsetAsync(w.det.ptr, 0, db, st), "memset entry sums"))) return s;

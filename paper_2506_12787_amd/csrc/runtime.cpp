@@ -95,6 +95,12 @@ void Buf::release() {
     cap = 0;
 }
 
+void Workspace::count_last() {
+    if (!last.uncounted) return;
+    last.n_keys = *total_host;
+    last.uncounted = false;
+}
+
 static int bits_for(uint64_t m) {
     int b = 0;
     while (b < 64 && (1ull << b) < m) ++b;
@@ -647,6 +653,7 @@ swf_status Ctx::forward_lists(Workspace& w, int sid, const float* tx, int B, int
                              gW == d.W ? 1.0f : (float)((double)gW / d.W), gH == d.H ? 1.0f : (float)((double)gH / d.H));
     if ((uint64_t)B * g.tiles >= (1ull << 31)) return fail(SWF_E_INVALID, "batch * tiles too large");
     w.last.valid = false;
+    w.last.uncounted = false;
     w.last.stream = st;
     // the status words and the culled-pair counters start at zero for every render
     swf_status s = enqueue_preprocess(w, sc, tx, B, flags, g, nullptr, w.status_dev, st);
@@ -657,8 +664,17 @@ swf_status Ctx::forward_lists(Workspace& w, int sid, const float* tx, int B, int
     // binning unless the full 64-bit sort is asked for or the grid has more tiles than a placement block holds
     if (!full && bin_fits(B, d.n, g)) {
         const bool spec = key_cap == 0 && spec_cap > 0 && spec_used;
-        s = lists_binned(w, d, B, g, st, spec ? spec_cap : key_cap, spec);
-        if (spec) *spec_used = true;
+        // Every pair in every tile: lists that fit so many entries whatever the deformation need no count on the
+        // host. The wait for it leaves the GPU idle between small calls (one RSSI query: 51 us with it, 36 without);
+        // on larger ones the lists and the blend run meanwhile, so the buffer is not made larger than this for it.
+        const uint64_t most = (uint64_t)B * (uint64_t)d.n * (uint64_t)g.tiles;
+        if (key_cap == 0 && spec_used && most <= kUncountedEntries && most <= max_list_entries) {
+            s = lists_binned(w, d, B, g, st, std::max<uint64_t>(most, 1), true);
+            w.last.uncounted = true;
+        } else {
+            s = lists_binned(w, d, B, g, st, spec ? spec_cap : key_cap, spec);
+            if (spec) *spec_used = true;
+        }
     } else
         s = lists_sorted(w, d, B, g, full, st, key_cap);
     if (s) return s;
@@ -824,7 +840,7 @@ swf_status Ctx::render(Workspace& w, int sid, const float* tx, int B, int flags,
             keep_acts = true;
         }
     }
-    s = forward_lists(w, sid, tx, B, flags, st, key_cap, spec_cap, &spec, rH, rW);
+    s = forward_lists(w, sid, tx, B, flags, st, key_cap, spec_cap, speculate ? &spec : nullptr, rH, rW);
     w.act_out = nullptr;
     if (s == SWF_E_OVERFLOW && B > 1 && key_cap == 0 && !(flags & SWF_KEEP_AUX)) {
         // more list entries (or pairs) than one launch sequence addresses: the first half of the queries, then
@@ -1086,6 +1102,7 @@ swf_status Ctx::enqueue_mixed(Workspace& w, const MixPlan& p, const float* tx, i
         stage_end(st);
     }
     stage_begin(SWF_STAGE_BLEND, st);
+    w.last.uncounted = false;
     launch_mix_blend(mb, (int)tile_cap, (const uint2*)w.ranges.ptr, svals, w.rec, out, st);
     stage_end(st);
     // the last render, as the status query sees it: one "query" holding every pair of the batch
@@ -1387,6 +1404,7 @@ swf_status swf_debug_keys(swf_ctx* h, uint32_t* counts, uint32_t* offsets, uint6
     Scene* sc = c->scene(c->ws.last.scene);
     if (!sc) return c->fail(SWF_E_STATE, "scene of the last render was released");
     hipDeviceSynchronize();
+    c->ws.count_last();
     const auto& L = c->ws.last;
     const size_t pairs = (size_t)L.B * L.N;
     if (n_keys) *n_keys = L.n_keys;
@@ -1454,6 +1472,7 @@ swf_status swf_last_device_status(swf_ctx* h, swf_device_status* out) {
     if (!w.last.valid) return c->fail(SWF_E_STATE, "no render on this context yet");
     swf_status s;
     if ((s = c->hip(hipStreamSynchronize(w.last.stream), "stream sync"))) return s;
+    w.count_last();
     uint32_t word = 0;
     unsigned long long cull[2] = {0, 0};
     if ((s = c->hip(hipMemcpy(&word, w.status_dev, sizeof(word), hipMemcpyDeviceToHost), "status D2H"))) return s;
@@ -1477,10 +1496,11 @@ swf_status swf_debug_blend_work(swf_ctx* h, uint64_t* evaluations, uint64_t* sta
     CTX_GUARD(c);
     if (!c->ws.last.valid) return c->fail(SWF_E_STATE, "no render to inspect");
     if (!c->scene(c->ws.last.scene)) return c->fail(SWF_E_STATE, "scene of the last render was released");
-    const auto& L = c->ws.last;
-    if (n_entries) *n_entries = L.n_keys;
     swf_status s = c->hip(hipDeviceSynchronize(), "sync");
     if (s) return s;
+    c->ws.count_last();
+    const auto& L = c->ws.last;
+    if (n_entries) *n_entries = L.n_keys;
     if ((s = c->ws.work.reserve(c, 3 * sizeof(unsigned long long), nullptr))) return s;
     unsigned long long* d = (unsigned long long*)c->ws.work.ptr;
     launch_clear_u32((uint32_t*)d, 6, nullptr);

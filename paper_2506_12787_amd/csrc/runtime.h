@@ -43,6 +43,7 @@ struct LastRender {
     int scene = -1, B = 0, N = 0, flags = 0;
     Grid grid{};
     uint64_t n_keys = 0;
+    bool uncounted = false;  // n_keys holds the lists' capacity: the host has not waited for the count
     bool full = false;
     bool binned = false;    // lists built by the binning path (no key array)
     void* keys = nullptr;
@@ -80,7 +81,11 @@ struct Workspace {
     }
     swf_status init(Ctx* c);
     void release();
+    void count_last();  // the last render's key count, if it was not waited for; its stream must have finished
 };
+
+// Entries up to which a render's lists are sized for every pair in every tile (1 MiB) instead of by their count.
+constexpr uint64_t kUncountedEntries = 1ull << 18;
 
 // What a render with SWF_KEEP_AUX wrote into a caller's aux buffer: the
 // backward re-runs that forward pass and must see the same scene parameters.
