@@ -91,3 +91,18 @@ def test_invalid_arguments(ctx):
     with pytest.raises(B.SwfError):
         ctx.beamscan(p, c, 90, 5000)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("side", range(1, 9))
+@pytest.mark.parametrize("nb,L,H,W", [(1, 1, 1, 1), (7, 33, 5, 13), (9, 64, 16, 8), (65, 65, 3, 43), (33, 31, 8, 65)])
+def test_query_pixel_and_path_remainders(ctx, side, nb, L, H, W):
+    # queries around the tiles of 8 and the blocks of 32 and 64, pixels around the 16-pixel tiles, the 32 of a wave
+    # and the 128 of a block, paths around the 32 of a pass; every array size
+    r = np.random.default_rng(100 * side + nb)
+    paths = np.stack([r.uniform(0.1, 1.0, (nb, L)), r.uniform(0, 2 * np.pi, (nb, L)),
+                      r.uniform(0, 0.5 * np.pi, (nb, L))], 2).astype(np.float32)
+    counts = r.integers(0, L + 1, nb).astype(np.int32)
+    counts[-1] = L
+    p, c = _dev(paths, counts)
+    got = ctx.beamscan(p, c, H, W, side=side, spacing_over_lambda=0.5).cpu().numpy()
+    _check(got, paths, counts, H, W, side, 0.5)
