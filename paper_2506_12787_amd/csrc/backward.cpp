@@ -18,8 +18,10 @@ namespace swf {
 // one rounding) and the 256 x 256 products run on BF16 matrix cores with FP32
 // accumulation; FP32: the products run on the FP32 matrix cores (gemm.hip).
 // Weight and bias gradients are accumulated in FP32 either way.
+// Only the rows of rg (pairs with a gradient, in groups of 32) are taken: a row whose dy is zero has zero dz in every
+// layer.
 swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, int B, const float* dy,
-                             const swf_grads* gr, bool bf16, hipStream_t st) {
+                             const RowGroups& rg, const swf_grads* gr, bool bf16, hipStream_t st) {
     swf_status s = SWF_OK;
     const int64_t N = d.n, P = (int64_t)B * N;
     const int nh = d.n_hidden, Hd = 256, I = d.in_dim;
@@ -34,13 +36,10 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     const size_t n_split = std::max({gemm_part_floats(Hd, Hd, P), gemm_part_floats(kOut, Hd, P),
                                      gemm_part_floats(Hd, kMeanFeat, N), gemm_part_floats(Hd, kTxFeat, B),
                                      (size_t)layer1_sums_blocks((int)N) * B * Hd,
-                                     (size_t)layer1_grad_blocks((int)N) * B * Hd,
-                                     (size_t)wgrad_mfma_blocks(P) * (Hd * Hd + Hd),
-                                     (size_t)wgrad_out_blocks(P) * kOut * Hd, (size_t)dz_f32_blocks(P) * Hd});
+                                     (size_t)layer1_grad_blocks((int)N) * B * Hd, wgrad_mfma_floats(P),
+                                     out_bwd_floats(P), (size_t)dz_f32_blocks(P) * Hd});
     const size_t n_cs = std::max<size_t>({(size_t)colsum_blocks(P) * Hd, (size_t)colsum_blocks(B) * N * Hd,
-                                          (size_t)colsum_blocks(N) * Hd * B,
-                                          (size_t)colsum_blocks(wgrad_mfma_blocks(P)) * (Hd * Hd + Hd),
-                                          (size_t)colsum_blocks(wgrad_out_blocks(P)) * kOut * Hd});
+                                          (size_t)colsum_blocks(N) * Hd * B});
     const size_t n_wb = bf16 ? ((size_t)(nh - 1) * Hd * Hd + (size_t)kOut * Hd + (size_t)P * kOut + 64) / 2 + 64 : 0;
     const size_t n_wt = bf16 ? 0 : (size_t)(nh - 1) * Hd * Hd;  // FP32: W^T of the 256 x 256 layers, fragment-major
     const size_t small =
@@ -60,65 +59,48 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     float* dg = R + (size_t)B * Hd;              // N x 26
     float* part = dg + ((size_t)N * kMeanFeat + 3) / 4 * 4;  // split-K partials (16-byte aligned)
     float* tmp = part + n_split;                 // column-sum partials
-    uint16_t* wb = (uint16_t*)(tmp + n_cs);      // BF16 weights: hidden layers 1.., output, then dy
+    uint16_t* wb = (uint16_t*)(((uintptr_t)(tmp + n_cs) + 15) & ~(uintptr_t)15);  // BF16 weights (launch_pack_bwd), then dy
     float* wt = (float*)(((uintptr_t)(tmp + n_cs + n_wb) + 15) & ~(uintptr_t)15);  // FP32 W^T, 16-byte aligned
     float* fmean = (float*)w.fmean.ptr, *ftx = (float*)w.ftx.ptr, *qs = (float*)w.qs.ptr;
     launch_tx_features(d, tx, B, qs, nullptr, st, ftx);
     launch_mean_features_f32(d, fmean, st);
     uint16_t* wl[8] = {};
-    uint16_t* dyb = nullptr;
     if (bf16) {
-        for (int l = 1; l < nh; ++l) {
-            wl[l] = wb + (size_t)(l - 1) * Hd * Hd;
-            launch_to_bf16(d.w[l], (int64_t)Hd * Hd, wl[l], st);
-        }
-        wl[nh] = wb + (size_t)(nh - 1) * Hd * Hd;
-        launch_to_bf16(d.w[nh], (int64_t)kOut * Hd, wl[nh], st);
-        if (nh == 1) {  // the single-hidden-layer path multiplies BF16 dy by the BF16 output weights
-            dyb = wl[nh] + (size_t)kOut * Hd;
-            launch_to_bf16(dy, P * kOut, dyb, st);
-        }
+        for (int l = 1; l <= nh; ++l) wl[l] = wb + (size_t)(l - 1) * Hd * Hd;
+        launch_pack_bwd(d.w, nh, wb, st);
     } else {
         for (int l = 1; l < nh; ++l) launch_pack_wt(d.w[l], wt + (size_t)(l - 1) * Hd * Hd, st);
     }
-    // ---- output layer (7 outputs)
-    if (bf16) {
-        // one pass over the last activations: the weight gradient and, with more than one hidden layer, the
-        // masked BF16 gradient of the last hidden pre-activations (K = 7)
-        launch_out_bwd_bf16(dy, wl[nh], act[nh - 1], P, nh > 1 ? dz[0] : nullptr, part, tmp, gr->weight[nh], st);
-    } else if (gr->weight[nh]) {
-        launch_gemm_f32(true, false, kOut, Hd, P, dy, kOut, act[nh - 1], Hd, gr->weight[nh], Hd, part, st);
-    }
-    if (gr->bias[nh]) launch_colsum(dy, P, kOut, 1, 0, tmp, gr->bias[nh], 0, st);
-    if (bf16) {
-        if (nh == 1)  // the layer-1 gradient before its ReLU mask (applied inside its sums below)
-            launch_gemm_f32(false, false, P, Hd, kOut, dyb, kOut, wl[nh], Hd, zf, Hd, part, st, nullptr, 0, true);
-    } else {
-        launch_gemm_f32(false, false, P, Hd, kOut, dy, kOut, d.w[nh], Hd, (float*)dz[0], Hd, part, st,
-                        (const float*)act[nh - 1], Hd);
+    // ---- output layer (7 outputs): one pass over the last activations gives its weight and bias gradients and the
+    // masked gradient of the last hidden pre-activations (K = 7); BF16 with one hidden layer forms that one below,
+    // in FP32 and before its ReLU mask (applied inside the layer-1 sums)
+    launch_out_bwd(bf16, dy, bf16 ? (const void*)wl[nh] : d.w[nh], act[nh - 1], P, rg, need_zf ? nullptr : dz[0], part,
+                   gr->weight[nh], gr->bias[nh], st);
+    if (need_zf) {
+        uint16_t* dyb = wl[nh] + (size_t)kOut * Hd;
+        launch_to_bf16(dy, P * kOut, dyb, st);
+        launch_gemm_f32(false, false, P, Hd, kOut, dyb, kOut, wl[nh], Hd, zf, Hd, part, st, nullptr, 0, true);
     }
     int cur = 0;
     const void* dz1 = nullptr;  // BF16: the second layer's pre-activation gradient
     for (int l = nh - 1; l >= 1; --l) {
-        if (gr->weight[l]) {
-            if (bf16)  // contraction over pairs; the bias gradient (column sums of dz) rides along
-                launch_wgrad_mfma(dz[cur], act[l - 1], P, part, tmp, gr->weight[l], gr->bias[l], st);
-            else
-                launch_gemm_f32(true, false, Hd, Hd, P, dz[cur], Hd, act[l - 1], Hd, gr->weight[l], Hd, part, st);
-        }
-        if (bf16 && gr->bias[l] && !gr->weight[l]) launch_colsum_bf16(dz[cur], P, Hd, 1, 0, tmp, gr->bias[l], 0, st);
         if (bf16) {
+            // contraction over pairs; the bias gradient (column sums of dz) rides along
+            launch_wgrad_mfma(dz[cur], act[l - 1], P, rg, part, gr->weight[l], gr->bias[l], st);
             // dz W on MFMA in one pass, BF16 and masked by the previous ReLU; the layer-1 gradient is formed
             // inside its sums below
             if (l > 1)
-                launch_dz_gemm(dz[cur], wl[l], act[l - 1], P, dz[cur ^ 1], false, st);
+                launch_dz_gemm(dz[cur], wl[l], act[l - 1], P, rg, dz[cur ^ 1], st);
             else
                 dz1 = dz[cur];
         } else {
+            if (gr->weight[l])
+                launch_gemm_f32(true, false, Hd, Hd, P, dz[cur], Hd, act[l - 1], Hd, gr->weight[l], Hd, part, st,
+                                nullptr, 0, false, &rg);
             // the input gradient on the FP32 matrix cores with the layer's W^T as register-fed weights, masked;
             // the bias gradient's per-block column sums of dz ride along (into the split-K space, free again)
             float* bp = gr->bias[l] ? part : nullptr;
-            launch_dz_f32((const float*)dz[cur], wt + (size_t)(l - 1) * Hd * Hd, (const float*)act[l - 1], P,
+            launch_dz_f32((const float*)dz[cur], wt + (size_t)(l - 1) * Hd * Hd, (const float*)act[l - 1], P, rg,
                           (float*)dz[cur ^ 1], bp, st);
             if (bp) launch_colsum(bp, dz_f32_blocks(P), Hd, 1, 0, tmp, gr->bias[l], 0, st);
         }
@@ -126,21 +108,23 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     }
     // ---- layer 1: the gradient of its pre-activations dz0, FP32; S = its sum over the batch per Gaussian
     // (N x 256), R = its sum over the Gaussians per query (B x 256), b0 = its sum over all pairs
-    if (bf16) {
-        if (dz1) {
-            // dz0 = (dz1 W1) masked, never stored: one pass gives S and per-block partial sums of R
-            launch_layer1_grad(dz1, wl[1], act[0], (int)B, (int)N, S, part, st);
-            if (gr->weight[0]) launch_colsum(part, layer1_grad_blocks((int)N), B * Hd, 1, 0, tmp, R, 0, st);
-        } else {
-            // one hidden layer: zf is dz0 before the ReLU mask
-            launch_layer1_sums(zf, act[0], (int)B, (int)N, S, part, st);
-            if (gr->weight[0]) launch_colsum(part, layer1_sums_blocks((int)N), B * Hd, 1, 0, tmp, R, 0, st);
-        }
+    int rblocks = 0;  // slices of the sums over Gaussians
+    if (dz1) {
+        // dz0 = (dz1 W1) masked, never stored: one pass gives S and per-block partial sums of R
+        launch_layer1_grad(dz1, wl[1], act[0], (int)B, (int)N, rg, S, part, st);
+        rblocks = layer1_grad_blocks((int)N);
     } else {
-        // dz0 carries layer 1's ReLU mask already (applied where it was formed): one pass gives S and per-block
-        // partial sums of R
-        launch_layer1_sums((const float*)dz[cur], nullptr, (int)B, (int)N, S, part, st);
-        if (gr->weight[0]) launch_colsum(part, layer1_sums_blocks((int)N), B * Hd, 1, 0, tmp, R, 0, st);
+        // BF16 with one hidden layer: zf is dz0 before the ReLU mask. FP32: dz0 carries layer 1's ReLU mask already
+        // (applied where it was formed). One pass gives S and per-block partial sums of R
+        launch_layer1_sums(need_zf ? zf : (const float*)dz[cur], need_zf ? act[0] : nullptr,
+                           need_zf ? nullptr : rg.bits, (int)B, (int)N, S, part, st);
+        rblocks = layer1_sums_blocks((int)N);
+    }
+    if (gr->weight[0]) {
+        if (rblocks <= 512)
+            launch_slice_sum(part, rblocks, (int64_t)B * Hd, R, st);
+        else
+            launch_colsum(part, rblocks, (int64_t)B * Hd, 1, 0, tmp, R, 0, st);
     }
     if (gr->bias[0]) launch_colsum(S, N, Hd, 1, 0, tmp, gr->bias[0], 0, st);  // b0: the sum of S over Gaussians
     if (gr->weight[0]) {
@@ -232,16 +216,17 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
     if (want_mlp) {
         if ((s = w.dy.reserve(this, (size_t)P * kOut * sizeof(float) + 16, st))) return s;
         dy = (float*)w.dy.ptr;
+        if ((s = w.groups.reserve(this, row_group_words(P) * sizeof(uint32_t), st))) return s;
     }
     stage_begin(SWF_STAGE_BWD_PREPROCESS, st);
     launch_preprocess_backward((const float*)w.dpair.ptr, w.rec, P, (flags & SWF_PAPER_DEFORM) != 0,
-                               (float*)w.dbase.ptr, dy, st);
+                               (float*)w.dbase.ptr, dy, (uint32_t*)w.groups.ptr, st);
     stage_end(st);
     // 4. MLP backward (the forward's activations; BF16 operands after a BF16 forward)
     float* dmu = nullptr;
     if (want_mlp) {
         stage_begin(SWF_STAGE_BWD_MLP, st);
-        s = mlp_backward(w, d, tx, B, dy, gr, bf16, st);
+        s = mlp_backward(w, d, tx, B, dy, row_groups((uint32_t*)w.groups.ptr, P), gr, bf16, st);
         last_mlp_bwd.valid = s == SWF_OK;
         last_mlp_bwd.scene = sid;
         last_mlp_bwd.B = B;

@@ -253,14 +253,24 @@ __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint
 
 // d(mean, M, opacity, amp) -> d(residual coordinates); the unmasked result
 // feeds the base parameters, the masked one (paper mode zeroes 2..4) the MLP.
-__global__ void preprocess_backward_kernel(const float* __restrict__ dpair, const float4* __restrict__ wm,
-                                           const float2* __restrict__ oa, const uint32_t* __restrict__ count,
-                                           int64_t P, int paper_mask, float* __restrict__ dbase,
-                                           float* __restrict__ dy) {
+//
+// With dy also which rows (pairs) have a gradient at all: bits[w] bit k is set
+// if row 32 w + k has a non-zero dy, or a non-finite residual (whose hidden
+// activations may not be finite: a zero gradient times those is no zero), and
+// groups[block] counts the block's groups of 32 rows with a set bit. Rows
+// behind the pixels' termination depth or outside every pixel's cutoff have
+// none: at N = 50k, 90 x 360, five of six.
+__global__ __launch_bounds__(256) void preprocess_backward_kernel(
+    const float* __restrict__ dpair, const float4* __restrict__ wm, const float2* __restrict__ oa,
+    const uint32_t* __restrict__ count, const uint2* __restrict__ rect, int64_t P, int paper_mask,
+    float* __restrict__ dbase, float* __restrict__ dy, uint32_t* __restrict__ bits, uint32_t* __restrict__ groups) {
+    __shared__ uint32_t s_n;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P) return;
+    const bool in = i < P;
     float r[kOut] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (count[i]) {
+    bool live = false;
+    if (in && count[i] == 0) live = rect[i].y == kCullNonFinite;
+    if (in && count[i]) {
         const float* g = dpair + i * 8;
         const float4 m = wm[i];
         const float op = oa[i].x;
@@ -272,12 +282,61 @@ __global__ void preprocess_backward_kernel(const float* __restrict__ dpair, cons
         r[5] = g[6] * op * (1.0f - op);
         r[6] = g[7];
     }
+    if (in) {
 #pragma unroll
-    for (int k = 0; k < kOut; ++k) dbase[i * kOut + k] = r[k];
-    if (dy) {
-#pragma unroll
-        for (int k = 0; k < kOut; ++k) dy[i * kOut + k] = (paper_mask && k >= 2 && k <= 4) ? 0.f : r[k];
+        for (int k = 0; k < kOut; ++k) dbase[i * kOut + k] = r[k];
     }
+    if (!dy) return;  // kernel-uniform
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    if (in) {
+#pragma unroll
+        for (int k = 0; k < kOut; ++k) {
+            const float v = (paper_mask && k >= 2 && k <= 4) ? 0.f : r[k];
+            dy[i * kOut + k] = v;
+            live = live || !(v == 0.f);
+        }
+    }
+    const uint64_t m = __ballot(live);
+    if ((lane_id() & 31u) == 0 && in) {
+        const uint32_t w = lane_id() ? (uint32_t)(m >> 32) : (uint32_t)m;
+        bits[i >> 5] = w;
+        if (w) atomicAdd(&s_n, 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) groups[blockIdx.x] = s_n;
+}
+
+// The groups of 32 rows with a gradient, in row order: list[0 .. count). Block
+// k takes 1024 groups (128 blocks of the pass above, whose counts give its
+// first position).
+__global__ __launch_bounds__(1024) void row_groups_kernel(const uint32_t* __restrict__ bits,
+                                                          const uint32_t* __restrict__ groups, int64_t n_groups,
+                                                          uint32_t* __restrict__ list, uint32_t* __restrict__ count) {
+    __shared__ uint32_t s_sum[16];
+    const int w = (int)threadIdx.x >> 6;
+    uint32_t before = 0;
+    for (int64_t j = threadIdx.x; j < (int64_t)blockIdx.x * 128; j += 1024) before += groups[j];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    if (lane_id() == 0) s_sum[w] = before;
+    __syncthreads();
+    uint32_t base = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) base += s_sum[k];
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    const bool f = i < n_groups && bits[i] != 0u;
+    const uint64_t m = __ballot(f);
+    if (lane_id() == 0) s_sum[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    uint32_t all = base;
+    for (int k = 0; k < 16; ++k) {
+        if (k < w) base += s_sum[k];
+        all += s_sum[k];
+    }
+    if (f) list[base + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull))] = (uint32_t)i;
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *count = all;
 }
 
 // Base-parameter gradients: sum over the batch, scatter to original ids.
@@ -394,6 +453,50 @@ __global__ __launch_bounds__(256) void colsum8_stage2_kernel(const float* __rest
     out[(int64_t)blockIdx.y * out_bs + c] = t;
 }
 
+// Sums of nb slices of a launch's partial results, slices in a fixed order:
+// out0[c] (c < n0) and out1[c - n0] = sum over j of part[j * stride + c]. 16
+// threads of four columns by 16 groups of slices, summed through LDS.
+// Destinations may be NULL.
+__global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict__ part, int nb, int64_t stride,
+                                                        int64_t n0, int64_t n1, float* __restrict__ out0,
+                                                        float* __restrict__ out1) {
+    __shared__ float4 red[16][16];
+    const int cx = (int)threadIdx.x & 15, gy = (int)threadIdx.x >> 4;
+    const int64_t c = (int64_t)blockIdx.x * 64 + 4 * cx;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c < n0 + n1) {
+#pragma unroll 4
+        for (int j = gy; j < nb; j += 16) {
+            const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)j * stride + c);
+            s.x += v.x;
+            s.y += v.y;
+            s.z += v.z;
+            s.w += v.w;
+        }
+    }
+    red[gy][cx] = s;
+    __syncthreads();
+    if (gy != 0 || c >= n0 + n1) return;
+#pragma unroll
+    for (int k = 1; k < 16; ++k) {
+        const float4 v = red[k][cx];
+        s.x += v.x;
+        s.y += v.y;
+        s.z += v.z;
+        s.w += v.w;
+    }
+    const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t e = c + k;
+        if (e < n0) {
+            if (out0) out0[e] = v[k];
+        } else if (e < n0 + n1 && out1) {
+            out1[e - n0] = v[k];
+        }
+    }
+}
+
 __global__ void fill_kernel(float* __restrict__ p, float v, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -426,56 +529,66 @@ __global__ void pe_chain_kernel(const float* __restrict__ dgm, const float* __re
 // ---- BF16 variants (the MLP backward of a BF16 forward) ----------------------
 __device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }  // round to nearest even
 
+// The BF16 weights of the backward, from the FP32 masters w[l] (row-major
+// [out][in]): per 256 x 256 layer l = 1 .. n - 1 the MFMA fragments of W as the
+// kernels below take them (fragment (t, c), lane 16 g + r, element j =
+// W[32 c + 8 g + j][16 t + r]; 65536 values), then the output layer's 7 x 256.
+struct BwdWeights {
+    const float* w[8];
+    int n;
+};
+__global__ __launch_bounds__(256) void pack_bwd_kernel(BwdWeights a, __bf16* __restrict__ out) {
+    const int e = (int)(blockIdx.x * 256 + threadIdx.x);
+    const int hid = (a.n - 1) * 65536;
+    if (e < hid) {
+        const int l = e >> 16, f = (e >> 9) & 127, ln = (e >> 3) & 63, j = e & 7;
+        const int t = f >> 3, c = f & 7, g = ln >> 4, r = ln & 15;
+        out[e] = to_bf16(a.w[1 + l][(size_t)(32 * c + 8 * g + j) * 256 + 16 * t + r]);
+    } else if (e < hid + kOut * 256) {
+        out[e] = to_bf16(a.w[a.n][e - hid]);
+    }
+}
+
 // Input gradient of a 256 x 256 layer on BF16 MFMA (v_mfma_f32_16x16x32_bf16,
-// FP32 accumulation): out[p][i] = sum_o dz[p][o] W[o][i] for every pair p, W
-// row-major [o][i] (the layer's [out][in] weights). kF32: FP32 result (the
-// layer-1 gradient, masked later inside its sums). Otherwise the result is
-// rounded to BF16 and zeroed where act[p][i] (the BF16 activation) is not > 0,
-// the previous layer's ReLU: one pass instead of a library GEMM and a masking
-// pass. The whole W sits in LDS in MFMA A-fragment order (fragment (t, c), lane
-// 16 g + r, element j = W[32 c + 8 g + j][16 t + r]). Each wave takes groups of
-// kDzPairs pairs: their dz rows are the B operands, in registers (16 bytes per
-// lane per 32-wide k chunk), the ReLU masks a per-wave bitmap in LDS; the next
-// group's rows and activations are loaded while the current one is computed,
-// and 16 x 16 output tiles are written as they finish.
+// FP32 accumulation): out[p][i] = sum_o dz[p][o] W[o][i] for the rows p of the
+// listed groups, rounded to BF16 and zeroed where act[p][i] (the BF16
+// activation) is not > 0, the previous layer's ReLU. The whole W sits in LDS in
+// MFMA A-fragment order (pack_bwd_kernel's). Each wave takes groups of 32 pairs:
+// their dz rows are the B operands, in registers (16 bytes per lane per 32-wide k
+// chunk), the ReLU masks a per-wave bitmap in LDS; the next group's rows and
+// activations are loaded while the current one is computed, and 16 x 16 output
+// tiles are written as they finish.
 constexpr int kDzWaves = 8;
 constexpr int kDzNcb = 2;
 constexpr int kDzPairs = 16 * kDzNcb;
+static_assert(kDzPairs == kRowGroup, "a wave takes one group of rows");
 
 typedef __bf16 dz_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float dz_f32x4 __attribute__((ext_vector_type(4)));
 typedef float dz_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 dz_bf16x2 __attribute__((ext_vector_type(2)));
 
-template <bool kF32>
 __global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __restrict__ dz,
-                                                                const __bf16* __restrict__ W,
+                                                                const uint4* __restrict__ wf,
                                                                 const __bf16* __restrict__ act, int64_t P,
-                                                                void* __restrict__ out) {
+                                                                RowGroups rg, __bf16* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) uint4 s_a[16 * 8 * 64];  // 128 fragments of 1 KiB
-    __shared__ uint8_t s_m[kF32 ? 1 : kDzWaves][kDzPairs][32];        // ReLU mask bits, pair-major
-    const uint16_t* Wb = reinterpret_cast<const uint16_t*>(W);
-    for (int e = threadIdx.x; e < 16 * 8 * 64; e += 64 * kDzWaves) {
-        const int f = e >> 6, l = e & 63, t = f >> 3, c = f & 7, g = l >> 4, r = l & 15;
-        const uint16_t* col = Wb + (size_t)(32 * c + 8 * g) * 256 + 16 * t + r;
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = (uint32_t)col[(2 * q) * 256] | ((uint32_t)col[(2 * q + 1) * 256] << 16);
-        s_a[e] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+    __shared__ uint8_t s_m[kDzWaves][kDzPairs][32];                   // ReLU mask bits, pair-major
+    const int64_t groups = (int64_t)*rg.count;
+    if ((int64_t)blockIdx.x * kDzWaves >= groups) return;  // block-uniform
+    for (int e = threadIdx.x; e < 16 * 8 * 64; e += 64 * kDzWaves) s_a[e] = wf[e];
     __syncthreads();
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), g = lane >> 4, n = lane & 15;
-    const int64_t groups = (P + kDzPairs - 1) / kDzPairs;
     const int64_t stride = (int64_t)gridDim.x * kDzWaves;
-    // rows (B layout: pair cb*16 + n, k = 32 c + 8 g + j) of group q; zero past P
+    // rows (B layout: pair cb*16 + n, k = 32 c + 8 g + j) of listed group q; zero past P
     auto load_rows = [&](const __bf16* src, int64_t q, dz_bf16x8 (&dst)[8][kDzNcb]) {
+        const int64_t first = q < groups ? (int64_t)rg.list[q] * kDzPairs : P;
 #pragma unroll
         for (int cb = 0; cb < kDzNcb; ++cb) {
-            const int64_t p = q * kDzPairs + cb * 16 + n;
+            const int64_t p = first + cb * 16 + n;
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                dst[c][cb] = (q < groups && p < P) ? *reinterpret_cast<const dz_bf16x8*>(src + p * 256 + 32 * c + 8 * g)
-                                                   : dz_bf16x8{};
+                dst[c][cb] = p < P ? *reinterpret_cast<const dz_bf16x8*>(src + p * 256 + 32 * c + 8 * g) : dz_bf16x8{};
         }
     };
     // mask byte of 8 activations (bit j set where element j is > 0)
@@ -494,20 +607,18 @@ __global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __
 #pragma unroll
         for (int cb = 0; cb < kDzNcb; ++cb)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) s_m[kF32 ? 0 : wave][cb * 16 + n][4 * c + g] = mask_byte(a[c][cb]);
+            for (int c = 0; c < 8; ++c) s_m[wave][cb * 16 + n][4 * c + g] = mask_byte(a[c][cb]);
         __builtin_amdgcn_wave_barrier();
     };
     int64_t grp = (int64_t)blockIdx.x * kDzWaves + wave;
     dz_bf16x8 b[8][kDzNcb], bn[8][kDzNcb], an[8][kDzNcb];
     load_rows(dz, grp, b);
-    if (!kF32) {
-        load_rows(act, grp, an);
-        store_masks(an);
-    }
+    load_rows(act, grp, an);
+    store_masks(an);
     for (; grp < groups; grp += stride) {
-        const int64_t p0 = grp * kDzPairs;
+        const int64_t p0 = (int64_t)rg.list[grp] * kDzPairs;
         load_rows(dz, grp + stride, bn);  // the next group, while this one is computed
-        if (!kF32) load_rows(act, grp + stride, an);
+        load_rows(act, grp + stride, an);
 #pragma unroll 1
         for (int t = 0; t < 16; ++t) {
             dz_f32x4 acc[kDzNcb];
@@ -524,26 +635,18 @@ __global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __
             for (int cb = 0; cb < kDzNcb; ++cb) {
                 const int64_t p = p0 + cb * 16 + n;
                 if (p >= P) continue;
-                if (kF32) {
-                    *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + p * 256 + 16 * t + 4 * g) =
-                        make_float4(acc[cb][0], acc[cb][1], acc[cb][2], acc[cb][3]);
-                } else {
-                    // features 16 t + 4 g + 0..3: bits 4 (g & 1) + 0..3 of mask byte 2 t + g / 2
-                    const uint32_t nib = ((uint32_t)s_m[wave][cb * 16 + n][2 * t + (g >> 1)] >> (4 * (g & 1))) & 15u;
-                    const dz_f32x2 lo2 = {acc[cb][0], acc[cb][1]}, hi2 = {acc[cb][2], acc[cb][3]};
-                    uint32_t v0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, dz_bf16x2));
-                    uint32_t v1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, dz_bf16x2));
-                    v0 &= ((nib & 1u) ? 0x0000ffffu : 0u) | ((nib & 2u) ? 0xffff0000u : 0u);
-                    v1 &= ((nib & 4u) ? 0x0000ffffu : 0u) | ((nib & 8u) ? 0xffff0000u : 0u);
-                    *reinterpret_cast<uint2*>(reinterpret_cast<__bf16*>(out) + p * 256 + 16 * t + 4 * g) =
-                        make_uint2(v0, v1);
-                }
+                // features 16 t + 4 g + 0..3: bits 4 (g & 1) + 0..3 of mask byte 2 t + g / 2
+                const uint32_t nib = ((uint32_t)s_m[wave][cb * 16 + n][2 * t + (g >> 1)] >> (4 * (g & 1))) & 15u;
+                const dz_f32x2 lo2 = {acc[cb][0], acc[cb][1]}, hi2 = {acc[cb][2], acc[cb][3]};
+                uint32_t v0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, dz_bf16x2));
+                uint32_t v1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, dz_bf16x2));
+                v0 &= ((nib & 1u) ? 0x0000ffffu : 0u) | ((nib & 2u) ? 0xffff0000u : 0u);
+                v1 &= ((nib & 4u) ? 0x0000ffffu : 0u) | ((nib & 8u) ? 0xffff0000u : 0u);
+                *reinterpret_cast<uint2*>(out + p * 256 + 16 * t + 4 * g) = make_uint2(v0, v1);
             }
         }
-        if (!kF32) {
-            __builtin_amdgcn_wave_barrier();  // this group's mask reads come before the next group's writes
-            store_masks(an);
-        }
+        __builtin_amdgcn_wave_barrier();  // this group's mask reads come before the next group's writes
+        store_masks(an);
 #pragma unroll
         for (int c = 0; c < 8; ++c)
 #pragma unroll
@@ -552,7 +655,9 @@ __global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __
 }
 
 // Layer-1 gradient of a BF16 backward without storing it. For the block's
-// Gaussians n0 .. n0 + kL1Rows - 1 and every query b in order: z[b][n] =
+// Gaussians (wave w: 16 from 16 (w gridDim + block) on, so that the front of the
+// depth order, where the rows with a gradient are, is dealt over all blocks) and
+// every query b in order, skipped by a wave none of whose rows has one: z[b][n] =
 // dz1[b][n] W (FP32 accumulation on MFMA; dz1 [B][N][256] BF16, the gradient of
 // the second layer's pre-activations; W its 256 x 256 BF16 weights, row-major
 // [out][in]), masked by act[b][n] > 0 (the layer-1 ReLU), gives S[n][:] = the sum
@@ -565,32 +670,29 @@ constexpr int kL1Waves = 8;
 constexpr int kL1Rows = 16 * kL1Waves;
 
 __global__ __launch_bounds__(64 * kL1Waves) void layer1_grad_kernel(const __bf16* __restrict__ dz1,
-                                                                    const __bf16* __restrict__ W,
+                                                                    const uint4* __restrict__ wf,
                                                                     const __bf16* __restrict__ act, int B, int N,
+                                                                    const uint32_t* __restrict__ bits,
                                                                     float* __restrict__ S,
                                                                     float* __restrict__ Rpart) {
     __shared__ __attribute__((aligned(16))) uint4 s_a[16 * 8 * 64];
     __shared__ uint8_t s_m[kL1Waves][16][32];  // ReLU mask bits of the wave's 16 pairs, current query
     __shared__ float s_r[kL1Waves][256];        // per-wave R partial, current query
-    const uint16_t* Wb = reinterpret_cast<const uint16_t*>(W);
-    for (int e = threadIdx.x; e < 16 * 8 * 64; e += 64 * kL1Waves) {
-        const int f = e >> 6, l = e & 63, t = f >> 3, c = f & 7, g = l >> 4, r = l & 15;
-        const uint16_t* col = Wb + (size_t)(32 * c + 8 * g) * 256 + 16 * t + r;
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = (uint32_t)col[(2 * q) * 256] | ((uint32_t)col[(2 * q + 1) * 256] << 16);
-        s_a[e] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+    for (int e = threadIdx.x; e < 16 * 8 * 64; e += 64 * kL1Waves) s_a[e] = wf[e];
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), g = lane >> 4, r = lane & 15;
-    const int nw = blockIdx.x * kL1Rows + wave * 16;  // the wave's first Gaussian
+    const int nw = (wave * (int)gridDim.x + (int)blockIdx.x) * 16;  // the wave's first Gaussian
     const int na = nw + r;                            // this lane's A row
-    // dz1 or act row of this lane's A row for query b (B layout of dz_gemm: k = 32 c + 8 g + j); zero past N
-    auto load_rows = [&](const __bf16* src, int b, dz_bf16x8 (&dst)[8]) {
+    // whether this lane's A row of query b has a gradient (rows without one were never written)
+    auto row_live = [&](int b) {
+        const int64_t p = (int64_t)b * N + na;
+        return b < B && na < N && ((bits[p >> 5] >> (p & 31)) & 1u);
+    };
+    // dz1 or act row of this lane's A row for query b (B layout of dz_gemm: k = 32 c + 8 g + j); zero if not live
+    auto load_rows = [&](const __bf16* src, int b, bool live, dz_bf16x8 (&dst)[8]) {
         const int64_t p = (int64_t)b * N + na;
 #pragma unroll
         for (int c = 0; c < 8; ++c)
-            dst[c] = (b < B && na < N) ? *reinterpret_cast<const dz_bf16x8*>(src + p * 256 + 32 * c + 8 * g)
-                                       : dz_bf16x8{};
+            dst[c] = live ? *reinterpret_cast<const dz_bf16x8*>(src + p * 256 + 32 * c + 8 * g) : dz_bf16x8{};
     };
     auto store_masks = [&](const dz_bf16x8 (&a)[8]) {
 #pragma unroll
@@ -608,16 +710,29 @@ __global__ __launch_bounds__(64 * kL1Waves) void layer1_grad_kernel(const __bf16
         __builtin_amdgcn_wave_barrier();
     };
     dz_bf16x8 a_cur[8], a_nxt[8], m_nxt[8];
-    load_rows(dz1, 0, a_cur);
-    load_rows(act, 0, m_nxt);
+    bool live = row_live(0), any = __ballot(live) != 0ull;  // any: wave-uniform
+    load_rows(dz1, 0, live, a_cur);
+    load_rows(act, 0, live, m_nxt);
     store_masks(m_nxt);
+    for (int k = lane; k < 256; k += 64) s_r[wave][k] = 0.f;
+    bool dirty = false;  // s_r of this wave holds a query's sums
     __syncthreads();  // s_a complete
     dz_f32x4 sacc[16];
 #pragma unroll
     for (int t = 0; t < 16; ++t) sacc[t] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
     for (int b = 0; b < B; ++b) {
-        load_rows(dz1, b + 1, a_nxt);  // the next query's rows while this one is computed
-        load_rows(act, b + 1, m_nxt);
+        live = row_live(b + 1);
+        const bool next = __ballot(live) != 0ull;
+        if (next) {  // the next query's rows while this one is computed
+            load_rows(dz1, b + 1, live, a_nxt);
+            load_rows(act, b + 1, live, m_nxt);
+        }
+        if (!any && dirty) {
+            for (int k = lane; k < 256; k += 64) s_r[wave][k] = 0.f;
+            dirty = false;
+        }
+        if (any) dirty = true;
+        if (any)
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
             dz_f32x4 acc = dz_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -645,9 +760,12 @@ __global__ __launch_bounds__(64 * kL1Waves) void layer1_grad_kernel(const __bf16
             for (int w = 0; w < kL1Waves; ++w) v += s_r[w][k];
             Rpart[((size_t)blockIdx.x * B + b) * 256 + k] = v;
         }
-        store_masks(m_nxt);  // this wave's reads of the query-b masks are complete
+        any = next;
+        if (next) {
+            store_masks(m_nxt);  // this wave's reads of the query-b masks are complete
 #pragma unroll
-        for (int c = 0; c < 8; ++c) a_cur[c] = a_nxt[c];
+            for (int c = 0; c < 8; ++c) a_cur[c] = a_nxt[c];
+        }
         __syncthreads();  // s_r is rewritten for the next query
     }
 #pragma unroll
@@ -660,40 +778,42 @@ __global__ __launch_bounds__(64 * kL1Waves) void layer1_grad_kernel(const __bf16
 }
 
 // Weight gradient of a 256 x 256 layer on BF16 MFMA over one slice of pairs:
-// part[blk][o][i] = sum over the slice's pairs p of dz[p][o] act[p][i] (dz, act
-// [P][256] BF16; FP32 accumulation); the caller adds the slices. The
+// part[blk][o][i] = sum over the pairs p of every gridDim-th listed group of
+// dz[p][o] act[p][i] (dz, act [P][256] BF16; FP32 accumulation); the caller adds
+// the slices. The
 // contraction runs over pairs, so both operands are staged through LDS
 // transposed, feature-major, 32 pairs at a time (rows padded to 80 bytes: the
 // 16-byte fragment reads of 16 consecutive features and the 2-byte staging
 // writes of consecutive pairs fall in distinct banks). Wave w accumulates the
 // 4 x 8 output tiles o in [64 (w % 4), +64), i in [128 (w / 4), +128) in
 // registers; the next 32 pairs are loaded while the current ones are multiplied.
-// With kBias the layer's bias gradient (the column sums of dz) comes along: waves
-// 0..3 multiply their dz fragments by a fragment of ones as well and write
-// part[nblk * 65536 + blk * 256 + o].
+// The layer's bias gradient (the column sums of dz) comes along: waves 0..3
+// multiply their dz fragments by a fragment of ones as well. A slice is 65536
+// values, then the 256 of the bias.
 constexpr int kWgWaves = 8;
 constexpr int kWgRow = 40;  // bf16 per staged feature row: 32 pairs + padding
 
-template <bool kBias>
+constexpr int kWgSlice = 65536 + 256;
+
 __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16* __restrict__ dz,
                                                                    const __bf16* __restrict__ act, int64_t P,
-                                                                   int64_t rpb, float* __restrict__ part) {
+                                                                   RowGroups rg, float* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) uint16_t t_dz[256 * kWgRow];
     __shared__ __attribute__((aligned(16))) uint16_t t_act[256 * kWgRow];
     const int tid = (int)threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
     const int o0 = 64 * (wave & 3), i0 = 128 * (wave >> 2);
-    const int64_t beg = (int64_t)blockIdx.x * rpb, end = min(P, beg + rpb);
+    const uint32_t ng = *rg.count;
     // staging: thread -> pair q = tid % 32 of the chunk, 8-feature pieces c = tid / 32 and c + 16
     const int q = tid & 31, c0 = tid >> 5;
     uint4 rd[2], ra[2];
-    auto load = [&](int64_t p0) {
-        const int64_t p = p0 + q;
+    auto load = [&](uint32_t k) {
+        const int64_t p = (int64_t)rg.list[k] * kRowGroup + q;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int c = c0 + 16 * h;
-            rd[h] = p < end ? *reinterpret_cast<const uint4*>(dz + p * 256 + 8 * c) : make_uint4(0u, 0u, 0u, 0u);
-            ra[h] = p < end ? *reinterpret_cast<const uint4*>(act + p * 256 + 8 * c) : make_uint4(0u, 0u, 0u, 0u);
+            rd[h] = p < P ? *reinterpret_cast<const uint4*>(dz + p * 256 + 8 * c) : make_uint4(0u, 0u, 0u, 0u);
+            ra[h] = p < P ? *reinterpret_cast<const uint4*>(act + p * 256 + 8 * c) : make_uint4(0u, 0u, 0u, 0u);
         }
     };
     auto stage = [&]() {
@@ -718,15 +838,15 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
 #pragma unroll
         for (int b = 0; b < 8; ++b) acc[a][b] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const bool bias_wave = kBias && (wave >> 2) == 0;  // waves 0..3 cover the 16 o-tiles once
+    const bool bias_wave = (wave >> 2) == 0;  // waves 0..3 cover the 16 o-tiles once
     const uint4 one4 = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);  // bf16 1.0 x 8
     const dz_bf16x8 ones = __builtin_bit_cast(dz_bf16x8, one4);
-    if (beg < end) load(beg);
-    for (int64_t p0 = beg; p0 < end; p0 += 32) {
+    if (blockIdx.x < ng) load(blockIdx.x);
+    for (uint32_t k = blockIdx.x; k < ng; k += gridDim.x) {
         __syncthreads();  // the previous chunk's fragment reads are complete
         stage();
         __syncthreads();
-        if (p0 + 32 < end) load(p0 + 32);
+        if (k + gridDim.x < ng) load(k + gridDim.x);
         dz_bf16x8 fa[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a)  // A(o, k = pair): 8 consecutive pairs of feature o
@@ -742,14 +862,14 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
             for (int a = 0; a < 4; ++a) accb[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], ones, accb[a], 0, 0, 0);
     }
     if (bias_wave && n == 0) {  // every column of the ones product is the row sum
-        float* ob = part + (size_t)gridDim.x * 65536 + (size_t)blockIdx.x * 256;
+        float* ob = part + (size_t)blockIdx.x * kWgSlice + 65536;
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) ob[o0 + 16 * a + 4 * g + jj] = accb[a][jj];
     }
     // D(row 4 g + jj, col n) of tile (a, b) is dW[o0 + 16 a + 4 g + jj][i0 + 16 b + n]
-    float* out = part + (size_t)blockIdx.x * 65536;
+    float* out = part + (size_t)blockIdx.x * kWgSlice;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -758,49 +878,68 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
             for (int jj = 0; jj < 4; ++jj) out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
 }
 
-// Output layer of a BF16 backward in one pass over the last hidden activations
-// act [P][256] (BF16), per block of pairs (one slice of rpb pairs): with dy
-// [P][7] FP32 (the upstream gradient as computed, not rounded) and Wo [7][256]
-// BF16,
-//   dz[p][f] = BF16(sum_o dy[p][o] Wo[o][f]), zero where act[p][f] is not > 0
+// Output layer of the backward in one pass over the last hidden activations
+// act [P][256] (T: BF16, or FP32 after an FP32 forward), over every gridDim-th
+// listed group: with dy [P][7] FP32 (the upstream gradient as computed, not
+// rounded) and Wo [7][256],
+//   dz[p][f] = T(sum_o dy[p][o] Wo[o][f]), zero where act[p][f] is not > 0
 //     (the gradient of the last hidden pre-activations; skipped if dz is NULL),
-//   part[blk][o][f] = sum over the slice of dy[p][o] act[p][f] (the weight
-//     gradient's partial; skipped if part is NULL; the caller adds the slices).
-// Thread: 8 features (16-byte loads and stores) of every 8th pair of the slice.
-__global__ __launch_bounds__(256) void out_bwd_bf16_kernel(const float* __restrict__ dy,
-                                                           const __bf16* __restrict__ wo,
-                                                           const __bf16* __restrict__ act, int64_t P, int64_t rpb,
-                                                           __bf16* __restrict__ dz, float* __restrict__ part) {
+//   part[blk] = the slice's sums of dy[p][o] act[p][f] (the weight gradient,
+//     7 x 256), then of dy[p][o] (the bias gradient, 7 and a pad); the caller
+//     adds the slices.
+// Thread: 8 features of every 8th pair.
+constexpr int kOutSlice = kOut * 256 + 8;
+
+template <typename T>
+__global__ __launch_bounds__(256) void out_bwd_kernel(const float* __restrict__ dy, const T* __restrict__ wo,
+                                                      const T* __restrict__ act, int64_t P, RowGroups rg,
+                                                      T* __restrict__ dz, float* __restrict__ part) {
+    constexpr bool kBf = sizeof(T) == 2;
     __shared__ __attribute__((aligned(16))) float s_w[kOut][256];
     __shared__ float s_red[4][kOut][256];  // one row per wave after the in-wave pair of rows is added
+    __shared__ float s_y[4][8];
     for (int i = threadIdx.x; i < kOut * 256; i += 256) s_w[i / 256][i % 256] = (float)wo[i];
     __syncthreads();
     const int f0 = (int)(threadIdx.x & 31) * 8, row = (int)(threadIdx.x >> 5);
-    const int64_t beg = (int64_t)blockIdx.x * rpb, end = min(P, beg + rpb);
-    float acc[kOut][8];
+    const uint32_t ng = *rg.count;
+    float acc[kOut][8], ysum[kOut];
 #pragma unroll
-    for (int o = 0; o < kOut; ++o)
+    for (int o = 0; o < kOut; ++o) {
+        ysum[o] = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[o][j] = 0.f;
-    for (int64_t p = beg + row; p < end; p += 8) {
-        float y[kOut];
+    }
+    for (uint32_t k = blockIdx.x; k < ng; k += gridDim.x) {
 #pragma unroll
-        for (int o = 0; o < kOut; ++o) y[o] = dy[p * kOut + o];
-        const uint4 a = *reinterpret_cast<const uint4*>(act + p * 256 + f0);
-        const uint32_t aw[4] = {a.x, a.y, a.z, a.w};
-        float av[8];
+        for (int i = 0; i < kRowGroup / 8; ++i) {
+            const int64_t p = (int64_t)rg.list[k] * kRowGroup + 8 * i + row;
+            if (p >= P) continue;
+            float y[kOut];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            av[2 * k] = __uint_as_float(aw[k] << 16);
-            av[2 * k + 1] = __uint_as_float(aw[k] & 0xffff0000u);
-        }
-        if (part) {
+            for (int o = 0; o < kOut; ++o) {
+                y[o] = dy[p * kOut + o];
+                ysum[o] += y[o];
+            }
+            float av[8];
+            if constexpr (kBf) {
+                const uint4 a = *reinterpret_cast<const uint4*>(act + p * 256 + f0);
+                const uint32_t aw[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+                for (int k2 = 0; k2 < 4; ++k2) {
+                    av[2 * k2] = __uint_as_float(aw[k2] << 16);
+                    av[2 * k2 + 1] = __uint_as_float(aw[k2] & 0xffff0000u);
+                }
+            } else {
+                const float4 a = load4(act + p * 256 + f0), b = load4(act + p * 256 + f0 + 4);
+                const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+                for (int j = 0; j < 8; ++j) av[j] = v[j];
+            }
 #pragma unroll
             for (int o = 0; o < kOut; ++o)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[o][j] = fmaf(y[o], av[j], acc[o][j]);
-        }
-        if (dz) {
+            if (!dz) continue;
             float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int o = 0; o < kOut; ++o) {
@@ -815,33 +954,46 @@ __global__ __launch_bounds__(256) void out_bwd_bf16_kernel(const float* __restri
                 z[6] = fmaf(y[o], w1.z, z[6]);
                 z[7] = fmaf(y[o], w1.w, z[7]);
             }
-            uint32_t ow[4];
+            if constexpr (kBf) {
+                uint32_t ow[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t lo = __builtin_bit_cast(uint16_t, to_bf16(z[2 * k]));
-                const uint32_t hi = __builtin_bit_cast(uint16_t, to_bf16(z[2 * k + 1]));
-                const uint32_t x = aw[k];
-                const uint32_t ml = ((x & 0x8000u) == 0 && (x & 0x7fffu) != 0) ? 0x0000ffffu : 0u;
-                const uint32_t mh = ((x & 0x80000000u) == 0 && (x & 0x7fff0000u) != 0) ? 0xffff0000u : 0u;
-                ow[k] = (lo | (hi << 16)) & (ml | mh);
+                for (int k2 = 0; k2 < 4; ++k2) {
+                    const uint32_t lo = __builtin_bit_cast(uint16_t, to_bf16(z[2 * k2]));
+                    const uint32_t hi = __builtin_bit_cast(uint16_t, to_bf16(z[2 * k2 + 1]));
+                    // positive as the forward's ReLU decides on the bits: sign clear and not zero
+                    const int32_t xl = (int32_t)__float_as_uint(av[2 * k2]), xh = (int32_t)__float_as_uint(av[2 * k2 + 1]);
+                    ow[k2] = (xl > 0 ? lo : 0u) | (xh > 0 ? hi << 16 : 0u);
+                }
+                *reinterpret_cast<uint4*>(dz + p * 256 + f0) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) z[j] = av[j] > 0.f ? z[j] : 0.f;
+                *reinterpret_cast<float4*>(dz + p * 256 + f0) = make_float4(z[0], z[1], z[2], z[3]);
+                *reinterpret_cast<float4*>(dz + p * 256 + f0 + 4) = make_float4(z[4], z[5], z[6], z[7]);
             }
-            *reinterpret_cast<uint4*>(dz + p * 256 + f0) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
         }
     }
-    if (!part) return;  // block-uniform
     // rows 2 w and 2 w + 1 are the two halves of wave w: add them across lanes l and l + 32
     const int wv = (int)(threadIdx.x >> 6);
 #pragma unroll
-    for (int o = 0; o < kOut; ++o)
+    for (int o = 0; o < kOut; ++o) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float v = acc[o][j] + __shfl_xor(acc[o][j], 32);
             if ((threadIdx.x & 32) == 0) s_red[wv][o][f0 + j] = v;
         }
+        const float v = ysum[o] + __shfl_xor(ysum[o], 32);
+        if ((threadIdx.x & 63) == 0) s_y[wv][o] = v;
+    }
     __syncthreads();
+    float* pb = part + (size_t)blockIdx.x * kOutSlice;
     for (int e = threadIdx.x; e < kOut * 256; e += 256) {
         const int o = e / 256, f = e % 256;
-        part[(size_t)blockIdx.x * kOut * 256 + e] = s_red[0][o][f] + s_red[1][o][f] + s_red[2][o][f] + s_red[3][o][f];
+        pb[e] = s_red[0][o][f] + s_red[1][o][f] + s_red[2][o][f] + s_red[3][o][f];
+    }
+    if (threadIdx.x < 8) {
+        const int o = (int)threadIdx.x;
+        pb[kOut * 256 + o] = o < kOut ? s_y[0][o] + s_y[1][o] + s_y[2][o] + s_y[3][o] : 0.f;
     }
 }
 
@@ -853,9 +1005,11 @@ __global__ __launch_bounds__(256) void out_bwd_bf16_kernel(const float* __restri
 // (4 row groups through LDS).
 constexpr int kSumRows = 32;
 
+// Rows without a gradient (bits, when given) count zero: they were not written.
 template <bool kMask>
 __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restrict__ z, const __bf16* __restrict__ act,
-                                                          int B, int N, float* __restrict__ S,
+                                                          const uint32_t* __restrict__ bits, int B, int N,
+                                                          float* __restrict__ S,
                                                           float* __restrict__ Rpart) {
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int c = tx * 4;
@@ -869,8 +1023,9 @@ __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restric
 #pragma unroll
         for (int i = 0; i < kSumRows / 4; ++i) {
             const int n = n0 + ty + 4 * i;
-            if (n < N) {
-                const size_t off = ((size_t)b * N + n) * 256 + c;
+            const int64_t p = (int64_t)b * N + n;
+            if (n < N && (!bits || ((bits[p >> 5] >> (p & 31)) & 1u))) {
+                const size_t off = (size_t)p * 256 + c;
                 const float4 v = load4(z + off);
                 float4 m = v;
                 if constexpr (kMask) {
@@ -913,26 +1068,6 @@ __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restric
 __global__ void to_bf16_kernel(const float* __restrict__ x, int64_t n, __bf16* __restrict__ y) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) y[i] = to_bf16(x[i]);
-}
-
-// Column sums of row-major BF16 matrices, first stage (FP32 partial sums).
-__global__ __launch_bounds__(256) void colsum_stage1_bf16_kernel(const __bf16* __restrict__ A, int64_t rows,
-                                                                 int64_t cols, int64_t rpb, int64_t bs,
-                                                                 float* __restrict__ part) {
-    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c >= cols) return;
-    const __bf16* Az = A + (int64_t)blockIdx.z * bs;
-    const int64_t r0 = (int64_t)blockIdx.y * rpb, r1 = min(rows, r0 + rpb);
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int64_t r = r0;
-    for (; r + 4 <= r1; r += 4) {
-        s0 += (float)Az[r * cols + c];
-        s1 += (float)Az[(r + 1) * cols + c];
-        s2 += (float)Az[(r + 2) * cols + c];
-        s3 += (float)Az[(r + 3) * cols + c];
-    }
-    for (; r < r1; ++r) s0 += (float)Az[r * cols + c];
-    part[((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * cols + c] = (s0 + s1) + (s2 + s3);
 }
 
 __global__ void mean_features_f32_kernel(const float* __restrict__ mx, const float* __restrict__ my, int n, int W,
@@ -982,11 +1117,30 @@ void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Reco
 #undef SWF_BLEND_BWD
 }
 
+size_t row_group_words(int64_t P) { return 2 * (size_t)((P + 31) / 32) + (size_t)((P + 255) / 256) + 16; }
+
+RowGroups row_groups(uint32_t* buf, int64_t P) {
+    RowGroups g;
+    g.count = buf;
+    g.bits = buf + 16;
+    g.list = buf + 16 + (P + 31) / 32;
+    return g;
+}
+
 void launch_preprocess_backward(const float* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
-                                float* dy, hipStream_t st) {
-    if (P > 0)
-        preprocess_backward_kernel<<<(unsigned)((P + 255) / 256), 256, 0, st>>>(dpair, r.wm, r.oa, r.count, P,
-                                                                                paper_mask ? 1 : 0, dbase, dy);
+                                float* dy, uint32_t* group_buf, hipStream_t st) {
+    if (P <= 0) {
+        if (dy) launch_clear_u32(group_buf, 1, st);
+        return;
+    }
+    const unsigned blocks = (unsigned)((P + 255) / 256);
+    const int64_t ng = (P + 31) / 32;
+    uint32_t* bits = dy ? group_buf + 16 : nullptr;
+    uint32_t* counts = dy ? bits + 2 * ng : nullptr;
+    preprocess_backward_kernel<<<blocks, 256, 0, st>>>(dpair, r.wm, r.oa, r.count, r.rect, P, paper_mask ? 1 : 0,
+                                                       dbase, dy, bits, counts);
+    if (dy)
+        row_groups_kernel<<<(unsigned)((ng + 1023) / 1024), 1024, 0, st>>>(bits, counts, ng, bits + ng, group_buf);
 }
 
 void launch_base_reduce(const float* dbase, const float* dmu_pe, const uint32_t* perm, int B, int N,
@@ -1031,79 +1185,81 @@ void launch_pe_chain(const float* dg, const DevScene& s, float* dmu, hipStream_t
     if (s.n > 0) pe_chain_kernel<<<(s.n + 255) / 256, 256, 0, st>>>(dg, s.mx, s.my, s.n, s.W, s.H, dmu);
 }
 
-void launch_dz_gemm(const void* dz, const void* W, const void* act, int64_t P, void* out, bool f32_out,
+void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t st) {
+    BwdWeights a{};
+    for (int l = 0; l <= n_hidden && l < 8; ++l) a.w[l] = w[l];
+    a.n = n_hidden;
+    const int n = (n_hidden - 1) * 65536 + kOut * 256;
+    pack_bwd_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(a, (__bf16*)out);
+}
+
+static void slice_sum(const float* part, int nb, int64_t stride, int64_t n0, int64_t n1, float* out0, float* out1,
+                      hipStream_t st) {
+    if (out0 || out1)
+        slice_sum_kernel<<<(unsigned)((n0 + n1 + 63) / 64), 256, 0, st>>>(part, nb, stride, n0, n1, out0, out1);
+}
+
+void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, const RowGroups& rg, void* out,
                     hipStream_t st) {
     if (P <= 0) return;
     const int64_t groups = (P + kDzPairs - 1) / kDzPairs;
     const int blocks = (int)std::min<int64_t>(n_compute_units(), (groups + kDzWaves - 1) / kDzWaves);
-    if (f32_out)
-        dz_gemm_kernel<true><<<blocks, 64 * kDzWaves, 0, st>>>((const __bf16*)dz, (const __bf16*)W, nullptr, P, out);
-    else
-        dz_gemm_kernel<false><<<blocks, 64 * kDzWaves, 0, st>>>((const __bf16*)dz, (const __bf16*)W,
-                                                                (const __bf16*)act, P, out);
+    dz_gemm_kernel<<<blocks, 64 * kDzWaves, 0, st>>>((const __bf16*)dz, (const uint4*)wf, (const __bf16*)act, P, rg,
+                                                     (__bf16*)out);
 }
 
-int wgrad_out_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (P + 255) / 256)); }
+int out_bwd_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (P + 255) / 256)); }
+size_t out_bwd_floats(int64_t P) { return (size_t)out_bwd_blocks(P) * kOutSlice; }
 
-void launch_out_bwd_bf16(const float* dy, const void* wo, const void* act, int64_t P, void* dz, float* part,
-                         float* tmp, float* dWo, hipStream_t st) {
-    if (!dz && !dWo) return;
-    const int nblk = wgrad_out_blocks(P);  // P = 0: one block writes zeros
-    const int64_t rpb = ((P + nblk - 1) / nblk + 7) / 8 * 8;
-    out_bwd_bf16_kernel<<<nblk, 256, 0, st>>>(dy, (const __bf16*)wo, (const __bf16*)act, P, rpb,
-                                              (__bf16*)dz, dWo ? part : nullptr);
-    if (dWo) launch_colsum(part, nblk, (int64_t)kOut * 256, 1, 0, tmp, dWo, 0, st);
+void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act, int64_t P, const RowGroups& rg,
+                    void* dz, float* part, float* dWo, float* dbo, hipStream_t st) {
+    if (!dz && !dWo && !dbo) return;
+    const int nblk = out_bwd_blocks(P);  // P = 0: one block writes zeros
+    if (bf16)
+        out_bwd_kernel<__bf16><<<nblk, 256, 0, st>>>(dy, (const __bf16*)wo, (const __bf16*)act, P, rg, (__bf16*)dz,
+                                                     part);
+    else
+        out_bwd_kernel<float><<<nblk, 256, 0, st>>>(dy, (const float*)wo, (const float*)act, P, rg, (float*)dz, part);
+    slice_sum(part, nblk, kOutSlice, kOut * 256, kOut, dWo, dbo, st);
 }
 
 int wgrad_mfma_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, (P + 1023) / 1024)); }
+size_t wgrad_mfma_floats(int64_t P) { return (size_t)wgrad_mfma_blocks(P) * kWgSlice; }
 
-void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, float* part, float* tmp, float* dW, float* db,
-                       hipStream_t st) {
+void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGroups& rg, float* part, float* dW,
+                       float* db, hipStream_t st) {
+    if (!dW && !db) return;
     const int nblk = wgrad_mfma_blocks(P);  // P = 0: one block writes zeros
-    const int64_t rpb = ((P + nblk - 1) / nblk + 31) / 32 * 32;
-    if (db)
-        wgrad_mfma_kernel<true><<<nblk, 64 * kWgWaves, 0, st>>>((const __bf16*)dz, (const __bf16*)act, P, rpb, part);
-    else
-        wgrad_mfma_kernel<false><<<nblk, 64 * kWgWaves, 0, st>>>((const __bf16*)dz, (const __bf16*)act, P, rpb, part);
-    launch_colsum(part, nblk, 65536, 1, 0, tmp, dW, 0, st);
-    if (db) launch_colsum(part + (size_t)nblk * 65536, nblk, 256, 1, 0, tmp, db, 0, st);
+    wgrad_mfma_kernel<<<nblk, 64 * kWgWaves, 0, st>>>((const __bf16*)dz, (const __bf16*)act, P, rg, part);
+    slice_sum(part, nblk, kWgSlice, 65536, 256, dW, db, st);
+}
+
+void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipStream_t st) {
+    slice_sum(part, nb, cols, cols, 0, out, nullptr, st);
 }
 
 int layer1_grad_blocks(int N) { return (N + kL1Rows - 1) / kL1Rows; }
 
-void launch_layer1_grad(const void* dz1, const void* W, const void* act, int B, int N, float* S, float* Rpart,
-                        hipStream_t st) {
+void launch_layer1_grad(const void* dz1, const void* wf, const void* act, int B, int N, const RowGroups& rg, float* S,
+                        float* Rpart, hipStream_t st) {
     if (N > 0 && B > 0)
         layer1_grad_kernel<<<layer1_grad_blocks(N), 64 * kL1Waves, 0, st>>>(
-            (const __bf16*)dz1, (const __bf16*)W, (const __bf16*)act, B, N, S, Rpart);
+            (const __bf16*)dz1, (const uint4*)wf, (const __bf16*)act, B, N, rg.bits, S, Rpart);
 }
 
 int layer1_sums_blocks(int N) { return (N + kSumRows - 1) / kSumRows; }
 
-void launch_layer1_sums(const float* z, const void* act, int B, int N, float* S, float* Rpart, hipStream_t st) {
+void launch_layer1_sums(const float* z, const void* act, const uint32_t* bits, int B, int N, float* S, float* Rpart,
+                        hipStream_t st) {
     if (N <= 0 || B <= 0) return;
     if (act)
-        layer1_sums_kernel<true><<<layer1_sums_blocks(N), 256, 0, st>>>(z, (const __bf16*)act, B, N, S, Rpart);
+        layer1_sums_kernel<true><<<layer1_sums_blocks(N), 256, 0, st>>>(z, (const __bf16*)act, bits, B, N, S, Rpart);
     else
-        layer1_sums_kernel<false><<<layer1_sums_blocks(N), 256, 0, st>>>(z, nullptr, B, N, S, Rpart);
+        layer1_sums_kernel<false><<<layer1_sums_blocks(N), 256, 0, st>>>(z, nullptr, bits, B, N, S, Rpart);
 }
 
 void launch_to_bf16(const float* x, int64_t n, void* y, hipStream_t st) {
     if (n > 0) to_bf16_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(x, n, (__bf16*)y);
-}
-
-void launch_colsum_bf16(const void* A, int64_t rows, int64_t cols, int nz, int64_t bs, float* part, float* out,
-                        int64_t out_bs, hipStream_t st) {
-    if (cols <= 0 || nz <= 0) return;
-    if (cols % 4 == 0 && bs % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 7) == 0) {
-        colsum4((const __bf16*)A, rows, cols, nz, bs, part, out, out_bs, st);
-        return;
-    }
-    const int nblk = colsum_blocks(rows);
-    const int64_t rpb = (rows + nblk - 1) / nblk;
-    const unsigned gx = (unsigned)((cols + 255) / 256);
-    colsum_stage1_bf16_kernel<<<dim3(gx, nblk, nz), 256, 0, st>>>((const __bf16*)A, rows, cols, rpb, bs, part);
-    colsum8_stage2_kernel<<<dim3((unsigned)((cols + 7) / 8), nz), 256, 0, st>>>(part, nblk, cols, out, out_bs);
 }
 
 void launch_mean_features_f32(const DevScene& s, float* out, hipStream_t st) {

@@ -174,6 +174,8 @@ void launch_paper_mlp(const DevScene& d, const float* txf, int B, const Grid& g,
 void launch_gmm_blend(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g, float* out,
                       float* chan, hipStream_t st);
 
+struct RowGroups;  // the pairs with a gradient, below
+
 // pe_mlp.hip
 void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, uint32_t* status, hipStream_t st,
                         float* feat_out = nullptr);
@@ -182,8 +184,8 @@ void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, ui
 // [dz_f32_blocks(P)][256]) also the per-block column sums of dz (the layer's bias gradient before their sum).
 void launch_pack_wt(const float* w, float* wt, hipStream_t st);
 int64_t dz_f32_blocks(int64_t P);
-void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P, float* out, float* bpart,
-                   hipStream_t st);
+void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P, const RowGroups& rg, float* out,
+                   float* bpart, hipStream_t st);
 void launch_mlp_fp32(const DevScene& s, const float* qs, int B, const Grid& g, bool paper_mask, const Records& r,
                      float* delta_out, hipStream_t st, float* const* act_out = nullptr);
 void launch_preprocess_static(const DevScene& s, int B, const Grid& g, const Records& r, hipStream_t st);
@@ -251,8 +253,20 @@ void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* b
 void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,
                            const float* grad_out, const float* aux_T, const uint32_t* aux_last, float* dpair,
                            hipStream_t st, float* det_part = nullptr, int N = 0, const uint32_t* det_off = nullptr);
+// Rows (pairs) of the MLP backward that have a gradient, in groups of 32: rows outside the listed groups have a zero
+// dy, so they add nothing to any weight gradient or sum and are neither read nor written by the kernels below (their
+// rows of dz hold anything).
+constexpr int kRowGroup = 32;
+struct RowGroups {
+    uint32_t* bits;   // per group the rows with a gradient
+    uint32_t* list;   // the groups with one, ascending
+    uint32_t* count;  // their number
+};
+size_t row_group_words(int64_t P);                  // uint32 words of the buffer below
+RowGroups row_groups(uint32_t* buf, int64_t P);
+// with dy: also the row groups, into group_buf
 void launch_preprocess_backward(const float* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
-                                float* dy, hipStream_t st);
+                                float* dy, uint32_t* group_buf, hipStream_t st);
 struct BaseGrads {  // destinations of the 7 base-parameter gradients (device; NULL skips one)
     float* p[7];
 };
@@ -261,12 +275,12 @@ void launch_base_reduce(const float* dbase, const float* dmu_pe, const uint32_t*
 // gemm.hip: C = op(A) op(B) in FP32 on the matrix cores, row-major (op(A) M x K, op(B) K x N; A / B FP32, or
 // BF16 bits when bf16). mask (optional, leading dimension ldm): C *= [mask > 0]. A small C over a long K is
 // split into gemm_split(M, N, K) K-slices summed in slice order; part then holds gemm_part_floats(M, N, K)
-// floats (unused otherwise).
+// floats (unused otherwise). kgroups: only the K rows (pairs) of these groups count.
 int gemm_split(int64_t M, int64_t N, int64_t K);
 size_t gemm_part_floats(int64_t M, int64_t N, int64_t K);
 void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
                      int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, const float* mask = nullptr,
-                     int64_t ldm = 0, bool bf16 = false);
+                     int64_t ldm = 0, bool bf16 = false, const RowGroups* kgroups = nullptr);
 void launch_fill(float* p, float v, int64_t n, hipStream_t st);
 // out[z * out_bs + c] = sum_r A[z * bs + r * cols + c] for z < nz; part holds
 // colsum_blocks(rows) * cols * nz floats
@@ -275,34 +289,38 @@ void launch_colsum(const float* A, int64_t rows, int64_t cols, int nz, int64_t b
                    int64_t out_bs, hipStream_t st);
 // dg: [N][26] gradient of gamma(mu_hat) summed over the batch -> dmu [N][2]
 void launch_pe_chain(const float* dg, const DevScene& s, float* dmu, hipStream_t st);
-// Input gradient of a 256 x 256 layer on MFMA: out = dz W (dz [P][256] BF16, W [256][256] BF16 row-major
-// [out][in]); FP32 output (f32_out) or BF16 output masked by act > 0 (act [P][256] BF16)
-void launch_dz_gemm(const void* dz, const void* W, const void* act, int64_t P, void* out, bool f32_out,
+// BF16 weights of the backward from the FP32 masters w[0 .. n_hidden]: per 256 x 256 layer 65536 values in fragment
+// order, then the output layer's 7 x 256
+void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t st);
+// Input gradient of a 256 x 256 layer on MFMA: out = dz W (dz [P][256] BF16, wf the layer's fragments), rounded to
+// BF16 and masked by act > 0 (act [P][256] BF16)
+void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, const RowGroups& rg, void* out,
                     hipStream_t st);
-// Weight gradient of a 256 x 256 layer on MFMA: dW [256][256] = dz^T act (dz, act [P][256] BF16; FP32 sums),
-// and, when db is not NULL, the bias gradient db [256] = the column sums of dz.
-// part: wgrad_mfma_blocks(P) * (65536 + 256) floats; tmp: column-sum scratch.
-int wgrad_mfma_blocks(int64_t P);
-void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, float* part, float* tmp, float* dW, float* db,
-                       hipStream_t st);
+// Weight gradient of a 256 x 256 layer on MFMA: dW [256][256] = dz^T act (dz, act [P][256] BF16; FP32 sums) and the
+// bias gradient db [256] = the column sums of dz (either may be NULL). part: wgrad_mfma_floats(P) floats.
+size_t wgrad_mfma_floats(int64_t P);
+void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGroups& rg, float* part, float* dW,
+                       float* db, hipStream_t st);
 // Layer-1 gradient sums of a BF16 backward straight from dz1 [B][N][256] (the second layer's pre-activation
-// gradient, BF16) and W (its 256 x 256 BF16 weights): S [N][256] = sum over b of (dz1 W) masked by act > 0, and
+// gradient, BF16) and wf (its weights' fragments): S [N][256] = sum over b of (dz1 W) masked by act > 0, and
 // Rpart [layer1_grad_blocks(N)][B][256] per-block sums over the Gaussians.
 int layer1_grad_blocks(int N);
-void launch_layer1_grad(const void* dz1, const void* W, const void* act, int B, int N, float* S, float* Rpart,
-                        hipStream_t st);
-// Output layer of a BF16 backward in one pass over act [P][256]: dz (may be NULL) = (dy Wo) rounded to BF16 and
-// masked by act > 0; dWo [7][256] (may be NULL) = dy^T act. part: wgrad_out_blocks(P) * 7 * 256 floats.
-void launch_out_bwd_bf16(const float* dy, const void* wo, const void* act, int64_t P, void* dz, float* part,
-                         float* tmp, float* dWo, hipStream_t st);
-int wgrad_out_blocks(int64_t P);  // blocks (pair slices) of launch_out_bwd_bf16
+void launch_layer1_grad(const void* dz1, const void* wf, const void* act, int B, int N, const RowGroups& rg, float* S,
+                        float* Rpart, hipStream_t st);
+// Output layer of the backward in one pass over act [P][256] (BF16 or FP32, as wo and dz): dz (may be NULL) = (dy Wo)
+// masked by act > 0; dWo [7][256] = dy^T act and dbo [7] = the column sums of dy (either may be NULL). part:
+// out_bwd_floats(P) floats.
+size_t out_bwd_floats(int64_t P);
+void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act, int64_t P, const RowGroups& rg,
+                    void* dz, float* part, float* dWo, float* dbo, hipStream_t st);
+// out[c] = sum of nb slices part[j][c] of cols values (a multiple of 4), in a fixed order
+void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipStream_t st);
 // S [N][256] = sum_b of z * [act > 0] (act BF16; null: z is masked already) and Rpart [layer1_sums_blocks(N)][B][256]
-// partial sums over Gaussians
+// partial sums over Gaussians; rows whose bit is clear (bits may be null) count zero
 int layer1_sums_blocks(int N);
-void launch_layer1_sums(const float* z, const void* act, int B, int N, float* S, float* Rpart, hipStream_t st);
+void launch_layer1_sums(const float* z, const void* act, const uint32_t* bits, int B, int N, float* S, float* Rpart,
+                        hipStream_t st);
 void launch_to_bf16(const float* x, int64_t n, void* y, hipStream_t st);
-void launch_colsum_bf16(const void* A, int64_t rows, int64_t cols, int nz, int64_t bs, float* part, float* out,
-                        int64_t out_bs, hipStream_t st);
 void launch_mean_features_f32(const DevScene& s, float* out, hipStream_t st);
 
 // blend.hip

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void mlp_fp32_kernel(MlpArgs a, Mi
 // Input gradient of a 256 x 256 layer of the FP32 backward on the same matrix
 // cores: out[p][i] = [act[p][i] > 0] sum_o W[o][i] dz[p][o], the layer function
 // above with W^T as its weights (fragment-major, packed by pack_wt_kernel) and
-// no bias. A wave takes 16 pairs; lane l = 16 g + r loads input chunk 4 q + j
+// no bias, over the listed groups. A wave takes 16 pairs; lane l = 16 g + r loads input chunk 4 q + j
 // (input 16 q + 4 g + j) of pair r as one 16-byte load per q, and stores the
 // masked output tile t (units 16 t + 4 g + i) with one 16-byte store. With
 // bpart, the layer's bias gradient rides along: bpart[block][o] = the sum of
@@ -229,11 +229,19 @@ __device__ float kZeroBias[256];  // zero-initialised: the layer's bias
 __global__ __launch_bounds__(64 * kFWaves, 3) void dz_f32_kernel(const float* __restrict__ dz,
                                                                  const float4* __restrict__ wt,
                                                                  const float* __restrict__ act, int64_t P,
-                                                                 float* __restrict__ out, float* __restrict__ bpart) {
+                                                                 RowGroups rg, float* __restrict__ out,
+                                                                 float* __restrict__ bpart) {
     __shared__ float4 s_b[kFWaves][64];
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     const int g = lane >> 4;
-    const int64_t p0 = ((int64_t)blockIdx.x * kFWaves + wave) * 16;
+    // the block's listed groups of 32 rows: two waves each
+    static_assert(kRowGroup == 32 && kFWaves == 4, "two groups per block");
+    const uint32_t ng = *rg.count, gi = 2 * blockIdx.x + (wave >> 1);
+    if (2 * blockIdx.x >= ng) {  // block-uniform: no rows, no bias sums
+        if (bpart) bpart[(size_t)blockIdx.x * 256 + threadIdx.x] = 0.0f;
+        return;
+    }
+    const int64_t p0 = gi < ng ? (int64_t)rg.list[gi] * kRowGroup + 16 * (wave & 1) : P;
     const int64_t row = p0 + (lane & 15);
     const bool in = row < P;
     float hin[64], hout[64];
@@ -390,11 +398,11 @@ void launch_pack_wt(const float* w, float* wt, hipStream_t st) { pack_wt_kernel<
 
 int64_t dz_f32_blocks(int64_t P) { return (P + kFWaves * 16 - 1) / (kFWaves * 16); }
 
-void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P, float* out, float* bpart,
-                   hipStream_t st) {
+void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P, const RowGroups& rg, float* out,
+                   float* bpart, hipStream_t st) {
     if (P > 0)
         dz_f32_kernel<<<(unsigned)dz_f32_blocks(P), 64 * kFWaves, 0, st>>>(dz, reinterpret_cast<const float4*>(wt),
-                                                                            act, P, out, bpart);
+                                                                            act, P, rg, out, bpart);
 }
 
 }  // namespace swf

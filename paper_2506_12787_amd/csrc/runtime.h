@@ -57,7 +57,7 @@ struct LastRender {
 // Scratch memory of one render stream: every pipeline stage writes here.
 struct Workspace {
     Buf qs, geo, wm, oa, rect, count, off, scan, keys, keys2, vals, vals2, hist, ranges, bins, delta, sortk, sortv,
-        grad, dpair, dbase, dy, act, dz, part, fmean, ftx, dmu, stage, work, beam, pool, ssim, mix, det;
+        grad, dpair, dbase, dy, act, dz, part, fmean, ftx, dmu, stage, work, beam, pool, ssim, mix, det, groups;
     Records rec;
     uint64_t* total_dev = nullptr;           // device status block: scan total, effective count, then:
     uint32_t* status_dev = nullptr;          //   status word (bit 0: key overflow at a fixed capacity)
@@ -72,7 +72,7 @@ struct Workspace {
     std::vector<Buf*> bufs() {
         return {&qs, &geo, &wm, &oa, &rect, &count, &off, &scan, &keys, &keys2, &vals, &vals2, &hist, &ranges, &bins,
                 &delta, &sortk, &sortv, &grad, &dpair, &dbase, &dy, &act, &dz, &part, &fmean, &ftx, &dmu,
-                &stage, &work, &beam, &pool, &ssim, &mix, &det};
+                &stage, &work, &beam, &pool, &ssim, &mix, &det, &groups};
     }
     uint64_t generation() {
         uint64_t g = 0;
@@ -204,7 +204,7 @@ struct Ctx {
     swf_status backward(Workspace& w, int sid, const float* tx, int B, int flags, const float* grad_out,
                         const void* aux, const swf_grads* grads, hipStream_t st);
     swf_status mlp_backward(Workspace& w, const DevScene& d, const float* tx, int B, const float* dy,
-                            const swf_grads* gr, bool bf16, hipStream_t st);
+                            const RowGroups& rg, const swf_grads* gr, bool bf16, hipStream_t st);
     void* noalloc_scratch = nullptr;  // device address of the static scan scratch (noalloc.hip) on `device`
     void stage_begin(int stage, hipStream_t st);
     void stage_end(hipStream_t st);
