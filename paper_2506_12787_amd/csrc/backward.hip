@@ -654,127 +654,124 @@ __global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __
     }
 }
 
-// Layer-1 gradient of a BF16 backward without storing it. For the block's
-// Gaussians (wave w: 16 from 16 (w gridDim + block) on, so that the front of the
-// depth order, where the rows with a gradient are, is dealt over all blocks) and
-// every query b in order, skipped by a wave none of whose rows has one: z[b][n] =
-// dz1[b][n] W (FP32 accumulation on MFMA; dz1 [B][N][256] BF16, the gradient of
-// the second layer's pre-activations; W its 256 x 256 BF16 weights, row-major
-// [out][in]), masked by act[b][n] > 0 (the layer-1 ReLU), gives S[n][:] = the sum
-// over b (complete, in order) and Rpart[block][b][:] = the sum over the block's
-// Gaussians. Pairs are the MFMA rows here (A = a wave's 16 dz1 rows, B = W
-// fragments from LDS, laid out as in dz_gemm_kernel), so a lane holds 4 pairs
-// of one feature per output tile: S accumulates in registers and the R partial
-// is a sum over those 4 and over the wave's 4 lane groups.
+// Layer-1 gradient of a BF16 backward without storing it: z[b][n] = dz1[b][n] W
+// (FP32 accumulation on MFMA; dz1 [B][N][256] BF16, the gradient of the second
+// layer's pre-activations; W its 256 x 256 BF16 weights' fragments), masked by
+// act[b][n] > 0 (the layer-1 ReLU), gives S[n][:] = the sum over b (complete, in
+// order) and Rpart[block][b][:] = the sum over the block's Gaussians.
+// A block takes 8 strips of 16 Gaussians (strip w from 16 (w gridDim + block) on,
+// so that the front of the depth order, where the rows with a gradient are, is
+// dealt over all blocks) and every query in order. Wave w forms output features
+// [32 w, 32 w + 32) of every strip: its 16 weight fragments stay in registers, the
+// strips' rows and ReLU masks are staged in LDS once per query (wave w loads strip
+// w, one query ahead) and read by all eight waves; a strip without a gradient in
+// a query is passed over. Pairs are the MFMA rows, so a lane holds 4 pairs of one
+// feature per product: S accumulates in registers over the queries, R over the
+// strips, then over the 4 lane groups. (With each wave forming every feature of
+// its own strip the weights came from LDS for each product and the few waves
+// with a gradient ran alone: 221 us at 800k pairs, a quarter of them with a
+// gradient, 331 with all.)
 constexpr int kL1Waves = 8;
 constexpr int kL1Rows = 16 * kL1Waves;
 
-__global__ __launch_bounds__(64 * kL1Waves) void layer1_grad_kernel(const __bf16* __restrict__ dz1,
-                                                                    const uint4* __restrict__ wf,
-                                                                    const __bf16* __restrict__ act, int B, int N,
-                                                                    const uint32_t* __restrict__ bits,
-                                                                    float* __restrict__ S,
-                                                                    float* __restrict__ Rpart) {
-    __shared__ __attribute__((aligned(16))) uint4 s_a[16 * 8 * 64];
-    __shared__ uint8_t s_m[kL1Waves][16][32];  // ReLU mask bits of the wave's 16 pairs, current query
-    __shared__ float s_r[kL1Waves][256];        // per-wave R partial, current query
-    for (int e = threadIdx.x; e < 16 * 8 * 64; e += 64 * kL1Waves) s_a[e] = wf[e];
-    const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), g = lane >> 4, r = lane & 15;
-    const int nw = (wave * (int)gridDim.x + (int)blockIdx.x) * 16;  // the wave's first Gaussian
-    const int na = nw + r;                            // this lane's A row
-    // whether this lane's A row of query b has a gradient (rows without one were never written)
-    auto row_live = [&](int b) {
-        const int64_t p = (int64_t)b * N + na;
-        return b < B && na < N && ((bits[p >> 5] >> (p & 31)) & 1u);
-    };
-    // dz1 or act row of this lane's A row for query b (B layout of dz_gemm: k = 32 c + 8 g + j); zero if not live
-    auto load_rows = [&](const __bf16* src, int b, bool live, dz_bf16x8 (&dst)[8]) {
-        const int64_t p = (int64_t)b * N + na;
+__global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2, 2))) void layer1_grad_kernel(
+    const __bf16* __restrict__ dz1, const uint4* __restrict__ wf, const __bf16* __restrict__ act, int B, int N,
+    const uint32_t* __restrict__ bits, float* __restrict__ S, float* __restrict__ Rpart) {
+    __shared__ __attribute__((aligned(16))) uint4 s_rows[kL1Waves][8][64];  // strip, 32-wide k chunk, lane
+    __shared__ uint8_t s_m[kL1Waves][16][32];  // ReLU mask bits of the strips' pairs
+    __shared__ int s_any[kL1Waves];            // the strip has a row with a gradient
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63), g = lane >> 4, r = lane & 15;
+    const int na = (wave * (int)gridDim.x + (int)blockIdx.x) * 16 + r;  // the Gaussian this lane loads
+    dz_bf16x8 w[2][8];  // fragments of output tiles 2 wave and 2 wave + 1
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int c = 0; c < 8; ++c)
-            dst[c] = live ? *reinterpret_cast<const dz_bf16x8*>(src + p * 256 + 32 * c + 8 * g) : dz_bf16x8{};
-    };
-    auto store_masks = [&](const dz_bf16x8 (&a)[8]) {
+            w[t][c] = __builtin_bit_cast(dz_bf16x8, wf[((2 * wave + t) * 8 + c) * 64 + lane]);
+    // rows of query b with a gradient (others were never written): dz1 and act of this lane's row, zero if not live
+    uint4 a_nxt[8], m_nxt[8];
+    bool live = false;
+    auto load = [&](int b) {
+        const int64_t p = (int64_t)b * N + na;
+        live = b < B && na < N && ((bits[p >> 5] >> (p & 31)) & 1u);
+        if (__ballot(live) == 0ull) return;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const uint4 u = __builtin_bit_cast(uint4, a[c]);
-            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+            const int64_t at = p * 256 + 32 * c + 8 * g;
+            a_nxt[c] = live ? *reinterpret_cast<const uint4*>(dz1 + at) : make_uint4(0u, 0u, 0u, 0u);
+            m_nxt[c] = live ? *reinterpret_cast<const uint4*>(act + at) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    };
+    auto stage = [&]() {
+        const bool any = __ballot(live) != 0ull;
+        if (lane == 0) s_any[wave] = any;
+        if (!any) return;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            s_rows[wave][c][lane] = a_nxt[c];
+            const uint32_t v[4] = {m_nxt[c].x, m_nxt[c].y, m_nxt[c].z, m_nxt[c].w};
             uint32_t m = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                m |= (((w[k] & 0x8000u) == 0 && (w[k] & 0x7fffu) != 0) ? 1u : 0u) << (2 * k);
-                m |= (((w[k] & 0x80000000u) == 0 && (w[k] & 0x7fff0000u) != 0) ? 1u : 0u) << (2 * k + 1);
+                m |= (((v[k] & 0x8000u) == 0 && (v[k] & 0x7fffu) != 0) ? 1u : 0u) << (2 * k);
+                m |= (((v[k] & 0x80000000u) == 0 && (v[k] & 0x7fff0000u) != 0) ? 1u : 0u) << (2 * k + 1);
             }
             s_m[wave][r][4 * c + g] = (uint8_t)m;
         }
-        __builtin_amdgcn_wave_barrier();
     };
-    dz_bf16x8 a_cur[8], a_nxt[8], m_nxt[8];
-    bool live = row_live(0), any = __ballot(live) != 0ull;  // any: wave-uniform
-    load_rows(dz1, 0, live, a_cur);
-    load_rows(act, 0, live, m_nxt);
-    store_masks(m_nxt);
-    for (int k = lane; k < 256; k += 64) s_r[wave][k] = 0.f;
-    bool dirty = false;  // s_r of this wave holds a query's sums
-    __syncthreads();  // s_a complete
-    dz_f32x4 sacc[16];
+    dz_f32x4 sacc[kL1Waves][2];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) sacc[t] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < kL1Waves; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sacc[s][t] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+    load(0);
     for (int b = 0; b < B; ++b) {
-        live = row_live(b + 1);
-        const bool next = __ballot(live) != 0ull;
-        if (next) {  // the next query's rows while this one is computed
-            load_rows(dz1, b + 1, live, a_nxt);
-            load_rows(act, b + 1, live, m_nxt);
-        }
-        if (!any && dirty) {
-            for (int k = lane; k < 256; k += 64) s_r[wave][k] = 0.f;
-            dirty = false;
-        }
-        if (any) dirty = true;
-        if (any)
+        __syncthreads();  // every wave is done with the previous query's rows
+        stage();
+        __syncthreads();
+        load(b + 1);
+        float rsum[2] = {0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            dz_f32x4 acc = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < kL1Waves; ++s) {
+            if (!__builtin_amdgcn_readfirstlane(s_any[s])) continue;
+            dz_f32x4 acc[2] = {dz_f32x4{0.f, 0.f, 0.f, 0.f}, dz_f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-            for (int c = 0; c < 8; ++c)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    a_cur[c], __builtin_bit_cast(dz_bf16x8, s_a[(t * 8 + c) * 64 + lane]), acc, 0, 0, 0);
-            // lane (g, r) holds pairs 4 g + jj of feature 16 t + r: mask bit r % 8 of byte 2 t + r / 8
-            float v = 0.f;
+            for (int c = 0; c < 8; ++c) {
+                const dz_bf16x8 a = __builtin_bit_cast(dz_bf16x8, s_rows[s][c][lane]);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w[t][c], acc[t], 0, 0, 0);
+            }
+            // lane (g, r) holds pairs 4 g + jj of features 32 wave + 16 t + r: mask bit r % 8 of byte 4 wave + 2 t + r / 8
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const uint32_t bit = ((uint32_t)s_m[wave][4 * g + jj][2 * t + (r >> 3)] >> (r & 7)) & 1u;
-                const float x = bit ? acc[jj] : 0.f;
-                sacc[t][jj] += x;
-                v += x;
+                const uint32_t word = *reinterpret_cast<const uint32_t*>(&s_m[s][4 * g + jj][4 * wave]);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const float x = (word >> (16 * t + r)) & 1u ? acc[t][jj] : 0.f;
+                    sacc[s][t][jj] += x;
+                    rsum[t] += x;
+                }
             }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            float v = rsum[t];
             v += __shfl_xor(v, 16);
             v += __shfl_xor(v, 32);
-            if (g == 0) s_r[wave][16 * t + r] = v;
+            if (g == 0) Rpart[((size_t)blockIdx.x * B + b) * 256 + 32 * wave + 16 * t + r] = v;
         }
-        __syncthreads();
-        for (int k = threadIdx.x; k < 256; k += 64 * kL1Waves) {
-            float v = 0.f;
-#pragma unroll
-            for (int w = 0; w < kL1Waves; ++w) v += s_r[w][k];
-            Rpart[((size_t)blockIdx.x * B + b) * 256 + k] = v;
-        }
-        any = next;
-        if (next) {
-            store_masks(m_nxt);  // this wave's reads of the query-b masks are complete
-#pragma unroll
-            for (int c = 0; c < 8; ++c) a_cur[c] = a_nxt[c];
-        }
-        __syncthreads();  // s_r is rewritten for the next query
     }
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int s = 0; s < kL1Waves; ++s)
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int n = nw + 4 * g + jj;
-            if (n < N) S[(size_t)n * 256 + 16 * t + r] = sacc[t][jj];
-        }
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int n = (s * (int)gridDim.x + (int)blockIdx.x) * 16 + 4 * g + jj;
+                if (n < N) S[(size_t)n * 256 + 32 * wave + 16 * t + r] = sacc[s][t][jj];
+            }
 }
 
 // Weight gradient of a 256 x 256 layer on BF16 MFMA over one slice of pairs:
