@@ -25,8 +25,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     swf_status s = SWF_OK;
     const int64_t N = d.n, P = (int64_t)B * N;
     const int nh = d.n_hidden, Hd = 256, I = d.in_dim;
-    const size_t esz = bf16 ? 2 : 4;                 // activation / dz element size
-    const size_t actb = (size_t)P * Hd * esz;
+    const size_t actb = act_layer_bytes(P, bf16);
     const size_t f32b = (size_t)P * Hd * sizeof(float);
     if (!w.act.ptr || w.act.cap < actb * nh) return fail(SWF_E_STATE, "the forward's activations are missing");
     // dz ping-pong; BF16 with a single hidden layer: also the FP32 layer-1 gradient (formed inside its sums)
@@ -170,7 +169,7 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
     const bool kept = t.seq == w.seq && t.tx == tx && (!acts_ready || t.acts);
     if (!kept) {
         if (acts_ready) {
-            const size_t actb = (size_t)B * d.n * 256 * (bf16 ? sizeof(uint16_t) : sizeof(float));
+            const size_t actb = act_layer_bytes((int64_t)B * d.n, bf16);
             if ((s = w.act.reserve(this, actb * d.n_hidden + 16, st))) return s;
             w.act_out = w.act.ptr;
         }

@@ -532,7 +532,8 @@ __device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }  // rou
 // The BF16 weights of the backward, from the FP32 masters w[l] (row-major
 // [out][in]): per 256 x 256 layer l = 1 .. n - 1 the MFMA fragments of W as the
 // kernels below take them (fragment (t, c), lane 16 g + r, element j =
-// W[32 c + 8 g + j][16 t + r]; 65536 values), then the output layer's 7 x 256.
+// W[chunk_feature(c, g, j)][16 t + r], the k order of the rows' chunks; 65536
+// values), then the output layer's 7 x 256.
 struct BwdWeights {
     const float* w[8];
     int n;
@@ -543,7 +544,7 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(BwdWeights a, __bf16* __r
     if (e < hid) {
         const int l = e >> 16, f = (e >> 9) & 127, ln = (e >> 3) & 63, j = e & 7;
         const int t = f >> 3, c = f & 7, g = ln >> 4, r = ln & 15;
-        out[e] = to_bf16(a.w[1 + l][(size_t)(32 * c + 8 * g + j) * 256 + 16 * t + r]);
+        out[e] = to_bf16(a.w[1 + l][(size_t)chunk_feature(c, g, j) * 256 + 16 * t + r]);
     } else if (e < hid + kOut * 256) {
         out[e] = to_bf16(a.w[a.n][e - hid]);
     }
@@ -553,11 +554,13 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(BwdWeights a, __bf16* __r
 // FP32 accumulation): out[p][i] = sum_o dz[p][o] W[o][i] for the rows p of the
 // listed groups, rounded to BF16 and zeroed where act[p][i] (the BF16
 // activation) is not > 0, the previous layer's ReLU. The whole W sits in LDS in
-// MFMA A-fragment order (pack_bwd_kernel's). Each wave takes groups of 32 pairs:
-// their dz rows are the B operands, in registers (16 bytes per lane per 32-wide k
-// chunk), the ReLU masks a per-wave bitmap in LDS; the next group's rows and
-// activations are loaded while the current one is computed, and 16 x 16 output
-// tiles are written as they finish.
+// MFMA A-fragment order (pack_bwd_kernel's). Each wave takes groups of 32 pairs.
+// In chunk order a lane's 16 bytes of dz are its B operand of a k chunk, two
+// stacked output tiles are its 16 bytes of out, and its mask is its 16 bytes of
+// act: every access is a contiguous KiB per wave, and no mask passes through LDS.
+// The next group's rows are loaded while the current one is computed, a chunk's
+// activations while the chunk before it is. 800k pairs, a quarter of them with a
+// gradient: 69 us (93 row-major, with the mask as bits in LDS; 285 over all rows).
 constexpr int kDzWaves = 8;
 constexpr int kDzNcb = 2;
 constexpr int kDzPairs = 16 * kDzNcb;
@@ -568,89 +571,93 @@ typedef float dz_f32x4 __attribute__((ext_vector_type(4)));
 typedef float dz_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 dz_bf16x2 __attribute__((ext_vector_type(2)));
 
-__global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __restrict__ dz,
-                                                                const uint4* __restrict__ wf,
-                                                                const __bf16* __restrict__ act, int64_t P,
-                                                                RowGroups rg, __bf16* __restrict__ out) {
+// 0xffff in each half of w whose BF16 is > 0 (activations are not negative), else 0
+__device__ __forceinline__ uint32_t positive_halves(uint32_t w) {
+    const uint32_t lo = (int32_t)(w << 16) > 0 ? 0x0000ffffu : 0u, hi = (int32_t)(w & 0xffff0000u) > 0 ? 0xffff0000u : 0u;
+    return lo | hi;
+}
+
+__global__ __launch_bounds__(64 * kDzWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void dz_gemm_kernel(
+    const __bf16* __restrict__ dz, const uint4* __restrict__ wf, const __bf16* __restrict__ act, int64_t P,
+    RowGroups rg, __bf16* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) uint4 s_a[16 * 8 * 64];  // 128 fragments of 1 KiB
-    __shared__ uint8_t s_m[kDzWaves][kDzPairs][32];                   // ReLU mask bits, pair-major
     const int64_t groups = (int64_t)*rg.count;
     if ((int64_t)blockIdx.x * kDzWaves >= groups) return;  // block-uniform
     for (int e = threadIdx.x; e < 16 * 8 * 64; e += 64 * kDzWaves) s_a[e] = wf[e];
     __syncthreads();
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), g = lane >> 4, n = lane & 15;
     const int64_t stride = (int64_t)gridDim.x * kDzWaves;
-    // rows (B layout: pair cb*16 + n, k = 32 c + 8 g + j) of listed group q; zero past P
-    auto load_rows = [&](const __bf16* src, int64_t q, dz_bf16x8 (&dst)[8][kDzNcb]) {
-        const int64_t first = q < groups ? (int64_t)rg.list[q] * kDzPairs : P;
-#pragma unroll
-        for (int cb = 0; cb < kDzNcb; ++cb) {
-            const int64_t p = first + cb * 16 + n;
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                dst[c][cb] = p < P ? *reinterpret_cast<const dz_bf16x8*>(src + p * 256 + 32 * c + 8 * g) : dz_bf16x8{};
-        }
+    // this lane's row of column block cb of listed group q (P: none)
+    auto row_of = [&](int64_t q, int cb) {
+        const int64_t p = q < groups ? (int64_t)rg.list[q] * kDzPairs + cb * 16 + n : P;
+        return p < P ? p : -1;
     };
-    // mask byte of 8 activations (bit j set where element j is > 0)
-    auto mask_byte = [](dz_bf16x8 v) {
-        const uint4 u = __builtin_bit_cast(uint4, v);
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-        uint32_t m = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            m |= (((w[k] & 0x8000u) == 0 && (w[k] & 0x7fffu) != 0) ? 1u : 0u) << (2 * k);
-            m |= (((w[k] & 0x80000000u) == 0 && (w[k] & 0x7fff0000u) != 0) ? 1u : 0u) << (2 * k + 1);
-        }
-        return (uint8_t)m;
-    };
-    auto store_masks = [&](dz_bf16x8 (&a)[8][kDzNcb]) {
-#pragma unroll
-        for (int cb = 0; cb < kDzNcb; ++cb)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) s_m[wave][cb * 16 + n][4 * c + g] = mask_byte(a[c][cb]);
-        __builtin_amdgcn_wave_barrier();
+    auto load = [&](const __bf16* src, int64_t p, int c) {
+        return p >= 0 ? *reinterpret_cast<const uint4*>(src + chunk_at(p, c, g)) : make_uint4(0u, 0u, 0u, 0u);
     };
     int64_t grp = (int64_t)blockIdx.x * kDzWaves + wave;
-    dz_bf16x8 b[8][kDzNcb], bn[8][kDzNcb], an[8][kDzNcb];
-    load_rows(dz, grp, b);
-    load_rows(act, grp, an);
-    store_masks(an);
+    int64_t p[kDzNcb];
+    uint4 b[8][kDzNcb], bn[8][kDzNcb];
+#pragma unroll
+    for (int cb = 0; cb < kDzNcb; ++cb) {
+        p[cb] = row_of(grp, cb);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) b[c][cb] = load(dz, p[cb], c);
+    }
     for (; grp < groups; grp += stride) {
-        const int64_t p0 = (int64_t)rg.list[grp] * kDzPairs;
-        load_rows(dz, grp + stride, bn);  // the next group, while this one is computed
-        load_rows(act, grp + stride, an);
+        int64_t pn[kDzNcb];
+#pragma unroll
+        for (int cb = 0; cb < kDzNcb; ++cb) {
+            pn[cb] = row_of(grp + stride, cb);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) bn[c][cb] = load(dz, pn[cb], c);
+        }
+        uint4 mk[kDzNcb];
+#pragma unroll
+        for (int cb = 0; cb < kDzNcb; ++cb) mk[cb] = load(act, p[cb], 0);
 #pragma unroll 1
-        for (int t = 0; t < 16; ++t) {
-            dz_f32x4 acc[kDzNcb];
-#pragma unroll
-            for (int cb = 0; cb < kDzNcb; ++cb) acc[cb] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const dz_bf16x8 a = __builtin_bit_cast(dz_bf16x8, s_a[(t * 8 + c) * 64 + lane]);
-#pragma unroll
-                for (int cb = 0; cb < kDzNcb; ++cb)
-                    acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[c][cb], acc[cb], 0, 0, 0);
-            }
+        for (int cp = 0; cp < 8; ++cp) {
+            uint4 m[kDzNcb];
 #pragma unroll
             for (int cb = 0; cb < kDzNcb; ++cb) {
-                const int64_t p = p0 + cb * 16 + n;
-                if (p >= P) continue;
-                // features 16 t + 4 g + 0..3: bits 4 (g & 1) + 0..3 of mask byte 2 t + g / 2
-                const uint32_t nib = ((uint32_t)s_m[wave][cb * 16 + n][2 * t + (g >> 1)] >> (4 * (g & 1))) & 15u;
-                const dz_f32x2 lo2 = {acc[cb][0], acc[cb][1]}, hi2 = {acc[cb][2], acc[cb][3]};
-                uint32_t v0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, dz_bf16x2));
-                uint32_t v1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, dz_bf16x2));
-                v0 &= ((nib & 1u) ? 0x0000ffffu : 0u) | ((nib & 2u) ? 0xffff0000u : 0u);
-                v1 &= ((nib & 4u) ? 0x0000ffffu : 0u) | ((nib & 8u) ? 0xffff0000u : 0u);
-                *reinterpret_cast<uint2*>(out + p * 256 + 16 * t + 4 * g) = make_uint2(v0, v1);
+                m[cb] = mk[cb];
+                if (cp < 7) mk[cb] = load(act, p[cb], cp + 1);
+            }
+            dz_f32x4 acc[2][kDzNcb];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int cb = 0; cb < kDzNcb; ++cb) acc[h][cb] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const dz_bf16x8 a = __builtin_bit_cast(dz_bf16x8, s_a[((2 * cp + h) * 8 + c) * 64 + lane]);
+#pragma unroll
+                    for (int cb = 0; cb < kDzNcb; ++cb)
+                        acc[h][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            a, __builtin_bit_cast(dz_bf16x8, b[c][cb]), acc[h][cb], 0, 0, 0);
+                }
+#pragma unroll
+            for (int cb = 0; cb < kDzNcb; ++cb) {
+                if (p[cb] < 0) continue;
+                uint32_t v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const dz_f32x2 f = {acc[k >> 1][cb][2 * (k & 1)], acc[k >> 1][cb][2 * (k & 1) + 1]};
+                    v[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, dz_bf16x2));
+                }
+                *reinterpret_cast<uint4*>(out + chunk_at(p[cb], cp, g)) =
+                    make_uint4(v[0] & positive_halves(m[cb].x), v[1] & positive_halves(m[cb].y),
+                               v[2] & positive_halves(m[cb].z), v[3] & positive_halves(m[cb].w));
             }
         }
-        __builtin_amdgcn_wave_barrier();  // this group's mask reads come before the next group's writes
-        store_masks(an);
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
+        for (int cb = 0; cb < kDzNcb; ++cb) {
+            p[cb] = pn[cb];
 #pragma unroll
-            for (int cb = 0; cb < kDzNcb; ++cb) b[c][cb] = bn[c][cb];
+            for (int c = 0; c < 8; ++c) b[c][cb] = bn[c][cb];
+        }
     }
 }
 
@@ -670,7 +677,7 @@ __global__ __launch_bounds__(64 * kDzWaves) void dz_gemm_kernel(const __bf16* __
 // strips, then over the 4 lane groups. (With each wave forming every feature of
 // its own strip the weights came from LDS for each product and the few waves
 // with a gradient ran alone: 221 us at 800k pairs, a quarter of them with a
-// gradient, 331 with all.)
+// gradient, 331 with all; 110 with row-major rows, 100 now.)
 constexpr int kL1Waves = 8;
 constexpr int kL1Rows = 16 * kL1Waves;
 
@@ -678,7 +685,7 @@ __global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2
     const __bf16* __restrict__ dz1, const uint4* __restrict__ wf, const __bf16* __restrict__ act, int B, int N,
     const uint32_t* __restrict__ bits, float* __restrict__ S, float* __restrict__ Rpart) {
     __shared__ __attribute__((aligned(16))) uint4 s_rows[kL1Waves][8][64];  // strip, 32-wide k chunk, lane
-    __shared__ uint8_t s_m[kL1Waves][16][32];  // ReLU mask bits of the strips' pairs
+    __shared__ __attribute__((aligned(8))) uint8_t s_m[kL1Waves][16][64];  // ReLU masks: byte f / 4, bit f % 4
     __shared__ int s_any[kL1Waves];            // the strip has a row with a gradient
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63), g = lane >> 4, r = lane & 15;
@@ -698,7 +705,7 @@ __global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2
         if (__ballot(live) == 0ull) return;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const int64_t at = p * 256 + 32 * c + 8 * g;
+            const size_t at = chunk_at(p, c, g);
             a_nxt[c] = live ? *reinterpret_cast<const uint4*>(dz1 + at) : make_uint4(0u, 0u, 0u, 0u);
             m_nxt[c] = live ? *reinterpret_cast<const uint4*>(act + at) : make_uint4(0u, 0u, 0u, 0u);
         }
@@ -710,14 +717,11 @@ __global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             s_rows[wave][c][lane] = a_nxt[c];
-            const uint32_t v[4] = {m_nxt[c].x, m_nxt[c].y, m_nxt[c].z, m_nxt[c].w};
-            uint32_t m = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                m |= (((v[k] & 0x8000u) == 0 && (v[k] & 0x7fffu) != 0) ? 1u : 0u) << (2 * k);
-                m |= (((v[k] & 0x80000000u) == 0 && (v[k] & 0x7fff0000u) != 0) ? 1u : 0u) << (2 * k + 1);
-            }
-            s_m[wave][r][4 * c + g] = (uint8_t)m;
+            const uint32_t lo = positive_halves(m_nxt[c].x) & 0x20001u, l2 = positive_halves(m_nxt[c].y) & 0x80004u;
+            const uint32_t hi = positive_halves(m_nxt[c].z) & 0x20001u, h2 = positive_halves(m_nxt[c].w) & 0x80004u;
+            const uint32_t ml = lo | l2, mh = hi | h2;
+            s_m[wave][r][8 * c + g] = (uint8_t)(ml | (ml >> 16));      // features 32 c + 4 g + 0..3
+            s_m[wave][r][8 * c + 4 + g] = (uint8_t)(mh | (mh >> 16));  // features 32 c + 16 + 4 g + 0..3
         }
     };
     dz_f32x4 sacc[kL1Waves][2];
@@ -743,13 +747,13 @@ __global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2
                 for (int t = 0; t < 2; ++t)
                     acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w[t][c], acc[t], 0, 0, 0);
             }
-            // lane (g, r) holds pairs 4 g + jj of features 32 wave + 16 t + r: mask bit r % 8 of byte 4 wave + 2 t + r / 8
+            // lane (g, r) holds pairs 4 g + jj of features 32 wave + 16 t + r: mask byte 8 wave + 4 t + r / 4
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const uint32_t word = *reinterpret_cast<const uint32_t*>(&s_m[s][4 * g + jj][4 * wave]);
+                const uint2 word = *reinterpret_cast<const uint2*>(&s_m[s][4 * g + jj][8 * wave]);
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    const float x = (word >> (16 * t + r)) & 1u ? acc[t][jj] : 0.f;
+                    const float x = ((t ? word.y : word.x) >> (8 * (r >> 2) + (r & 3))) & 1u ? acc[t][jj] : 0.f;
                     sacc[s][t][jj] += x;
                     rsum[t] += x;
                 }
@@ -801,7 +805,8 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
     const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
     const int o0 = 64 * (wave & 3), i0 = 128 * (wave >> 2);
     const uint32_t ng = *rg.count;
-    // staging: thread -> pair q = tid % 32 of the chunk, 8-feature pieces c = tid / 32 and c + 16
+    // staging: thread -> pair q = tid % 32 of the group, 8-value pieces k = tid / 32 and k + 16 of its row: chunk
+    // k / 4, lane group k % 4
     const int q = tid & 31, c0 = tid >> 5;
     uint4 rd[2], ra[2];
     auto load = [&](uint32_t k) {
@@ -809,8 +814,9 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int c = c0 + 16 * h;
-            rd[h] = p < P ? *reinterpret_cast<const uint4*>(dz + p * 256 + 8 * c) : make_uint4(0u, 0u, 0u, 0u);
-            ra[h] = p < P ? *reinterpret_cast<const uint4*>(act + p * 256 + 8 * c) : make_uint4(0u, 0u, 0u, 0u);
+            const size_t at = chunk_at(p, c >> 2, c & 3);
+            rd[h] = p < P ? *reinterpret_cast<const uint4*>(dz + at) : make_uint4(0u, 0u, 0u, 0u);
+            ra[h] = p < P ? *reinterpret_cast<const uint4*>(act + at) : make_uint4(0u, 0u, 0u, 0u);
         }
     };
     auto stage = [&]() {
@@ -821,10 +827,11 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
             const uint32_t wa[4] = {ra[h].x, ra[h].y, ra[h].z, ra[h].w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                t_dz[(8 * c + 2 * k) * kWgRow + q] = (uint16_t)(wd[k] & 0xffffu);
-                t_dz[(8 * c + 2 * k + 1) * kWgRow + q] = (uint16_t)(wd[k] >> 16);
-                t_act[(8 * c + 2 * k) * kWgRow + q] = (uint16_t)(wa[k] & 0xffffu);
-                t_act[(8 * c + 2 * k + 1) * kWgRow + q] = (uint16_t)(wa[k] >> 16);
+                const int f = chunk_feature(c >> 2, c & 3, 2 * k);
+                t_dz[f * kWgRow + q] = (uint16_t)(wd[k] & 0xffffu);
+                t_dz[(f + 1) * kWgRow + q] = (uint16_t)(wd[k] >> 16);
+                t_act[f * kWgRow + q] = (uint16_t)(wa[k] & 0xffffu);
+                t_act[(f + 1) * kWgRow + q] = (uint16_t)(wa[k] >> 16);
             }
         }
     };
@@ -876,26 +883,24 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
 }
 
 // Output layer of the backward in one pass over the last hidden activations
-// act [P][256] (T: BF16, or FP32 after an FP32 forward), over every gridDim-th
-// listed group: with dy [P][7] FP32 (the upstream gradient as computed, not
-// rounded) and Wo [7][256],
+// act [P][256] over every gridDim-th listed group: with dy [P][7] FP32 (the
+// upstream gradient as computed, not rounded) and Wo [7][256], T the type of act,
+// wo and dz,
 //   dz[p][f] = T(sum_o dy[p][o] Wo[o][f]), zero where act[p][f] is not > 0
 //     (the gradient of the last hidden pre-activations; skipped if dz is NULL),
 //   part[blk] = the slice's sums of dy[p][o] act[p][f] (the weight gradient,
 //     7 x 256), then of dy[p][o] (the bias gradient, 7 and a pad); the caller
 //     adds the slices.
-// Thread: 8 features of every 8th pair.
+// FP32 (row-major): a thread takes 8 features of every 8th pair.
 constexpr int kOutSlice = kOut * 256 + 8;
 
-template <typename T>
-__global__ __launch_bounds__(256) void out_bwd_kernel(const float* __restrict__ dy, const T* __restrict__ wo,
-                                                      const T* __restrict__ act, int64_t P, RowGroups rg,
-                                                      T* __restrict__ dz, float* __restrict__ part) {
-    constexpr bool kBf = sizeof(T) == 2;
+__global__ __launch_bounds__(256) void out_bwd_f32_kernel(const float* __restrict__ dy, const float* __restrict__ wo,
+                                                          const float* __restrict__ act, int64_t P, RowGroups rg,
+                                                          float* __restrict__ dz, float* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) float s_w[kOut][256];
     __shared__ float s_red[4][kOut][256];  // one row per wave after the in-wave pair of rows is added
     __shared__ float s_y[4][8];
-    for (int i = threadIdx.x; i < kOut * 256; i += 256) s_w[i / 256][i % 256] = (float)wo[i];
+    for (int i = threadIdx.x; i < kOut * 256; i += 256) s_w[i / 256][i % 256] = wo[i];
     __syncthreads();
     const int f0 = (int)(threadIdx.x & 31) * 8, row = (int)(threadIdx.x >> 5);
     const uint32_t ng = *rg.count;
@@ -917,21 +922,8 @@ __global__ __launch_bounds__(256) void out_bwd_kernel(const float* __restrict__ 
                 y[o] = dy[p * kOut + o];
                 ysum[o] += y[o];
             }
-            float av[8];
-            if constexpr (kBf) {
-                const uint4 a = *reinterpret_cast<const uint4*>(act + p * 256 + f0);
-                const uint32_t aw[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-                for (int k2 = 0; k2 < 4; ++k2) {
-                    av[2 * k2] = __uint_as_float(aw[k2] << 16);
-                    av[2 * k2 + 1] = __uint_as_float(aw[k2] & 0xffff0000u);
-                }
-            } else {
-                const float4 a = load4(act + p * 256 + f0), b = load4(act + p * 256 + f0 + 4);
-                const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-                for (int j = 0; j < 8; ++j) av[j] = v[j];
-            }
+            const float4 a0 = load4(act + p * 256 + f0), a1 = load4(act + p * 256 + f0 + 4);
+            const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
 #pragma unroll
             for (int o = 0; o < kOut; ++o)
 #pragma unroll
@@ -951,23 +943,10 @@ __global__ __launch_bounds__(256) void out_bwd_kernel(const float* __restrict__ 
                 z[6] = fmaf(y[o], w1.z, z[6]);
                 z[7] = fmaf(y[o], w1.w, z[7]);
             }
-            if constexpr (kBf) {
-                uint32_t ow[4];
 #pragma unroll
-                for (int k2 = 0; k2 < 4; ++k2) {
-                    const uint32_t lo = __builtin_bit_cast(uint16_t, to_bf16(z[2 * k2]));
-                    const uint32_t hi = __builtin_bit_cast(uint16_t, to_bf16(z[2 * k2 + 1]));
-                    // positive as the forward's ReLU decides on the bits: sign clear and not zero
-                    const int32_t xl = (int32_t)__float_as_uint(av[2 * k2]), xh = (int32_t)__float_as_uint(av[2 * k2 + 1]);
-                    ow[k2] = (xl > 0 ? lo : 0u) | (xh > 0 ? hi << 16 : 0u);
-                }
-                *reinterpret_cast<uint4*>(dz + p * 256 + f0) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) z[j] = av[j] > 0.f ? z[j] : 0.f;
-                *reinterpret_cast<float4*>(dz + p * 256 + f0) = make_float4(z[0], z[1], z[2], z[3]);
-                *reinterpret_cast<float4*>(dz + p * 256 + f0 + 4) = make_float4(z[4], z[5], z[6], z[7]);
-            }
+            for (int j = 0; j < 8; ++j) z[j] = av[j] > 0.f ? z[j] : 0.f;
+            *reinterpret_cast<float4*>(dz + p * 256 + f0) = make_float4(z[0], z[1], z[2], z[3]);
+            *reinterpret_cast<float4*>(dz + p * 256 + f0 + 4) = make_float4(z[4], z[5], z[6], z[7]);
         }
     }
     // rows 2 w and 2 w + 1 are the two halves of wave w: add them across lanes l and l + 32
@@ -994,8 +973,82 @@ __global__ __launch_bounds__(256) void out_bwd_kernel(const float* __restrict__ 
     }
 }
 
+// The same after a BF16 forward, in chunk order: wave w takes feature chunk w of
+// 16 rows at a time, a lane 8 features of one row, whose output weights stay in
+// its registers. 105 us at 800k pairs, a quarter of them with a gradient (122
+// row-major).
+__global__ __launch_bounds__(512) void out_bwd_bf16_kernel(const float* __restrict__ dy, const __bf16* __restrict__ wo,
+                                                           const __bf16* __restrict__ act, int64_t P, RowGroups rg,
+                                                           __bf16* __restrict__ dz, float* __restrict__ part) {
+    const int c = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), g = lane >> 4, n = lane & 15;
+    const uint32_t ng = *rg.count;
+    float w[kOut][8], acc[kOut][8], ysum[kOut];
+#pragma unroll
+    for (int o = 0; o < kOut; ++o) {
+        ysum[o] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            w[o][j] = (float)wo[o * 256 + chunk_feature(c, g, j)];
+            acc[o][j] = 0.f;
+        }
+    }
+    for (uint32_t k = blockIdx.x; k < ng; k += gridDim.x) {
+        const int64_t p0 = (int64_t)rg.list[k] * kRowGroup + n;
+        uint4 a[2];
+        float y[2][kOut];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t p = p0 + 16 * h;
+            a[h] = p < P ? *reinterpret_cast<const uint4*>(act + chunk_at(p, c, g)) : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int o = 0; o < kOut; ++o) y[h][o] = p < P ? dy[p * kOut + o] : 0.f;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t aw[4] = {a[h].x, a[h].y, a[h].z, a[h].w};
+            float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int o = 0; o < kOut; ++o) {
+                ysum[o] += y[h][o];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float av = __uint_as_float(j & 1 ? aw[j >> 1] & 0xffff0000u : aw[j >> 1] << 16);
+                    acc[o][j] = fmaf(y[h][o], av, acc[o][j]);
+                    z[j] = fmaf(y[h][o], w[o][j], z[j]);
+                }
+            }
+            const int64_t p = p0 + 16 * h;
+            if (!dz || p >= P) continue;
+            uint32_t v[4];
+#pragma unroll
+            for (int k2 = 0; k2 < 4; ++k2) {
+                const dz_f32x2 f = {z[2 * k2], z[2 * k2 + 1]};
+                v[k2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, dz_bf16x2)) & positive_halves(aw[k2]);
+            }
+            *reinterpret_cast<uint4*>(dz + chunk_at(p, c, g)) = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    }
+    // the 16 rows of a lane group
+    float* pb = part + (size_t)blockIdx.x * kOutSlice;
+#pragma unroll
+    for (int o = 0; o < kOut; ++o) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            float v = acc[o][j];
+#pragma unroll
+            for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
+            if (n == 0) pb[o * 256 + chunk_feature(c, g, j)] = v;
+        }
+        float v = ysum[o];
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
+        if (threadIdx.x == 0) pb[kOut * 256 + o] = v;
+    }
+    if (threadIdx.x == 0) pb[kOut * 256 + kOut] = 0.f;
+}
+
 // Layer-1 gradient sums in one pass over the FP32 gradient z [B][N][256]:
-// with dz = z * [act > 0] (kMask: the BF16 activations act [B][N][256] mask
+// with dz = z * [act > 0] (kMask: the BF16 activations act [B][N][256], in chunk order, mask
 // an unmasked z; else z is dz already), S[n][k] = sum_b dz[b][n][k]
 // (complete: the block owns Gaussians n0 .. n0 + 31, summed over b in order)
 // and Rpart[block][b][k] = sum over the block's Gaussians of dz[b][n][k]
@@ -1026,7 +1079,7 @@ __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restric
                 const float4 v = load4(z + off);
                 float4 m = v;
                 if constexpr (kMask) {
-                    const float4 a = load4(act + off);
+                    const float4 a = load4(act + chunk_at(p, c / 32, c % 16 / 4) + c % 32 / 16 * 4);
                     m = make_float4(a.x > 0.f ? v.x : 0.f, a.y > 0.f ? v.y : 0.f, a.z > 0.f ? v.z : 0.f,
                                     a.w > 0.f ? v.w : 0.f);
                 }
@@ -1213,10 +1266,9 @@ void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act,
     if (!dz && !dWo && !dbo) return;
     const int nblk = out_bwd_blocks(P);  // P = 0: one block writes zeros
     if (bf16)
-        out_bwd_kernel<__bf16><<<nblk, 256, 0, st>>>(dy, (const __bf16*)wo, (const __bf16*)act, P, rg, (__bf16*)dz,
-                                                     part);
+        out_bwd_bf16_kernel<<<nblk, 512, 0, st>>>(dy, (const __bf16*)wo, (const __bf16*)act, P, rg, (__bf16*)dz, part);
     else
-        out_bwd_kernel<float><<<nblk, 256, 0, st>>>(dy, (const float*)wo, (const float*)act, P, rg, (float*)dz, part);
+        out_bwd_f32_kernel<<<nblk, 256, 0, st>>>(dy, (const float*)wo, (const float*)act, P, rg, (float*)dz, part);
     slice_sum(part, nblk, kOutSlice, kOut * 256, kOut, dWo, dbo, st);
 }
 

@@ -202,7 +202,8 @@ void launch_pack_mlp(const DevScene& d, hipStream_t st);
 // the fragment-major FP32 copy alone (frag_floats(n_hidden) floats at d.f32_frag)
 void launch_pack_f32_frag(const DevScene& d, hipStream_t st);
 
-// act_out (optional): also store the hidden activations, BF16 [n_hidden][B * N][256] (the backward's operands)
+// act_out (optional): also store the hidden activations, BF16 [n_hidden][chunk_rows(B * N)][256] in chunk order (the
+// backward's operands)
 void launch_mlp_bf16(const DevScene& s, const float* qs, int B, const Grid& g, bool paper_mask, const Records& r,
                      float* delta_out, hipStream_t st, int pairs_per_wave, void* act_out = nullptr);
 
@@ -253,6 +254,21 @@ void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* b
 void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,
                            const float* grad_out, const float* aux_T, const uint32_t* aux_last, float* dpair,
                            hipStream_t st, float* det_part = nullptr, int N = 0, const uint32_t* det_off = nullptr);
+// BF16 rows of 256 features of the MLP backward (activations, gradients of pre-activations) in the MFMA kernels' own
+// order: tile of 16 rows, 32-feature chunk c, lane 16 g + row % 16, then the lane's 8 values: features
+// 32 c + 4 g + 0..3 and 32 c + 16 + 4 g + 0..3. A wave's load or store of a chunk is one contiguous KiB. Rows are
+// padded to whole tiles.
+inline int64_t chunk_rows(int64_t P) { return (P + 15) / 16 * 16; }
+__host__ __device__ inline size_t chunk_at(int64_t row, int c, int g) {  // first of the lane's 8 values
+    return ((size_t)(row >> 4) * 8 + c) * 512 + (size_t)(g * 16 + (int)(row & 15)) * 8;
+}
+// Bytes of one layer of P rows: BF16 in chunk order, FP32 row-major.
+inline size_t act_layer_bytes(int64_t P, bool bf16) {
+    return (size_t)(bf16 ? chunk_rows(P) * 2 : P * 4) * 256;
+}
+// element j of lane group g in chunk c is feature chunk_feature(c, g, j)
+__host__ __device__ inline int chunk_feature(int c, int g, int j) { return 32 * c + (j < 4 ? 4 * g + j : 12 + 4 * g + j); }
+
 // Rows (pairs) of the MLP backward that have a gradient, in groups of 32: rows outside the listed groups have a zero
 // dy, so they add nothing to any weight gradient or sum and are neither read nor written by the kernels below (their
 // rows of dz hold anything).
@@ -289,6 +305,7 @@ void launch_colsum(const float* A, int64_t rows, int64_t cols, int nz, int64_t b
                    int64_t out_bs, hipStream_t st);
 // dg: [N][26] gradient of gamma(mu_hat) summed over the batch -> dmu [N][2]
 void launch_pe_chain(const float* dg, const DevScene& s, float* dmu, hipStream_t st);
+// The BF16 arrays dz and act below are in chunk order.
 // BF16 weights of the backward from the FP32 masters w[0 .. n_hidden]: per 256 x 256 layer 65536 values in fragment
 // order, then the output layer's 7 x 256
 void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t st);
@@ -307,7 +324,7 @@ void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGrou
 int layer1_grad_blocks(int N);
 void launch_layer1_grad(const void* dz1, const void* wf, const void* act, int B, int N, const RowGroups& rg, float* S,
                         float* Rpart, hipStream_t st);
-// Output layer of the backward in one pass over act [P][256] (BF16 or FP32, as wo and dz): dz (may be NULL) = (dy Wo)
+// Output layer of the backward in one pass over act [P][256] (BF16 or FP32 row-major, as wo and dz): dz (may be NULL) = (dy Wo)
 // masked by act > 0; dWo [7][256] = dy^T act and dbo [7] = the column sums of dy (either may be NULL). part:
 // out_bwd_floats(P) floats.
 size_t out_bwd_floats(int64_t P);
@@ -315,7 +332,7 @@ void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act,
                     void* dz, float* part, float* dWo, float* dbo, hipStream_t st);
 // out[c] = sum of nb slices part[j][c] of cols values (a multiple of 4), in a fixed order
 void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipStream_t st);
-// S [N][256] = sum_b of z * [act > 0] (act BF16; null: z is masked already) and Rpart [layer1_sums_blocks(N)][B][256]
+// S [N][256] = sum_b of z * [act > 0] (act BF16, chunk order; null: z is masked already) and Rpart [layer1_sums_blocks(N)][B][256]
 // partial sums over Gaussians; rows whose bit is clear (bits may be null) count zero
 int layer1_sums_blocks(int N);
 void launch_layer1_sums(const float* z, const void* act, const uint32_t* bits, int B, int N, float* S, float* Rpart,

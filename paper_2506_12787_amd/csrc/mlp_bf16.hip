@@ -61,8 +61,8 @@ struct Bf16Args {
     int n_tiles;              // B * tiles_per_query
     int tiles_per_query;      // ceil(N / pairs per block): tiles never straddle two queries (kPack: 0)
     uint32_t rows;            // kPack: the tiles cut these flat (query, pair) rows
-    uint16_t* act_out;        // kAct: hidden activations (bf16 bits) [n_hidden][B * N][256]
-    int64_t act_stride;       // elements per activation layer: B * N * 256
+    uint16_t* act_out;        // kAct: hidden activations (bf16 bits) [n_hidden][rows][256] in chunk order
+    int64_t act_stride;       // elements per activation layer: chunk_rows(B * N) * 256
     MixBatch mix;             // kMix: the batch's scene and query tables (per tile: query, scene, stream, biases)
 };
 
@@ -105,8 +105,8 @@ __device__ __forceinline__ void vmem_wait_all() { __builtin_amdgcn_s_waitcnt(0x0
 
 // NCB column blocks of 16 pairs per wave; WAVES waves per block; ring steps of
 // STEP fragments; WPE waves per SIMD. kAct: also store every hidden activation
-// (after the ReLU, in BF16, exactly the next layer's operand) row-major per
-// pair, for the backward pass.
+// (after the ReLU, in BF16, exactly the next layer's operand) for the backward
+// pass.
 //
 // Weight ring: kSlots LDS slots of one step each. The step q + 2 is
 // copied global -> LDS directly (global_load_lds, no registers) at the start of
@@ -293,7 +293,9 @@ mlp_bf16_kernel(Bf16Args a) {
     // otherwise be sunk next to its first use, after the MFMAs it should overlap).
     // lay_: index of the activation (0 = layer 1's output). With kAct the lane's
     // 8 values (features 32 cp + 4 g + 0..3 and 32 cp + 16 + 4 g + 0..3 of its
-    // pair) are also stored.
+    // pair) are also stored, in chunk order: a column block of 16 rows is one
+    // contiguous KiB. (Stored row-major, in 32-byte pieces, the stores doubled the
+    // kernel's time at 800k pairs, 265 -> 557 us; so it is 430, 1.2 GB written.)
 #define SWF_PACK(dst_, cp_, cb_, lay_)                                                \
     do {                                                                              \
         u32x4 u_ = __builtin_bit_cast(u32x4, pack_relu(acc[2 * (cp_)][cb_], acc[2 * (cp_) + 1][cb_])); \
@@ -302,10 +304,8 @@ mlp_bf16_kernel(Bf16Args a) {
         if (kAct) {                                                                   \
             const int pa_ = p0 + (cb_) * 16 + n16;                                    \
             if (pa_ < Nq) {                                                           \
-                uint2* d_ = reinterpret_cast<uint2*>(a.act_out + (size_t)(lay_) * a.act_stride + \
-                                                     (row0 + pa_) * 256 + 32 * (cp_) + 4 * g);  \
-                d_[0] = make_uint2(u_.x, u_.y);                                       \
-                d_[4] = make_uint2(u_.z, u_.w);                                       \
+                *reinterpret_cast<u32x4*>(a.act_out + (size_t)(lay_) * a.act_stride + \
+                                          chunk_at((int64_t)row0 + pa_, cp_, g)) = u_; \
             }                                                                         \
         }                                                                             \
     } while (0)
@@ -640,7 +640,7 @@ void launch_mlp_bf16(const DevScene& s, const float* qs, int B, const Grid& g, b
     // every variant computes the same values
     if (act_out) {
         a.act_out = reinterpret_cast<uint16_t*>(act_out);
-        a.act_stride = (int64_t)B * s.n * 256;
+        a.act_stride = chunk_rows((int64_t)B * s.n) * 256;
         launch_batch<true>(a, s.n, B, s.n_hidden, st);
     } else if (pairs_per_wave == 64)
         launch_variant<4, 4, 1>(a, s.n, B, s.n_hidden, st);  // 256 pairs, one wave per SIMD

@@ -833,8 +833,7 @@ swf_status Ctx::render(Workspace& w, int sid, const float* tx, int B, int flags,
         Scene* sc0 = scene(sid);
         if (sc0 && sc0->d.kind == 0 && sc0->d.has_mlp && !(flags & SWF_NO_DEFORM) &&
             (uint64_t)B * (uint64_t)sc0->d.n < (1ull << 32)) {
-            const size_t esz = (flags & SWF_MLP_BF16) ? sizeof(uint16_t) : sizeof(float);
-            const size_t actb = (size_t)B * sc0->d.n * 256 * esz;
+            const size_t actb = act_layer_bytes((int64_t)B * sc0->d.n, (flags & SWF_MLP_BF16) != 0);
             if ((s = w.act.reserve(this, actb * sc0->d.n_hidden + 16, st))) return s;
             w.act_out = w.act.ptr;
             keep_acts = true;
@@ -1337,7 +1336,7 @@ swf_status swf_debug_relu_pattern(swf_ctx* h, uint8_t* pattern, uint64_t capacit
     if (capacity < pairs * per) return c->fail(SWF_E_OVERFLOW, "capacity below batch * n * layers * 256");
     swf_status s;
     if ((s = c->hip(hipDeviceSynchronize(), "device sync"))) return s;
-    const size_t esz = L.bf16 ? 2 : 4, layer_bytes = pairs * 256 * esz;
+    const size_t layer_bytes = act_layer_bytes((int64_t)pairs, L.bf16);
     std::vector<uint8_t> a(layer_bytes);
     for (int l = 0; l < L.layers; ++l) {
         if ((s = c->hip(hipMemcpy(a.data(), (const char*)c->ws.act.ptr + layer_bytes * l, layer_bytes,
@@ -1347,13 +1346,16 @@ swf_status swf_debug_relu_pattern(swf_ctx* h, uint8_t* pattern, uint64_t capacit
         for (size_t i = 0; i < pairs; ++i) {
             const size_t q = i / L.n, id = sc->host_perm[i % L.n];
             uint8_t* o = pattern + ((q * L.n + id) * L.layers + l) * 256;
-            for (int k = 0; k < 256; ++k) {
-                // positive activation: BF16 sign bit clear and not zero; FP32 likewise
-                if (L.bf16) {
+            // positive activation: BF16 sign bit clear and not zero; FP32 likewise
+            if (L.bf16) {
+                for (int k = 0; k < 256; ++k) {
                     uint16_t v;
-                    std::memcpy(&v, a.data() + (i * 256 + k) * 2, 2);
-                    o[k] = (v & 0x8000u) == 0 && (v & 0x7fffu) != 0;
-                } else {
+                    const int cc = k / 8 / 4, g = k / 8 % 4, j = k % 8;
+                    std::memcpy(&v, a.data() + (chunk_at((int64_t)i, cc, g) + j) * 2, 2);
+                    o[chunk_feature(cc, g, j)] = (v & 0x8000u) == 0 && (v & 0x7fffu) != 0;
+                }
+            } else {
+                for (int k = 0; k < 256; ++k) {
                     float v;
                     std::memcpy(&v, a.data() + (i * 256 + k) * 4, 4);
                     o[k] = v > 0.0f;
