@@ -294,8 +294,10 @@ mlp_bf16_kernel(Bf16Args a) {
     // lay_: index of the activation (0 = layer 1's output). With kAct the lane's
     // 8 values (features 32 cp + 4 g + 0..3 and 32 cp + 16 + 4 g + 0..3 of its
     // pair) are also stored, in chunk order: a column block of 16 rows is one
-    // contiguous KiB. (Stored row-major, in 32-byte pieces, the stores doubled the
-    // kernel's time at 800k pairs, 265 -> 557 us; so it is 430, 1.2 GB written.)
+    // contiguous KiB. The stores are non-temporal: they are
+    // more than the caches hold and must not turn the weights out of L2. (At 800k
+    // pairs, 1.6 GB: 265 us without the stores, 362 with them, 430 with ordinary
+    // stores, 557 with ordinary stores row-major in 32-byte pieces.)
 #define SWF_PACK(dst_, cp_, cb_, lay_)                                                \
     do {                                                                              \
         u32x4 u_ = __builtin_bit_cast(u32x4, pack_relu(acc[2 * (cp_)][cb_], acc[2 * (cp_) + 1][cb_])); \
@@ -304,8 +306,9 @@ mlp_bf16_kernel(Bf16Args a) {
         if (kAct) {                                                                   \
             const int pa_ = p0 + (cb_) * 16 + n16;                                    \
             if (pa_ < Nq) {                                                           \
-                *reinterpret_cast<u32x4*>(a.act_out + (size_t)(lay_) * a.act_stride + \
-                                          chunk_at((int64_t)row0 + pa_, cp_, g)) = u_; \
+                __builtin_nontemporal_store(                                          \
+                    u_, reinterpret_cast<u32x4*>(a.act_out + (size_t)(lay_) * a.act_stride + \
+                                                 chunk_at((int64_t)row0 + pa_, cp_, g))); \
             }                                                                         \
         }                                                                             \
     } while (0)
