@@ -38,8 +38,10 @@ class _RenderFn(torch.autograd.Function):
         tx, aux = ctx.saved_tensors
         r = ctx.renderer
         dev = grad_out.device
-        grads = [torch.zeros(s, device=dev, dtype=torch.float32) for s in ctx.shapes]
         n_g = len(GAUSSIAN_KEYS)
+        # the backward overwrites every gradient buffer; only an MLP that the render passed by keeps its zeros
+        fills = [torch.zeros if ctx.flags & B.NO_DEFORM and i >= n_g else torch.empty for i in range(len(ctx.shapes))]
+        grads = [f(s, device=dev, dtype=torch.float32) for f, s in zip(fills, ctx.shapes)]
         gd = dict(zip(GAUSSIAN_KEYS, grads[:n_g]))
         if ctx.has_mlp:
             L = (len(grads) - n_g) // 2

@@ -189,7 +189,7 @@ void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P
 void launch_mlp_fp32(const DevScene& s, const float* qs, int B, const Grid& g, bool paper_mask, const Records& r,
                      float* delta_out, hipStream_t st, float* const* act_out = nullptr);
 void launch_preprocess_static(const DevScene& s, int B, const Grid& g, const Records& r, hipStream_t st);
-void launch_gather_params(float* const* src, const uint32_t* perm, int n, float* const* dst, hipStream_t st);
+void launch_gather_params(const float* const* src, const uint32_t* perm, int n, float* const* dst, hipStream_t st);
 void launch_permute_delta(const float* delta_sorted, const uint32_t* perm, int B, int n, float* delta_out,
                           hipStream_t st);
 
@@ -199,6 +199,14 @@ void compute_mean_features_bf16(DevScene& s, hipStream_t st);
 // pack.hip: rebuild the fragment-major FP32 copy and the BF16 weight stream from
 // the FP32 master weights d.w[] on the device (after a device-side MLP update)
 void launch_pack_mlp(const DevScene& d, hipStream_t st);
+// dst[k][0 .. n[k]) = src[k][0 .. n[k]) for k < sets, in one launch
+struct CopySet {
+    const float* src[16];
+    float* dst[16];
+    uint32_t n[16];
+    int sets;
+};
+void launch_copy_sets(const CopySet& c, hipStream_t st);
 // the fragment-major FP32 copy alone (frag_floats(n_hidden) floats at d.f32_frag)
 void launch_pack_f32_frag(const DevScene& d, hipStream_t st);
 

@@ -89,7 +89,17 @@ __global__ void pack_frag_kernel(PackArgs a) {
     a.frag[e] = v;
 }
 
+__global__ void copy_sets_kernel(CopySet c) {
+    const int k = blockIdx.y;
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < c.n[k]; i += gridDim.x * 256) c.dst[k][i] = c.src[k][i];
+}
+
 }  // namespace
+
+void launch_copy_sets(const CopySet& c, hipStream_t st) {
+    // 65536 elements at most: one per thread of 64 blocks x 4
+    if (c.sets > 0) copy_sets_kernel<<<dim3(64, c.sets), 256, 0, st>>>(c);
+}
 
 static PackArgs pack_args(const DevScene& d) {
     PackArgs a{};

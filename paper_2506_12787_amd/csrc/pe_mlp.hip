@@ -340,7 +340,7 @@ __global__ void gather_params_kernel(Ptr7 p, const uint32_t* __restrict__ perm, 
 
 }  // namespace
 
-void launch_gather_params(float* const* src, const uint32_t* perm, int n, float* const* dst, hipStream_t st) {
+void launch_gather_params(const float* const* src, const uint32_t* perm, int n, float* const* dst, hipStream_t st) {
     Ptr7 p;
     for (int k = 0; k < 7; ++k) {
         p.s[k] = src[k];

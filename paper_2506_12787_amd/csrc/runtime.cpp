@@ -498,6 +498,21 @@ swf_status Ctx::pack_mlp(Scene* s, const swf_mlp* mlp, bool dev, bool alloc) {
     return st;
 }
 
+// Whether a kernel on `device` may read [p, p + bytes): all of it in one allocation of that device's memory.
+static bool kernel_readable(const void* p, size_t bytes, int device) {
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    const bool ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice &&
+                    at.device == device &&
+                    hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess &&
+                    (size_t)((const char*)p - (const char*)base) + bytes <= size;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+
+// Sources on the device that its kernels can read are read where they are (one launch per group of arrays); host
+// arrays, and whatever else a copy takes as a source, are copied one by one, as a copy each cost 4 us of the stream.
 swf_status Ctx::update_scene(int id, const swf_gaussians* g, const swf_mlp* mlp, bool dev, hipStream_t st) {
     Scene* s = scene(id);
     if (!s) return fail(SWF_E_NOT_FOUND, "unknown scene id");
@@ -511,17 +526,23 @@ swf_status Ctx::update_scene(int id, const swf_gaussians* g, const swf_mlp* mlp,
                                g->amplitude};
         float* dst[7] = {d.mx, d.my, d.lsx, d.lsy, d.rot, d.logit, d.amp};
         const size_t bytes = (size_t)d.n * sizeof(float);
-        if ((r = ws.stage.reserve(this, 7 * bytes + 16, st))) return r;
+        bool direct = dev;
         for (int k = 0; k < 7; ++k) {
             if (!src[k]) return fail(SWF_E_INVALID, "null parameter array");
+            direct = direct && kernel_readable(src[k], bytes, device);
+        }
+        const float* from[7];
+        if (!direct && (r = ws.stage.reserve(this, 7 * bytes + 16, st))) return r;
+        for (int k = 0; k < 7; ++k) {
+            from[k] = src[k];
+            if (direct) continue;
             float* tmp = (float*)((char*)ws.stage.ptr + k * bytes);
             if ((r = hip(hipMemcpyAsync(tmp, src[k], bytes, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st),
                          "update copy")))
                 return r;
+            from[k] = tmp;
         }
-        float* tmps[7];
-        for (int k = 0; k < 7; ++k) tmps[k] = (float*)((char*)ws.stage.ptr + k * bytes);
-        launch_gather_params(tmps, d.perm, d.n, dst, st);
+        launch_gather_params(from, d.perm, d.n, dst, st);
         if (d.has_mlp) compute_mean_features_bf16(d, st);
         // host sources: the copies read pageable memory; device sources stay stream-ordered
         if (!dev && (r = hip(hipStreamSynchronize(st), "update sync"))) return r;
@@ -535,14 +556,28 @@ swf_status Ctx::update_scene(int id, const swf_gaussians* g, const swf_mlp* mlp,
             if (!(mlp->room_hi[k] > mlp->room_lo[k])) return fail(SWF_E_INVALID, "room_hi must exceed room_lo");
         if (dev) {
             // device sources: copy the masters and rebuild the derived layouts on `st`
+            CopySet c{};
+            bool direct = true;
             for (int l = 0; l <= d.n_hidden; ++l) {
                 const size_t rows = l == d.n_hidden ? kOut : d.hidden, cols = l == 0 ? d.in_dim : d.hidden;
-                if ((r = hip(hipMemcpyAsync(d.w[l], mlp->weight[l], rows * cols * sizeof(float),
-                                            hipMemcpyDeviceToDevice, st), "update copy")))
-                    return r;
-                if ((r = hip(hipMemcpyAsync(d.b[l], mlp->bias[l], rows * sizeof(float), hipMemcpyDeviceToDevice, st),
-                             "update copy")))
-                    return r;
+                const float* from[2] = {mlp->weight[l], mlp->bias[l]};
+                float* to[2] = {d.w[l], d.b[l]};
+                const size_t cnt[2] = {rows * cols, rows};
+                for (int k = 0; k < 2; ++k) {
+                    c.src[2 * l + k] = from[k];
+                    c.dst[2 * l + k] = to[k];
+                    c.n[2 * l + k] = (uint32_t)cnt[k];
+                    direct = direct && kernel_readable(from[k], cnt[k] * sizeof(float), device);
+                }
+            }
+            c.sets = 2 * (d.n_hidden + 1);
+            if (direct) {
+                launch_copy_sets(c, st);
+            } else {
+                for (int k = 0; k < c.sets; ++k)
+                    if ((r = hip(hipMemcpyAsync(c.dst[k], c.src[k], c.n[k] * sizeof(float), hipMemcpyDeviceToDevice,
+                                                st), "update copy")))
+                        return r;
             }
             for (int k = 0; k < 3; ++k) {
                 d.room_lo[k] = mlp->room_lo[k];

@@ -88,12 +88,12 @@ class Trainer:
             out, aux = lib.render(self.sid, None, flags=flags | B.KEEP_AUX, batch=nb)
         loss, grad = lib.hybrid_loss(out, target, self.lambda1)
         freeze = fine and self.stop_grad_positions
-        gg = {k: (None if (freeze and k in ("mean_x", "mean_y")) else torch.zeros_like(t))
+        gg = {k: (None if (freeze and k in ("mean_x", "mean_y")) else torch.empty_like(t))
               for k, t in self.g.items()}
         grads = dict(gg)
         if fine:
-            grads["weight"] = [torch.zeros_like(w) for w in self.Ws]
-            grads["bias"] = [torch.zeros_like(b) for b in self.bs]
+            grads["weight"] = [torch.empty_like(w) for w in self.Ws]
+            grads["bias"] = [torch.empty_like(b) for b in self.bs]
         lib.render_backward(self.sid, txs, flags, grad, aux, grads)
         # Adam: the Gaussians (the canonical positions only while not frozen), then the MLP in the fine stage
         ps = [self.g[k] for k in GAUSSIAN_KEYS if gg[k] is not None]
