@@ -70,6 +70,9 @@ __device__ __forceinline__ float wave_sum8(float (&a)[8]) {
 // divisions and nested branches).
 // kWrap: periodic azimuth, as in the forward kernel (same staged image, same
 // displacement, same culling exemption), so that every decision replays exactly.
+// The per-pair sums over tiles and waves are FP64 atomics, whose order shows only
+// below the last bit of their FP32 values: with FP32 ones a BF16 gradient that
+// is rounded from them could fall either way from run to run.
 // kDet: instead of adding into dpair, each wave writes its 8 sums of an entry
 // to part[slot * 32 + wave * 8 + k] (zeroed beforehand), slot = the pair's
 // first slot (det_off: the exclusive scan of the key counts) + the tile's
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals, const float4* __restrict__ geo,
     const float4* __restrict__ wm, const float2* __restrict__ oa, int H, int W, int TW, int tiles,
     const float* __restrict__ grad_out, const float* __restrict__ aux_T, const uint32_t* __restrict__ aux_last,
-    float* __restrict__ dpair, const uint2* __restrict__ rect = nullptr, const uint32_t* __restrict__ det_off = nullptr) {
+    double* __restrict__ dpair, float* __restrict__ part = nullptr, const uint2* __restrict__ rect = nullptr, const uint32_t* __restrict__ det_off = nullptr) {
     constexpr int kN = TILE * TILE;
     constexpr bool kCull = TILE == 16;
     constexpr int kWaves = kN / 64;
@@ -165,9 +168,9 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
         const int l = (int)lane_id(), k = l >> 3;
         if ((l & 7) == 0 && v != 0.0f) {
             if constexpr (kDet)
-                dpair[(size_t)s_slot[jj] * 32 + (size_t)wq * 8 + k] = v;
+                part[(size_t)s_slot[jj] * 32 + (size_t)wq * 8 + k] = v;
             else
-                atomicAdd(dpair + (size_t)s_v[jj] * 8 + k, v);
+                atomicAdd(dpair + (size_t)s_v[jj] * 8 + k, (double)v);
         }
     };
 
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
 // on), the four waves' sums of its entry in that tile's list, found by binary
 // search (a list holds its pairs in increasing order).
 __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint32_t* __restrict__ det_off,
-                                  const float* __restrict__ part, int64_t P, float* __restrict__ dpair) {
+                                  const float* __restrict__ part, int64_t P, double* __restrict__ dpair) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P) return;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -265,7 +268,7 @@ __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint
 // behind the pixels' termination depth or outside every pixel's cutoff have
 // none: at N = 50k, 90 x 360, five of six.
 __global__ __launch_bounds__(256) void preprocess_backward_kernel(
-    const float* __restrict__ dpair, const float4* __restrict__ wm, const float2* __restrict__ oa,
+    const double* __restrict__ dpair, const float4* __restrict__ wm, const float2* __restrict__ oa,
     const uint32_t* __restrict__ count, const uint2* __restrict__ rect, int64_t P, int paper_mask,
     float* __restrict__ dbase, float* __restrict__ dy, uint32_t* __restrict__ bits, uint32_t* __restrict__ groups) {
     __shared__ uint32_t s_n;
@@ -275,7 +278,9 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
     bool live = false;
     if (in && count[i] == 0) live = rect[i].y == kCullNonFinite;
     if (in && count[i]) {
-        const float* g = dpair + i * 8;
+        float g[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g[k] = (float)dpair[i * 8 + k];
         const float4 m = wm[i];
         const float op = oa[i].x;
         r[0] = -(g[0] * m.x + g[1] * m.z);
@@ -1149,14 +1154,14 @@ __global__ void mean_features_f32_kernel(const float* __restrict__ mx, const flo
 }  // namespace
 
 void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,
-                           const float* grad_out, const float* aux_T, const uint32_t* aux_last, float* dpair,
+                           const float* grad_out, const float* aux_T, const uint32_t* aux_last, double* dpair,
                            hipStream_t st, float* det_part, int N, const uint32_t* det_off) {
     const unsigned blocks = (unsigned)(B * g.tiles);
     if (!blocks) return;
-    float* dst = det_part ? det_part : dpair;
 #define SWF_BLEND_BWD(TILE, WRAP, DET)                                                                         \
     blend_backward_kernel<TILE, WRAP, DET><<<blocks, TILE * TILE, 0, st>>>(                                    \
-        ranges, vals, r.geo, r.wm, r.oa, g.H, g.W, g.TW, g.tiles, grad_out, aux_T, aux_last, dst, r.rect, det_off)
+        ranges, vals, r.geo, r.wm, r.oa, g.H, g.W, g.TW, g.tiles, grad_out, aux_T, aux_last, dpair, det_part, r.rect,  \
+        det_off)
 #define SWF_BLEND_BWD_T(TILE, DET)   \
     do {                             \
         if (g.wrap)                  \
@@ -1192,7 +1197,7 @@ RowGroups row_groups(uint32_t* buf, int64_t P) {
     return g;
 }
 
-void launch_preprocess_backward(const float* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
+void launch_preprocess_backward(const double* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
                                 float* dy, uint32_t* group_buf, hipStream_t st) {
     if (P <= 0) {
         if (dy) launch_clear_u32(group_buf, 1, st);
