@@ -57,60 +57,76 @@ __global__ __launch_bounds__(256) void tx_features_kernel(const float* __restric
 
 // ---- FP32 MLP on the matrix cores ---------------------------------------------
 // v_mfma_f32_16x16x4_f32 (FP32 products and sums): per layer D = W H with 16
-// output units x 16 pairs per instruction and K = 4 inputs. A wave holds 16
-// pairs; the hidden state stays in registers as B operands: for input chunk c
-// lane l holds input k(c, l / 16) of pair l % 16. The result of output tile t
-// (4 registers per lane: units 16 t + 4 (l / 16) + i, i = 0..3) is, after the
-// ReLU, exactly the next layer's chunks 4 t + i, since the fragment-major
-// weights list their input columns in that order. Layer 1 takes the 26 mean
-// features (chunk c of lane group g = feature 4 c + g, zero past 26) with the
-// per-query TX part qs[b] + b1 as its bias; the output layer is one tile of 16
-// rows, 7 used. Weight fragments (16 bytes per lane, 4 instructions each) are
-// read from the L2-resident packed copy kPrefetch fragments ahead of their use;
-// a scheduling barrier after each fragment's instructions keeps every load
-// where it is written (left free, the compiler sinks the loads next to their
-// use, which leaves one or two in flight and exposes the L2 latency).
+// output units x 16 pairs per instruction and K = 4 inputs. A block of four
+// waves takes kNcb column blocks of 16 pairs through the network together: wave
+// w forms output tiles 4 w .. 4 w + 3 of every column block, so that a weight
+// fragment (16 bytes per lane, 4 instructions per column block) is loaded once
+// per block, and 4 kNcb independent sums are in flight. The hidden state lies in
+// LDS as B operands: piece (cb, q), lane l = 16 g + n, holds inputs
+// 16 q + 4 g + 0..3 of pair n of column block cb. The result of output tile t
+// (4 registers per lane: units 16 t + 4 g + i) is, after the ReLU, exactly the
+// next layer's piece t, since the fragment-major weights list their input
+// columns in that order; every access is a contiguous KiB. Layer 1 takes the 26
+// mean features (piece q, element j of lane group g = feature 4 (4 q + j) + g,
+// zero past 26) with the per-query TX part qs[b] + b1 as its bias; the output
+// layer is one tile of 16 rows, 7 used, one column block per wave. An output's
+// sum runs over its inputs in the same order whatever kNcb is.
+//
+// Bound by the matrix cores: 3264 instructions of 32 cycles per 16 pairs. With
+// whole networks per wave (weights from L2 for 16 pairs at a time, three waves
+// per SIMD) the last waves of a launch ran alone on their SIMDs: 100k pairs 428
+// us, now 350; 16 pairs 74 us, now 13; at full rate 81 % of the instructions' own
+// time (64-pair blocks, 10 rounds).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kFWaves = 4;     // waves per block, 16 pairs each
-constexpr int kPrefetch = 2;   // weight fragments in flight ahead of the one in use
+constexpr int kFWaves = 4;  // waves per block, 4 output tiles each
+constexpr int kCus = 256;
 
-// store (optional): the lane's 16-byte slice of each output tile; mask (optional, with store): stored values
-// are zeroed where mask <= 0 (read at the tile's start, its latency under the tile's instructions).
-template <int kTiles, int kIn, bool kRelu>
-__device__ __forceinline__ void f32_mfma_layer(const float4* __restrict__ wf, const float* brow, int lane,
-                                               const float (&hin)[kIn], float (&hout)[64], float* store,
-                                               const float* mask = nullptr) {
-    constexpr int G = kIn / 4;  // fragments per output tile
-    constexpr int F = kTiles * G;
-    const int g = lane >> 4;
-    float4 wq[kPrefetch];
+// Weight fragments of kAhead pieces are in flight ahead of the one in use; a layer's first ones are loaded before the
+// barriers in front of it.
+template <int kNcb>
+constexpr int kAhead = kNcb >= 4 ? 1 : 2;
+
+// The first fragments of the wave's tiles. wf: fragments of its first tile, kQ per tile.
+template <int kNcb, int kQ>
+__device__ __forceinline__ void f32_first(const float4* __restrict__ wf, int lane, float4 (&w)[kAhead<kNcb> + 1][4]) {
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i) wq[i] = i < F ? wf[i * 64 + lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int d = 0; d < kAhead<kNcb>; ++d)
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) {
-        const float4 b4 = *reinterpret_cast<const float4*>(brow + 16 * t + 4 * g);
-        f32x4 acc = f32x4{b4.x, b4.y, b4.z, b4.w};
-        const float4 mk = mask ? *reinterpret_cast<const float4*>(mask + 16 * t + 4 * g)
-                               : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+        for (int i = 0; i < 4; ++i) w[d][i] = wf[((size_t)i * kQ + d) * 64 + lane];
+}
+
+// acc[i][cb] += tile 4 wave + i of the layer over kQ pieces of the state; w holds the first fragments.
+template <int kNcb, int kQ>
+__device__ __forceinline__ void f32_coop_layer(const float4* __restrict__ wf, const float4* s_h, int lane,
+                                               float4 (&w)[kAhead<kNcb> + 1][4], f32x4 (&acc)[4][kNcb]) {
+    constexpr int kA = kAhead<kNcb>;
+    float4 bn[kNcb];
 #pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const int f = t * G + q;
-            const float4 w = wq[0];
+    for (int cb = 0; cb < kNcb; ++cb) bn[cb] = s_h[cb * 16 * 64 + lane];
 #pragma unroll
-            for (int i = 0; i + 1 < kPrefetch; ++i) wq[i] = wq[i + 1];
-            if (f + kPrefetch < F) wq[kPrefetch - 1] = wf[(f + kPrefetch) * 64 + lane];
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, hin[4 * q + 0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, hin[4 * q + 1], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, hin[4 * q + 2], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, hin[4 * q + 3], acc, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < kQ; ++q) {
+        float4 b[kNcb];
+#pragma unroll
+        for (int cb = 0; cb < kNcb; ++cb) {
+            b[cb] = bn[cb];
+            if (q + 1 < kQ) bn[cb] = s_h[(cb * 16 + q + 1) * 64 + lane];
         }
+        if (q + kA < kQ)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) hout[4 * t + i] = kRelu ? fmaxf(acc[i], 0.0f) : acc[i];
-        if (store)
-            *reinterpret_cast<float4*>(store + 16 * t + 4 * g) =
-                make_float4(mk.x > 0.0f ? hout[4 * t] : 0.0f, mk.y > 0.0f ? hout[4 * t + 1] : 0.0f,
-                            mk.z > 0.0f ? hout[4 * t + 2] : 0.0f, mk.w > 0.0f ? hout[4 * t + 3] : 0.0f);
+            for (int i = 0; i < 4; ++i) w[(q + kA) % (kA + 1)][i] = wf[((size_t)i * kQ + q + kA) * 64 + lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 wi = w[q % (kA + 1)][i];
+                const float wv = j == 0 ? wi.x : j == 1 ? wi.y : j == 2 ? wi.z : wi.w;
+#pragma unroll
+                for (int cb = 0; cb < kNcb; ++cb) {
+                    const float bv = j == 0 ? b[cb].x : j == 1 ? b[cb].y : j == 2 ? b[cb].z : b[cb].w;
+                    acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv, bv, acc[i][cb], 0, 0, 0);
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay where they are written
     }
 }
 
@@ -121,94 +137,133 @@ __device__ __forceinline__ void f32_mfma_layer(const float4* __restrict__ wf, co
 // past their query's pairs do nothing.
 constexpr int kMixGroups = 24;  // 16-pair groups per 384-pair MLP tile of a mixed batch
 
-template <bool kMix>
-__global__ __launch_bounds__(64 * kFWaves, 3) void mlp_fp32_kernel(MlpArgs a, MixBatch mix) {
-    __shared__ float outv[kFWaves][16][8];
+// gw0: the block's first group of 16 pairs; s_h, outv, s_q (the pairs' queries): LDS for kNcb column blocks.
+template <bool kMix, int kNcb>
+__device__ __forceinline__ void mlp_fp32_block(const MlpArgs& a, const MixBatch& mix, int64_t gw0, float4* s_h,
+                                               float (*outv)[16][8], uint32_t* s_q) {
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     const int g = lane >> 4;
-    // the wave's 16 pairs: this lane's record row and its index p in the scene; rows past the query are computed
-    // on index 0 and not written
-    bool active;  // wave-uniform
+    // waves 0 .. kNcb - 1: the 16 pairs of column block `wave`: this lane's record row and its index p in the
+    // scene; rows past the query are computed on index 0 and not written
+    const MixScene* sc = nullptr;  // block-uniform: a block's pairs lie in one MLP tile of one query
     size_t row = 0;
-    int p = 0, npairs = 0;
-    const MixScene* sc = nullptr;
-    const float* qrow = nullptr;  // the layer-1 bias of the lane's query (its TX term)
+    int p = 0;
+    bool in = false;
     if constexpr (kMix) {
-        const int gw = (int)blockIdx.x * kFWaves + wave;
-        const int tile = gw / kMixGroups;
-        active = tile < mix.queries[mix.B].mlp_tile_base;
-        if (active) {
-            const int q = mix_find(mix.queries, mix.B, tile, [](const MixQuery& x) { return x.mlp_tile_base; });
-            sc = &mix.scenes[mix.queries[q].scene];
-            const int pb = (tile - mix.queries[q].mlp_tile_base) * (16 * kMixGroups) + (gw % kMixGroups) * 16;
-            npairs = sc->N;
-            active = pb < npairs;
-            p = pb + (lane & 15);
-            row = (size_t)mix.queries[q].pair_base + p;
-            qrow = a.qs + (size_t)q * 256;
-        }
+        static_assert(kMixGroups % kNcb == 0, "a block within one tile");
+        const int gw = (int)gw0 + wave;
+        const int tile = (int)gw0 / kMixGroups;
+        if (tile >= mix.queries[mix.B].mlp_tile_base) return;  // block-uniform
+        const int q = mix_find(mix.queries, mix.B, tile, [](const MixQuery& x) { return x.mlp_tile_base; });
+        sc = &mix.scenes[mix.queries[q].scene];
+        const int pb = (tile - mix.queries[q].mlp_tile_base) * (16 * kMixGroups);
+        if (pb + ((int)gw0 % kMixGroups) * 16 >= sc->N) return;  // block-uniform: no pair in the block
+        p = pb + (gw % kMixGroups) * 16 + (lane & 15);
+        in = wave < kNcb && p < sc->N;
+        row = (size_t)mix.queries[q].pair_base + p;
+        if ((int)threadIdx.x < kNcb * 16) s_q[threadIdx.x] = (uint32_t)q;
     } else {
         const size_t total = (size_t)a.N * a.B;
-        const size_t p0 = ((size_t)blockIdx.x * kFWaves + wave) * 16;
-        active = p0 < total;
-        row = p0 + (lane & 15);
-        npairs = row < total ? a.N : 0;  // a row past the batch: no pair
-        p = row < total ? (int)(row % a.N) : 0;
-        qrow = a.qs + (size_t)(row < total ? row / a.N : 0) * 256;
+        row = ((size_t)gw0 + wave) * 16 + (lane & 15);
+        in = wave < kNcb && row < total;
+        p = in ? (int)(row % a.N) : 0;
+        if (wave < kNcb && lane < 16) s_q[wave * 16 + lane] = in ? (uint32_t)(row / a.N) : 0u;
     }
-    const bool in = kMix ? p < npairs : npairs > 0;
     if (!in) p = 0;
-    if (active) {
+    if (wave < kNcb) {
+        float f[kMeanFeat];
+        if constexpr (kMix)
+            mean_features(sc->mx[p], sc->my[p], sc->W, sc->H, f);
+        else
+            mean_features(a.mx[p], a.my[p], a.sW, a.sH, f);
         float x[8];
-        {
-            float f[kMeanFeat];
-            if constexpr (kMix)
-                mean_features(sc->mx[p], sc->my[p], sc->W, sc->H, f);
-            else
-                mean_features(a.mx[p], a.my[p], a.sW, a.sH, f);
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const float v0 = 4 * c < kMeanFeat ? f[4 * c] : 0.0f;
-                const float v1 = 4 * c + 1 < kMeanFeat ? f[4 * c + 1] : 0.0f;
-                const float v2 = 4 * c + 2 < kMeanFeat ? f[4 * c + 2] : 0.0f;
-                const float v3 = 4 * c + 3 < kMeanFeat ? f[4 * c + 3] : 0.0f;
-                x[c] = g == 0 ? v0 : (g == 1 ? v1 : (g == 2 ? v2 : v3));
+        for (int c = 0; c < 8; ++c) {
+            const float v0 = 4 * c < kMeanFeat ? f[4 * c] : 0.0f;
+            const float v1 = 4 * c + 1 < kMeanFeat ? f[4 * c + 1] : 0.0f;
+            const float v2 = 4 * c + 2 < kMeanFeat ? f[4 * c + 2] : 0.0f;
+            const float v3 = 4 * c + 3 < kMeanFeat ? f[4 * c + 3] : 0.0f;
+            x[c] = g == 0 ? v0 : (g == 1 ? v1 : (g == 2 ? v2 : v3));
+        }
+        s_h[(wave * 16) * 64 + lane] = make_float4(x[0], x[1], x[2], x[3]);
+        s_h[(wave * 16 + 1) * 64 + lane] = make_float4(x[4], x[5], x[6], x[7]);
+    }
+    // the network's weights: the batch's scene (kMix, four hidden layers) or the launch's
+    const float* frag = kMix ? sc->f32_frag : nullptr;
+    const int n_mid = kMix ? 3 : a.n_mid;
+    const float4* wf1 = kMix ? reinterpret_cast<const float4*>(frag) : a.wf1;
+    const float4* wfo = kMix ? reinterpret_cast<const float4*>(frag + frag_out_at(4)) : a.wfo;
+    const float* bo16 = kMix ? frag + frag_out_at(4) + kFragOut : a.bo16;
+    float4 w[kAhead<kNcb> + 1][4];
+    wf1 += (size_t)4 * wave * 2 * 64;
+    f32_first<kNcb, 2>(wf1, lane, w);
+    __syncthreads();
+    f32x4 acc[4][kNcb];
+    // the sums through the ReLU into the state (and, kept for the backward, to activation `lay`)
+    const auto leave = [&](int lay) {
+        float* st = kMix ? nullptr : a.act_out[lay];
+        const size_t row0 = (size_t)gw0 * 16, total = kMix ? 0 : (size_t)a.N * a.B;
+        __syncthreads();  // every wave has read the layer's input
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int cb = 0; cb < kNcb; ++cb) {
+                const int t = 4 * wave + i;
+                const float4 h = make_float4(fmaxf(acc[i][cb][0], 0.0f), fmaxf(acc[i][cb][1], 0.0f),
+                                             fmaxf(acc[i][cb][2], 0.0f), fmaxf(acc[i][cb][3], 0.0f));
+                s_h[(cb * 16 + t) * 64 + lane] = h;
+                const size_t r = row0 + cb * 16 + (lane & 15);
+                if (st && r < total) *reinterpret_cast<float4*>(st + r * 256 + 16 * t + 4 * g) = h;
             }
-        }
-        // the network's weights: the batch's scene (kMix, four hidden layers) or the launch's
-        const float* frag = kMix ? sc->f32_frag : nullptr;
-        const int n_mid = kMix ? 3 : a.n_mid;
-        const auto WH = [&](int l) -> const float4* {
-            return kMix ? reinterpret_cast<const float4*>(frag + frag_hidden_at(l + 1)) : a.wfh[l];
-        };
-        const auto BH = [&](int l) -> const float* { return kMix ? sc->bias_h[l] : a.bh[l]; };
-        const float4* wf1 = kMix ? reinterpret_cast<const float4*>(frag) : a.wf1;
-        const float4* wfo = kMix ? reinterpret_cast<const float4*>(frag + frag_out_at(4)) : a.wfo;
-        const float* bo16 = kMix ? frag + frag_out_at(4) + kFragOut : a.bo16;
-        const auto st_of = [&](int l) -> float* {
-            return (!kMix && in && a.act_out[l]) ? a.act_out[l] + row * 256 : nullptr;
-        };
-        float hA[64], hB[64];
-        f32_mfma_layer<16, 8, true>(wf1, qrow, lane, x, hA, st_of(0));
-        int l = 0;
-        for (; l + 2 <= n_mid; l += 2) {
-            f32_mfma_layer<16, 64, true>(WH(l), BH(l), lane, hA, hB, st_of(l + 1));
-            f32_mfma_layer<16, 64, true>(WH(l + 1), BH(l + 1), lane, hB, hA, st_of(l + 2));
-        }
-        if (l < n_mid) {
-            f32_mfma_layer<16, 64, true>(WH(l), BH(l), lane, hA, hB, st_of(l + 1));
+        __syncthreads();
+    };
 #pragma unroll
-            for (int k = 0; k < 64; ++k) hA[k] = hB[k];
-        }
-        // output layer: lane l holds outputs 4 (l / 16) + i of pair l % 16
-        f32_mfma_layer<1, 64, false>(wfo, bo16, lane, hA, hB, nullptr);
-        if (g < 2) {
+    for (int cb = 0; cb < kNcb; ++cb) {
+        const float* qrow = a.qs + (size_t)s_q[cb * 16 + (lane & 15)] * 256;  // the layer's bias (the TX term)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) outv[wave][lane & 15][4 * g + i] = hB[i];
+        for (int i = 0; i < 4; ++i) {
+            const float4 b4 = *reinterpret_cast<const float4*>(qrow + 16 * (4 * wave + i) + 4 * g);
+            acc[i][cb] = f32x4{b4.x, b4.y, b4.z, b4.w};
         }
     }
-    __syncthreads();
-    if (active && lane < 16 && in) {  // lanes 0..15 hold the wave's 16 pairs (lane l: pair l)
+    f32_coop_layer<kNcb, 2>(wf1, s_h, lane, w, acc);
+#pragma unroll 1
+    for (int l = 0; l < n_mid; ++l) {
+        const float4* wh = (kMix ? reinterpret_cast<const float4*>(frag + frag_hidden_at(l + 1)) : a.wfh[l]) +
+                           (size_t)4 * wave * 16 * 64;
+        const float* bh = kMix ? sc->bias_h[l] : a.bh[l];
+        f32_first<kNcb, 16>(wh, lane, w);
+        float4 b4[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b4[i] = *reinterpret_cast<const float4*>(bh + 16 * (4 * wave + i) + 4 * g);
+        __builtin_amdgcn_sched_barrier(0);
+        leave(l);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int cb = 0; cb < kNcb; ++cb) acc[i][cb] = f32x4{b4[i].x, b4[i].y, b4[i].z, b4[i].w};
+        f32_coop_layer<kNcb, 16>(wh, s_h, lane, w, acc);
+    }
+    leave(n_mid);
+    if (wave >= kNcb) return;  // no barrier follows for these waves' outputs
+    // output layer: lane l holds outputs 4 (l / 16) + i of pair l % 16
+    f32x4 o = f32x4{bo16[4 * g], bo16[4 * g + 1], bo16[4 * g + 2], bo16[4 * g + 3]};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const float4 w = wfo[q * 64 + lane], b = s_h[(wave * 16 + q) * 64 + lane];
+        o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, b.x, o, 0, 0, 0);
+        o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, b.y, o, 0, 0, 0);
+        o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, b.z, o, 0, 0, 0);
+        o = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, b.w, o, 0, 0, 0);
+    }
+    if (g < 2) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) outv[wave][lane & 15][4 * g + i] = o[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (lane < 16 && in) {  // lanes 0..15 hold the wave's 16 pairs (lane l: pair l)
         if constexpr (kMix)
             mix_epilogue(*sc, a, row, p, outv[wave][lane]);
         else
@@ -216,21 +271,33 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void mlp_fp32_kernel(MlpArgs a, Mi
     }
 }
 
+// Blocks [0, n4) take 64 pairs each, the others 16 (launch_mlp_fp32's split).
+template <bool kMix>
+__global__ __launch_bounds__(64 * kFWaves, 2) void mlp_fp32_kernel(MlpArgs a, MixBatch mix, int n4) {
+    __shared__ __attribute__((aligned(16))) float4 s_h[kFWaves * 16 * 64];
+    __shared__ float outv[kFWaves][16][8];
+    __shared__ uint32_t s_q[kFWaves * 16];
+    const int64_t b = blockIdx.x;
+    if (kMix || b < n4)  // block-uniform
+        mlp_fp32_block<kMix, kFWaves>(a, mix, b * kFWaves, s_h, outv, s_q);
+    else if constexpr (!kMix)
+        mlp_fp32_block<false, 1>(a, mix, (int64_t)n4 * kFWaves + (b - n4), s_h, outv, s_q);
+}
+
 // Input gradient of a 256 x 256 layer of the FP32 backward on the same matrix
 // cores: out[p][i] = [act[p][i] > 0] sum_o W[o][i] dz[p][o], the layer function
 // above with W^T as its weights (fragment-major, packed by pack_wt_kernel) and
-// no bias, over the listed groups. A wave takes 16 pairs; lane l = 16 g + r loads input chunk 4 q + j
-// (input 16 q + 4 g + j) of pair r as one 16-byte load per q, and stores the
-// masked output tile t (units 16 t + 4 g + i) with one 16-byte store. With
+// no bias, over the listed groups, two to a block. A wave brings 16 rows into the
+// state: lane l = 16 g + r loads piece q (inputs 16 q + 4 g + 0..3) of row r as
+// 16 bytes; masked output tile t (units 16 t + 4 g + i) goes out as 16 bytes. With
 // bpart, the layer's bias gradient rides along: bpart[block][o] = the sum of
 // dz[p][o] over the block's 64 pairs (fixed order; rows past P count zero).
-__device__ float kZeroBias[256];  // zero-initialised: the layer's bias
-
-__global__ __launch_bounds__(64 * kFWaves, 3) void dz_f32_kernel(const float* __restrict__ dz,
+__global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __restrict__ dz,
                                                                  const float4* __restrict__ wt,
                                                                  const float* __restrict__ act, int64_t P,
                                                                  RowGroups rg, float* __restrict__ out,
                                                                  float* __restrict__ bpart) {
+    __shared__ __attribute__((aligned(16))) float4 s_h[kFWaves * 16 * 64];
     __shared__ float4 s_b[kFWaves][64];
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     const int g = lane >> 4;
@@ -243,51 +310,83 @@ __global__ __launch_bounds__(64 * kFWaves, 3) void dz_f32_kernel(const float* __
     }
     const int64_t p0 = gi < ng ? (int64_t)rg.list[gi] * kRowGroup + 16 * (wave & 1) : P;
     const int64_t row = p0 + (lane & 15);
-    const bool in = row < P;
-    float hin[64], hout[64];
+    {
+        const bool in = row < P;
+        float hin[64];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const float4 v = in ? *reinterpret_cast<const float4*>(dz + row * 256 + 16 * q + 4 * g)
-                            : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        hin[4 * q] = v.x;
-        hin[4 * q + 1] = v.y;
-        hin[4 * q + 2] = v.z;
-        hin[4 * q + 3] = v.w;
-    }
-    if (p0 < P)  // wave-uniform
-        f32_mfma_layer<16, 64, false>(wt, kZeroBias, lane, hin, hout, in ? out + row * 256 : nullptr,
-                                      in ? act + row * 256 : nullptr);
-    if (!bpart) return;  // kernel-uniform: no wave reaches the barrier below
-    // Column sums of dz over the wave's 16 rows, halving: at step s a lane keeps
-    // the upper half of its values if bit s of r is set (else the lower half)
-    // and adds its partner's (lane ^ 2^s) matching half. After four steps lane
-    // (r, g) holds columns 16 q + 4 g + j, j = 0..3, with q the 4-bit reversal of r.
+        for (int q = 0; q < 16; ++q) {
+            const float4 v = in ? *reinterpret_cast<const float4*>(dz + row * 256 + 16 * q + 4 * g)
+                                : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            s_h[(wave * 16 + q) * 64 + lane] = v;
+            hin[4 * q] = v.x;
+            hin[4 * q + 1] = v.y;
+            hin[4 * q + 2] = v.z;
+            hin[4 * q + 3] = v.w;
+        }
+        if (bpart) {
+            // Column sums of dz over the wave's 16 rows, halving: at step s a lane keeps
+            // the upper half of its values if bit s of r is set (else the lower half)
+            // and adds its partner's (lane ^ 2^s) matching half. After four steps lane
+            // (r, g) holds columns 16 q + 4 g + j, j = 0..3, with q the 4-bit reversal of r.
 #pragma unroll
-    for (int step = 0; step < 4; ++step) {
-        const int half = 32 >> step;
-        const bool up = (lane >> step) & 1;
+            for (int step = 0; step < 4; ++step) {
+                const int half = 32 >> step;
+                const bool up = (lane >> step) & 1;
 #pragma unroll
-        for (int i = 0; i < half; ++i) {
-            const float send = up ? hin[i] : hin[half + i];
-            const float keep = up ? hin[half + i] : hin[i];
-            hin[i] = keep + __shfl_xor(send, 1 << step);
+                for (int i = 0; i < half; ++i) {
+                    const float send = up ? hin[i] : hin[half + i];
+                    const float keep = up ? hin[half + i] : hin[i];
+                    hin[i] = keep + __shfl_xor(send, 1 << step);
+                }
+            }
+            const int r = lane & 15;
+            const int q = ((r & 1) << 3) | ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3);
+            s_b[wave][4 * q + g] = make_float4(hin[0], hin[1], hin[2], hin[3]);
         }
     }
-    const int r = lane & 15;
-    const int q = ((r & 1) << 3) | ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3);
-    s_b[wave][4 * q + g] = make_float4(hin[0], hin[1], hin[2], hin[3]);
     __syncthreads();
-    static_assert(64 * kFWaves == 256, "one thread per column");
-    const int c = (int)threadIdx.x;
-    const float* sb = reinterpret_cast<const float*>(s_b);
-    float sum = sb[c];
+    if (bpart) {
+        static_assert(64 * kFWaves == 256, "one thread per column");
+        const int c = (int)threadIdx.x;
+        const float* sb = reinterpret_cast<const float*>(s_b);
+        float sum = sb[c];
 #pragma unroll
-    for (int w = 1; w < kFWaves; ++w) sum += sb[w * 256 + c];
-    bpart[(size_t)blockIdx.x * 256 + c] = sum;
+        for (int w = 1; w < kFWaves; ++w) sum += sb[w * 256 + c];
+        bpart[(size_t)blockIdx.x * 256 + c] = sum;
+    }
+    // rows of the column blocks: two per listed group
+    wt += (size_t)4 * wave * 16 * 64;
+    float4 w[kAhead<kFWaves> + 1][4];
+    f32_first<kFWaves, 16>(wt, lane, w);
+    int64_t rows[kFWaves];
+#pragma unroll
+    for (int cb = 0; cb < kFWaves; ++cb) {
+        const uint32_t k = 2 * blockIdx.x + (cb >> 1);
+        const int64_t r = k < ng ? (int64_t)rg.list[k] * kRowGroup + 16 * (cb & 1) + (lane & 15) : P;
+        rows[cb] = r < P ? r : -1;
+    }
+    f32x4 acc[4][kFWaves];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int cb = 0; cb < kFWaves; ++cb) acc[i][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32_coop_layer<kFWaves, 16>(wt, s_h, lane, w, acc);
+#pragma unroll
+    for (int cb = 0; cb < kFWaves; ++cb) {
+        if (rows[cb] < 0) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const size_t at = (size_t)rows[cb] * 256 + 16 * (4 * wave + i) + 4 * g;
+            const float4 mk = *reinterpret_cast<const float4*>(act + at);
+            *reinterpret_cast<float4*>(out + at) =
+                make_float4(mk.x > 0.0f ? acc[i][cb][0] : 0.0f, mk.y > 0.0f ? acc[i][cb][1] : 0.0f,
+                            mk.z > 0.0f ? acc[i][cb][2] : 0.0f, mk.w > 0.0f ? acc[i][cb][3] : 0.0f);
+        }
+    }
 }
 
 // W^T of a 256 x 256 layer (W row-major [out][in]) in the fragment order of
-// f32_mfma_layer: fragment q of output tile t, lane l = 16 g + r, element j
+// f32_coop_layer: fragment q of output tile t, lane l = 16 g + r, element j
 // holds W^T[16 t + r][16 q + 4 g + j] = W[16 q + 4 g + j][16 t + r].
 __global__ void pack_wt_kernel(const float* __restrict__ w, float* __restrict__ wt) {
     const int e = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -361,10 +460,18 @@ void launch_mlp_fp32(const DevScene& s, const float* qs, int B, const Grid& g, b
     MlpArgs a = make_args(s, qs, B, g, paper_mask, r, delta_out);
     if (act_out)
         for (int l = 0; l < s.n_hidden && l < 8; ++l) a.act_out[l] = act_out[l];
-    const size_t total = (size_t)s.n * B;
-    const size_t per_block = (size_t)kFWaves * 16;
-    const unsigned blocks = (unsigned)((total + per_block - 1) / per_block);
-    if (blocks) mlp_fp32_kernel<false><<<blocks, 64 * kFWaves, 0, st>>>(a, MixBatch{});
+    const size_t groups = ((size_t)s.n * B + 15) / 16;
+    if (!groups) return;
+    // Whole rounds of 64-pair blocks (57 us each), then the rest: 64-pair blocks take one round more however few
+    // they are, 16-pair blocks one shorter round (24 us) per 256 groups, with four times the weight loads. One
+    // render of n Gaussians, us (16-pair / 64-pair blocks for the rest): n = 16: 48 / 83; 4,000: 69 / 103; 8,000: 94 /
+    // 112; 12,000: 117 / 117; 20,000: 142 / 174; 100,000: 414 / 446.
+    int64_t n4 = (int64_t)(groups / (4 * kCus)) * kCus, rest = (int64_t)groups - 4 * n4;
+    if (rest > 2 * kCus) {
+        n4 += (rest + 3) / 4;
+        rest = 0;
+    }
+    mlp_fp32_kernel<false><<<(unsigned)(n4 + rest), 64 * kFWaves, 0, st>>>(a, MixBatch{}, (int)n4);
 }
 
 void launch_mix_mlp_fp32(const MixBatch& m, const float* qs, const Records& r, int64_t pair_cap, int B_cap,
@@ -378,7 +485,7 @@ void launch_mix_mlp_fp32(const MixBatch& m, const float* qs, const Records& r, i
     a.inv_tile = 1.0f / 16.0f;
     a.paper_mask = paper_mask ? 1 : 0;
     a.wrap = wrap ? 1 : 0;
-    if (blocks > 0) mlp_fp32_kernel<true><<<(unsigned)blocks, 64 * kFWaves, 0, st>>>(a, m);
+    if (blocks > 0) mlp_fp32_kernel<true><<<(unsigned)blocks, 64 * kFWaves, 0, st>>>(a, m, 0);
 }
 
 void launch_preprocess_static(const DevScene& s, int B, const Grid& g, const Records& r, hipStream_t st) {

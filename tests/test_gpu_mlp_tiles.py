@@ -3,7 +3,8 @@ same products and sums). Batches around the sizes where the shape changes: few
 Gaussians per query cut as flat rows (several queries per tile), batches of one
 and of two rounds over the compute units;
 residuals against the tiling that never straddles two queries, and the stored
-activations of a batch against those of its queries alone."""
+activations of a batch against those of its queries alone. Likewise the FP32
+MLP's blocks."""
 import numpy as np
 import pytest
 
@@ -60,3 +61,21 @@ def test_stored_activations_do_not_depend_on_the_batch(pair, n, nb):
     whole = pattern(tx)
     for q in range(nb):
         np.testing.assert_array_equal(whole[q], pattern(tx[q:q + 1].contiguous())[0])
+
+
+@pytest.mark.parametrize("n,nb", [(1, 1), (15, 2), (16, 3), (17, 5), (64, 2), (8192, 2), (8193, 2), (12_305, 4),
+                                  (16_384, 3), (16_385, 2), (24_577, 3)])
+@pytest.mark.parametrize("hidden_layers", [1, 4, 7])
+def test_fp32_residuals_do_not_depend_on_the_blocks(pair, n, nb, hidden_layers):
+    """64- and 16-pair blocks form the same sums: a batch's residuals are those of its queries alone, whose pairs
+    fall into other blocks (the kinds change at 512 groups of 16 pairs and at whole rounds of 1024)."""
+    import torch
+    from paper_2506_12787_amd import binding as B
+    lib = pair[0]
+    mlp = synth.mlp_weights(seed=n + 1, n_hidden=hidden_layers, out_scale=1.0)
+    sid = lib.upload_scene(synth.gaussians(n, 90, 360, seed=n), 90, 360, mlp=mlp)
+    tx = torch.from_numpy(synth.tx_positions(nb, seed=n + 2)).cuda()
+    whole = lib.debug_deform(sid, tx, B.MLP_FP32)
+    for q in range(nb):
+        assert torch.equal(whole[q], lib.debug_deform(sid, tx[q:q + 1].contiguous(), B.MLP_FP32)[0]), q
+    lib.release_scene(sid)
