@@ -32,7 +32,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     const bool need_zf = bf16 && nh == 1;
     if ((s = w.dz.reserve(this, need_zf ? actb * 2 + f32b + 16 : actb * 2 + 16, st))) return s;
     // scratch: S (N x 256), R (B x 256), dg (N x 26), split-K partials, column-sum partials, BF16 weights
-    const size_t n_split = std::max({gemm_part_floats(Hd, Hd, P), gemm_part_floats(kOut, Hd, P),
+    const size_t n_split = std::max({bf16 ? (size_t)0 : wgrad_f32_floats(P), gemm_part_floats(kOut, Hd, P),
                                      gemm_part_floats(Hd, kMeanFeat, N), gemm_part_floats(Hd, kTxFeat, B),
                                      (size_t)layer1_sums_blocks((int)N) * B * Hd,
                                      (size_t)layer1_grad_blocks((int)N) * B * Hd, wgrad_mfma_floats(P),
@@ -94,8 +94,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
                 dz1 = dz[cur];
         } else {
             if (gr->weight[l])
-                launch_gemm_f32(true, false, Hd, Hd, P, dz[cur], Hd, act[l - 1], Hd, gr->weight[l], Hd, part, st,
-                                nullptr, 0, false, &rg);
+                launch_wgrad_f32((const float*)dz[cur], (const float*)act[l - 1], P, rg, part, gr->weight[l], st);
             // the input gradient on the FP32 matrix cores with the layer's W^T as register-fed weights, masked;
             // the bias gradient's per-block column sums of dz ride along (into the split-K space, free again)
             float* bp = gr->bias[l] ? part : nullptr;

@@ -891,6 +891,85 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
             for (int jj = 0; jj < 4; ++jj) out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
 }
 
+// The same contraction after an FP32 forward (dz, act [P][256] FP32 row-major) on
+// the FP32 matrix cores (v_mfma_f32_16x16x4_f32): part[blk][o][i] over every
+// gridDim-th listed group. Each row is read once, as 16 bytes per thread, and
+// staged as it lies (rows padded by 16 floats: the 4 rows that one fragment read
+// touches fall in distinct banks), double-buffered, one barrier per 32 rows; the
+// next rows are loaded while the current ones are multiplied. Tiles per wave as
+// above. 160k pairs: 223 us per layer on the general product's 128 x 128 tiles,
+// which read each row twice; 178 here (the instructions' own time: 146).
+constexpr int kWfRow = 256 + 16;
+
+__global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* __restrict__ dz,
+                                                                  const float* __restrict__ act, int64_t P,
+                                                                  RowGroups rg, float* __restrict__ part) {
+    __shared__ __attribute__((aligned(16))) float s_rows[2 * 2 * kRowGroup * kWfRow];  // [buffer][dz, act][32][kWfRow]
+    const int tid = (int)threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
+    const int o0 = 64 * (wave & 3), i0 = 128 * (wave >> 2);
+    const uint32_t ng = *rg.count;
+    // staging: wave w takes rows w, w + 8, .. of the group, a lane 4 columns
+    float4 rd[4], ra[4];
+    auto load = [&](uint32_t k) {
+        const int64_t p0 = (int64_t)rg.list[k] * kRowGroup + wave;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const int64_t p = p0 + 8 * h;
+            rd[h] = p < P ? load4(dz + p * 256 + 4 * lane) : make_float4(0.f, 0.f, 0.f, 0.f);
+            ra[h] = p < P ? load4(act + p * 256 + 4 * lane) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    auto stage = [&](int buf) {
+        float* b = s_rows + buf * 2 * kRowGroup * kWfRow;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            *reinterpret_cast<float4*>(b + (wave + 8 * h) * kWfRow + 4 * lane) = rd[h];
+            *reinterpret_cast<float4*>(b + (kRowGroup + wave + 8 * h) * kWfRow + 4 * lane) = ra[h];
+        }
+    };
+    dz_f32x4 acc[4][8];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 8; ++b) acc[a][b] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+    if (blockIdx.x < ng) {
+        load(blockIdx.x);
+        stage(0);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (uint32_t k = blockIdx.x; k < ng; k += gridDim.x, buf ^= 1) {
+        const bool more = k + gridDim.x < ng;
+        if (more) load(k + gridDim.x);
+        const float* b0 = s_rows + buf * 2 * kRowGroup * kWfRow;
+#pragma unroll
+        for (int q = 0; q < kRowGroup / 4; ++q) {  // rows 4 q + g
+            const float* rz = b0 + (4 * q + g) * kWfRow + o0 + n;
+            const float* rx = b0 + (kRowGroup + 4 * q + g) * kWfRow + i0 + n;
+            float fa[4], fb[8];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) fa[a] = rz[16 * a];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) fb[b] = rx[16 * b];
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[a], fb[b], acc[a][b], 0, 0, 0);
+        }
+        if (more) stage(buf ^ 1);  // read last before the barrier that ended the step before
+        __syncthreads();
+    }
+    float* out = part + (size_t)blockIdx.x * 65536;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
+}
+
 // Output layer of the backward in one pass over the last hidden activations
 // act [P][256] over every gridDim-th listed group: with dy [P][7] FP32 (the
 // upstream gradient as computed, not rounded) and Wo [7][256], T the type of act,
@@ -1301,6 +1380,16 @@ void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGrou
     const int nblk = wgrad_mfma_blocks(P);  // P = 0: one block writes zeros
     wgrad_mfma_kernel<<<nblk, 64 * kWgWaves, 0, st>>>((const __bf16*)dz, (const __bf16*)act, P, rg, part);
     slice_sum(part, nblk, kWgSlice, 65536, 256, dW, db, st);
+}
+
+int wgrad_f32_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, (P + 255) / 256)); }
+size_t wgrad_f32_floats(int64_t P) { return (size_t)wgrad_f32_blocks(P) * 65536; }
+
+void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGroups& rg, float* part, float* dW,
+                      hipStream_t st) {
+    const int nblk = wgrad_f32_blocks(P);  // P = 0: one block writes zeros
+    wgrad_f32_kernel<<<nblk, 64 * kWgWaves, 0, st>>>(dz, act, P, rg, part);
+    slice_sum(part, nblk, 65536, 65536, 0, dW, nullptr, st);
 }
 
 void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipStream_t st) {

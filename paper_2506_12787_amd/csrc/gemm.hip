@@ -37,8 +37,6 @@ struct GemmArgs {
     int a_vec, b_vec;   // FP32 operand whose runs of 4 are 16-byte aligned (ld % 4 == 0, aligned base)
     int c_vec;          // the result (and mask) rows take 16-byte stores (loads) at multiples of 4
     int tc;             // store the transpose: C[n * ldc + m] (no mask)
-    const uint32_t* kgrp;    // K stages: the listed groups of 32 K rows, *kcount of them dealt over the slices; or null
-    const uint32_t* kcount;
 };
 
 template <bool kBf>
@@ -117,19 +115,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     const int wm = wave % kWM, wn = wave / kWM;
     const int64_t m0 = (int64_t)blockIdx.x * TM, n0 = (int64_t)blockIdx.y * TN;
-    static_assert(kGK == kRowGroup, "one listed group per K stage");
     const int64_t kb = (int64_t)blockIdx.z * g.kc;
-    int64_t ke = g.K < kb + g.kc ? g.K : kb + g.kc;
-    int steps = ke > kb ? (int)((ke - kb + kGK - 1) / kGK) : 0;
-    int64_t s0 = 0;  // kgrp: the slice's first listed group
-    if (g.kgrp) {
-        const int64_t n = *g.kcount, per = (n + gridDim.z - 1) / gridDim.z;
-        s0 = (int64_t)blockIdx.z * per;
-        steps = (int)(n < s0 + per ? (n > s0 ? n - s0 : 0) : per);
-        ke = g.K;
-    }
-    // first K row of stage s; a listed group is whole or ends at K
-    const auto k_of = [&](int s) { return g.kgrp ? (int64_t)g.kgrp[s0 + s] * kGK : kb + (int64_t)s * kGK; };
+    const int64_t ke = g.K < kb + g.kc ? g.K : kb + g.kc;
+    const int steps = ke > kb ? (int)((ke - kb + kGK - 1) / kGK) : 0;
+    const auto k_of = [&](int s) { return kb + (int64_t)s * kGK; };  // first K row of stage s
     const bool akc = g.a_kc != 0, bkc = g.b_kc != 0;
     const bool avec = g.a_vec != 0, bvec = g.b_vec != 0;
 
@@ -280,7 +269,7 @@ size_t gemm_part_floats(int64_t M, int64_t N, int64_t K) {
 
 void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
                      int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, const float* mask, int64_t ldm,
-                     bool bf16, const RowGroups* kgroups) {
+                     bool bf16) {
     if (M <= 0 || N <= 0) return;
     // a product with few rows and many columns (without a mask) runs as its transpose, C^T = op(B)^T op(A)^T,
     // on the narrow tile, and stores the transpose back
@@ -316,8 +305,6 @@ void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const vo
     g.a_vec = !bf16 && lda % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
     g.b_vec = !bf16 && ldb % 4 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;
     g.tc = tc ? 1 : 0;
-    g.kgrp = kgroups ? kgroups->list : nullptr;
-    g.kcount = kgroups ? kgroups->count : nullptr;
     // 16-byte rows of the result: the destination of this launch (the slices' partials, or C) and the mask
     const bool c_al = slices > 1 ? (N % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0)
                                  : (ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0);
@@ -329,12 +316,9 @@ void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const vo
             gemm_f32_kernel<true, 128, 32><<<grid, 256, 0, st>>>(g);
         else
             gemm_f32_kernel<false, 128, 32><<<grid, 256, 0, st>>>(g);
-    } else if (wide(M, N)) {
+    } else if (bf16 && wide(M, N)) {  // the FP32 products of this library have a side below 128
         const dim3 grid((unsigned)cdiv(M, 128), (unsigned)cdiv(N, 128), (unsigned)slices);
-        if (bf16)
-            gemm_f32_kernel<true, 128, 128><<<grid, 256, 0, st>>>(g);
-        else
-            gemm_f32_kernel<false, 128, 128><<<grid, 256, 0, st>>>(g);
+        gemm_f32_kernel<true, 128, 128><<<grid, 256, 0, st>>>(g);
     } else {
         const dim3 grid((unsigned)cdiv(M, 64), (unsigned)cdiv(N, 64), (unsigned)slices);
         if (bf16)

@@ -299,12 +299,12 @@ void launch_base_reduce(const float* dbase, const float* dmu_pe, const uint32_t*
 // gemm.hip: C = op(A) op(B) in FP32 on the matrix cores, row-major (op(A) M x K, op(B) K x N; A / B FP32, or
 // BF16 bits when bf16). mask (optional, leading dimension ldm): C *= [mask > 0]. A small C over a long K is
 // split into gemm_split(M, N, K) K-slices summed in slice order; part then holds gemm_part_floats(M, N, K)
-// floats (unused otherwise). kgroups: only the K rows (pairs) of these groups count.
+// floats (unused otherwise).
 int gemm_split(int64_t M, int64_t N, int64_t K);
 size_t gemm_part_floats(int64_t M, int64_t N, int64_t K);
 void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
                      int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, const float* mask = nullptr,
-                     int64_t ldm = 0, bool bf16 = false, const RowGroups* kgroups = nullptr);
+                     int64_t ldm = 0, bool bf16 = false);
 void launch_fill(float* p, float v, int64_t n, hipStream_t st);
 // out[z * out_bs + c] = sum_r A[z * bs + r * cols + c] for z < nz; part holds
 // colsum_blocks(rows) * cols * nz floats
@@ -326,6 +326,11 @@ void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, 
 size_t wgrad_mfma_floats(int64_t P);
 void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGroups& rg, float* part, float* dW,
                        float* db, hipStream_t st);
+int wgrad_f32_blocks(int64_t P);
+size_t wgrad_f32_floats(int64_t P);
+// dW [256][256] = dz^T act over the listed rows, FP32 row-major; part: wgrad_f32_floats(P)
+void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGroups& rg, float* part, float* dW,
+                      hipStream_t st);
 // Layer-1 gradient sums of a BF16 backward straight from dz1 [B][N][256] (the second layer's pre-activation
 // gradient, BF16) and wf (its weights' fragments): S [N][256] = sum over b of (dz1 W) masked by act > 0, and
 // Rpart [layer1_grad_blocks(N)][B][256] per-block sums over the Gaussians.

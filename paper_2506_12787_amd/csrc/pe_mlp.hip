@@ -141,7 +141,7 @@ constexpr int kMixGroups = 24;  // 16-pair groups per 384-pair MLP tile of a mix
 template <bool kMix, int kNcb>
 __device__ __forceinline__ void mlp_fp32_block(const MlpArgs& a, const MixBatch& mix, int64_t gw0, float4* s_h,
                                                float (*outv)[16][8], uint32_t* s_q) {
-    const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
     const int g = lane >> 4;
     // waves 0 .. kNcb - 1: the 16 pairs of column block `wave`: this lane's record row and its index p in the
     // scene; rows past the query are computed on index 0 and not written
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
                                                                  float* __restrict__ bpart) {
     __shared__ __attribute__((aligned(16))) float4 s_h[kFWaves * 16 * 64];
     __shared__ float4 s_b[kFWaves][64];
-    const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
     const int g = lane >> 4;
     // the block's listed groups of 32 rows: two waves each
     static_assert(kRowGroup == 32 && kFWaves == 4, "two groups per block");
