@@ -891,10 +891,9 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
             for (int jj = 0; jj < 4; ++jj) out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
 }
 
-// The same contraction after an FP32 forward (dz, act [P][256] FP32 row-major) on
-// the FP32 matrix cores (v_mfma_f32_16x16x4_f32): part[blk][o][i] over every
+// The same contraction after an FP32 forward (dz, act [P][256] FP32) on the FP32 matrix cores (v_mfma_f32_16x16x4_f32): part[blk][o][i] over every
 // gridDim-th listed group. Each row is read once, as 16 bytes per thread, and
-// staged as it lies (rows padded by 16 floats: the 4 rows that one fragment read
+// staged row by row (padded by 16 floats: the 4 rows that one fragment read
 // touches fall in distinct banks), double-buffered, one barrier per 32 rows; the
 // next rows are loaded while the current ones are multiplied. Tiles per wave as
 // above. 160k pairs: 223 us per layer on the general product's 128 x 128 tiles,
@@ -909,23 +908,25 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
     const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
     const int o0 = 64 * (wave & 3), i0 = 128 * (wave >> 2);
     const uint32_t ng = *rg.count;
-    // staging: wave w takes rows w, w + 8, .. of the group, a lane 4 columns
+    // staging: wave w takes pieces w and w + 8 of the group's two tiles of 16 rows
     float4 rd[4], ra[4];
     auto load = [&](uint32_t k) {
-        const int64_t p0 = (int64_t)rg.list[k] * kRowGroup + wave;
+        const int64_t p0 = (int64_t)rg.list[k] * kRowGroup + n;
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
-            const int64_t p = p0 + 8 * h;
-            rd[h] = p < P ? load4(dz + p * 256 + 4 * lane) : make_float4(0.f, 0.f, 0.f, 0.f);
-            ra[h] = p < P ? load4(act + p * 256 + 4 * lane) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const int64_t p = p0 + 16 * (h >> 1);
+            const size_t at = piece_at(p, wave + 8 * (h & 1), g);
+            rd[h] = p < P ? load4(dz + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+            ra[h] = p < P ? load4(act + at) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     };
     auto stage = [&](int buf) {
         float* b = s_rows + buf * 2 * kRowGroup * kWfRow;
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
-            *reinterpret_cast<float4*>(b + (wave + 8 * h) * kWfRow + 4 * lane) = rd[h];
-            *reinterpret_cast<float4*>(b + (kRowGroup + wave + 8 * h) * kWfRow + 4 * lane) = ra[h];
+            float* d = b + (16 * (h >> 1) + n) * kWfRow + 16 * (wave + 8 * (h & 1)) + 4 * g;
+            *reinterpret_cast<float4*>(d) = rd[h];
+            *reinterpret_cast<float4*>(d + kRowGroup * kWfRow) = ra[h];
         }
     };
     dz_f32x4 acc[4][8];
@@ -979,95 +980,64 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
 //   part[blk] = the slice's sums of dy[p][o] act[p][f] (the weight gradient,
 //     7 x 256), then of dy[p][o] (the bias gradient, 7 and a pad); the caller
 //     adds the slices.
-// FP32 (row-major): a thread takes 8 features of every 8th pair.
+// Wave w takes feature chunk w of 16 rows at a time, a lane 8 features of one
+// row, whose output weights stay in its registers, the next group's loads in
+// flight. 800k pairs, a quarter of them with a gradient, BF16: 73 us (105 with
+// each group loaded when it is due); 160k pairs, FP32: 78 us (88 row-major,
+// 8 features of every 8th row per thread).
 constexpr int kOutSlice = kOut * 256 + 8;
 
-__global__ __launch_bounds__(256) void out_bwd_f32_kernel(const float* __restrict__ dy, const float* __restrict__ wo,
-                                                          const float* __restrict__ act, int64_t P, RowGroups rg,
-                                                          float* __restrict__ dz, float* __restrict__ part) {
-    __shared__ __attribute__((aligned(16))) float s_w[kOut][256];
-    __shared__ float s_red[4][kOut][256];  // one row per wave after the in-wave pair of rows is added
-    __shared__ float s_y[4][8];
-    for (int i = threadIdx.x; i < kOut * 256; i += 256) s_w[i / 256][i % 256] = wo[i];
-    __syncthreads();
-    const int f0 = (int)(threadIdx.x & 31) * 8, row = (int)(threadIdx.x >> 5);
-    const uint32_t ng = *rg.count;
-    float acc[kOut][8], ysum[kOut];
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) {
-        ysum[o] = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[o][j] = 0.f;
+// the lane's 8 values of chunk c (features chunk_feature(c, g, 0..7)) of a row, as floats
+template <typename T>
+struct OutRow;
+template <>
+struct OutRow<__bf16> {
+    uint4 v;
+    __device__ void load(const __bf16* a, int64_t p, int c, int g) {
+        v = *reinterpret_cast<const uint4*>(a + chunk_at(p, c, g));
     }
-    for (uint32_t k = blockIdx.x; k < ng; k += gridDim.x) {
+    __device__ void clear() { v = make_uint4(0u, 0u, 0u, 0u); }
+    __device__ float at(int j) const {
+        const uint32_t w = j < 2 ? v.x : j < 4 ? v.y : j < 6 ? v.z : v.w;
+        return __uint_as_float(j & 1 ? w & 0xffff0000u : w << 16);
+    }
+    // dz = z rounded, where the activation is > 0
+    __device__ void store_masked(__bf16* dz, int64_t p, int c, int g, const float (&z)[8]) const {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        uint32_t o[4];
 #pragma unroll
-        for (int i = 0; i < kRowGroup / 8; ++i) {
-            const int64_t p = (int64_t)rg.list[k] * kRowGroup + 8 * i + row;
-            if (p >= P) continue;
-            float y[kOut];
-#pragma unroll
-            for (int o = 0; o < kOut; ++o) {
-                y[o] = dy[p * kOut + o];
-                ysum[o] += y[o];
-            }
-            const float4 a0 = load4(act + p * 256 + f0), a1 = load4(act + p * 256 + f0 + 4);
-            const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-#pragma unroll
-            for (int o = 0; o < kOut; ++o)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[o][j] = fmaf(y[o], av[j], acc[o][j]);
-            if (!dz) continue;
-            float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int o = 0; o < kOut; ++o) {
-                const float4 w0 = *reinterpret_cast<const float4*>(&s_w[o][f0]);
-                const float4 w1 = *reinterpret_cast<const float4*>(&s_w[o][f0 + 4]);
-                z[0] = fmaf(y[o], w0.x, z[0]);
-                z[1] = fmaf(y[o], w0.y, z[1]);
-                z[2] = fmaf(y[o], w0.z, z[2]);
-                z[3] = fmaf(y[o], w0.w, z[3]);
-                z[4] = fmaf(y[o], w1.x, z[4]);
-                z[5] = fmaf(y[o], w1.y, z[5]);
-                z[6] = fmaf(y[o], w1.z, z[6]);
-                z[7] = fmaf(y[o], w1.w, z[7]);
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) z[j] = av[j] > 0.f ? z[j] : 0.f;
-            *reinterpret_cast<float4*>(dz + p * 256 + f0) = make_float4(z[0], z[1], z[2], z[3]);
-            *reinterpret_cast<float4*>(dz + p * 256 + f0 + 4) = make_float4(z[4], z[5], z[6], z[7]);
+        for (int k = 0; k < 4; ++k) {
+            const dz_f32x2 f = {z[2 * k], z[2 * k + 1]};
+            o[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, dz_bf16x2)) & positive_halves(w[k]);
         }
+        *reinterpret_cast<uint4*>(dz + chunk_at(p, c, g)) = make_uint4(o[0], o[1], o[2], o[3]);
     }
-    // rows 2 w and 2 w + 1 are the two halves of wave w: add them across lanes l and l + 32
-    const int wv = (int)(threadIdx.x >> 6);
+};
+template <>
+struct OutRow<float> {
+    float4 v[2];
+    __device__ void load(const float* a, int64_t p, int c, int g) {
+        v[0] = load4(a + piece_at(p, 2 * c, g));
+        v[1] = load4(a + piece_at(p, 2 * c + 1, g));
+    }
+    __device__ void clear() { v[0] = v[1] = make_float4(0.f, 0.f, 0.f, 0.f); }
+    __device__ float at(int j) const {
+        const float4 q = v[j >> 2];
+        return (j & 3) == 0 ? q.x : (j & 3) == 1 ? q.y : (j & 3) == 2 ? q.z : q.w;
+    }
+    __device__ void store_masked(float* dz, int64_t p, int c, int g, const float (&z)[8]) const {
 #pragma unroll
-    for (int o = 0; o < kOut; ++o) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float v = acc[o][j] + __shfl_xor(acc[o][j], 32);
-            if ((threadIdx.x & 32) == 0) s_red[wv][o][f0 + j] = v;
-        }
-        const float v = ysum[o] + __shfl_xor(ysum[o], 32);
-        if ((threadIdx.x & 63) == 0) s_y[wv][o] = v;
+        for (int h = 0; h < 2; ++h)
+            *reinterpret_cast<float4*>(dz + piece_at(p, 2 * c + h, g)) =
+                make_float4(v[h].x > 0.f ? z[4 * h] : 0.f, v[h].y > 0.f ? z[4 * h + 1] : 0.f,
+                            v[h].z > 0.f ? z[4 * h + 2] : 0.f, v[h].w > 0.f ? z[4 * h + 3] : 0.f);
     }
-    __syncthreads();
-    float* pb = part + (size_t)blockIdx.x * kOutSlice;
-    for (int e = threadIdx.x; e < kOut * 256; e += 256) {
-        const int o = e / 256, f = e % 256;
-        pb[e] = s_red[0][o][f] + s_red[1][o][f] + s_red[2][o][f] + s_red[3][o][f];
-    }
-    if (threadIdx.x < 8) {
-        const int o = (int)threadIdx.x;
-        pb[kOut * 256 + o] = o < kOut ? s_y[0][o] + s_y[1][o] + s_y[2][o] + s_y[3][o] : 0.f;
-    }
-}
+};
 
-// The same after a BF16 forward, in chunk order: wave w takes feature chunk w of
-// 16 rows at a time, a lane 8 features of one row, whose output weights stay in
-// its registers, the next group's loads in flight. 73 us at 800k pairs, a quarter
-// of them with a gradient (105 with each group loaded when it is due).
-__global__ __launch_bounds__(512) void out_bwd_bf16_kernel(const float* __restrict__ dy, const __bf16* __restrict__ wo,
-                                                           const __bf16* __restrict__ act, int64_t P, RowGroups rg,
-                                                           __bf16* __restrict__ dz, float* __restrict__ part) {
+template <typename T>
+__global__ __launch_bounds__(512) void out_bwd_kernel(const float* __restrict__ dy, const T* __restrict__ wo,
+                                                      const T* __restrict__ act, int64_t P, RowGroups rg,
+                                                      T* __restrict__ dz, float* __restrict__ part) {
     const int c = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), g = lane >> 4, n = lane & 15;
     const uint32_t ng = *rg.count;
     float w[kOut][8], acc[kOut][8], ysum[kOut];
@@ -1080,14 +1050,17 @@ __global__ __launch_bounds__(512) void out_bwd_bf16_kernel(const float* __restri
             acc[o][j] = 0.f;
         }
     }
-    uint4 a[2], a_nxt[2];
+    OutRow<T> a[2], a_nxt[2];
     float y[2][kOut], y_nxt[2][kOut];
     auto load = [&](uint32_t k) {  // one group ahead
         const int64_t p0 = k < ng ? (int64_t)rg.list[k] * kRowGroup + n : P;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int64_t p = p0 + 16 * h;
-            a_nxt[h] = p < P ? *reinterpret_cast<const uint4*>(act + chunk_at(p, c, g)) : make_uint4(0u, 0u, 0u, 0u);
+            if (p < P)
+                a_nxt[h].load(act, p, c, g);
+            else
+                a_nxt[h].clear();
 #pragma unroll
             for (int o = 0; o < kOut; ++o) y_nxt[h][o] = p < P ? dy[p * kOut + o] : 0.f;
         }
@@ -1104,27 +1077,18 @@ __global__ __launch_bounds__(512) void out_bwd_bf16_kernel(const float* __restri
         load(k + gridDim.x);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint32_t aw[4] = {a[h].x, a[h].y, a[h].z, a[h].w};
             float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int o = 0; o < kOut; ++o) {
                 ysum[o] += y[h][o];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const float av = __uint_as_float(j & 1 ? aw[j >> 1] & 0xffff0000u : aw[j >> 1] << 16);
-                    acc[o][j] = fmaf(y[h][o], av, acc[o][j]);
+                    acc[o][j] = fmaf(y[h][o], a[h].at(j), acc[o][j]);
                     z[j] = fmaf(y[h][o], w[o][j], z[j]);
                 }
             }
             const int64_t p = p0 + 16 * h;
-            if (!dz || p >= P) continue;
-            uint32_t v[4];
-#pragma unroll
-            for (int k2 = 0; k2 < 4; ++k2) {
-                const dz_f32x2 f = {z[2 * k2], z[2 * k2 + 1]};
-                v[k2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, dz_bf16x2)) & positive_halves(aw[k2]);
-            }
-            *reinterpret_cast<uint4*>(dz + chunk_at(p, c, g)) = make_uint4(v[0], v[1], v[2], v[3]);
+            if (dz && p < P) a[h].store_masked(dz, p, c, g, z);
         }
     }
     // the 16 rows of a lane group
@@ -1147,8 +1111,8 @@ __global__ __launch_bounds__(512) void out_bwd_bf16_kernel(const float* __restri
 }
 
 // Layer-1 gradient sums in one pass over the FP32 gradient z [B][N][256]:
-// with dz = z * [act > 0] (kMask: the BF16 activations act [B][N][256], in chunk order, mask
-// an unmasked z; else z is dz already), S[n][k] = sum_b dz[b][n][k]
+// with dz = z * [act > 0] (kMask: the BF16 activations act [B][N][256] mask an
+// unmasked z, row-major; else z is dz already, in piece order), S[n][k] = sum_b dz[b][n][k]
 // (complete: the block owns Gaussians n0 .. n0 + 31, summed over b in order)
 // and Rpart[block][b][k] = sum over the block's Gaussians of dz[b][n][k]
 // (4 row groups through LDS).
@@ -1174,8 +1138,7 @@ __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restric
             const int n = n0 + ty + 4 * i;
             const int64_t p = (int64_t)b * N + n;
             if (n < N && (!bits || ((bits[p >> 5] >> (p & 31)) & 1u))) {
-                const size_t off = (size_t)p * 256 + c;
-                const float4 v = load4(z + off);
+                const float4 v = load4(z + (kMask ? (size_t)p * 256 + c : piece_at(p, c / 16, c % 16 / 4)));
                 float4 m = v;
                 if constexpr (kMask) {
                     const float4 a = load4(act + chunk_at(p, c / 32, c % 16 / 4) + c % 32 / 16 * 4);
@@ -1365,9 +1328,10 @@ void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act,
     if (!dz && !dWo && !dbo) return;
     const int nblk = out_bwd_blocks(P);  // P = 0: one block writes zeros
     if (bf16)
-        out_bwd_bf16_kernel<<<nblk, 512, 0, st>>>(dy, (const __bf16*)wo, (const __bf16*)act, P, rg, (__bf16*)dz, part);
+        out_bwd_kernel<__bf16><<<nblk, 512, 0, st>>>(dy, (const __bf16*)wo, (const __bf16*)act, P, rg, (__bf16*)dz,
+                                                     part);
     else
-        out_bwd_f32_kernel<<<nblk, 256, 0, st>>>(dy, (const float*)wo, (const float*)act, P, rg, (float*)dz, part);
+        out_bwd_kernel<float><<<nblk, 512, 0, st>>>(dy, (const float*)wo, (const float*)act, P, rg, (float*)dz, part);
     slice_sum(part, nblk, kOutSlice, kOut * 256, kOut, dWo, dbo, st);
 }
 

@@ -262,18 +262,20 @@ void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* b
 void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,
                            const float* grad_out, const float* aux_T, const uint32_t* aux_last, double* dpair,
                            hipStream_t st, float* det_part = nullptr, int N = 0, const uint32_t* det_off = nullptr);
-// BF16 rows of 256 features of the MLP backward (activations, gradients of pre-activations) in the MFMA kernels' own
-// order: tile of 16 rows, 32-feature chunk c, lane 16 g + row % 16, then the lane's 8 values: features
-// 32 c + 4 g + 0..3 and 32 c + 16 + 4 g + 0..3. A wave's load or store of a chunk is one contiguous KiB. Rows are
-// padded to whole tiles.
+// Rows of 256 features of the MLP backward (activations, gradients of pre-activations) lie in the MFMA kernels' own
+// order. BF16: tile of 16 rows, 32-feature chunk c, lane 16 g + row % 16, then the lane's 8 values: features
+// 32 c + 4 g + 0..3 and 32 c + 16 + 4 g + 0..3. FP32: tile of 16 rows, 16-feature piece t, lane, then its 4 values:
+// features 16 t + 4 g + 0..3. A wave's load or store of a chunk or piece is one contiguous KiB. Rows are padded to
+// whole tiles.
 inline int64_t chunk_rows(int64_t P) { return (P + 15) / 16 * 16; }
 __host__ __device__ inline size_t chunk_at(int64_t row, int c, int g) {  // first of the lane's 8 values
     return ((size_t)(row >> 4) * 8 + c) * 512 + (size_t)(g * 16 + (int)(row & 15)) * 8;
 }
-// Bytes of one layer of P rows: BF16 in chunk order, FP32 row-major.
-inline size_t act_layer_bytes(int64_t P, bool bf16) {
-    return (size_t)(bf16 ? chunk_rows(P) * 2 : P * 4) * 256;
+__host__ __device__ inline size_t piece_at(int64_t row, int t, int g) {  // first of the lane's 4 values
+    return ((size_t)(row >> 4) * 16 + t) * 256 + (size_t)(g * 16 + (int)(row & 15)) * 4;
 }
+// bytes of one layer of P rows
+inline size_t act_layer_bytes(int64_t P, bool bf16) { return (size_t)chunk_rows(P) * 256 * (bf16 ? 2 : 4); }
 // element j of lane group g in chunk c is feature chunk_feature(c, g, j)
 __host__ __device__ inline int chunk_feature(int c, int g, int j) { return 32 * c + (j < 4 ? 4 * g + j : 12 + 4 * g + j); }
 
@@ -313,7 +315,7 @@ void launch_colsum(const float* A, int64_t rows, int64_t cols, int nz, int64_t b
                    int64_t out_bs, hipStream_t st);
 // dg: [N][26] gradient of gamma(mu_hat) summed over the batch -> dmu [N][2]
 void launch_pe_chain(const float* dg, const DevScene& s, float* dmu, hipStream_t st);
-// The BF16 arrays dz and act below are in chunk order.
+// The arrays dz and act below are in chunk order (BF16) or piece order (FP32).
 // BF16 weights of the backward from the FP32 masters w[0 .. n_hidden]: per 256 x 256 layer 65536 values in fragment
 // order, then the output layer's 7 x 256
 void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t st);
@@ -328,7 +330,7 @@ void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGrou
                        float* db, hipStream_t st);
 int wgrad_f32_blocks(int64_t P);
 size_t wgrad_f32_floats(int64_t P);
-// dW [256][256] = dz^T act over the listed rows, FP32 row-major; part: wgrad_f32_floats(P)
+// dW [256][256] = dz^T act over the listed rows, FP32; part: wgrad_f32_floats(P)
 void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGroups& rg, float* part, float* dW,
                       hipStream_t st);
 // Layer-1 gradient sums of a BF16 backward straight from dz1 [B][N][256] (the second layer's pre-activation
@@ -337,7 +339,7 @@ void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGro
 int layer1_grad_blocks(int N);
 void launch_layer1_grad(const void* dz1, const void* wf, const void* act, int B, int N, const RowGroups& rg, float* S,
                         float* Rpart, hipStream_t st);
-// Output layer of the backward in one pass over act [P][256] (BF16 or FP32 row-major, as wo and dz): dz (may be NULL) = (dy Wo)
+// Output layer of the backward in one pass over act [P][256] (BF16 or FP32, as wo and dz): dz (may be NULL) = (dy Wo)
 // masked by act > 0; dWo [7][256] = dy^T act and dbo [7] = the column sums of dy (either may be NULL). part:
 // out_bwd_floats(P) floats.
 size_t out_bwd_floats(int64_t P);

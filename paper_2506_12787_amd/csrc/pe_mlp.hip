@@ -213,7 +213,9 @@ __device__ __forceinline__ void mlp_fp32_block(const MlpArgs& a, const MixBatch&
                                              fmaxf(acc[i][cb][2], 0.0f), fmaxf(acc[i][cb][3], 0.0f));
                 s_h[(cb * 16 + t) * 64 + lane] = h;
                 const size_t r = row0 + cb * 16 + (lane & 15);
-                if (st && r < total) *reinterpret_cast<float4*>(st + r * 256 + 16 * t + 4 * g) = h;
+                if (st && r < total)  // one contiguous KiB per column block
+                    __builtin_nontemporal_store(f32x4{h.x, h.y, h.z, h.w},
+                                                reinterpret_cast<f32x4*>(st + piece_at((int64_t)r, t, g)));
             }
         __syncthreads();
     };
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
         float hin[64];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const float4 v = in ? *reinterpret_cast<const float4*>(dz + row * 256 + 16 * q + 4 * g)
+            const float4 v = in ? *reinterpret_cast<const float4*>(dz + piece_at(row, q, g))
                                 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             s_h[(wave * 16 + q) * 64 + lane] = v;
             hin[4 * q] = v.x;
@@ -376,7 +378,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
         if (rows[cb] < 0) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const size_t at = (size_t)rows[cb] * 256 + 16 * (4 * wave + i) + 4 * g;
+            const size_t at = piece_at(rows[cb], 4 * wave + i, g);
             const float4 mk = *reinterpret_cast<const float4*>(act + at);
             *reinterpret_cast<float4*>(out + at) =
                 make_float4(mk.x > 0.0f ? acc[i][cb][0] : 0.0f, mk.y > 0.0f ? acc[i][cb][1] : 0.0f,

@@ -656,7 +656,7 @@ swf_status Ctx::enqueue_preprocess(Workspace& w, Scene* sc, const float* tx, int
         else {
             float* ap[8] = {};  // per-layer activation stores, [n_hidden][B * N][256]
             for (int l = 0; w.act_out && l < d.n_hidden && l < 8; ++l)
-                ap[l] = (float*)w.act_out + (size_t)l * B * d.n * 256;
+                ap[l] = (float*)((char*)w.act_out + act_layer_bytes((int64_t)B * d.n, false) * l);
             launch_mlp_fp32(d, (const float*)w.qs.ptr, B, g, (flags & SWF_PAPER_DEFORM) != 0, w.rec, delta_sorted, st,
                             w.act_out ? ap : nullptr);
         }
@@ -1392,7 +1392,7 @@ swf_status swf_debug_relu_pattern(swf_ctx* h, uint8_t* pattern, uint64_t capacit
             } else {
                 for (int k = 0; k < 256; ++k) {
                     float v;
-                    std::memcpy(&v, a.data() + (i * 256 + k) * 4, 4);
+                    std::memcpy(&v, a.data() + (piece_at((int64_t)i, k / 16, k % 16 / 4) + k % 4) * 4, 4);
                     o[k] = v > 0.0f;
                 }
             }
