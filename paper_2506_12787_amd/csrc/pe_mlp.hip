@@ -95,10 +95,29 @@ __device__ __forceinline__ void f32_first(const float4* __restrict__ wf, int lan
         for (int i = 0; i < 4; ++i) w[d][i] = wf[((size_t)i * kQ + d) * 64 + lane];
 }
 
-// acc[i][cb] += tile 4 wave + i of the layer over kQ pieces of the state; w holds the first fragments.
-template <int kNcb, int kQ>
+template <int kCtrl, int kBank = 0xf>
+__device__ __forceinline__ float dpp(float old, float v) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), kCtrl, 0xf, kBank, kBank == 0xf));
+}
+// v of lane ^ (1 << step), step < 4, in registers
+__device__ __forceinline__ float lane_xor(float v, int step) {
+    if (step == 0) return dpp<0xb1>(0.f, v);                   // quad_perm 1,0,3,2
+    if (step == 1) return dpp<0x4e>(0.f, v);                   // quad_perm 2,3,0,1
+    if (step == 3) return dpp<0x128>(0.f, v);                  // row_ror:8
+    return dpp<0x114, 0xa>(dpp<0x104, 0x5>(v, v), v);          // row_shl:4 into banks 0, 2; row_shr:4 into 1, 3
+}
+
+struct NoHook {
+    __device__ void operator()(int) const {}
+};
+
+// acc[i][cb] += tile 4 wave + i of the layer over kQ pieces of the state; w holds the first fragments. hook(q) runs
+// before piece q's instructions (the caller's own loads, in flight under them).
+template <int kNcb, int kQ, typename Hook = NoHook>
 __device__ __forceinline__ void f32_coop_layer(const float4* __restrict__ wf, const float4* s_h, int lane,
-                                               float4 (&w)[kAhead<kNcb> + 1][4], f32x4 (&acc)[4][kNcb]) {
+                                               float4 (&w)[kAhead<kNcb> + 1][4], f32x4 (&acc)[4][kNcb],
+                                               Hook hook = Hook()) {
     constexpr int kA = kAhead<kNcb>;
     float4 bn[kNcb];
 #pragma unroll
@@ -114,6 +133,7 @@ __device__ __forceinline__ void f32_coop_layer(const float4* __restrict__ wf, co
         if (q + kA < kQ)
 #pragma unroll
             for (int i = 0; i < 4; ++i) w[(q + kA) % (kA + 1)][i] = wf[((size_t)i * kQ + q + kA) * 64 + lane];
+        hook(q);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -294,6 +314,10 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void mlp_fp32_kernel(MlpArgs a, Mi
 // 16 bytes; masked output tile t (units 16 t + 4 g + i) goes out as 16 bytes. With
 // bpart, the layer's bias gradient rides along: bpart[block][o] = the sum of
 // dz[p][o] over the block's 64 pairs (fixed order; rows past P count zero).
+// A block's 16 loads per lane go out together and the ReLU masks are loaded under
+// the matrix instructions, so that little but those is waited for: 160k pairs 202
+// us (230 with each load in a branch of its own, 247 with a layer per wave; the
+// instructions' own time is 146, the bytes' 103).
 __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __restrict__ dz,
                                                                  const float4* __restrict__ wt,
                                                                  const float* __restrict__ act, int64_t P,
@@ -314,11 +338,14 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
     const int64_t row = p0 + (lane & 15);
     {
         const bool in = row < P;
+        const float* px = dz + piece_at(in ? row : 0, 0, g);  // a row that is none reads row 0 and counts zero
+        float4 x[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[q] = *reinterpret_cast<const float4*>(px + 256 * q);
         float hin[64];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const float4 v = in ? *reinterpret_cast<const float4*>(dz + piece_at(row, q, g))
-                                : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const float4 v = in ? x[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             s_h[(wave * 16 + q) * 64 + lane] = v;
             hin[4 * q] = v.x;
             hin[4 * q + 1] = v.y;
@@ -338,7 +365,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
                 for (int i = 0; i < half; ++i) {
                     const float send = up ? hin[i] : hin[half + i];
                     const float keep = up ? hin[half + i] : hin[i];
-                    hin[i] = keep + __shfl_xor(send, 1 << step);
+                    hin[i] = keep + lane_xor(send, step);
                 }
             }
             const int r = lane & 15;
@@ -372,17 +399,32 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int cb = 0; cb < kFWaves; ++cb) acc[i][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32_coop_layer<kFWaves, 16>(wt, s_h, lane, w, acc);
+    // under the instructions of piece q: the activations of output tile q / 4, column block q % 4, kept as 4 bits
+    // (a row that is none reads row 0 and is not stored)
+    const float* pm[kFWaves];
+#pragma unroll
+    for (int cb = 0; cb < kFWaves; ++cb) pm[cb] = act + piece_at(max(rows[cb], (int64_t)0), 4 * wave, g);
+    float4 mk = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint64_t bits = 0;
+    const auto keep = [&](int q) {
+        const uint32_t b = (mk.x > 0.f ? 1u : 0u) | (mk.y > 0.f ? 2u : 0u) | (mk.z > 0.f ? 4u : 0u) |
+                           (mk.w > 0.f ? 8u : 0u);
+        bits |= (uint64_t)b << (4 * q);
+    };
+    f32_coop_layer<kFWaves, 16>(wt, s_h, lane, w, acc, [&](int q) {
+        if (q) keep(q - 1);
+        mk = *reinterpret_cast<const float4*>(pm[q & 3] + 256 * (q >> 2));
+    });
+    keep(15);
 #pragma unroll
     for (int cb = 0; cb < kFWaves; ++cb) {
         if (rows[cb] < 0) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const size_t at = piece_at(rows[cb], 4 * wave + i, g);
-            const float4 mk = *reinterpret_cast<const float4*>(act + at);
-            *reinterpret_cast<float4*>(out + at) =
-                make_float4(mk.x > 0.0f ? acc[i][cb][0] : 0.0f, mk.y > 0.0f ? acc[i][cb][1] : 0.0f,
-                            mk.z > 0.0f ? acc[i][cb][2] : 0.0f, mk.w > 0.0f ? acc[i][cb][3] : 0.0f);
+            const uint32_t m = (uint32_t)(bits >> (4 * (4 * i + cb)));
+            *reinterpret_cast<float4*>(out + piece_at(rows[cb], 4 * wave + i, g)) =
+                make_float4(m & 1u ? acc[i][cb][0] : 0.0f, m & 2u ? acc[i][cb][1] : 0.0f,
+                            m & 4u ? acc[i][cb][2] : 0.0f, m & 8u ? acc[i][cb][3] : 0.0f);
         }
     }
 }
