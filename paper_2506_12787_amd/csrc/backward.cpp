@@ -36,7 +36,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
                                      gemm_part_floats(Hd, kMeanFeat, N), gemm_part_floats(Hd, kTxFeat, B),
                                      (size_t)layer1_sums_blocks((int)N) * B * Hd,
                                      (size_t)layer1_grad_blocks((int)N) * B * Hd, wgrad_mfma_floats(P),
-                                     out_bwd_floats(P), (size_t)dz_f32_blocks(P) * Hd});
+                                     out_bwd_floats(P)});
     const size_t n_cs = std::max<size_t>({(size_t)colsum_blocks(P) * Hd, (size_t)colsum_blocks(B) * N * Hd,
                                           (size_t)colsum_blocks(N) * Hd * B});
     const size_t n_wb = bf16 ? ((size_t)(nh - 1) * Hd * Hd + (size_t)kOut * Hd + (size_t)P * kOut + 64) / 2 + 64 : 0;
@@ -93,14 +93,11 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
             else
                 dz1 = dz[cur];
         } else {
-            if (gr->weight[l])
-                launch_wgrad_f32((const float*)dz[cur], (const float*)act[l - 1], P, rg, part, gr->weight[l], st);
-            // the input gradient on the FP32 matrix cores with the layer's W^T as register-fed weights, masked;
-            // the bias gradient's per-block column sums of dz ride along (into the split-K space, free again)
-            float* bp = gr->bias[l] ? part : nullptr;
+            launch_wgrad_f32((const float*)dz[cur], (const float*)act[l - 1], P, rg, part, gr->weight[l], gr->bias[l],
+                             st);
+            // the input gradient on the FP32 matrix cores with the layer's W^T as weights, masked
             launch_dz_f32((const float*)dz[cur], wt + (size_t)(l - 1) * Hd * Hd, (const float*)act[l - 1], P, rg,
-                          (float*)dz[cur ^ 1], bp, st);
-            if (bp) launch_colsum(bp, dz_f32_blocks(P), Hd, 1, 0, tmp, gr->bias[l], 0, st);
+                          (float*)dz[cur ^ 1], st);
         }
         cur ^= 1;
     }

@@ -895,8 +895,8 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
 // gridDim-th listed group. Each row is read once, as 16 bytes per thread, and
 // staged row by row (padded by 16 floats: the 4 rows that one fragment read
 // touches fall in distinct banks), double-buffered, one barrier per 32 rows; the
-// next rows are loaded while the current ones are multiplied. Tiles per wave as
-// above. 160k pairs: 223 us per layer on the general product's 128 x 128 tiles,
+// next rows are loaded while the current ones are multiplied. Tiles per wave and
+// slices as above; the bias gradient is summed from the fragments. 160k pairs: 223 us per layer on the general product's 128 x 128 tiles,
 // which read each row twice; 178 here (the instructions' own time: 146).
 constexpr int kWfRow = 256 + 16;
 
@@ -934,6 +934,7 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 8; ++b) acc[a][b] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+    float bias[4] = {0.f, 0.f, 0.f, 0.f};  // sums of dz over rows 4 q + g
     if (blockIdx.x < ng) {
         load(blockIdx.x);
         stage(0);
@@ -954,6 +955,8 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
 #pragma unroll
             for (int b = 0; b < 8; ++b) fb[b] = rx[16 * b];
 #pragma unroll
+            for (int a = 0; a < 4; ++a) bias[a] += fa[a];
+#pragma unroll
             for (int b = 0; b < 8; ++b)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
@@ -962,7 +965,14 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
         if (more) stage(buf ^ 1);  // read last before the barrier that ended the step before
         __syncthreads();
     }
-    float* out = part + (size_t)blockIdx.x * 65536;
+    float* out = part + (size_t)blockIdx.x * kWgSlice;
+    if (wave < 4)  // these cover the 16 o-tiles once
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            float v = bias[a] + __shfl_xor(bias[a], 16);
+            v += __shfl_xor(v, 32);
+            if (g == 0) out[65536 + o0 + 16 * a + n] = v;
+        }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -1133,18 +1143,25 @@ __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restric
     __shared__ float4 red[4][64];
     for (int b = 0; b < B; ++b) {
         float4 racc = make_float4(0.f, 0.f, 0.f, 0.f);
+        // a row that does not count reads the query's first instead, so that the loads go out together
+        float4 v[kSumRows / 4], a[kSumRows / 4];
+        bool on[kSumRows / 4];
 #pragma unroll
         for (int i = 0; i < kSumRows / 4; ++i) {
             const int n = n0 + ty + 4 * i;
-            const int64_t p = (int64_t)b * N + n;
-            if (n < N && (!bits || ((bits[p >> 5] >> (p & 31)) & 1u))) {
-                const float4 v = load4(z + (kMask ? (size_t)p * 256 + c : piece_at(p, c / 16, c % 16 / 4)));
-                float4 m = v;
-                if constexpr (kMask) {
-                    const float4 a = load4(act + chunk_at(p, c / 32, c % 16 / 4) + c % 32 / 16 * 4);
-                    m = make_float4(a.x > 0.f ? v.x : 0.f, a.y > 0.f ? v.y : 0.f, a.z > 0.f ? v.z : 0.f,
-                                    a.w > 0.f ? v.w : 0.f);
-                }
+            int64_t p = (int64_t)b * N + (n < N ? n : 0);
+            on[i] = n < N && (!bits || ((bits[p >> 5] >> (p & 31)) & 1u));
+            if (!on[i]) p = (int64_t)b * N;
+            v[i] = load4(z + (kMask ? (size_t)p * 256 + c : piece_at(p, c / 16, c % 16 / 4)));
+            if constexpr (kMask) a[i] = load4(act + chunk_at(p, c / 32, c % 16 / 4) + c % 32 / 16 * 4);
+        }
+#pragma unroll
+        for (int i = 0; i < kSumRows / 4; ++i) {
+            if (on[i]) {
+                float4 m = v[i];
+                if constexpr (kMask)
+                    m = make_float4(a[i].x > 0.f ? m.x : 0.f, a[i].y > 0.f ? m.y : 0.f, a[i].z > 0.f ? m.z : 0.f,
+                                    a[i].w > 0.f ? m.w : 0.f);
                 sacc[i].x += m.x;
                 sacc[i].y += m.y;
                 sacc[i].z += m.z;
@@ -1347,13 +1364,14 @@ void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGrou
 }
 
 int wgrad_f32_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, (P + 255) / 256)); }
-size_t wgrad_f32_floats(int64_t P) { return (size_t)wgrad_f32_blocks(P) * 65536; }
+size_t wgrad_f32_floats(int64_t P) { return (size_t)wgrad_f32_blocks(P) * kWgSlice; }
 
 void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGroups& rg, float* part, float* dW,
-                      hipStream_t st) {
+                      float* db, hipStream_t st) {
+    if (!dW && !db) return;
     const int nblk = wgrad_f32_blocks(P);  // P = 0: one block writes zeros
     wgrad_f32_kernel<<<nblk, 64 * kWgWaves, 0, st>>>(dz, act, P, rg, part);
-    slice_sum(part, nblk, 65536, 65536, 0, dW, nullptr, st);
+    slice_sum(part, nblk, kWgSlice, 65536, 256, dW, db, st);
 }
 
 void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipStream_t st) {

@@ -180,12 +180,10 @@ struct RowGroups;  // the pairs with a gradient, below
 void launch_tx_features(const DevScene& s, const float* tx, int B, float* qs, uint32_t* status, hipStream_t st,
                         float* feat_out = nullptr);
 // FP32 backward of a 256 x 256 layer on the FP32 matrix cores: wt = W^T packed fragment-major (65536 floats, from
-// W [256][256] row-major); out [P][256] = (dz [P][256] W) masked by act [P][256] > 0; with bpart (non-null,
-// [dz_f32_blocks(P)][256]) also the per-block column sums of dz (the layer's bias gradient before their sum).
+// W [256][256] row-major); out [P][256] = (dz [P][256] W) masked by act [P][256] > 0.
 void launch_pack_wt(const float* w, float* wt, hipStream_t st);
-int64_t dz_f32_blocks(int64_t P);
 void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P, const RowGroups& rg, float* out,
-                   float* bpart, hipStream_t st);
+                   hipStream_t st);
 void launch_mlp_fp32(const DevScene& s, const float* qs, int B, const Grid& g, bool paper_mask, const Records& r,
                      float* delta_out, hipStream_t st, float* const* act_out = nullptr);
 void launch_preprocess_static(const DevScene& s, int B, const Grid& g, const Records& r, hipStream_t st);
@@ -330,9 +328,9 @@ void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGrou
                        float* db, hipStream_t st);
 int wgrad_f32_blocks(int64_t P);
 size_t wgrad_f32_floats(int64_t P);
-// dW [256][256] = dz^T act over the listed rows, FP32; part: wgrad_f32_floats(P)
+// dW [256][256] = dz^T act and db [256] = the column sums of dz over the listed rows, FP32; part: wgrad_f32_floats(P)
 void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGroups& rg, float* part, float* dW,
-                      hipStream_t st);
+                      float* db, hipStream_t st);
 // Layer-1 gradient sums of a BF16 backward straight from dz1 [B][N][256] (the second layer's pre-activation
 // gradient, BF16) and wf (its weights' fragments): S [N][256] = sum over b of (dz1 W) masked by act > 0, and
 // Rpart [layer1_grad_blocks(N)][B][256] per-block sums over the Gaussians.

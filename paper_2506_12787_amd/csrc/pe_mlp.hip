@@ -95,19 +95,6 @@ __device__ __forceinline__ void f32_first(const float4* __restrict__ wf, int lan
         for (int i = 0; i < 4; ++i) w[d][i] = wf[((size_t)i * kQ + d) * 64 + lane];
 }
 
-template <int kCtrl, int kBank = 0xf>
-__device__ __forceinline__ float dpp(float old, float v) {
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), kCtrl, 0xf, kBank, kBank == 0xf));
-}
-// v of lane ^ (1 << step), step < 4, in registers
-__device__ __forceinline__ float lane_xor(float v, int step) {
-    if (step == 0) return dpp<0xb1>(0.f, v);                   // quad_perm 1,0,3,2
-    if (step == 1) return dpp<0x4e>(0.f, v);                   // quad_perm 2,3,0,1
-    if (step == 3) return dpp<0x128>(0.f, v);                  // row_ror:8
-    return dpp<0x114, 0xa>(dpp<0x104, 0x5>(v, v), v);          // row_shl:4 into banks 0, 2; row_shr:4 into 1, 3
-}
-
 struct NoHook {
     __device__ void operator()(int) const {}
 };
@@ -311,9 +298,7 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void mlp_fp32_kernel(MlpArgs a, Mi
 // above with W^T as its weights (fragment-major, packed by pack_wt_kernel) and
 // no bias, over the listed groups, two to a block. A wave brings 16 rows into the
 // state: lane l = 16 g + r loads piece q (inputs 16 q + 4 g + 0..3) of row r as
-// 16 bytes; masked output tile t (units 16 t + 4 g + i) goes out as 16 bytes. With
-// bpart, the layer's bias gradient rides along: bpart[block][o] = the sum of
-// dz[p][o] over the block's 64 pairs (fixed order; rows past P count zero).
+// 16 bytes; masked output tile t (units 16 t + 4 g + i) goes out as 16 bytes.
 // A block's 16 loads per lane go out together and the ReLU masks are loaded under
 // the matrix instructions, so that little but those is waited for: 160k pairs 202
 // us (230 with each load in a branch of its own, 247 with a layer per wave; the
@@ -321,19 +306,14 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void mlp_fp32_kernel(MlpArgs a, Mi
 __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __restrict__ dz,
                                                                  const float4* __restrict__ wt,
                                                                  const float* __restrict__ act, int64_t P,
-                                                                 RowGroups rg, float* __restrict__ out,
-                                                                 float* __restrict__ bpart) {
+                                                                 RowGroups rg, float* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) float4 s_h[kFWaves * 16 * 64];
-    __shared__ float4 s_b[kFWaves][64];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
     const int g = lane >> 4;
     // the block's listed groups of 32 rows: two waves each
     static_assert(kRowGroup == 32 && kFWaves == 4, "two groups per block");
     const uint32_t ng = *rg.count, gi = 2 * blockIdx.x + (wave >> 1);
-    if (2 * blockIdx.x >= ng) {  // block-uniform: no rows, no bias sums
-        if (bpart) bpart[(size_t)blockIdx.x * 256 + threadIdx.x] = 0.0f;
-        return;
-    }
+    if (2 * blockIdx.x >= ng) return;  // block-uniform: no rows
     const int64_t p0 = gi < ng ? (int64_t)rg.list[gi] * kRowGroup + 16 * (wave & 1) : P;
     const int64_t row = p0 + (lane & 15);
     {
@@ -342,47 +322,11 @@ __global__ __launch_bounds__(64 * kFWaves, 2) void dz_f32_kernel(const float* __
         float4 x[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) x[q] = *reinterpret_cast<const float4*>(px + 256 * q);
-        float hin[64];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const float4 v = in ? x[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            s_h[(wave * 16 + q) * 64 + lane] = v;
-            hin[4 * q] = v.x;
-            hin[4 * q + 1] = v.y;
-            hin[4 * q + 2] = v.z;
-            hin[4 * q + 3] = v.w;
-        }
-        if (bpart) {
-            // Column sums of dz over the wave's 16 rows, halving: at step s a lane keeps
-            // the upper half of its values if bit s of r is set (else the lower half)
-            // and adds its partner's (lane ^ 2^s) matching half. After four steps lane
-            // (r, g) holds columns 16 q + 4 g + j, j = 0..3, with q the 4-bit reversal of r.
-#pragma unroll
-            for (int step = 0; step < 4; ++step) {
-                const int half = 32 >> step;
-                const bool up = (lane >> step) & 1;
-#pragma unroll
-                for (int i = 0; i < half; ++i) {
-                    const float send = up ? hin[i] : hin[half + i];
-                    const float keep = up ? hin[half + i] : hin[i];
-                    hin[i] = keep + lane_xor(send, step);
-                }
-            }
-            const int r = lane & 15;
-            const int q = ((r & 1) << 3) | ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3);
-            s_b[wave][4 * q + g] = make_float4(hin[0], hin[1], hin[2], hin[3]);
-        }
+        for (int q = 0; q < 16; ++q)
+            s_h[(wave * 16 + q) * 64 + lane] = in ? x[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
     __syncthreads();
-    if (bpart) {
-        static_assert(64 * kFWaves == 256, "one thread per column");
-        const int c = (int)threadIdx.x;
-        const float* sb = reinterpret_cast<const float*>(s_b);
-        float sum = sb[c];
-#pragma unroll
-        for (int w = 1; w < kFWaves; ++w) sum += sb[w * 256 + c];
-        bpart[(size_t)blockIdx.x * 256 + c] = sum;
-    }
     // rows of the column blocks: two per listed group
     wt += (size_t)4 * wave * 16 * 64;
     float4 w[kAhead<kFWaves> + 1][4];
@@ -547,13 +491,11 @@ void launch_permute_delta(const float* delta_sorted, const uint32_t* perm, int B
 
 void launch_pack_wt(const float* w, float* wt, hipStream_t st) { pack_wt_kernel<<<256, 256, 0, st>>>(w, wt); }
 
-int64_t dz_f32_blocks(int64_t P) { return (P + kFWaves * 16 - 1) / (kFWaves * 16); }
-
 void launch_dz_f32(const float* dz, const float* wt, const float* act, int64_t P, const RowGroups& rg, float* out,
-                   float* bpart, hipStream_t st) {
+                   hipStream_t st) {
     if (P > 0)
-        dz_f32_kernel<<<(unsigned)dz_f32_blocks(P), 64 * kFWaves, 0, st>>>(dz, reinterpret_cast<const float4*>(wt),
-                                                                            act, P, rg, out, bpart);
+        dz_f32_kernel<<<(unsigned)((P + 63) / 64), 64 * kFWaves, 0, st>>>(dz, reinterpret_cast<const float4*>(wt), act,
+                                                                          P, rg, out);
 }
 
 }  // namespace swf
