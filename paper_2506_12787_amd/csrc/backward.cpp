@@ -31,21 +31,19 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     // dz ping-pong; BF16 with a single hidden layer: also the FP32 layer-1 gradient (formed inside its sums)
     const bool need_zf = bf16 && nh == 1;
     if ((s = w.dz.reserve(this, need_zf ? actb * 2 + f32b + 16 : actb * 2 + 16, st))) return s;
-    // scratch: S (N x 256), R (B x 256), dg (N x 26), split-K partials, column-sum partials, BF16 weights
+    // scratch: S (N x 256), R (B x 256), split-K partials, column-sum partials, BF16 weights
     const size_t n_split = std::max({bf16 ? (size_t)0 : wgrad_f32_floats(P), gemm_part_floats(kOut, Hd, P),
-                                     gemm_part_floats(Hd, kMeanFeat, N), gemm_part_floats(Hd, kTxFeat, B),
+                                     mean_grad_floats(N), gemm_part_floats(Hd, kTxFeat, B),
                                      (size_t)layer1_sums_blocks((int)N) * B * Hd,
                                      (size_t)layer1_grad_blocks((int)N) * B * Hd, wgrad_mfma_floats(P),
                                      out_bwd_floats(P)});
-    const size_t n_cs = std::max<size_t>({(size_t)colsum_blocks(P) * Hd, (size_t)colsum_blocks(B) * N * Hd,
-                                          (size_t)colsum_blocks(N) * Hd * B});
+    const size_t n_cs = (size_t)colsum_blocks(N) * Hd * B;
     const size_t n_wb = bf16 ? ((size_t)(nh - 1) * Hd * Hd + (size_t)kOut * Hd + (size_t)P * kOut + 64) / 2 + 64 : 0;
     const size_t n_wt = bf16 ? 0 : (size_t)(nh - 1) * Hd * Hd;  // FP32: W^T of the 256 x 256 layers, fragment-major
     const size_t small =
-        ((size_t)N * Hd + (size_t)B * Hd + (size_t)N * kMeanFeat + 4 + n_split + n_cs + n_wb + n_wt + 64) *
+        ((size_t)N * Hd + (size_t)B * Hd + 4 + n_split + n_cs + n_wb + n_wt + 64) *
         sizeof(float);
     if ((s = w.part.reserve(this, small, st))) return s;
-    if ((s = w.fmean.reserve(this, (size_t)N * kMeanFeat * sizeof(float) + 16, st))) return s;
     if ((s = w.ftx.reserve(this, (size_t)B * kTxFeat * sizeof(float) + 16, st))) return s;
     if ((s = w.dmu.reserve(this, (size_t)N * 2 * sizeof(float) + 16, st))) return s;
     if ((s = w.qs.reserve(this, (size_t)B * Hd * sizeof(float), st))) return s;
@@ -55,14 +53,12 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     float* zf = need_zf ? (float*)((char*)w.dz.ptr + actb * 2) : nullptr;  // FP32 layer-1 gradient (nh == 1)
     float* S = (float*)w.part.ptr;               // N x 256
     float* R = S + (size_t)N * Hd;               // B x 256
-    float* dg = R + (size_t)B * Hd;              // N x 26
-    float* part = dg + ((size_t)N * kMeanFeat + 3) / 4 * 4;  // split-K partials (16-byte aligned)
+    float* part = R + (size_t)B * Hd;            // split-K partials (16-byte aligned)
     float* tmp = part + n_split;                 // column-sum partials
     uint16_t* wb = (uint16_t*)(((uintptr_t)(tmp + n_cs) + 15) & ~(uintptr_t)15);  // BF16 weights (launch_pack_bwd), then dy
     float* wt = (float*)(((uintptr_t)(tmp + n_cs + n_wb) + 15) & ~(uintptr_t)15);  // FP32 W^T, 16-byte aligned
-    float* fmean = (float*)w.fmean.ptr, *ftx = (float*)w.ftx.ptr, *qs = (float*)w.qs.ptr;
+    float *ftx = (float*)w.ftx.ptr, *qs = (float*)w.qs.ptr;
     launch_tx_features(d, tx, B, qs, nullptr, st, ftx);
-    launch_mean_features_f32(d, fmean, st);
     uint16_t* wl[8] = {};
     if (bf16) {
         for (int l = 1; l <= nh; ++l) wl[l] = wb + (size_t)(l - 1) * Hd * Hd;
@@ -121,15 +117,11 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
         else
             launch_colsum(part, rblocks, (int64_t)B * Hd, 1, 0, tmp, R, 0, st);
     }
-    if (gr->bias[0]) launch_colsum(S, N, Hd, 1, 0, tmp, gr->bias[0], 0, st);  // b0: the sum of S over Gaussians
-    if (gr->weight[0]) {
-        // dW1 [256 x 89] = [S^T gamma(mu_hat) | R^T gamma(s_hat)]
-        launch_gemm_f32(true, false, Hd, kMeanFeat, N, S, Hd, fmean, kMeanFeat, gr->weight[0], I, part, st);
+    // dW1 [256 x 89] = [S^T gamma(mu_hat) | R^T gamma(s_hat)]; the mean part with b0 (the sum of S over Gaussians) and
+    // d mu, through d gamma(mu_hat) = S W1m
+    if (gr->weight[0])
         launch_gemm_f32(true, false, Hd, kTxFeat, B, R, Hd, ftx, kTxFeat, gr->weight[0] + kMeanFeat, I, part, st);
-    }
-    // d gamma(mu_hat) = S W1m (N x 26), then through the features to d mu
-    launch_gemm_f32(false, false, N, kMeanFeat, Hd, S, Hd, d.w[0], I, dg, kMeanFeat, part, st);
-    launch_pe_chain(dg, d, (float*)w.dmu.ptr, st);
+    launch_mean_grad(S, d, part, gr->weight[0], gr->bias[0], (float*)w.dmu.ptr, st);
     return hip(hipGetLastError(), "mlp backward");
 }
 

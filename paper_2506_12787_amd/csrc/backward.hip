@@ -465,10 +465,10 @@ __global__ __launch_bounds__(256) void colsum8_stage2_kernel(const float* __rest
 // Sums of nb slices of a launch's partial results, slices in a fixed order:
 // out0[c] (c < n0) and out1[c - n0] = sum over j of part[j * stride + c]. 16
 // threads of four columns by 16 groups of slices, summed through LDS.
-// Destinations may be NULL.
+// Destinations may be NULL; out0 has rows of w0 values, ld0 apart.
 __global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict__ part, int nb, int64_t stride,
                                                         int64_t n0, int64_t n1, float* __restrict__ out0,
-                                                        float* __restrict__ out1) {
+                                                        float* __restrict__ out1, uint32_t w0, uint32_t ld0) {
     __shared__ float4 red[16][16];
     const int cx = (int)threadIdx.x & 15, gy = (int)threadIdx.x >> 4;
     const int64_t c = (int64_t)blockIdx.x * 64 + 4 * cx;
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict_
     for (int k = 0; k < 4; ++k) {
         const int64_t e = c + k;
         if (e < n0) {
-            if (out0) out0[e] = v[k];
+            if (out0) out0[w0 ? (size_t)((uint32_t)e / w0) * ld0 + (uint32_t)e % w0 : (size_t)e] = v[k];
         } else if (e < n0 + n1 && out1) {
             out1[e - n0] = v[k];
         }
@@ -509,30 +509,6 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict_
 __global__ void fill_kernel(float* __restrict__ p, float v, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
-}
-
-// d mu0 per Gaussian from dg = d gamma(mu_hat) (26 per Gaussian, already
-// summed over the batch): the chain rule through the sin / cos features.
-__global__ void pe_chain_kernel(const float* __restrict__ dgm, const float* __restrict__ mx,
-                                const float* __restrict__ my, int N, int Wd, int Hd, float* __restrict__ dmu) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    const float* dg = dgm + (size_t)p * kMeanFeat;
-    float hx, lx, hy, ly;
-    div_two(mx[p], (float)Wd, hx, lx);
-    div_two(my[p], (float)Hd, hy, ly);
-    float gx = dg[0], gy = dg[1];
-#pragma unroll
-    for (int k = 0; k < kMeanBands; ++k) {
-        float sx, cx, sy, cy;
-        sincospi_scaled(hx, lx, k, sx, cx);
-        sincospi_scaled(hy, ly, k, sy, cy);
-        const float f = 3.14159265358979323846f * (float)(1 << k);
-        gx += f * (dg[2 + 2 * k] * cx - dg[2 + 2 * kMeanBands + 2 * k] * sx);
-        gy += f * (dg[3 + 2 * k] * cy - dg[3 + 2 * kMeanBands + 2 * k] * sy);
-    }
-    dmu[(size_t)p * 2] = gx / (float)Wd;
-    dmu[(size_t)p * 2 + 1] = gy / (float)Hd;
 }
 
 // ---- BF16 variants (the MLP backward of a BF16 forward) ----------------------
@@ -1199,16 +1175,148 @@ __global__ void to_bf16_kernel(const float* __restrict__ x, int64_t n, __bf16* _
     if (i < n) y[i] = to_bf16(x[i]);
 }
 
-__global__ void mean_features_f32_kernel(const float* __restrict__ mx, const float* __restrict__ my, int n, int W,
-                                         int H, float* __restrict__ out) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    float f[kMeanFeat];
-    mean_features(mx[p], my[p], W, H, f);
-#pragma unroll
-    for (int k = 0; k < kMeanFeat; ++k) out[(size_t)p * kMeanFeat + k] = f[k];
-}
+// What layer 1 takes from S [N][256], its pre-activation gradient summed over the
+// batch, in one pass: the mean part of its weight gradient S^T gamma(mu_hat) and
+// its bias gradient (a slice of 256 x 26 and 256 values per block, to be summed),
+// and per Gaussian d gamma(mu_hat) = S W1m taken through the sin / cos features
+// to dmu [N][2]. FP32 on the matrix cores (v_mfma_f32_16x16x4_f32). A block takes
+// every gridDim-th group of 32 rows: staged in LDS (rows padded by 16 floats, so
+// that 4 rows fall in distinct banks), read as columns by wave w for units
+// [64 w, 64 w + 64) of the weight gradient, and as rows for the same units'
+// share of d gamma, which the waves then add through LDS. The next rows are
+// loaded while the current ones are multiplied. As separate launches (features,
+// column sums, two products of few columns with their slices' sums, the chain)
+// this read S three times: 96 us for 50k Gaussians, 28 and 6 for the slices now.
+constexpr int kMgRows = 32, kMgRow = 256 + 16, kMgFeat = 48, kMgDg = 36;
+constexpr int kMgSlice = 256 * kMeanFeat + 256;
 
+__global__ __launch_bounds__(256, 2) void mean_grad_kernel(const float* __restrict__ S, const float* __restrict__ w1,
+                                                           int in_dim, const float* __restrict__ mx,
+                                                           const float* __restrict__ my, int N, int Wd, int Hd,
+                                                           float* __restrict__ dmu, float* __restrict__ part) {
+    __shared__ __attribute__((aligned(16))) float s_s[kMgRows][kMgRow];
+    __shared__ float s_f[kMgRows][kMgFeat];  // gamma(mu_hat), zero from 26 on
+    __shared__ __attribute__((aligned(16))) float s_d[4][kMgRows][kMgDg];
+    const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
+    // W1m as A operands of the wave's units: tile t, units 16 q + 4 g + e of q = 4 wave + 0..3
+    float wa[2][4][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                wa[t][q][e] = 16 * t + n < kMeanFeat
+                                  ? w1[(size_t)(64 * wave + 16 * q + 4 * g + e) * in_dim + 16 * t + n]
+                                  : 0.f;
+    dz_f32x4 acc[4][2];
+    float bias[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[a][t] = dz_f32x4{0.f, 0.f, 0.f, 0.f};
+    // staging: wave w takes rows w, w + 4, .., a lane 4 units; rows past N read the last and count zero
+    float4 nx[kMgRows / 4];
+    auto load = [&](int r0) {
+#pragma unroll
+        for (int h = 0; h < kMgRows / 4; ++h)
+            nx[h] = load4(S + (size_t)min(r0 + wave + 4 * h, N - 1) * 256 + 4 * lane);
+    };
+    int r0 = (int)blockIdx.x * kMgRows;
+    const int step = (int)gridDim.x * kMgRows;
+    if (r0 < N) load(r0);
+    for (; r0 < N; r0 += step) {
+#pragma unroll
+        for (int h = 0; h < kMgRows / 4; ++h)
+            *reinterpret_cast<float4*>(&s_s[wave + 4 * h][4 * lane]) =
+                r0 + wave + 4 * h < N ? nx[h] : make_float4(0.f, 0.f, 0.f, 0.f);
+        {
+            // features: band tid / 32 of row tid % 32; the seventh group takes the identity, the eighth the zeros
+            const int r = tid & 31, k = tid >> 5, p = r0 + r;
+            float hx, lx, hy, ly;
+            div_two(mx[min(p, N - 1)], (float)Wd, hx, lx);
+            div_two(my[min(p, N - 1)], (float)Hd, hy, ly);
+            if (k < kMeanBands) {
+                float sx, cx, sy, cy;
+                sincospi_scaled(hx, lx, k, sx, cx);
+                sincospi_scaled(hy, ly, k, sy, cy);
+                s_f[r][2 + 2 * k] = p < N ? sx : 0.f;
+                s_f[r][3 + 2 * k] = p < N ? sy : 0.f;
+                s_f[r][2 + 2 * kMeanBands + 2 * k] = p < N ? cx : 0.f;
+                s_f[r][3 + 2 * kMeanBands + 2 * k] = p < N ? cy : 0.f;
+            } else if (k == kMeanBands) {
+                s_f[r][0] = p < N ? hx + lx : 0.f;
+                s_f[r][1] = p < N ? hy + ly : 0.f;
+            } else {
+#pragma unroll
+                for (int j = kMeanFeat; j < 32; ++j) s_f[r][j] = 0.f;
+            }
+        }
+        __syncthreads();
+        if (r0 + step < N) load(r0 + step);
+#pragma unroll
+        for (int c = 0; c < kMgRows / 4; ++c) {  // rows 4 c + g
+            float fa[4], fb[2];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                fa[a] = s_s[4 * c + g][64 * wave + 16 * a + n];
+                bias[a] += fa[a];
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) fb[t] = s_f[4 * c + g][16 * t + n];
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[a], fb[t], acc[a][t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int rt = 0; rt < kMgRows / 16; ++rt) {
+            dz_f32x4 d[2] = {dz_f32x4{0.f, 0.f, 0.f, 0.f}, dz_f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 b4 = load4(&s_s[16 * rt + n][64 * wave + 16 * q + 4 * g]);
+                const float b[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[t][q][e], b[e], d[t], 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)  // lane (g, n): features 16 t + 4 g + i of row n
+                *reinterpret_cast<float4*>(&s_d[wave][16 * rt + n][16 * t + 4 * g]) =
+                    make_float4(d[t][0], d[t][1], d[t][2], d[t][3]);
+        }
+        __syncthreads();
+        if (tid < 2 * kMgRows && r0 + (tid & 31) < N) {  // d mu of one axis of one row
+            const int r = tid & 31, ax = tid >> 5;
+            const auto dg = [&](int k) { return (s_d[0][r][k] + s_d[1][r][k]) + (s_d[2][r][k] + s_d[3][r][k]); };
+            float v = dg(ax);
+#pragma unroll
+            for (int k = 0; k < kMeanBands; ++k) {
+                const int si = 2 + 2 * k + ax, ci = si + 2 * kMeanBands;
+                const float f = 3.14159265358979323846f * (float)(1 << k);
+                v += f * (dg(si) * s_f[r][ci] - dg(ci) * s_f[r][si]);
+            }
+            dmu[(size_t)(r0 + r) * 2 + ax] = v / (float)(ax ? Hd : Wd);
+        }
+        __syncthreads();
+    }
+    float* out = part + (size_t)blockIdx.x * kMgSlice;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (16 * t + n < kMeanFeat)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    out[(size_t)(64 * wave + 16 * a + 4 * g + i) * kMeanFeat + 16 * t + n] = acc[a][t][i];
+        float v = bias[a] + __shfl_xor(bias[a], 16);
+        v += __shfl_xor(v, 32);
+        if (g == 0) out[256 * kMeanFeat + 64 * wave + 16 * a + n] = v;
+    }
+}
 
 }  // namespace
 
@@ -1310,10 +1418,6 @@ void launch_fill(float* p, float v, int64_t n, hipStream_t st) {
     if (n > 0) fill_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p, v, n);
 }
 
-void launch_pe_chain(const float* dg, const DevScene& s, float* dmu, hipStream_t st) {
-    if (s.n > 0) pe_chain_kernel<<<(s.n + 255) / 256, 256, 0, st>>>(dg, s.mx, s.my, s.n, s.W, s.H, dmu);
-}
-
 void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t st) {
     BwdWeights a{};
     for (int l = 0; l <= n_hidden && l < 8; ++l) a.w[l] = w[l];
@@ -1322,10 +1426,12 @@ void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t
     pack_bwd_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(a, (__bf16*)out);
 }
 
+// w0: out0's row length, rows ld0 apart (0: one row)
 static void slice_sum(const float* part, int nb, int64_t stride, int64_t n0, int64_t n1, float* out0, float* out1,
-                      hipStream_t st) {
+                      hipStream_t st, uint32_t w0 = 0, uint32_t ld0 = 0) {
     if (out0 || out1)
-        slice_sum_kernel<<<(unsigned)((n0 + n1 + 63) / 64), 256, 0, st>>>(part, nb, stride, n0, n1, out0, out1);
+        slice_sum_kernel<<<(unsigned)((n0 + n1 + 63) / 64), 256, 0, st>>>(part, nb, stride, n0, n1, out0, out1, w0,
+                                                                          ld0);
 }
 
 void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, const RowGroups& rg, void* out,
@@ -1402,8 +1508,13 @@ void launch_to_bf16(const float* x, int64_t n, void* y, hipStream_t st) {
     if (n > 0) to_bf16_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(x, n, (__bf16*)y);
 }
 
-void launch_mean_features_f32(const DevScene& s, float* out, hipStream_t st) {
-    if (s.n > 0) mean_features_f32_kernel<<<(s.n + 255) / 256, 256, 0, st>>>(s.mx, s.my, s.n, s.W, s.H, out);
+int mean_grad_blocks(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (N + kMgRows - 1) / kMgRows)); }
+size_t mean_grad_floats(int64_t N) { return (size_t)mean_grad_blocks(N) * kMgSlice; }
+
+void launch_mean_grad(const float* S, const DevScene& d, float* part, float* dW, float* db, float* dmu, hipStream_t st) {
+    const int nb = mean_grad_blocks(d.n);  // no Gaussians: one block writes zeros
+    mean_grad_kernel<<<nb, 256, 0, st>>>(S, d.w[0], d.in_dim, d.mx, d.my, d.n, d.W, d.H, dmu, part);
+    slice_sum(part, nb, kMgSlice, 256 * kMeanFeat, 256, dW, db, st, kMeanFeat, d.in_dim);
 }
 
 }  // namespace swf

@@ -311,8 +311,6 @@ void launch_fill(float* p, float v, int64_t n, hipStream_t st);
 int colsum_blocks(int64_t rows);
 void launch_colsum(const float* A, int64_t rows, int64_t cols, int nz, int64_t bs, float* part, float* out,
                    int64_t out_bs, hipStream_t st);
-// dg: [N][26] gradient of gamma(mu_hat) summed over the batch -> dmu [N][2]
-void launch_pe_chain(const float* dg, const DevScene& s, float* dmu, hipStream_t st);
 // The arrays dz and act below are in chunk order (BF16) or piece order (FP32).
 // BF16 weights of the backward from the FP32 masters w[0 .. n_hidden]: per 256 x 256 layer 65536 values in fragment
 // order, then the output layer's 7 x 256
@@ -351,7 +349,10 @@ int layer1_sums_blocks(int N);
 void launch_layer1_sums(const float* z, const void* act, const uint32_t* bits, int B, int N, float* S, float* Rpart,
                         hipStream_t st);
 void launch_to_bf16(const float* x, int64_t n, void* y, hipStream_t st);
-void launch_mean_features_f32(const DevScene& s, float* out, hipStream_t st);
+// From S [N][256]: dW (rows in_dim apart) = S^T gamma(mu_hat) [256][26], db = S's column sums, dmu [N][2]; dW, db may be
+// null; part: mean_grad_floats(N)
+size_t mean_grad_floats(int64_t N);
+void launch_mean_grad(const float* S, const DevScene& d, float* part, float* dW, float* db, float* dmu, hipStream_t st);
 
 // blend.hip
 void launch_blend_forward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,

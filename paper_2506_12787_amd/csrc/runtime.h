@@ -57,7 +57,7 @@ struct LastRender {
 // Scratch memory of one render stream: every pipeline stage writes here.
 struct Workspace {
     Buf qs, geo, wm, oa, rect, count, off, scan, keys, keys2, vals, vals2, hist, ranges, bins, delta, sortk, sortv,
-        grad, dpair, dbase, dy, act, dz, part, fmean, ftx, dmu, stage, work, beam, pool, ssim, mix, det, groups;
+        grad, dpair, dbase, dy, act, dz, part, ftx, dmu, stage, work, beam, pool, ssim, mix, det, groups;
     Records rec;
     uint64_t* total_dev = nullptr;           // device status block: scan total, effective count, then:
     uint32_t* status_dev = nullptr;          //   status word (bit 0: key overflow at a fixed capacity)
@@ -71,7 +71,7 @@ struct Workspace {
     LastRender last;
     std::vector<Buf*> bufs() {
         return {&qs, &geo, &wm, &oa, &rect, &count, &off, &scan, &keys, &keys2, &vals, &vals2, &hist, &ranges, &bins,
-                &delta, &sortk, &sortv, &grad, &dpair, &dbase, &dy, &act, &dz, &part, &fmean, &ftx, &dmu,
+                &delta, &sortk, &sortv, &grad, &dpair, &dbase, &dy, &act, &dz, &part, &ftx, &dmu,
                 &stage, &work, &beam, &pool, &ssim, &mix, &det, &groups};
     }
     uint64_t generation() {
