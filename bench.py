@@ -455,7 +455,7 @@ def bench_large(a):
     T_tiles = -(-W // 16) * -(-H // 16)
     keys = work["entries"]
     # tile counts of every block of pairs (2048 pairs, 1024 up to 256 tiles), tiles rounded up to whole waves
-    hist_entries = Bq * (-(-T_tiles // 64) * 64) * -(-N // (1024 if T_tiles <= 256 else 2048))
+    hist_entries = Bq * (-(-T_tiles // 64) * 64 if T_tiles >= 64 else -(-T_tiles // 4) * 4) * -(-N // (1024 if T_tiles <= 256 else 2048))
     list_bytes = pairs * 24 + keys * 4 + hist_entries * 12 + Bq * T_tiles * 8
     list_ms = st["scan"] + st["emit_keys"] + st["radix_sort"] + st["tile_ranges"]
     flops = float(FLOP_PER_PAIR) * pairs
@@ -1008,7 +1008,7 @@ def main():
     pairs = N * Bq
     if binned:
         # tile counts of every block of pairs (2048 pairs, 1024 up to 256 tiles), tiles rounded up to whole waves
-        hist_entries = Bq * (-(-T_tiles // 64) * 64) * -(-N // (1024 if T_tiles <= 256 else 2048))
+        hist_entries = Bq * (-(-T_tiles // 64) * 64 if T_tiles >= 64 else -(-T_tiles // 4) * 4) * -(-N // (1024 if T_tiles <= 256 else 2048))
         bin_bytes = pairs * 24 + work["entries"] * 4 + hist_entries * 12 + Bq * T_tiles * 8
         bin_ms = st_ms["scan"] + st_ms["radix_sort"] + st_ms["tile_ranges"]
         bin_note = ("binning: rect+count read twice (24 B/pair), 4 B/list entry written, tile-count prefixes 12 B/entry, "

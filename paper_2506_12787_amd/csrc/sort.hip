@@ -378,13 +378,14 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(const K* __rest
 // then 0 .. tx1).
 struct BinGeom {
     int N, TW, TH, tiles;  // pairs per query and its tile grid (mixed batches: of the largest query; TW, TH unused)
-    int stride;            // tiles per query rounded up to whole waves
+    int stride;            // tiles per query, rounded up
+    int chunk;             // (query, tile) columns per workgroup of bin_offsets: 64 or 256
     int pb, nbq;           // pairs per block, blocks per query
     int cap;               // most pairs in a placement wave's row list and segment list
 };
 
 constexpr int kMaxTiles = 4096;   // tiles per query the binning path takes
-constexpr int kColChunk = 256;    // (query, tile) columns per workgroup of bin_offsets
+constexpr int kHeldRows = 32;     // rows of a column that a thread of bin_offsets keeps in registers
 constexpr int kPlaceWaves = 12;   // most waves of a placement block
 constexpr int kSegCols = 8;       // tiles per column segment of the placement
 
@@ -394,21 +395,29 @@ constexpr int kSegCols = 8;       // tiles per column segment of the placement
 // waves the lists leave room for in LDS (24 per CU at the values taken), then how full the segment lists are.
 // Halved (to 256 at least) while the batch has fewer than two blocks per compute unit: one query of 100k pairs is
 // placed in 98 blocks at 1024 pairs, in 391 at 256.
+//
+// Columns: whole waves of tiles per query, but fours below 64 tiles, where most of a wave would be padding (1024
+// queries of one tile: bin_offsets 7.0 us, 16.2 at 64 columns each). bin_offsets takes a column's rows (the blocks of
+// its query) with one thread up to 8 rows, else with four, each of which keeps 32 rows in registers, or, past those
+// 128 rows and while the columns are few, with 16, whose workgroups of 64 columns are spread over more compute units.
+// us with 4 / 16: 100k pairs at 90 x 360, 1 query (391 rows) 25 / 10, 8 queries (98 rows) 11 / 11; 500k pairs at 360 x
+// 1440, 1 query 29 / 15, 8 (16,896 columns) 20 / 17, 16 22 / 29, 64 121 / 202.
 BinGeom bin_geom(int64_t B, int N, int TW, int TH, int tiles) {
     BinGeom b;
     b.N = N;
     b.TW = TW;
     b.TH = TH;
     b.tiles = tiles;
-    b.stride = std::max(64, (tiles + 63) & ~63);
+    b.stride = tiles < 64 ? std::max(4, (tiles + 3) & ~3) : (tiles + 63) & ~63;
     b.pb = tiles <= 256 ? 1024 : 2048;
     while (b.pb > 256 && B * ((N + b.pb - 1) / b.pb) < 512) b.pb /= 2;
     b.nbq = std::max(1, (N + b.pb - 1) / b.pb);
     b.cap = std::min(b.pb, tiles <= 256 ? 640 : 512);
+    b.chunk = b.nbq > 4 * kHeldRows && B * b.stride <= 16384 ? 64 : 256;
     return b;
 }
 
-// The bins buffer. Column e = q * stride + tile; chunk e / 256.
+// The bins buffer. Column e = q * stride + tile; chunk e / G.chunk.
 struct BinBufs {
     unsigned long long* ctot;  // list entries of a chunk of columns
     uint32_t* cbase;           // first list position of the chunk
@@ -416,7 +425,7 @@ struct BinBufs {
     uint32_t* hist;            // [B][nbq][stride]
 };
 
-int64_t bin_chunks(int64_t B, const BinGeom& G) { return (B * G.stride + kColChunk - 1) / kColChunk; }
+int64_t bin_chunks(int64_t B, const BinGeom& G) { return (B * G.stride + G.chunk - 1) / G.chunk; }
 
 size_t bin_words(int64_t B, const BinGeom& G) {
     const size_t ch = ((size_t)bin_chunks(B, G) + 1) & ~(size_t)1;
@@ -533,11 +542,11 @@ __global__ __launch_bounds__(kThreads) void bin_hist_kernel(const uint2* __restr
     for (int t = Q.tiles + (int)threadIdx.x; t < G.stride; t += kThreads) row[t] = 0u;
 }
 
-// Block c: the columns [256 c, 256 c + 256) of the (query, tile) pairs. Per
+// Block c: the kChunk columns from kChunk c on of the (query, tile) pairs. Per
 // column the exclusive prefix over the query's nbq blocks, in place (the rows
-// are cut into blockDim / 256 groups, summed, then rewritten; up to kHeldRows
-// rows of a group stay in registers between), the columns' starts within the
-// chunk and the chunk's total. The last block to finish (a counter the caller
+// are cut into kGroups groups, summed, then rewritten; up to kHeldRows rows of a
+// group stay in registers between), the columns' starts within the chunk and the
+// chunk's total. The last block to finish (a counter the caller
 // zeroed) scans the chunk totals into the chunks' first positions and writes
 // the entry count, the count usable at a fixed capacity (total if it fits, else
 // 0 with the overflow bit of the status word), and the count to the host. One
@@ -552,16 +561,15 @@ struct BinTotals {
     unsigned long long* host;   // pinned host copy of the total, or null
 };
 
-constexpr int kHeldRows = 32;
-
-__global__ __launch_bounds__(1024) void bin_offsets_kernel(BinBufs bb, BinGeom G, int64_t cols, BinTotals T) {
-    __shared__ uint32_t part[4][kColChunk];
+template <int kChunk, int kGroups>
+__global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb, BinGeom G, int64_t cols, BinTotals T) {
+    __shared__ uint32_t part[kGroups][kChunk];
     __shared__ uint64_t wsum[16];
     __shared__ int last;
-    const int groups = (int)blockDim.x / kColChunk;
-    const int col = (int)threadIdx.x & (kColChunk - 1), grp = (int)threadIdx.x / kColChunk;
-    const int w = (int)threadIdx.x >> 6, W = (int)blockDim.x >> 6;
-    const int64_t e = (int64_t)blockIdx.x * kColChunk + col;
+    constexpr int groups = kGroups, W = kChunk * kGroups / 64;
+    const int col = (int)threadIdx.x & (kChunk - 1), grp = (int)threadIdx.x / kChunk;
+    const int w = (int)threadIdx.x >> 6;
+    const int64_t e = (int64_t)blockIdx.x * kChunk + col;
     const bool in = e < cols;
     const int q = (int)((uint32_t)min(e, cols - 1) / (uint32_t)G.stride);
     const int R = (G.nbq + groups - 1) / groups;
@@ -601,7 +609,7 @@ __global__ __launch_bounds__(1024) void bin_offsets_kernel(BinBufs bb, BinGeom G
             run += v[k];
         }
     }
-    // the columns' starts within the chunk: the first 256 threads (4 waves) hold one column each
+    // the columns' starts within the chunk: the first kChunk threads hold one column each
     uint32_t inc = 0;
     if (grp == 0) {
         inc = wave_inclusive_scan<uint32_t>(tot);
@@ -614,7 +622,8 @@ __global__ __launch_bounds__(1024) void bin_offsets_kernel(BinBufs bb, BinGeom G
         if (in) bb.lstart[e] = before + inc - tot;
     }
     if (threadIdx.x == 0) {
-        const unsigned long long ct = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        unsigned long long ct = 0;
+        for (int k = 0; k < kChunk / 64; ++k) ct += wsum[k];
         __hip_atomic_store(&bb.ctot[blockIdx.x], ct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence();
         last = __hip_atomic_fetch_add(T.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
@@ -706,15 +715,15 @@ __global__ __launch_bounds__(64 * kPlaceWaves) void bin_place_kernel(const uint2
         const uint32_t all = gridDim.y * (uint32_t)G.stride;
         for (int t = threadIdx.x; t < Q.tiles; t += (int)blockDim.x) {
             const uint32_t e = e0 + (uint32_t)t, f = e + 1u;
-            const uint32_t a = bb.lstart[e] + bb.cbase[e / kColChunk];
-            const uint32_t z = f < all ? bb.lstart[f] + bb.cbase[f / kColChunk] : (uint32_t)*total;
+            const uint32_t a = bb.lstart[e] + bb.cbase[e / (uint32_t)G.chunk];
+            const uint32_t z = f < all ? bb.lstart[f] + bb.cbase[f / (uint32_t)G.chunk] : (uint32_t)*total;
             ranges[Q.tile0 + t] = !over && a < z ? make_uint2(a, z) : make_uint2(0u, 0u);
         }
     }
     if (over || np == 0) return;
     const uint32_t* hrow = bb.hist + ((size_t)q * G.nbq + j) * G.stride;
     for (int t = threadIdx.x; t < Q.tiles; t += (int)blockDim.x)
-        s_base[t] = bb.lstart[e0 + t] + bb.cbase[(e0 + t) / kColChunk] + hrow[t];
+        s_base[t] = bb.lstart[e0 + t] + bb.cbase[(e0 + t) / (uint32_t)G.chunk] + hrow[t];
     const int nk = (np + 63) / 64;
     const int TW = Q.TW;
     for (int i = threadIdx.x; i < nk * 64; i += (int)blockDim.x) {
@@ -980,10 +989,15 @@ static void offsets_launch(const BinGeom& G, int B, uint32_t* bins, const BinCou
     t.status = c.status;
     t.done = c.done;
     t.host = reinterpret_cast<unsigned long long*>(c.host);
-    // few rows per column: one row group (a quarter of the threads)
-    const int threads = G.nbq <= 8 ? kColChunk : 4 * kColChunk;
-    bin_offsets_kernel<<<(unsigned)bin_chunks(B, G), threads, 0, st>>>(bin_bufs(bins, B, G), G,
-                                                                       (int64_t)B * G.stride, t);
+    const unsigned blocks = (unsigned)bin_chunks(B, G);
+    const BinBufs bb = bin_bufs(bins, B, G);
+    const int64_t cols = (int64_t)B * G.stride;
+    if (G.chunk == 64)
+        bin_offsets_kernel<64, 16><<<blocks, 1024, 0, st>>>(bb, G, cols, t);
+    else if (G.nbq > 8)
+        bin_offsets_kernel<256, 4><<<blocks, 1024, 0, st>>>(bb, G, cols, t);
+    else
+        bin_offsets_kernel<256, 1><<<blocks, 256, 0, st>>>(bb, G, cols, t);
 }
 
 static void place_launch(const BinGeom& G, int B, int TH, bool wrap, const Records& r, uint32_t* bins,
