@@ -142,10 +142,8 @@ void launch_mix_clear_tail(const MixBatch& m, int64_t pair_cap, const Records& r
 struct BinCount;
 bool mix_bin_fits(int B, int max_tiles);
 size_t mix_bin_entries(int B, int max_n, int max_tiles);
-void launch_mix_bin_hist(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
-                         unsigned long long* cull, hipStream_t st);
-void launch_mix_bin_offsets(const MixBatch& m, int max_n, int max_tiles, uint32_t* bins, const BinCount& c,
-                            hipStream_t st);
+void launch_mix_bin_count(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
+                          unsigned long long* cull, const BinCount& c, hipStream_t st);
 void launch_mix_bin_place(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
                           const uint64_t* total, const uint64_t* n_dev, uint32_t* vals, uint2* ranges,
                           hipStream_t st);
@@ -238,10 +236,6 @@ void launch_effective_count(const uint64_t* total, uint64_t cap, uint64_t* n_eff
 // into per-tile lists and the tile ranges.
 bool bin_fits(int B, int N, const Grid& g);  // the tile grid and batch fit the binning path
 size_t bin_entries(int B, int N, const Grid& g);  // uint32 entries of `bins`
-// cull (may be null): two device counters that receive the number of culled
-// pairs, non-finite / degenerate and off the grid (also launch_emit_keys)
-void launch_bin_hist(const Records& r, int B, int N, const Grid& g, uint32_t* bins, unsigned long long* cull,
-                     hipStream_t st);
 struct BinCount {  // where the number of list entries goes
     uint64_t* total;   // device
     uint64_t cap;      // 0, or the lists' fixed capacity: then n_eff and status are set
@@ -250,7 +244,10 @@ struct BinCount {  // where the number of list entries goes
     uint32_t* done;    // zero at launch
     uint64_t* host;    // pinned host copy of the total (may be null)
 };
-void launch_bin_offsets(int B, int N, const Grid& g, uint32_t* bins, const BinCount& c, hipStream_t st);
+// cull (may be null): two device counters that receive the number of culled
+// pairs, non-finite / degenerate and off the grid (also launch_emit_keys)
+void launch_bin_count(const Records& r, int B, int N, const Grid& g, uint32_t* bins, unsigned long long* cull,
+                      const BinCount& c, hipStream_t st);
 void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* bins, const uint64_t* total,
                       const uint64_t* n_dev, uint32_t* vals, uint2* ranges, hipStream_t st);
 

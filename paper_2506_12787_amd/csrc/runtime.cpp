@@ -785,8 +785,7 @@ swf_status Ctx::lists_binned(Workspace& w, const DevScene& d, int B, const Grid&
     if ((s = w.bins.reserve(this, bin_entries(B, d.n, g) * sizeof(uint32_t) + 16, st))) return s;
     uint32_t* bins = (uint32_t*)w.bins.ptr;
     stage_begin(SWF_STAGE_SCAN, st);
-    launch_bin_hist(w.rec, B, d.n, g, bins, w.cull_dev, st);
-    launch_bin_offsets(B, d.n, g, bins, bin_count(w, key_cap, readback), st);
+    launch_bin_count(w.rec, B, d.n, g, bins, w.cull_dev, bin_count(w, key_cap, readback), st);
     stage_end(st);
     uint64_t nk;
     const uint64_t* n_dev;
@@ -1098,8 +1097,7 @@ swf_status Ctx::enqueue_mixed(Workspace& w, const MixPlan& p, const float* tx, i
             return s;
         uint32_t* bins = (uint32_t*)w.bins.ptr;
         stage_begin(SWF_STAGE_SCAN, st);
-        launch_mix_bin_hist(mb, k.bin_n, k.bin_tiles, w.rec, bins, w.cull_dev, st);
-        launch_mix_bin_offsets(mb, k.bin_n, k.bin_tiles, bins, bin_count(w, k.key_cap, false), st);
+        launch_mix_bin_count(mb, k.bin_n, k.bin_tiles, w.rec, bins, w.cull_dev, bin_count(w, k.key_cap, false), st);
         stage_end(st);
         if ((s = bin_key_count(w, st, k.key_cap, nk, n_dev, false))) return s;
         if ((s = w.vals.reserve(this, nk * 4 + 16, st))) return s;

@@ -379,7 +379,8 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(const K* __rest
 struct BinGeom {
     int N, TW, TH, tiles;  // pairs per query and its tile grid (mixed batches: of the largest query; TW, TH unused)
     int stride;            // tiles per query, rounded up
-    int chunk;             // (query, tile) columns per workgroup of bin_offsets: 64 or 256
+    int chunk;             // (query, tile) columns whose first positions share a base
+    bool whole;            // a block of bin_hist has all of its query's pairs, and writes its offsets as well
     int pb, nbq;           // pairs per block, blocks per query
     int cap;               // most pairs in a placement wave's row list and segment list
 };
@@ -402,6 +403,13 @@ constexpr int kSegCols = 8;       // tiles per column segment of the placement
 // 128 rows and while the columns are few, with 16, whose workgroups of 64 columns are spread over more compute units.
 // us with 4 / 16: 100k pairs at 90 x 360, 1 query (391 rows) 25 / 10, 8 queries (98 rows) 11 / 11; 500k pairs at 360 x
 // 1440, 1 query 29 / 15, 8 (16,896 columns) 20 / 17, 16 22 / 29, 64 121 / 202.
+//
+// A query of one block needs no column prefixes: bin_hist scans its own counts, the query is a chunk, and bin_offsets
+// is not launched. Up to 128 queries, whose blocks count themselves off one by one at the end; us of bin_hist and
+// bin_offsets / of bin_hist alone: 50 pairs of one tile, 1 query 7.8 / 5.2, 64 9.3 / 8.2, 256 10.0 / 13.7, 1024 11.4 /
+// 39.9; 250 pairs of 138 tiles, 1 query 8.9 / 6.2, 64 12.5 / 8.6.
+constexpr int kWholeQueries = 128;
+
 BinGeom bin_geom(int64_t B, int N, int TW, int TH, int tiles) {
     BinGeom b;
     b.N = N;
@@ -413,7 +421,8 @@ BinGeom bin_geom(int64_t B, int N, int TW, int TH, int tiles) {
     while (b.pb > 256 && B * ((N + b.pb - 1) / b.pb) < 512) b.pb /= 2;
     b.nbq = std::max(1, (N + b.pb - 1) / b.pb);
     b.cap = std::min(b.pb, tiles <= 256 ? 640 : 512);
-    b.chunk = b.nbq > 4 * kHeldRows && B * b.stride <= 16384 ? 64 : 256;
+    b.whole = b.nbq == 1 && B <= kWholeQueries;
+    b.chunk = b.whole ? b.stride : b.nbq > 4 * kHeldRows && B * b.stride <= 16384 ? 64 : 256;
     return b;
 }
 
@@ -474,6 +483,57 @@ __device__ __forceinline__ BinQuery bin_query(const BinGeom& G, const MixBatch& 
     return b;
 }
 
+struct BinTotals {
+    unsigned long long* total;  // entries of all lists
+    uint64_t cap;               // 0: the host sizes the lists from the count
+    unsigned long long* n_eff;
+    uint32_t* status;
+    uint32_t* done;             // zero at launch
+    unsigned long long* host;   // pinned host copy of the total, or null
+};
+
+// Chunk `blk`'s total ct (thread 0's) is final. The last of the launch's nblk
+// blocks to get here scans the chunk totals into the chunks' first positions and
+// writes the counts. wsum: 16 words of LDS.
+__device__ __forceinline__ void finish_totals(const BinBufs& bb, unsigned long long ct, int nblk, int blk,
+                                              uint64_t* wsum, const BinTotals& T) {
+    __shared__ int last;
+    const int w = (int)threadIdx.x >> 6, W = (int)blockDim.x >> 6;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&bb.ctot[blk], ct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        last = __hip_atomic_fetch_add(T.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nblk - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    uint64_t base = 0;
+    for (int i0 = 0; i0 < nblk; i0 += (int)blockDim.x) {
+        const int i = i0 + (int)threadIdx.x;
+        const uint64_t x = i < nblk ? __hip_atomic_load(&bb.ctot[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+        const uint64_t ix = wave_inclusive_scan<uint64_t>(x);
+        if (lane_id() == 63) wsum[w] = ix;
+        __syncthreads();
+        uint64_t before = 0, all = 0;
+        for (int k = 0; k < W; ++k) {
+            const uint64_t y = wsum[k];
+            before += k < w ? y : 0ull;
+            all += y;
+        }
+        if (i < nblk) bb.cbase[i] = (uint32_t)(base + before + ix - x);
+        base += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        *T.total = base;
+        if (T.cap) {
+            *T.n_eff = base <= T.cap ? base : 0ull;
+            *T.status = base > T.cap ? 1u : 0u;
+        }
+        if (T.host) __hip_atomic_store(T.host, (unsigned long long)base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // Tile counts of one block of pairs of one query. A rectangle adds one to every
 // tile it covers, which is the two-dimensional running sum of +1 / -1 at its
 // four corners: four LDS atomics per pair (eight for a wrapped rectangle)
@@ -483,12 +543,17 @@ __device__ __forceinline__ BinQuery bin_query(const BinGeom& G, const MixBatch& 
 // pairs at 90 x 360 and 140 us for 0.8M pairs at 180 x 720.
 constexpr int kHistCells = kMaxTiles + 600;  // (TH + 1) (TW + 1) for TH TW <= kMaxTiles and TH, TW <= 512
 
-template <bool kMix>
+// kWhole: the block has all of its query's pairs, so its counts are the query's.
+// It scans them over the tiles (in the cells, 16 per thread at most) into the
+// query's first positions, leaves zero column prefixes, and takes its part in
+// the totals.
+template <bool kMix, bool kWhole>
 __global__ __launch_bounds__(kThreads) void bin_hist_kernel(const uint2* __restrict__ rect,
                                                             const uint32_t* __restrict__ count, BinGeom G,
-                                                            uint32_t* __restrict__ hist,
-                                                            unsigned long long* __restrict__ cull, MixBatch mix) {
+                                                            BinBufs bb, unsigned long long* __restrict__ cull,
+                                                            MixBatch mix, BinTotals T) {
     __shared__ int h[kHistCells];
+    __shared__ uint64_t wsum[16];
     __shared__ uint32_t nculled[2];
     const int j = blockIdx.x, q = blockIdx.y;
     const BinQuery Q = bin_query<kMix>(G, mix, q);
@@ -529,17 +594,50 @@ __global__ __launch_bounds__(kThreads) void bin_hist_kernel(const uint2* __restr
         }
     }
     __syncthreads();
-    uint32_t* row = hist + ((size_t)q * G.nbq + j) * G.stride;
+    uint32_t* row = bb.hist + ((size_t)q * G.nbq + j) * G.stride;
     for (int y = threadIdx.x >> 6; y < Q.TH; y += kWaves) {
         int carry = 0;
         for (int c0 = 0; c0 < Q.TW; c0 += 64) {
             const int c = c0 + (int)lane_id();
             const int v = wave_inclusive_scan<int>(c < Q.TW ? h[y * pitch + c] : 0) + carry;
-            if (c < Q.TW) row[y * Q.TW + c] = (uint32_t)v;
+            if (c < Q.TW) {
+                if constexpr (kWhole)
+                    h[y * pitch + c] = v;
+                else
+                    row[y * Q.TW + c] = (uint32_t)v;
+            }
             carry = __shfl(v, 63, 64);
         }
     }
-    for (int t = Q.tiles + (int)threadIdx.x; t < G.stride; t += kThreads) row[t] = 0u;
+    if constexpr (!kWhole) {
+        for (int t = Q.tiles + (int)threadIdx.x; t < G.stride; t += kThreads) row[t] = 0u;
+        return;
+    }
+    __syncthreads();
+    // thread i takes the tiles from i per on, in row-major order
+    const int per = (G.stride + kThreads - 1) / kThreads, t0 = (int)threadIdx.x * per;
+    const int t1 = min(t0 + per, G.stride);
+    auto cell = [&](int t) { return t < Q.tiles ? (uint32_t)h[t / Q.TW * pitch + t % Q.TW] : 0u; };
+    uint32_t sum = 0;
+    for (int t = t0; t < t1; ++t) sum += cell(t);
+    const uint32_t inc = wave_inclusive_scan<uint32_t>(sum);
+    const int w = (int)threadIdx.x >> 6;
+    if (lane_id() == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t run = inc - sum;
+    unsigned long long all = 0;
+    for (int k = 0; k < kWaves; ++k) {
+        if (k < w) run += (uint32_t)wsum[k];
+        all += wsum[k];
+    }
+    uint32_t* ls = bb.lstart + (size_t)q * G.stride;
+    for (int t = t0; t < t1; ++t) {
+        ls[t] = run;
+        row[t] = 0u;
+        run += cell(t);
+    }
+    __syncthreads();  // wsum is read
+    finish_totals(bb, all, (int)gridDim.y, q, wsum, T);
 }
 
 // Block c: the kChunk columns from kChunk c on of the (query, tile) pairs. Per
@@ -552,21 +650,11 @@ __global__ __launch_bounds__(kThreads) void bin_hist_kernel(const uint2* __restr
 // 0 with the overflow bit of the status word), and the count to the host. One
 // launch; column prefixes, scan and count in five took 27 us per call at any
 // size below 16k tiles.
-struct BinTotals {
-    unsigned long long* total;  // entries of all lists
-    uint64_t cap;               // 0: the host sizes the lists from the count
-    unsigned long long* n_eff;
-    uint32_t* status;
-    uint32_t* done;             // zero at launch
-    unsigned long long* host;   // pinned host copy of the total, or null
-};
-
 template <int kChunk, int kGroups>
 __global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb, BinGeom G, int64_t cols, BinTotals T) {
     __shared__ uint32_t part[kGroups][kChunk];
     __shared__ uint64_t wsum[16];
-    __shared__ int last;
-    constexpr int groups = kGroups, W = kChunk * kGroups / 64;
+    constexpr int groups = kGroups;
     const int col = (int)threadIdx.x & (kChunk - 1), grp = (int)threadIdx.x / kChunk;
     const int w = (int)threadIdx.x >> 6;
     const int64_t e = (int64_t)blockIdx.x * kChunk + col;
@@ -621,42 +709,10 @@ __global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb
         for (int k = 0; k < w; ++k) before += (uint32_t)wsum[k];
         if (in) bb.lstart[e] = before + inc - tot;
     }
-    if (threadIdx.x == 0) {
-        unsigned long long ct = 0;
+    unsigned long long ct = 0;
+    if (threadIdx.x == 0)
         for (int k = 0; k < kChunk / 64; ++k) ct += wsum[k];
-        __hip_atomic_store(&bb.ctot[blockIdx.x], ct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();
-        last = __hip_atomic_fetch_add(T.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    const int nblk = (int)gridDim.x;
-    uint64_t base = 0;
-    for (int i0 = 0; i0 < nblk; i0 += (int)blockDim.x) {
-        const int i = i0 + (int)threadIdx.x;
-        const uint64_t x = i < nblk ? __hip_atomic_load(&bb.ctot[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
-        const uint64_t ix = wave_inclusive_scan<uint64_t>(x);
-        if (lane_id() == 63) wsum[w] = ix;
-        __syncthreads();
-        uint64_t before = 0, all = 0;
-        for (int k = 0; k < W; ++k) {
-            const uint64_t y = wsum[k];
-            before += k < w ? y : 0ull;
-            all += y;
-        }
-        if (i < nblk) bb.cbase[i] = (uint32_t)(base + before + ix - x);
-        base += all;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        *T.total = base;
-        if (T.cap) {
-            *T.n_eff = base <= T.cap ? base : 0ull;
-            *T.status = base > T.cap ? 1u : 0u;
-        }
-        if (T.host) __hip_atomic_store(T.host, (unsigned long long)base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    finish_totals(bb, ct, (int)gridDim.x, (int)blockIdx.x, wsum, T);
 }
 
 // base + the set bits of m below this lane
@@ -972,16 +1028,9 @@ static BinGeom mix_geom(int B, int max_n, int max_tiles) { return bin_geom(B, ma
 size_t bin_entries(int B, int N, const Grid& g) { return bin_words(B, geom_of(B, N, g)); }
 size_t mix_bin_entries(int B, int max_n, int max_tiles) { return bin_words(B, mix_geom(B, max_n, max_tiles)); }
 
-static void hist_launch(const BinGeom& G, int B, const Records& r, uint32_t* bins, unsigned long long* cull,
-                        hipStream_t st, const MixBatch* m) {
-    const BinBufs bb = bin_bufs(bins, B, G);
-    if (m)
-        bin_hist_kernel<true><<<dim3(G.nbq, B), kThreads, 0, st>>>(r.rect, r.count, G, bb.hist, cull, *m);
-    else
-        bin_hist_kernel<false><<<dim3(G.nbq, B), kThreads, 0, st>>>(r.rect, r.count, G, bb.hist, cull, MixBatch{});
-}
-
-static void offsets_launch(const BinGeom& G, int B, uint32_t* bins, const BinCount& c, hipStream_t st) {
+// Tile counts, and the lists' first positions and totals
+static void count_launch(const BinGeom& G, int B, const Records& r, uint32_t* bins, unsigned long long* cull,
+                         const BinCount& c, hipStream_t st, const MixBatch* m) {
     BinTotals t;
     t.total = reinterpret_cast<unsigned long long*>(c.total);
     t.cap = c.cap;
@@ -989,8 +1038,18 @@ static void offsets_launch(const BinGeom& G, int B, uint32_t* bins, const BinCou
     t.status = c.status;
     t.done = c.done;
     t.host = reinterpret_cast<unsigned long long*>(c.host);
-    const unsigned blocks = (unsigned)bin_chunks(B, G);
     const BinBufs bb = bin_bufs(bins, B, G);
+    const dim3 grid(G.nbq, B);
+    if (m && G.whole)
+        bin_hist_kernel<true, true><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bb, cull, *m, t);
+    else if (m)
+        bin_hist_kernel<true, false><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bb, cull, *m, t);
+    else if (G.whole)
+        bin_hist_kernel<false, true><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bb, cull, MixBatch{}, t);
+    else
+        bin_hist_kernel<false, false><<<grid, kThreads, 0, st>>>(r.rect, r.count, G, bb, cull, MixBatch{}, t);
+    if (G.whole) return;
+    const unsigned blocks = (unsigned)bin_chunks(B, G);
     const int64_t cols = (int64_t)B * G.stride;
     if (G.chunk == 64)
         bin_offsets_kernel<64, 16><<<blocks, 1024, 0, st>>>(bb, G, cols, t);
@@ -1021,13 +1080,9 @@ static void place_launch(const BinGeom& G, int B, int TH, bool wrap, const Recor
                                                                    MixBatch{});
 }
 
-void launch_bin_hist(const Records& r, int B, int N, const Grid& g, uint32_t* bins, unsigned long long* cull,
-                     hipStream_t st) {
-    hist_launch(geom_of(B, N, g), B, r, bins, cull, st, nullptr);
-}
-
-void launch_bin_offsets(int B, int N, const Grid& g, uint32_t* bins, const BinCount& c, hipStream_t st) {
-    offsets_launch(geom_of(B, N, g), B, bins, c, st);
+void launch_bin_count(const Records& r, int B, int N, const Grid& g, uint32_t* bins, unsigned long long* cull,
+                      const BinCount& c, hipStream_t st) {
+    count_launch(geom_of(B, N, g), B, r, bins, cull, c, st, nullptr);
 }
 
 void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* bins, const uint64_t* total,
@@ -1037,14 +1092,9 @@ void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* b
 
 bool mix_bin_fits(int B, int max_tiles) { return B <= 65535 && max_tiles <= kMaxTiles; }
 
-void launch_mix_bin_hist(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
-                         unsigned long long* cull, hipStream_t st) {
-    if (m.B > 0) hist_launch(mix_geom(m.B, max_n, max_tiles), m.B, r, bins, cull, st, &m);
-}
-
-void launch_mix_bin_offsets(const MixBatch& m, int max_n, int max_tiles, uint32_t* bins, const BinCount& c,
-                            hipStream_t st) {
-    if (m.B > 0) offsets_launch(mix_geom(m.B, max_n, max_tiles), m.B, bins, c, st);
+void launch_mix_bin_count(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,
+                          unsigned long long* cull, const BinCount& c, hipStream_t st) {
+    if (m.B > 0) count_launch(mix_geom(m.B, max_n, max_tiles), m.B, r, bins, cull, c, st, &m);
 }
 
 void launch_mix_bin_place(const MixBatch& m, int max_n, int max_tiles, const Records& r, uint32_t* bins,

@@ -24,7 +24,7 @@ CASES = [
     (1, 16, 16, 1, 4.0), (50, 16, 16, 3, 4.0), (63, 16, 17, 2, 4.0), (65, 7, 200, 1, 12.0), (256, 33, 130, 2, 12.0),
     (257, 128, 129, 1, 12.0), (1025, 90, 360, 2, 12.0), (700, 90, 360, 600, 6.0), (4097, 180, 720, 1, 20.0),
     (9001, 360, 1440, 2, 60.0), (2049, 4096, 256, 1, 200.0), (3000, 144, 1824, 150, 30.0),
-    (10, 16, 16, 300, 4.0), (9, 30, 50, 130, 9.0), (40_000, 90, 360, 1, 6.0), (33_000, 60, 100, 3, 6.0),
+    (10, 16, 16, 300, 4.0), (5, 16, 16, 128, 4.0), (5, 16, 16, 129, 4.0), (9, 30, 50, 130, 9.0), (40_000, 90, 360, 1, 6.0), (33_000, 60, 100, 3, 6.0),
 ]
 
 
