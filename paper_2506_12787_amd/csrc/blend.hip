@@ -99,13 +99,16 @@ __global__ __launch_bounds__(TILE* TILE) void blend_forward_kernel(const uint2* 
     const float cx = (float)(tx * TILE - bx0) + 0.5f * (float)(TILE - 1);  // tile centre, block-relative
 
     const uint2 rg = ranges[gtile];
-    float T = 1.0f, C = 0.0f;
+    // T runs on past the termination (it only falls further), so that T < kTMin says that the pixel is done and no
+    // entry's alpha waits for the one before it (with a flag in its condition, a chain through the scalar unit per
+    // entry: one query of 100k Gaussians at 90 x 360 35.6 us, now 30.6; 64 of them 199 and 194; bound by vector issue,
+    // 22 instructions per entry and wave). The aux keeps the last T at or above the floor. Pixels outside: done.
+    float T = inside ? 1.0f : 0.0f, C = 0.0f, T_kept = 1.0f;
     uint32_t last = 0;
-    bool done = !inside;
     uint32_t evals = 0, staged = 0, visits = 0;
 
     for (uint32_t start = rg.x; start < rg.y; start += kN) {
-        if (__syncthreads_count(done) == kN) break;
+        if (__syncthreads_count(T < kTMin) == kN) break;
         const uint32_t i = start + threadIdx.x;
         const int cnt = (int)min((uint32_t)kN, rg.y - start);
         if (i < rg.y) {
@@ -152,7 +155,7 @@ __global__ __launch_bounds__(TILE* TILE) void blend_forward_kernel(const uint2* 
             if ((int)lane_id() < kUnroll) idx[nlist + lane_id()] = (uint32_t)kN * 32u;  // padding
             __builtin_amdgcn_wave_barrier();
             for (int j0 = 0; j0 < nlist; j0 += kUnroll) {
-                if (__all(done)) break;
+                if (__all(T < kTMin)) break;
                 if (kVisit) visits += kUnroll;
                 const uint4 ja = *reinterpret_cast<const uint4*>(idx + j0);  // 8 record offsets
                 const uint4 jb = *reinterpret_cast<const uint4*>(idx + j0 + 4);
@@ -168,20 +171,18 @@ __global__ __launch_bounds__(TILE* TILE) void blend_forward_kernel(const uint2* 
                                           : blend_q(fx, fy, make_float2(r0.x, r0.y), m, dx, dy, u, w);
                     const float2 o = make_float2(r0.z, r0.w);
                     const float a = fminf(kAlphaMax, blend_raw_alpha(q, o.x));
-                    const float ae = (!done && q <= kQMax && a >= kAlphaMin) ? a : 0.0f;
+                    const float ae = (q <= kQMax && a >= kAlphaMin) ? a : 0.0f;
                     const float Tn = T * (1.0f - ae);
                     const bool stop = Tn < kTMin;
                     C = stop ? C : fmaf(o.y * ae, T, C);
                     if (kAux) last = (!stop && ae > 0.0f) ? base + (uint32_t)j : last;
-                    // without aux the final T is not kept: a stopped lane may
-                    // take Tn (< the floor), it adds nothing afterwards either way
-                    T = (kAux && stop) ? T : Tn;
-                    done = done || stop;
+                    if (kAux) T_kept = stop ? T_kept : Tn;
+                    T = Tn;
                 }
             }
         } else {
             for (int j0 = 0; j0 < cnt; j0 += kUnroll) {
-                if (__all(done)) break;
+                if (__all(T < kTMin)) break;
 #pragma unroll
                 for (int jj = 0; jj < kUnroll; ++jj) {
                     const int j = j0 + jj;
@@ -190,18 +191,18 @@ __global__ __launch_bounds__(TILE* TILE) void blend_forward_kernel(const uint2* 
                     const float q = kWrap ? blend_q_wrap(fx, fy, make_float2(r0.x, r0.y), s_rec[2 * j + 1], Wf, rw,
                                                          dx, dy, u, w)
                                           : blend_q(fx, fy, make_float2(r0.x, r0.y), s_rec[2 * j + 1], dx, dy, u, w);
-                    if (kCount) evals += (!done && j < cnt && q <= kQMax) ? 1u : 0u;
+                    if (kCount) evals += (T >= kTMin && j < cnt && q <= kQMax) ? 1u : 0u;
                     const float2 o = make_float2(r0.z, r0.w);
                     const float a = fminf(kAlphaMax, blend_raw_alpha(q, o.x));
-                    // a skipped entry (cutoff, alpha floor, or a finished pixel) acts
-                    // with alpha 0: T * (1 - 0) and C + 0 * T are exact no-ops
-                    const float ae = (!done && q <= kQMax && a >= kAlphaMin) ? a : 0.0f;
+                    // a skipped entry (cutoff or alpha floor) acts with alpha 0: T * (1 - 0) and C + 0 * T are exact
+                    // no-ops; a finished pixel stops again
+                    const float ae = (q <= kQMax && a >= kAlphaMin) ? a : 0.0f;
                     const float Tn = T * (1.0f - ae);
-                    const bool stop = Tn < kTMin;  // only reachable through ae > 0
+                    const bool stop = Tn < kTMin;
                     C = stop ? C : fmaf(o.y * ae, T, C);
                     if (kAux) last = (!stop && ae > 0.0f) ? base + (uint32_t)j : last;
-                    T = stop ? T : Tn;
-                    done = done || stop;
+                    if (kAux) T_kept = stop ? T_kept : Tn;
+                    T = Tn;
                 }
             }
         }
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(TILE* TILE) void blend_forward_kernel(const uint2* 
         const size_t pix = (size_t)b * H * W + (size_t)py * W + px;
         out[pix] = C;
         if (kAux) {
-            aux_T[pix] = T;
+            aux_T[pix] = T_kept;
             aux_last[pix] = last;
         }
     }
