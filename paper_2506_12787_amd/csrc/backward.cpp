@@ -171,9 +171,9 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
     const float* auxT = (const float*)aux;
     const uint32_t* auxL = (const uint32_t*)((const char*)aux + sizeof(float) * npix);
     // 2. blend backward -> per-pair gradients of (mean, M, opacity, amp)
-    if ((s = w.dpair.reserve(this, (size_t)P * 8 * sizeof(double) + 16, st))) return s;
+    if ((s = w.dpair.reserve(this, (size_t)P * 8 * sizeof(float) + 16, st))) return s;
     if ((s = w.dbase.reserve(this, (size_t)P * kOut * sizeof(float) + 16, st))) return s;
-    if ((s = hip(hipMemsetAsync(w.dpair.ptr, 0, (size_t)P * 8 * sizeof(double), st), "memset dpair"))) return s;
+    if ((s = hip(hipMemsetAsync(w.dpair.ptr, 0, (size_t)P * 8 * sizeof(float), st), "memset dpair"))) return s;
     stage_begin(SWF_STAGE_BWD_BLEND, st);
     float* det_part = nullptr;
     const uint32_t* det_off = nullptr;
@@ -196,7 +196,7 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
         det_off = (const uint32_t*)w.off.ptr;
     }
     launch_blend_backward((const uint2*)w.ranges.ptr, w.last.vals, w.rec, B, w.last.grid, grad_out, auxT, auxL,
-                          (double*)w.dpair.ptr, st, det_part, d.n, det_off);
+                          (float*)w.dpair.ptr, st, det_part, d.n, det_off);
     stage_end(st);
     // 3. preprocess backward -> residual-coordinate gradients
     float* dy = nullptr;
@@ -206,7 +206,7 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
         if ((s = w.groups.reserve(this, row_group_words(P) * sizeof(uint32_t), st))) return s;
     }
     stage_begin(SWF_STAGE_BWD_PREPROCESS, st);
-    launch_preprocess_backward((const double*)w.dpair.ptr, w.rec, P, (flags & SWF_PAPER_DEFORM) != 0,
+    launch_preprocess_backward((const float*)w.dpair.ptr, w.rec, P, (flags & SWF_PAPER_DEFORM) != 0,
                                (float*)w.dbase.ptr, dy, (uint32_t*)w.groups.ptr, st);
     stage_end(st);
     // 4. MLP backward (the forward's activations; BF16 operands after a BF16 forward)

@@ -34,45 +34,57 @@ __device__ __forceinline__ float dpp(float old, float v) {
         __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), kCtrl, 0xf, kBank, kBank == 0xf));
 }
 
-// Wave sums of 8 values at once: three halving exchanges leave each lane one
-// value summed over 8 lanes, three more sums finish it. All in registers (lane
-// swaps and DPP; every lane of the wave is active): as shuffles through LDS, ten
-// in a row, they were a quarter of the blend backward's time. Lane l returns the
-// total of value l / 8.
+// Wave sums of 8 values at once: halving exchanges with lanes l ^ 1, l ^ 2 and
+// l ^ 4 leave each lane one value summed over 8 lanes, sums with l ^ 8, l ^ 16 and
+// l ^ 32 finish it. All in registers (DPP and lane swaps; every lane of the wave is
+// active): as shuffles through LDS, ten in a row, they were a quarter of the blend
+// backward's time. (Halving with l ^ 32, 16 and 8 first takes a third fewer
+// instructions, but adds in another order: a gradient that is rounded to BF16
+// further on then falls the other way here and there.) Lane l < 8 returns the total
+// of value index 4 (l & 1) + 2 ((l >> 1) & 1) + ((l >> 2) & 1).
 __device__ __forceinline__ float wave_sum8(float (&a)[8]) {
+    const unsigned l = lane_id();
+    {
+        const bool hi = l & 1u;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {  // lanes l and l + 32
-        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[k]), __float_as_uint(a[k + 4]), false, false);
-        a[k] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        for (int k = 0; k < 4; ++k) {
+            const float send = hi ? a[k] : a[k + 4], keep = hi ? a[k + 4] : a[k];
+            a[k] = keep + dpp<0xb1, 0xf>(0.f, send);  // quad_perm 1,0,3,2
+        }
     }
+    {
+        const bool hi = l & 2u;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {  // l and l ^ 16
-        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[k]), __float_as_uint(a[k + 2]), false, false);
-        a[k] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        for (int k = 0; k < 2; ++k) {
+            const float send = hi ? a[k] : a[k + 2], keep = hi ? a[k + 2] : a[k];
+            a[k] = keep + dpp<0x4e, 0xf>(0.f, send);  // quad_perm 2,3,0,1
+        }
     }
-    // l and l ^ 8 (row_ror:8): banks 0, 1 of a row keep a[0], banks 2, 3 a[1]
-    const float send = dpp<0x128, 0xc>(dpp<0x128, 0x3>(a[0], a[0]), a[1]);
-    float v = ((lane_id() & 8u) ? a[1] : a[0]) + send;
-    v += dpp<0xb1, 0xf>(0.f, v);   // quad_perm 1,0,3,2
-    v += dpp<0x4e, 0xf>(0.f, v);   // quad_perm 2,3,0,1
-    v += dpp<0x141, 0xf>(0.f, v);  // row_half_mirror: the other quad
-    return v;
+    float v;
+    {
+        const bool hi = l & 4u;
+        const float send = hi ? a[0] : a[1], keep = hi ? a[1] : a[0];
+        // row_shl:4 into banks 0 and 2, row_shr:4 into 1 and 3
+        v = keep + dpp<0x114, 0xa>(dpp<0x104, 0x5>(send, send), send);
+    }
+    v += dpp<0x128, 0xf>(0.f, v);  // row_ror:8
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
 // With 16x16 tiles each wave (an 8x8 quadrant) walks only the entries that can
 // reach the cutoff on its rectangle (the forward kernel's culling): the others
 // leave every one of its pixels unchanged.
 // Bound by vector issue (80 % of the time): per entry and wave about 22
-// instructions to find that no pixel takes it, 56 more if one does. Hence the
-// sums of du and dw instead of the mean gradient's two products, one reciprocal
-// per pixel, indices broadcast from a register. 50k Gaussians, 16 positions of
-// 90 x 360, 1.5M entries evaluated: 208 us (346 with LDS shuffles, three
-// divisions and nested branches).
+// instructions to find that no pixel takes it, 80 more if one does. Hence one
+// reciprocal for a pixel's two quotients, the opacity's taken when the entry is
+// staged, and indices broadcast from a register. 50k Gaussians, 16 positions of
+// 90 x 360, 1.5M entries evaluated: 233 us (346 with LDS shuffles, three
+// divisions and nested branches; every wave's sums are the same bit for bit).
 // kWrap: periodic azimuth, as in the forward kernel (same staged image, same
 // displacement, same culling exemption), so that every decision replays exactly.
-// The per-pair sums over tiles and waves are FP64 atomics, whose order shows only
-// below the last bit of their FP32 values: with FP32 ones a BF16 gradient that
-// is rounded from them could fall either way from run to run.
 // kDet: instead of adding into dpair, each wave writes its 8 sums of an entry
 // to part[slot * 32 + wave * 8 + k] (zeroed beforehand), slot = the pair's
 // first slot (det_off: the exclusive scan of the key counts) + the tile's
@@ -83,13 +95,13 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals, const float4* __restrict__ geo,
     const float4* __restrict__ wm, const float2* __restrict__ oa, int H, int W, int TW, int tiles,
     const float* __restrict__ grad_out, const float* __restrict__ aux_T, const uint32_t* __restrict__ aux_last,
-    double* __restrict__ dpair, float* __restrict__ part = nullptr, const uint2* __restrict__ rect = nullptr, const uint32_t* __restrict__ det_off = nullptr) {
+    float* __restrict__ dpair, float* __restrict__ part = nullptr, const uint2* __restrict__ rect = nullptr, const uint32_t* __restrict__ det_off = nullptr) {
     constexpr int kN = TILE * TILE;
     constexpr bool kCull = TILE == 16;
     constexpr int kWaves = kN / 64;
     __shared__ float2 s_pos[kN];
     __shared__ float4 s_wm[kN];
-    __shared__ float2 s_oa[kN];
+    __shared__ float4 s_oa[kN];  // opacity, amplitude, 1 / opacity
     __shared__ uint32_t s_v[kN];
     __shared__ uint32_t s_slot[kDet ? kN : 1];
     __shared__ uint8_t s_strip[kCull ? kN : 1];
@@ -134,8 +146,7 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
     // Straight-line, one pixel per lane: a pixel that the entry leaves unchanged selects zeros (of the displacement's
     // image too, so that an overflow there stays its own).
     auto entry = [&](int beg, int jj) {
-        const float4 m = s_wm[jj];
-        const float2 o = s_oa[jj];
+        const float4 m = s_wm[jj], o = s_oa[jj];  // o: opacity, amplitude, 1 / opacity
         float dx, dy, u, w;
         const float q = kWrap ? blend_q_wrap(fx, fy, s_pos[jj], m, Wf, rw, dx, dy, u, w)
                               : blend_q(fx, fy, s_pos[jj], m, dx, dy, u, w);
@@ -145,18 +156,21 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
         if (__ballot(contrib) == 0ull) return;
         float gv[8];
         {
-            // om is in [0.01, 1] where it counts: one refined reciprocal serves both quotients
+            // Quotients by om (in [0.01, 1] where it counts) and the opacity: a product with the refined reciprocal and
+            // one correction, which rounds as the division does
             const float om = 1.0f - a, r0 = __builtin_amdgcn_rcpf(om), r = fmaf(fmaf(-om, r0, 1.0f), r0, r0);
             const float Tq = T * r, Tb = fmaf(fmaf(-om, Tq, T), r, Tq);  // T / om
-            const float dC_da = fmaf(o.y, T, -S) * r;
+            const float Sq = S * r, So = __builtin_amdgcn_div_fixupf(fmaf(fmaf(-om, Sq, S), r, Sq), om, S);  // S / om
+            const float dC_da = o.y * Tb - So;
             gv[7] = contrib ? G * a * Tb : 0.f;
             const bool moves = contrib && !(raw > kAlphaMax);
             const float ga = G * dC_da;
-            gv[6] = moves ? ga * e : 0.f;    // d alpha / d opacity = exp(-q/2)
-            const float dq = -(o.x * gv[6]);  // twice d alpha / d q = -alpha / 2
+            const float eq = raw * o.z, ro = fmaf(fmaf(-o.x, eq, raw), o.z, eq);  // raw / opacity = exp(-q/2)
+            gv[6] = moves ? ga * ro : 0.f;           // d alpha / d opacity
+            const float dq = moves ? -ga * a : 0.f;  // twice d alpha / d q = -alpha / 2
             const float du = dq * (moves ? u : 0.f), dw = dq * (moves ? w : 0.f);
-            gv[0] = du;
-            gv[1] = dw;
+            gv[0] = -(du * m.x + dw * m.z);
+            gv[1] = -(du * m.y + dw * m.w);
             gv[2] = du * dx;
             gv[3] = du * dy;
             gv[4] = dw * dx;
@@ -165,12 +179,13 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
             T = contrib ? Tb : T;
         }
         const float v = wave_sum8(gv);
-        const int l = (int)lane_id(), k = l >> 3;
-        if ((l & 7) == 0 && v != 0.0f) {
+        const unsigned l = lane_id();
+        if (l < 8u && v != 0.0f) {
+            const int k = 4 * (int)(l & 1u) + 2 * (int)((l >> 1) & 1u) + (int)((l >> 2) & 1u);
             if constexpr (kDet)
                 part[(size_t)s_slot[jj] * 32 + (size_t)wq * 8 + k] = v;
             else
-                atomicAdd(dpair + (size_t)s_v[jj] * 8 + k, (double)v);
+                atomicAdd(dpair + (size_t)s_v[jj] * 8 + k, v);
         }
     };
 
@@ -187,7 +202,8 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
                 const float4 m = wm[v];
                 s_pos[threadIdx.x] = pos;
                 s_wm[threadIdx.x] = m;
-                s_oa[threadIdx.x] = oa[v];
+                const float2 o = oa[v];
+                s_oa[threadIdx.x] = make_float4(o.x, o.y, 1.0f / o.x, 0.0f);
                 s_v[threadIdx.x] = v;
                 if constexpr (kDet) {  // this tile's slot of the pair: row-major in its (possibly wrapped) rectangle
                     const uint2 rr = rect[v];
@@ -234,7 +250,7 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
 // on), the four waves' sums of its entry in that tile's list, found by binary
 // search (a list holds its pairs in increasing order).
 __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint32_t* __restrict__ det_off,
-                                  const float* __restrict__ part, int64_t P, double* __restrict__ dpair) {
+                                  const float* __restrict__ part, int64_t P, float* __restrict__ dpair) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P) return;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -257,8 +273,7 @@ __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint
     for (int k = 0; k < 8; ++k) dpair[i * 8 + k] = acc[k];
 }
 
-// Sums over the pixels of (du, dw, du dx, du dy, dw dx, dw dy, d opacity, d amp)
-// -> d(residual coordinates) through the pair's M; the unmasked result
+// d(mean, M, opacity, amp) -> d(residual coordinates); the unmasked result
 // feeds the base parameters, the masked one (paper mode zeroes 2..4) the MLP.
 //
 // With dy also which rows (pairs) have a gradient at all: bits[w] bit k is set
@@ -268,7 +283,7 @@ __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint
 // behind the pixels' termination depth or outside every pixel's cutoff have
 // none: at N = 50k, 90 x 360, five of six.
 __global__ __launch_bounds__(256) void preprocess_backward_kernel(
-    const double* __restrict__ dpair, const float4* __restrict__ wm, const float2* __restrict__ oa,
+    const float* __restrict__ dpair, const float4* __restrict__ wm, const float2* __restrict__ oa,
     const uint32_t* __restrict__ count, const uint2* __restrict__ rect, int64_t P, int paper_mask,
     float* __restrict__ dbase, float* __restrict__ dy, uint32_t* __restrict__ bits, uint32_t* __restrict__ groups) {
     __shared__ uint32_t s_n;
@@ -278,13 +293,11 @@ __global__ __launch_bounds__(256) void preprocess_backward_kernel(
     bool live = false;
     if (in && count[i] == 0) live = rect[i].y == kCullNonFinite;
     if (in && count[i]) {
-        float g[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) g[k] = (float)dpair[i * 8 + k];
+        const float* g = dpair + i * 8;
         const float4 m = wm[i];
         const float op = oa[i].x;
-        r[0] = -(g[0] * m.x + g[1] * m.z);
-        r[1] = -(g[0] * m.y + g[1] * m.w);
+        r[0] = g[0];
+        r[1] = g[1];
         r[2] = -(g[2] * m.x + g[3] * m.y);
         r[3] = -(g[4] * m.z + g[5] * m.w);
         r[4] = -g[2] * m.y + g[3] * m.x - g[4] * m.w + g[5] * m.z;
@@ -1321,7 +1334,7 @@ __global__ __launch_bounds__(256, 2) void mean_grad_kernel(const float* __restri
 }  // namespace
 
 void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,
-                           const float* grad_out, const float* aux_T, const uint32_t* aux_last, double* dpair,
+                           const float* grad_out, const float* aux_T, const uint32_t* aux_last, float* dpair,
                            hipStream_t st, float* det_part, int N, const uint32_t* det_off) {
     const unsigned blocks = (unsigned)(B * g.tiles);
     if (!blocks) return;
@@ -1364,7 +1377,7 @@ RowGroups row_groups(uint32_t* buf, int64_t P) {
     return g;
 }
 
-void launch_preprocess_backward(const double* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
+void launch_preprocess_backward(const float* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
                                 float* dy, uint32_t* group_buf, hipStream_t st) {
     if (P <= 0) {
         if (dy) launch_clear_u32(group_buf, 1, st);

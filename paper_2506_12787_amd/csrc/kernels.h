@@ -255,7 +255,7 @@ void launch_bin_place(const Records& r, int B, int N, const Grid& g, uint32_t* b
 // det_part (may be null): per (list entry, wave) sums, 32 floats per entry of the lists, zeroed by the caller;
 // with it the per-pair sums in dpair are taken in a fixed order (N: Gaussians per query)
 void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Records& r, int B, const Grid& g,
-                           const float* grad_out, const float* aux_T, const uint32_t* aux_last, double* dpair,
+                           const float* grad_out, const float* aux_T, const uint32_t* aux_last, float* dpair,
                            hipStream_t st, float* det_part = nullptr, int N = 0, const uint32_t* det_off = nullptr);
 // Rows of 256 features of the MLP backward (activations, gradients of pre-activations) lie in the MFMA kernels' own
 // order. BF16: tile of 16 rows, 32-feature chunk c, lane 16 g + row % 16, then the lane's 8 values: features
@@ -286,7 +286,7 @@ struct RowGroups {
 size_t row_group_words(int64_t P);                  // uint32 words of the buffer below
 RowGroups row_groups(uint32_t* buf, int64_t P);
 // with dy: also the row groups, into group_buf
-void launch_preprocess_backward(const double* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
+void launch_preprocess_backward(const float* dpair, const Records& r, int64_t P, bool paper_mask, float* dbase,
                                 float* dy, uint32_t* group_buf, hipStream_t st);
 struct BaseGrads {  // destinations of the 7 base-parameter gradients (device; NULL skips one)
     float* p[7];
