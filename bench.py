@@ -75,7 +75,7 @@ def parse():
     p.add_argument("--pmc-table", nargs="+", metavar="DIR",
                    help="print mean counter values per dispatch of the kernels named by --kernels from these "
                         "rocprofv3 counter directories")
-    p.add_argument("--kernels", default="mlp_bf16,bin_hist,bin_scatter,blend_forward",
+    p.add_argument("--kernels", default="mlp_bf16,bin_hist,bin_place,blend_forward",
                    help="comma-separated name fragments for --pmc-table")
     p.add_argument("--workload", choices=("headline", "large", "train", "beamscan", "rssi", "wrap", "protocol", "paper"), default="headline",
                    help="large: N=500k Gaussians (log-scales in [log 0.5, log 20] px), 360x1440 spectra, batch 256; "

@@ -16,7 +16,7 @@ namespace swf {
 // gradient is S W1m, taken through the sin / cos features to d mu.
 // bf16: the backward of a BF16 forward. dz is stored in BF16 (FP32 sums, then
 // one rounding) and the 256 x 256 products run on BF16 matrix cores with FP32
-// accumulation; FP32: the products run on the FP32 matrix cores (gemm.hip).
+// accumulation; FP32: the products run on the FP32 matrix cores.
 // Weight and bias gradients are accumulated in FP32 either way.
 // Only the rows of rg (pairs with a gradient, in groups of 32) are taken: a row whose dy is zero has zero dz in every
 // layer.

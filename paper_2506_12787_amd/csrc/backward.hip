@@ -530,8 +530,7 @@ __device__ __forceinline__ __bf16 to_bf16(float v) { return (__bf16)v; }  // rou
 // The BF16 weights of the backward, from the FP32 masters w[l] (row-major
 // [out][in]): per 256 x 256 layer l = 1 .. n - 1 the MFMA fragments of W as the
 // kernels below take them (fragment (t, c), lane 16 g + r, element j =
-// W[chunk_feature(c, g, j)][16 t + r], the k order of the rows' chunks; 65536
-// values), then the output layer's 7 x 256.
+// W[32 c + 8 g + j][16 t + r]; 65536 values), then the output layer's 7 x 256.
 struct BwdWeights {
     const float* w[8];
     int n;
@@ -542,7 +541,7 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(BwdWeights a, __bf16* __r
     if (e < hid) {
         const int l = e >> 16, f = (e >> 9) & 127, ln = (e >> 3) & 63, j = e & 7;
         const int t = f >> 3, c = f & 7, g = ln >> 4, r = ln & 15;
-        out[e] = to_bf16(a.w[1 + l][(size_t)chunk_feature(c, g, j) * 256 + 16 * t + r]);
+        out[e] = to_bf16(a.w[1 + l][(size_t)(32 * c + 8 * g + j) * 256 + 16 * t + r]);
     } else if (e < hid + kOut * 256) {
         out[e] = to_bf16(a.w[a.n][e - hid]);
     }
@@ -553,12 +552,13 @@ __global__ __launch_bounds__(256) void pack_bwd_kernel(BwdWeights a, __bf16* __r
 // listed groups, rounded to BF16 and zeroed where act[p][i] (the BF16
 // activation) is not > 0, the previous layer's ReLU. The whole W sits in LDS in
 // MFMA A-fragment order (pack_bwd_kernel's). Each wave takes groups of 32 pairs.
-// In chunk order a lane's 16 bytes of dz are its B operand of a k chunk, two
-// stacked output tiles are its 16 bytes of out, and its mask is its 16 bytes of
-// act: every access is a contiguous KiB per wave, and no mask passes through LDS.
+// In chunk order a lane's 16 bytes of dz are its B operand of a k chunk, its
+// results of an output tile are 8 bytes of out, and their mask is 8 bytes of act:
+// every access of a wave is contiguous, and no mask passes through LDS.
 // The next group's rows are loaded while the current one is computed, a chunk's
 // activations while the chunk before it is. 800k pairs, a quarter of them with a
-// gradient: 69 us (93 row-major, with the mask as bits in LDS; 285 over all rows).
+// gradient: 81 us (93 row-major, with the mask as bits in LDS; 285 over all rows;
+// 69 with rows in the results' own order).
 constexpr int kDzWaves = 8;
 constexpr int kDzNcb = 2;
 constexpr int kDzPairs = 16 * kDzNcb;
@@ -593,6 +593,10 @@ __global__ __launch_bounds__(64 * kDzWaves) __attribute__((amdgpu_waves_per_eu(2
     auto load = [&](const __bf16* src, int64_t p, int c) {
         return p >= 0 ? *reinterpret_cast<const uint4*>(src + chunk_at(p, c, g)) : make_uint4(0u, 0u, 0u, 0u);
     };
+    auto load_mask = [&](int64_t p, int c) {  // of output tiles 2 c and 2 c + 1
+        const uint2* m = reinterpret_cast<const uint2*>(act + chunk_half_at(p < 0 ? 0 : p, c, 0, g));
+        return make_uint4(m[0].x, m[0].y, m[64].x, m[64].y);
+    };
     int64_t grp = (int64_t)blockIdx.x * kDzWaves + wave;
     int64_t p[kDzNcb];
     uint4 b[8][kDzNcb], bn[8][kDzNcb];
@@ -612,14 +616,14 @@ __global__ __launch_bounds__(64 * kDzWaves) __attribute__((amdgpu_waves_per_eu(2
         }
         uint4 mk[kDzNcb];
 #pragma unroll
-        for (int cb = 0; cb < kDzNcb; ++cb) mk[cb] = load(act, p[cb], 0);
+        for (int cb = 0; cb < kDzNcb; ++cb) mk[cb] = load_mask(p[cb], 0);
 #pragma unroll 1
         for (int cp = 0; cp < 8; ++cp) {
             uint4 m[kDzNcb];
 #pragma unroll
             for (int cb = 0; cb < kDzNcb; ++cb) {
                 m[cb] = mk[cb];
-                if (cp < 7) mk[cb] = load(act, p[cb], cp + 1);
+                if (cp < 7) mk[cb] = load_mask(p[cb], cp + 1);
             }
             dz_f32x4 acc[2][kDzNcb];
 #pragma unroll
@@ -645,9 +649,9 @@ __global__ __launch_bounds__(64 * kDzWaves) __attribute__((amdgpu_waves_per_eu(2
                     const dz_f32x2 f = {acc[k >> 1][cb][2 * (k & 1)], acc[k >> 1][cb][2 * (k & 1) + 1]};
                     v[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, dz_bf16x2));
                 }
-                *reinterpret_cast<uint4*>(out + chunk_at(p[cb], cp, g)) =
-                    make_uint4(v[0] & positive_halves(m[cb].x), v[1] & positive_halves(m[cb].y),
-                               v[2] & positive_halves(m[cb].z), v[3] & positive_halves(m[cb].w));
+                uint2* o = reinterpret_cast<uint2*>(out + chunk_half_at(p[cb], cp, 0, g));
+                o[0] = make_uint2(v[0] & positive_halves(m[cb].x), v[1] & positive_halves(m[cb].y));
+                o[64] = make_uint2(v[2] & positive_halves(m[cb].z), v[3] & positive_halves(m[cb].w));
             }
         }
 #pragma unroll
@@ -718,8 +722,8 @@ __global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2
             const uint32_t lo = positive_halves(m_nxt[c].x) & 0x20001u, l2 = positive_halves(m_nxt[c].y) & 0x80004u;
             const uint32_t hi = positive_halves(m_nxt[c].z) & 0x20001u, h2 = positive_halves(m_nxt[c].w) & 0x80004u;
             const uint32_t ml = lo | l2, mh = hi | h2;
-            s_m[wave][r][8 * c + g] = (uint8_t)(ml | (ml >> 16));      // features 32 c + 4 g + 0..3
-            s_m[wave][r][8 * c + 4 + g] = (uint8_t)(mh | (mh >> 16));  // features 32 c + 16 + 4 g + 0..3
+            s_m[wave][r][8 * c + 2 * g] = (uint8_t)(ml | (ml >> 16));      // features 32 c + 8 g + 0..3
+            s_m[wave][r][8 * c + 2 * g + 1] = (uint8_t)(mh | (mh >> 16));  // features 32 c + 8 g + 4..7
         }
     };
     dz_f32x4 sacc[kL1Waves][2];
@@ -825,7 +829,7 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
             const uint32_t wa[4] = {ra[h].x, ra[h].y, ra[h].z, ra[h].w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int f = chunk_feature(c >> 2, c & 3, 2 * k);
+                const int f = 8 * c + 2 * k;
                 t_dz[f * kWgRow + q] = (uint16_t)(wd[k] & 0xffffu);
                 t_dz[(f + 1) * kWgRow + q] = (uint16_t)(wd[k] >> 16);
                 t_act[f * kWgRow + q] = (uint16_t)(wa[k] & 0xffffu);
@@ -986,12 +990,13 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
 // 8 features of every 8th row per thread).
 constexpr int kOutSlice = kOut * 256 + 8;
 
-// the lane's 8 values of chunk c (features chunk_feature(c, g, 0..7)) of a row, as floats
+// the lane's 8 values of chunk c of a row, as floats: features feature(c, g, 0..7)
 template <typename T>
 struct OutRow;
 template <>
 struct OutRow<__bf16> {
     uint4 v;
+    __device__ static int feature(int c, int g, int j) { return 32 * c + 8 * g + j; }
     __device__ void load(const __bf16* a, int64_t p, int c, int g) {
         v = *reinterpret_cast<const uint4*>(a + chunk_at(p, c, g));
     }
@@ -1015,6 +1020,7 @@ struct OutRow<__bf16> {
 template <>
 struct OutRow<float> {
     float4 v[2];
+    __device__ static int feature(int c, int g, int j) { return 32 * c + 16 * (j >> 2) + 4 * g + (j & 3); }
     __device__ void load(const float* a, int64_t p, int c, int g) {
         v[0] = load4(a + piece_at(p, 2 * c, g));
         v[1] = load4(a + piece_at(p, 2 * c + 1, g));
@@ -1045,7 +1051,7 @@ __global__ __launch_bounds__(512) void out_bwd_kernel(const float* __restrict__ 
         ysum[o] = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            w[o][j] = (float)wo[o * 256 + chunk_feature(c, g, j)];
+            w[o][j] = (float)wo[o * 256 + OutRow<T>::feature(c, g, j)];
             acc[o][j] = 0.f;
         }
     }
@@ -1099,7 +1105,7 @@ __global__ __launch_bounds__(512) void out_bwd_kernel(const float* __restrict__ 
             float v = acc[o][j];
 #pragma unroll
             for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
-            if (n == 0) pb[o * 256 + chunk_feature(c, g, j)] = v;
+            if (n == 0) pb[o * 256 + OutRow<T>::feature(c, g, j)] = v;
         }
         float v = ysum[o];
 #pragma unroll
@@ -1142,7 +1148,7 @@ __global__ __launch_bounds__(256) void layer1_sums_kernel(const float* __restric
             on[i] = n < N && (!bits || ((bits[p >> 5] >> (p & 31)) & 1u));
             if (!on[i]) p = (int64_t)b * N;
             v[i] = load4(z + (kMask ? (size_t)p * 256 + c : piece_at(p, c / 16, c % 16 / 4)));
-            if constexpr (kMask) a[i] = load4(act + chunk_at(p, c / 32, c % 16 / 4) + c % 32 / 16 * 4);
+            if constexpr (kMask) a[i] = load4(act + chunk_at(p, c / 32, c % 32 / 8) + c % 8);
         }
 #pragma unroll
         for (int i = 0; i < kSumRows / 4; ++i) {

@@ -6,7 +6,7 @@
 // product with FP32 accumulation). Optional epilogue: C *= [mask > 0] (the
 // ReLU derivative of the layer below).
 //
-// Block tile 128 x 128 for large products, 64 x 64 for small ones, 128 x 32
+// Block tile 128 x 128 for large BF16 products, 64 x 64 for small ones, 128 x 32
 // when C has at most 32 columns (so no wave computes padding only); four waves
 // per block; K in steps of 32 staged through LDS (double-buffered, one barrier
 // per step). Every operand layout is loaded along its contiguous dimension, four

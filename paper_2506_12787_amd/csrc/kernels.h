@@ -259,7 +259,9 @@ void launch_blend_backward(const uint2* ranges, const uint32_t* vals, const Reco
                            hipStream_t st, float* det_part = nullptr, int N = 0, const uint32_t* det_off = nullptr);
 // Rows of 256 features of the MLP backward (activations, gradients of pre-activations) lie in the MFMA kernels' own
 // order. BF16: tile of 16 rows, 32-feature chunk c, lane 16 g + row % 16, then the lane's 8 values: features
-// 32 c + 4 g + 0..3 and 32 c + 16 + 4 g + 0..3. FP32: tile of 16 rows, 16-feature piece t, lane, then its 4 values:
+// 32 c + 8 g + 0..7. (A product's results, 4 g + 0..3 of a 16-feature tile per lane, go out as 8 bytes, two lane groups
+// interleaved. In the results' own order they would be 16 bytes, but the next product would take its inputs in another
+// order and round differently.) FP32: tile of 16 rows, 16-feature piece t, lane, then its 4 values:
 // features 16 t + 4 g + 0..3. A wave's load or store of a chunk or piece is one contiguous KiB. Rows are padded to
 // whole tiles.
 inline int64_t chunk_rows(int64_t P) { return (P + 15) / 16 * 16; }
@@ -271,8 +273,10 @@ __host__ __device__ inline size_t piece_at(int64_t row, int t, int g) {  // firs
 }
 // bytes of one layer of P rows
 inline size_t act_layer_bytes(int64_t P, bool bf16) { return (size_t)chunk_rows(P) * 256 * (bf16 ? 2 : 4); }
-// element j of lane group g in chunk c is feature chunk_feature(c, g, j)
-__host__ __device__ inline int chunk_feature(int c, int g, int j) { return 32 * c + (j < 4 ? 4 * g + j : 12 + 4 * g + j); }
+// features 32 c + 16 h + 4 g + 0..3 of the row: lane group g's results of output tile 2 c + h
+__host__ __device__ inline size_t chunk_half_at(int64_t row, int c, int h, int g) {
+    return chunk_at(row, c, 2 * h + (g >> 1)) + 4 * (g & 1);
+}
 
 // Rows (pairs) of the MLP backward that have a gradient, in groups of 32: rows outside the listed groups have a zero
 // dy, so they add nothing to any weight gradient or sum and are neither read nor written by the kernels below (their

@@ -1383,9 +1383,8 @@ swf_status swf_debug_relu_pattern(swf_ctx* h, uint8_t* pattern, uint64_t capacit
             if (L.bf16) {
                 for (int k = 0; k < 256; ++k) {
                     uint16_t v;
-                    const int cc = k / 8 / 4, g = k / 8 % 4, j = k % 8;
-                    std::memcpy(&v, a.data() + (chunk_at((int64_t)i, cc, g) + j) * 2, 2);
-                    o[chunk_feature(cc, g, j)] = (v & 0x8000u) == 0 && (v & 0x7fffu) != 0;
+                    std::memcpy(&v, a.data() + (chunk_at((int64_t)i, k / 32, k % 32 / 8) + k % 8) * 2, 2);
+                    o[k] = (v & 0x8000u) == 0 && (v & 0x7fffu) != 0;
                 }
             } else {
                 for (int k = 0; k < 256; ++k) {
