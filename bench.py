@@ -477,7 +477,7 @@ def bench_large(a):
         "stage_rooflines": {
             "lists": {"bound": "hbm", "achieved": list_bytes / (list_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                       "unit": "GB/s", "frac": list_bytes / (list_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                      "algorithmic_bytes": list_bytes, "ms": list_ms, "list_entries": keys, "segments": segs,
+                      "algorithmic_bytes": list_bytes, "ms": list_ms, "list_entries": keys,
                       "note": "binning: rect+count read twice (24 B/pair), 4 B/list entry written, histogram scan "
                               "12 B/entry, ranges 8 B/tile"},
             "blend": {"bound": "alu", "evaluations": work["evaluations"], "ops_per_evaluation": BLEND_OPS_PER_EVAL,
