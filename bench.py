@@ -625,7 +625,9 @@ def bench_train(a):
                               "frac": None if ach is None else ach / PEAK["bf16"], "flop_per_step": bwd_flop},
                      "note": "5,148 B per pair: the rows the backward must read and write once each (BF16); the "
                              "kernels read each layer's gradient and activations twice (weight and input gradient "
-                             "in separate passes), 7,220 B per pair"},
+                             "in separate passes), 7,220 B per pair. Counted over every pair; rows without a gradient "
+                             "(about three quarters here) are passed by, so the rates are those of the dense work, "
+                             "not of bytes or products executed"},
         "backward_reused_forward": reused[0],
         "deterministic_ms_per_step": det_ms,
         "fp32": {"ms_per_step": fp32_ms, "stages_ms_per_step": stages32,
