@@ -668,7 +668,7 @@ __global__ __launch_bounds__(64 * kDzWaves) __attribute__((amdgpu_waves_per_eu(2
 // layer's pre-activations; W its 256 x 256 BF16 weights' fragments), masked by
 // act[b][n] > 0 (the layer-1 ReLU), gives S[n][:] = the sum over b (complete, in
 // order) and Rpart[block][b][:] = the sum over the block's Gaussians.
-// A block takes 8 strips of 16 Gaussians (strip w from 16 (w gridDim + block) on,
+// A block takes up to 8 strips of 16 Gaussians (strip w from 16 (w gridDim + block) on,
 // so that the front of the depth order, where the rows with a gradient are, is
 // dealt over all blocks) and every query in order. Wave w forms output features
 // [32 w, 32 w + 32) of every strip: its 16 weight fragments stay in registers, the
@@ -681,7 +681,6 @@ __global__ __launch_bounds__(64 * kDzWaves) __attribute__((amdgpu_waves_per_eu(2
 // with a gradient ran alone: 221 us at 800k pairs, a quarter of them with a
 // gradient, 331 with all; 110 with row-major rows, 100 now.)
 constexpr int kL1Waves = 8;
-constexpr int kL1Rows = 16 * kL1Waves;
 
 __global__ __launch_bounds__(64 * kL1Waves) __attribute__((amdgpu_waves_per_eu(2, 2))) void layer1_grad_kernel(
     const __bf16* __restrict__ dz1, const uint4* __restrict__ wf, const __bf16* __restrict__ act, int B, int N,
@@ -1503,7 +1502,14 @@ void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipSt
     slice_sum(part, nb, cols, cols, 0, out, nullptr, st);
 }
 
-int layer1_grad_blocks(int N) { return (N + kL1Rows - 1) / kL1Rows; }
+// Whole rounds of blocks over the compute units, the strips of 16 dealt evenly over them (at most 8 to a block): us at 8
+// queries of 2k / 10k / 20k / 50k Gaussians 21 / 31 / 42 / 55, with 8 strips to every block 49 / 51 / 49 / 57. 10k
+// Gaussians are 625 strips, two or three to each of 256 blocks instead of eight to 79 of them.
+int layer1_grad_blocks(int N) {
+    const int strips = (N + 15) / 16, cus = n_compute_units();
+    const int rounds = (strips + kL1Waves * cus - 1) / (kL1Waves * cus);
+    return std::min(strips, rounds * cus);
+}
 
 void launch_layer1_grad(const void* dz1, const void* wf, const void* act, int B, int N, const RowGroups& rg, float* S,
                         float* Rpart, hipStream_t st) {
