@@ -16,6 +16,8 @@
 // (d_mean, d_log_scale, d_rotation, d_logit, d_amp); the MLP backward is a
 // chain of row-parallel products (dZ_{l-1} = (dZ_l W_l) . [H_{l-1} > 0]) and
 // split-K weight-gradient reductions (dW_l = dZ_l^T H_{l-1}) in FP32.
+#include <cmath>
+
 #include "cull.h"
 #include "kernels.h"
 #include "swf_device.h"
@@ -1461,7 +1463,12 @@ void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, 
                                                      (__bf16*)out);
 }
 
-int out_bwd_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (P + 255) / 256)); }
+// One block per compute unit as soon as there are groups for it, two from 512 rows per block on: 40k pairs 26 us (FP32 33) with 256
+// rows to a block (157 blocks), 22 (28) now.
+int out_bwd_blocks(int64_t P) {
+    const int64_t G = (P + kRowGroup - 1) / kRowGroup;
+    return (int)std::max<int64_t>(1, P >= 131072 ? 512 : std::min<int64_t>(256, G));
+}
 size_t out_bwd_floats(int64_t P) { return (size_t)out_bwd_blocks(P) * kOutSlice; }
 
 void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act, int64_t P, const RowGroups& rg,
@@ -1476,7 +1483,17 @@ void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act,
     slice_sum(part, nblk, kOutSlice, kOut * 256, kOut, dWo, dbo, st);
 }
 
-int wgrad_mfma_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, (P + 1023) / 1024)); }
+// Blocks of a weight gradient: each has its share of the G = P / 32 groups to multiply (group_us each) and a slice of
+// 257 KiB that is written and read again (0.12 us of the whole chip's bandwidth), so about sqrt(G group_us / 0.12) of
+// them, as many as there are compute units at most: 40k pairs 52 us with 1024 rows to a block, 24 here (40 and 131
+// blocks); FP32 80 with 256 rows to a block, 60 here (157 and 256); the slices' sums 4 us longer each.
+static int wgrad_blocks(int64_t P, double group_us) {
+    const int64_t G = (P + kRowGroup - 1) / kRowGroup;
+    const auto best = (int64_t)std::ceil(std::sqrt((double)G * group_us / 0.12));
+    return (int)std::max<int64_t>(1, std::min({(int64_t)256, G, best}));
+}
+
+int wgrad_mfma_blocks(int64_t P) { return wgrad_blocks(P, 1.6); }
 size_t wgrad_mfma_floats(int64_t P) { return (size_t)wgrad_mfma_blocks(P) * kWgSlice; }
 
 void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGroups& rg, float* part, float* dW,
@@ -1487,7 +1504,7 @@ void launch_wgrad_mfma(const void* dz, const void* act, int64_t P, const RowGrou
     slice_sum(part, nblk, kWgSlice, 65536, 256, dW, db, st);
 }
 
-int wgrad_f32_blocks(int64_t P) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, (P + 255) / 256)); }
+int wgrad_f32_blocks(int64_t P) { return wgrad_blocks(P, 7.3); }
 size_t wgrad_f32_floats(int64_t P) { return (size_t)wgrad_f32_blocks(P) * kWgSlice; }
 
 void launch_wgrad_f32(const float* dz, const float* act, int64_t P, const RowGroups& rg, float* part, float* dW,
