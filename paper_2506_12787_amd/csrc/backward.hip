@@ -1463,8 +1463,8 @@ void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, 
                                                      (__bf16*)out);
 }
 
-// One block per compute unit as soon as there are groups for it, two from 512 rows per block on: 40k pairs 26 us (FP32 33) with 256
-// rows to a block (157 blocks), 22 (28) now.
+// One block per compute unit as soon as there are groups for it, two from 512 rows per block on: 40k pairs 26 us (FP32
+// 33) with 256 rows to a block (157 blocks), 22 (28) now.
 int out_bwd_blocks(int64_t P) {
     const int64_t G = (P + kRowGroup - 1) / kRowGroup;
     return (int)std::max<int64_t>(1, P >= 131072 ? 512 : std::min<int64_t>(256, G));
