@@ -697,17 +697,19 @@ __global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb
             run += v[k];
         }
     }
-    // the columns' starts within the chunk: the first kChunk threads hold one column each
-    uint32_t inc = 0;
+    // the columns' starts within the chunk: the first kChunk threads hold one column each. Summed in 64 bits: 64 columns
+    // of 2^26 pairs are 2^32 entries, and only a total that shows it is refused (the positions are not used then, so
+    // they may be cut to 32).
+    uint64_t inc = 0;
     if (grp == 0) {
-        inc = wave_inclusive_scan<uint32_t>(tot);
+        inc = wave_inclusive_scan<uint64_t>(tot);
         if (lane_id() == 63) wsum[w] = inc;
     }
     __syncthreads();
     if (grp == 0) {
-        uint32_t before = 0;
-        for (int k = 0; k < w; ++k) before += (uint32_t)wsum[k];
-        if (in) bb.lstart[e] = before + inc - tot;
+        uint64_t before = 0;
+        for (int k = 0; k < w; ++k) before += wsum[k];
+        if (in) bb.lstart[e] = (uint32_t)(before + inc - tot);
     }
     unsigned long long ct = 0;
     if (threadIdx.x == 0)
