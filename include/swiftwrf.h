@@ -85,7 +85,9 @@ enum {
     SWF_DETERMINISTIC = 1 << 7 /* swf_render_backward: gradients summed in a fixed
                                 order (bitwise the same from run to run) instead of
                                 by atomic adds; takes 128 bytes per list entry of
-                                device memory and one more pass                   */
+                                device memory (batch * n * tiles entries where
+                                the render did not wait for their count: 32 MiB
+                                at most) and one more pass                        */
 };
 
 typedef struct swf_ctx swf_ctx;

@@ -179,11 +179,9 @@ swf_status Ctx::backward(Workspace& w, int sid, const float* tx, int B, int flag
     const uint32_t* det_off = nullptr;
     if (flags & SWF_DETERMINISTIC) {
         // per (list entry, wave) sums, zero where a wave contributes nothing, stored per pair: a pair's entries
-        // from its first slot on (the exclusive scan of the key counts), in the row-major order of its tiles
-        if (w.last.uncounted) {
-            if ((s = hip(hipStreamSynchronize(w.last.stream), "stream sync"))) return s;
-            w.count_last();
-        }
+        // from its first slot on (the exclusive scan of the key counts), in the row-major order of its tiles. After a
+        // render that did not wait for its count there is room for every entry its lists can hold (32 MiB at most):
+        // waiting for the count here would wait for all that the render's stream holds by now
         const size_t db = (size_t)w.last.n_keys * 32 * sizeof(float);
         if ((s = w.det.reserve(this, db + 16, st))) return s;
         if (db && (s = hip(hipMemsetAsync(w.det.ptr, 0, db, st), "memset entry sums"))) return s;
