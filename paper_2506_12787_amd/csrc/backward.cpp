@@ -31,14 +31,17 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     // dz ping-pong; BF16 with a single hidden layer: also the FP32 layer-1 gradient (formed inside its sums)
     const bool need_zf = bf16 && nh == 1;
     if ((s = w.dz.reserve(this, need_zf ? actb * 2 + f32b + 16 : actb * 2 + 16, st))) return s;
-    // scratch: S (N x 256), R (B x 256), split-K partials, column-sum partials, BF16 weights
-    const size_t n_split = std::max({bf16 ? (size_t)0 : wgrad_f32_floats(P), gemm_part_floats(kOut, Hd, P),
-                                     mean_grad_floats(N), gemm_part_floats(Hd, kTxFeat, B),
-                                     (size_t)layer1_sums_blocks((int)N) * B * Hd,
-                                     (size_t)layer1_grad_blocks((int)N) * B * Hd, wgrad_mfma_floats(P),
-                                     out_bwd_floats(P)});
-    const size_t n_cs = (size_t)colsum_blocks(N) * Hd * B;
-    const size_t n_wb = bf16 ? ((size_t)(nh - 1) * Hd * Hd + (size_t)kOut * Hd + (size_t)P * kOut + 64) / 2 + 64 : 0;
+    // scratch: S (N x 256), R (B x 256), the launches' slices, column-sum partials, packed weights. Only what this
+    // backward's launches take: the layer-1 slices of the form it runs, the column sums where those are many, BF16 dy
+    // where it is multiplied (500k Gaussians x 64 queries, BF16, four hidden layers: 0.78 GB, 2.11 with all of them)
+    const int rblocks = bf16 && nh > 1 ? layer1_grad_blocks((int)N) : layer1_sums_blocks((int)N);
+    const size_t n_split = std::max({mean_grad_floats(N), gemm_part_floats(Hd, kTxFeat, B),
+                                     (size_t)rblocks * B * Hd, out_bwd_floats(P),
+                                     bf16 ? wgrad_mfma_floats(P) : wgrad_f32_floats(P)});
+    const bool many = rblocks > 512;  // slices of the sums over Gaussians: column sums in two stages
+    const size_t n_cs = many ? (size_t)colsum_blocks(rblocks) * Hd * B : 0;
+    const size_t n_wb =
+        bf16 ? ((size_t)(nh - 1) * Hd * Hd + (size_t)kOut * Hd + (need_zf ? (size_t)P * kOut : 0) + 64) / 2 + 64 : 0;
     const size_t n_wt = bf16 ? 0 : (size_t)(nh - 1) * Hd * Hd;  // FP32: W^T of the 256 x 256 layers, fragment-major
     const size_t small =
         ((size_t)N * Hd + (size_t)B * Hd + 4 + n_split + n_cs + n_wb + n_wt + 64) *
@@ -53,7 +56,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     float* zf = need_zf ? (float*)((char*)w.dz.ptr + actb * 2) : nullptr;  // FP32 layer-1 gradient (nh == 1)
     float* S = (float*)w.part.ptr;               // N x 256
     float* R = S + (size_t)N * Hd;               // B x 256
-    float* part = R + (size_t)B * Hd;            // split-K partials (16-byte aligned)
+    float* part = R + (size_t)B * Hd;            // slices (16-byte aligned)
     float* tmp = part + n_split;                 // column-sum partials
     uint16_t* wb = (uint16_t*)(((uintptr_t)(tmp + n_cs) + 15) & ~(uintptr_t)15);  // BF16 weights (launch_pack_bwd), then dy
     float* wt = (float*)(((uintptr_t)(tmp + n_cs + n_wb) + 15) & ~(uintptr_t)15);  // FP32 W^T, 16-byte aligned
@@ -99,23 +102,20 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     }
     // ---- layer 1: the gradient of its pre-activations dz0, FP32; S = its sum over the batch per Gaussian
     // (N x 256), R = its sum over the Gaussians per query (B x 256), b0 = its sum over all pairs
-    int rblocks = 0;  // slices of the sums over Gaussians
     if (dz1) {
         // dz0 = (dz1 W1) masked, never stored: one pass gives S and per-block partial sums of R
         launch_layer1_grad(dz1, wl[1], act[0], (int)B, (int)N, rg, S, part, st);
-        rblocks = layer1_grad_blocks((int)N);
     } else {
         // BF16 with one hidden layer: zf is dz0 before the ReLU mask. FP32: dz0 carries layer 1's ReLU mask already
         // (applied where it was formed). One pass gives S and per-block partial sums of R
         launch_layer1_sums(need_zf ? zf : (const float*)dz[cur], need_zf ? act[0] : nullptr,
                            need_zf ? nullptr : rg.bits, (int)B, (int)N, S, part, st);
-        rblocks = layer1_sums_blocks((int)N);
     }
     if (gr->weight[0]) {
-        if (rblocks <= 512)
-            launch_slice_sum(part, rblocks, (int64_t)B * Hd, R, st);
-        else
+        if (many)
             launch_colsum(part, rblocks, (int64_t)B * Hd, 1, 0, tmp, R, 0, st);
+        else
+            launch_slice_sum(part, rblocks, (int64_t)B * Hd, R, st);
     }
     // dW1 [256 x 89] = [S^T gamma(mu_hat) | R^T gamma(s_hat)]; the mean part with b0 (the sum of S over Gaussians) and
     // d mu, through d gamma(mu_hat) = S W1m
