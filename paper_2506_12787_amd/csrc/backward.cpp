@@ -35,7 +35,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     // backward's launches take: the layer-1 slices of the form it runs, the column sums where those are many, BF16 dy
     // where it is multiplied (500k Gaussians x 64 queries, BF16, four hidden layers: 0.78 GB, 2.11 with all of them)
     const int rblocks = bf16 && nh > 1 ? layer1_grad_blocks((int)N) : layer1_sums_blocks((int)N);
-    const size_t n_split = std::max({mean_grad_floats(N), gemm_part_floats(Hd, kTxFeat, B),
+    const size_t n_split = std::max({mean_grad_floats(N), gemm_part_floats(Hd, kTxFeat, B, false),
                                      (size_t)rblocks * B * Hd, out_bwd_floats(P),
                                      bf16 ? wgrad_mfma_floats(P) : wgrad_f32_floats(P)});
     const bool many = rblocks > 512;  // slices of the sums over Gaussians: column sums in two stages
@@ -77,7 +77,7 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     if (need_zf) {
         uint16_t* dyb = wl[nh] + (size_t)kOut * Hd;
         launch_to_bf16(dy, P * kOut, dyb, st);
-        launch_gemm_f32(false, false, P, Hd, kOut, dyb, kOut, wl[nh], Hd, zf, Hd, part, st, nullptr, 0, true);
+        launch_gemm_f32(false, false, P, Hd, kOut, dyb, kOut, wl[nh], Hd, zf, Hd, part, st, true);
     }
     int cur = 0;
     const void* dz1 = nullptr;  // BF16: the second layer's pre-activation gradient
@@ -113,14 +113,14 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     }
     if (gr->weight[0]) {
         if (many)
-            launch_colsum(part, rblocks, (int64_t)B * Hd, 1, 0, tmp, R, 0, st);
+            launch_colsum(part, rblocks, (int64_t)B * Hd, tmp, R, st);
         else
             launch_slice_sum(part, rblocks, (int64_t)B * Hd, R, st);
     }
     // dW1 [256 x 89] = [S^T gamma(mu_hat) | R^T gamma(s_hat)]; the mean part with b0 (the sum of S over Gaussians) and
     // d mu, through d gamma(mu_hat) = S W1m
     if (gr->weight[0])
-        launch_gemm_f32(true, false, Hd, kTxFeat, B, R, Hd, ftx, kTxFeat, gr->weight[0] + kMeanFeat, I, part, st);
+        launch_gemm_f32(true, false, Hd, kTxFeat, B, R, Hd, ftx, kTxFeat, gr->weight[0] + kMeanFeat, I, part, st, false);
     launch_mean_grad(S, d, part, gr->weight[0], gr->bias[0], (float*)w.dmu.ptr, st);
     return hip(hipGetLastError(), "mlp backward");
 }

@@ -384,29 +384,6 @@ __global__ void base_reduce_kernel(const float* __restrict__ dbase, const float*
         if (out.p[k]) out.p[k][id] = s[k];
 }
 
-// Column sums of row-major [rows x cols] matrices (one per z, batch stride
-// bs), in two stages: part[z][y][c] over row block y, then out[z][c].
-__global__ __launch_bounds__(256) void colsum_stage1_kernel(const float* __restrict__ A, int64_t rows, int64_t cols,
-                                                            int64_t rpb, int64_t bs, float* __restrict__ part) {
-    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c >= cols) return;
-    const float* Az = A + (int64_t)blockIdx.z * bs;
-    const int64_t r0 = (int64_t)blockIdx.y * rpb, r1 = min(rows, r0 + rpb);
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int64_t r = r0;
-    for (; r + 4 <= r1; r += 4) {
-        s0 += Az[r * cols + c];
-        s1 += Az[(r + 1) * cols + c];
-        s2 += Az[(r + 2) * cols + c];
-        s3 += Az[(r + 3) * cols + c];
-    }
-    for (; r < r1; ++r) s0 += Az[r * cols + c];
-    part[((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * cols + c] = (s0 + s1) + (s2 + s3);
-}
-
-// Column sums, vectorised (cols % 4 == 0): 4 consecutive columns per thread,
-// 64 threads over 256 columns, 4 row groups per block summed through LDS in a
-// fixed order (deterministic). One row block writes the result directly.
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ float4 load4(const __bf16* p) {
     const uint2 u = *reinterpret_cast<const uint2*>(p);
@@ -414,19 +391,20 @@ __device__ __forceinline__ float4 load4(const __bf16* p) {
                        __uint_as_float(u.y & 0xffff0000u));
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void colsum4_stage1_kernel(const T* __restrict__ A, int64_t rows, int64_t cols,
-                                                             int64_t rpb, int64_t bs, float* __restrict__ part,
-                                                             float* __restrict__ out, int64_t out_bs) {
+// Column sums of a row-major [rows x cols] matrix of many rows (cols % 4 == 0),
+// in two stages: part[y][c] over row block y (4 consecutive columns per thread,
+// 64 threads over 256 columns, 4 row groups per block summed through LDS in a
+// fixed order), then out[c].
+__global__ __launch_bounds__(256) void colsum4_stage1_kernel(const float* __restrict__ A, int64_t rows, int64_t cols,
+                                                             int64_t rpb, float* __restrict__ part) {
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int64_t c = (int64_t)blockIdx.x * 256 + tx * 4;
-    const T* Az = A + (int64_t)blockIdx.z * bs;
     const int64_t r0 = (int64_t)blockIdx.y * rpb, r1 = min(rows, r0 + rpb);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     if (c < cols) {
 #pragma unroll 4
         for (int64_t r = r0 + ty; r < r1; r += 4) {
-            const float4 v = load4(Az + r * cols + c);
+            const float4 v = load4(A + r * cols + c);
             s.x += v.x;
             s.y += v.y;
             s.z += v.z;
@@ -446,27 +424,18 @@ __global__ __launch_bounds__(256) void colsum4_stage1_kernel(const T* __restrict
         t.z += u.z;
         t.w += u.w;
     }
-    if (gridDim.y == 1) {
-        float* o = out + (int64_t)blockIdx.z * out_bs + c;
-        o[0] = t.x;
-        o[1] = t.y;
-        o[2] = t.z;
-        o[3] = t.w;
-    } else {
-        *reinterpret_cast<float4*>(part + ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * cols + c) = t;
-    }
+    *reinterpret_cast<float4*>(part + (int64_t)blockIdx.y * cols + c) = t;
 }
 
 // Second stage: 8 columns per block, 32 groups of row blocks each, summed
 // through LDS in a fixed order.
 __global__ __launch_bounds__(256) void colsum8_stage2_kernel(const float* __restrict__ part, int nblk, int64_t cols,
-                                                             float* __restrict__ out, int64_t out_bs) {
+                                                             float* __restrict__ out) {
     const int cc = threadIdx.x & 7, g = threadIdx.x >> 3;
     const int64_t c = (int64_t)blockIdx.x * 8 + cc;
-    const float* pz = part + (int64_t)blockIdx.y * nblk * cols;
     float s = 0.f;
     if (c < cols)
-        for (int b = g; b < nblk; b += 32) s += pz[(int64_t)b * cols + c];
+        for (int b = g; b < nblk; b += 32) s += part[(int64_t)b * cols + c];
     __shared__ float red[32][8];
     red[g][cc] = s;
     __syncthreads();
@@ -474,7 +443,7 @@ __global__ __launch_bounds__(256) void colsum8_stage2_kernel(const float* __rest
     float t = 0.f;
 #pragma unroll
     for (int k = 0; k < 32; ++k) t += red[k][cc];
-    out[(int64_t)blockIdx.y * out_bs + c] = t;
+    out[c] = t;
 }
 
 // Sums of nb slices of a launch's partial results, slices in a fixed order:
@@ -519,11 +488,6 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict_
             out1[e - n0] = v[k];
         }
     }
-}
-
-__global__ void fill_kernel(float* __restrict__ p, float v, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
 }
 
 // ---- BF16 variants (the MLP backward of a BF16 forward) ----------------------
@@ -1407,35 +1371,12 @@ void launch_base_reduce(const float* dbase, const float* dmu_pe, const uint32_t*
 
 int colsum_blocks(int64_t rows) { return (int)std::max<int64_t>(1, std::min<int64_t>(2048, (rows + 255) / 256)); }
 
-namespace {
-template <typename T>
-void colsum4(const T* A, int64_t rows, int64_t cols, int nz, int64_t bs, float* part, float* out, int64_t out_bs,
-             hipStream_t st) {
+void launch_colsum(const float* A, int64_t rows, int64_t cols, float* part, float* out, hipStream_t st) {
+    if (cols <= 0) return;
     const int nblk = colsum_blocks(rows);
     const int64_t rpb = (rows + nblk - 1) / nblk;
-    colsum4_stage1_kernel<T><<<dim3((unsigned)((cols + 255) / 256), nblk, nz), 256, 0, st>>>(A, rows, cols, rpb, bs,
-                                                                                          part, out, out_bs);
-    if (nblk > 1)
-        colsum8_stage2_kernel<<<dim3((unsigned)((cols + 7) / 8), nz), 256, 0, st>>>(part, nblk, cols, out, out_bs);
-}
-}  // namespace
-
-void launch_colsum(const float* A, int64_t rows, int64_t cols, int nz, int64_t bs, float* part, float* out,
-                   int64_t out_bs, hipStream_t st) {
-    if (cols <= 0 || nz <= 0) return;
-    if (cols % 4 == 0 && bs % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0) {
-        colsum4(A, rows, cols, nz, bs, part, out, out_bs, st);
-        return;
-    }
-    const int nblk = colsum_blocks(rows);
-    const int64_t rpb = (rows + nblk - 1) / nblk;
-    const unsigned gx = (unsigned)((cols + 255) / 256);
-    colsum_stage1_kernel<<<dim3(gx, nblk, nz), 256, 0, st>>>(A, rows, cols, rpb, bs, part);
-    colsum8_stage2_kernel<<<dim3((unsigned)((cols + 7) / 8), nz), 256, 0, st>>>(part, nblk, cols, out, out_bs);
-}
-
-void launch_fill(float* p, float v, int64_t n, hipStream_t st) {
-    if (n > 0) fill_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p, v, n);
+    colsum4_stage1_kernel<<<dim3((unsigned)((cols + 255) / 256), nblk), 256, 0, st>>>(A, rows, cols, rpb, part);
+    colsum8_stage2_kernel<<<(unsigned)((cols + 7) / 8), 256, 0, st>>>(part, nblk, cols, out);
 }
 
 void launch_pack_bwd(const float* const* w, int n_hidden, void* out, hipStream_t st) {

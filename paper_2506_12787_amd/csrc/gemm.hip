@@ -1,20 +1,20 @@
-// FP32 GEMM on the matrix cores for the MLP backward (the differentiated
-// layers of the deformation network, Sec. 4.2): C = op(A) op(B) over row-major
-// matrices, op(A) M x K and op(B) K x N, FP32 products and FP32 sums
-// (v_mfma_f32_16x16x4_f32). The operands are FP32, or BF16 bits widened on
-// load (a product of two BF16 values is exact in FP32, so this equals a BF16
-// product with FP32 accumulation). Optional epilogue: C *= [mask > 0] (the
-// ReLU derivative of the layer below).
+// FP32 GEMM on the matrix cores for what the MLP backward's own kernels do not
+// take (the differentiated layers of the deformation network, Sec. 4.2): the
+// transceiver part of layer 1's weight gradient (256 x 63 over the batch, FP32)
+// and, where a BF16 network has a single hidden layer, that layer's gradient
+// (pairs x 256 over 7, BF16 operands). C = op(A) op(B) over row-major matrices,
+// op(A) M x K and op(B) K x N, FP32 products and FP32 sums
+// (v_mfma_f32_16x16x4_f32). BF16 bits are widened on load (a product of two BF16
+// values is exact in FP32, so this equals a BF16 product with FP32 accumulation).
 //
-// Block tile 128 x 128 for large BF16 products, 64 x 64 for small ones, 128 x 32
-// when C has at most 32 columns (so no wave computes padding only); four waves
-// per block; K in steps of 32 staged through LDS (double-buffered, one barrier
-// per step). Every operand layout is loaded along its contiguous dimension, four
-// elements per thread and run (one 16-byte load where the run is aligned and
-// inside the matrix). Products with a small C and a long K (weight gradients:
-// K = pairs or Gaussians) are cut into K-slices whose partial products are
-// summed afterwards in a fixed order, so every result is the same from run to
-// run.
+// Block tile 64 x 64; BF16: 128 x 128 for large products, 128 x 32 when C has at
+// most 32 columns (so no wave computes padding only); four waves per block; K in
+// steps of 32 staged through LDS (double-buffered, one barrier per step). Every
+// operand layout is loaded along its contiguous dimension, four elements per
+// thread and run (one 16-byte load where the run is aligned and inside the
+// matrix). Products with a small C and a long K are cut into K-slices whose
+// partial products are summed afterwards in a fixed order, so every result is
+// the same from run to run.
 #include <algorithm>
 
 #include "kernels.h"
@@ -30,13 +30,12 @@ struct GemmArgs {
     const void* A;
     const void* B;
     float* C;           // result (one slice) or the slices' partial products
-    const float* mask;  // C *= [mask > 0] (one slice only), or null
-    int64_t M, N, K, lda, ldb, ldc, ldm;
+    int64_t M, N, K, lda, ldb, ldc;
     int64_t kc;         // K per slice (blockIdx.z)
     int a_kc, b_kc;     // operand contiguous along K (else along M / N)
     int a_vec, b_vec;   // FP32 operand whose runs of 4 are 16-byte aligned (ld % 4 == 0, aligned base)
-    int c_vec;          // the result (and mask) rows take 16-byte stores (loads) at multiples of 4
-    int tc;             // store the transpose: C[n * ldc + m] (no mask)
+    int c_vec;          // the result rows take 16-byte stores at multiples of 4
+    int tc;             // store the transpose: C[n * ldc + m]
 };
 
 template <bool kBf>
@@ -118,7 +117,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     const int64_t kb = (int64_t)blockIdx.z * g.kc;
     const int64_t ke = g.K < kb + g.kc ? g.K : kb + g.kc;
     const int steps = ke > kb ? (int)((ke - kb + kGK - 1) / kGK) : 0;
-    const auto k_of = [&](int s) { return kb + (int64_t)s * kGK; };  // first K row of stage s
     const bool akc = g.a_kc != 0, bkc = g.b_kc != 0;
     const bool avec = g.a_vec != 0, bvec = g.b_vec != 0;
 
@@ -130,8 +128,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 
     float va[TM / 8], vb[TN / 8];
     if (steps > 0) {
-        tile_load<kBf, TM>(g.A, g.lda, akc, avec, m0, g.M, k_of(0), ke, va);
-        tile_load<kBf, TN>(g.B, g.ldb, bkc, bvec, n0, g.N, k_of(0), ke, vb);
+        tile_load<kBf, TM>(g.A, g.lda, akc, avec, m0, g.M, kb, ke, va);
+        tile_load<kBf, TN>(g.B, g.ldb, bkc, bvec, n0, g.N, kb, ke, vb);
         tile_store<TM>(As[0], akc, va);
         tile_store<TN>(Bs[0], bkc, vb);
     }
@@ -140,7 +138,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
         const int cur = s & 1;
         const bool more = s + 1 < steps;
         if (more) {
-            const int64_t k1 = k_of(s + 1);
+            const int64_t k1 = kb + (int64_t)(s + 1) * kGK;
             tile_load<kBf, TM>(g.A, g.lda, akc, avec, m0, g.M, k1, ke, va);
             tile_load<kBf, TN>(g.B, g.ldb, bkc, bvec, n0, g.N, k1, ke, vb);
         }
@@ -164,8 +162,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
         __syncthreads();
     }
     // lane l holds rows 4 (l / 16) + r, column l % 16 of each 16 x 16 result: staged in LDS (every read of the
-    // K stages ended at the last barrier), then written out row by row, 4 consecutive elements per thread, the
-    // mask read the same way
+    // K stages ended at the last barrier), then written out row by row, 4 consecutive elements per thread
     auto Cs = reinterpret_cast<float (*)[TN + 4]>(smem);
 #pragma unroll
     for (int i = 0; i < I; ++i)
@@ -177,7 +174,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     __syncthreads();
     const bool split = gridDim.z > 1;
     float* __restrict__ C = split ? g.C + (size_t)blockIdx.z * (size_t)(g.M * g.N) : g.C;
-    const float* __restrict__ mk = split ? nullptr : g.mask;
     const int64_t ldc = split ? g.N : g.ldc;
     const bool vec = g.c_vec != 0;
     if (g.tc && !split) {
@@ -201,32 +197,24 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
         const int row = e / (TN / 4), c4 = (e % (TN / 4)) * 4;
         const int64_t m = m0 + row, n = n0 + c4;
         if (m >= g.M || n >= g.N) continue;
-        float4 v = *reinterpret_cast<const float4*>(&Cs[row][c4]);
+        const float4 v = *reinterpret_cast<const float4*>(&Cs[row][c4]);
         if (vec && n + 3 < g.N) {
-            if (mk) {
-                const float4 f = *reinterpret_cast<const float4*>(mk + m * g.ldm + n);
-                v.x = f.x > 0.0f ? v.x : 0.0f;
-                v.y = f.y > 0.0f ? v.y : 0.0f;
-                v.z = f.z > 0.0f ? v.z : 0.0f;
-                v.w = f.w > 0.0f ? v.w : 0.0f;
-            }
             *reinterpret_cast<float4*>(C + m * ldc + n) = v;
         } else {
             const float vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (n + q < g.N) C[m * ldc + n + q] = (mk && !(mk[m * g.ldm + n + q] > 0.0f)) ? 0.0f : vv[q];
+                if (n + q < g.N) C[m * ldc + n + q] = vv[q];
         }
     }
 }
 
-// C[m][n] (ld ldc; tc: C[n][m]) = sum over the slices of part[z][m][n], then
-// the mask. A block takes 64 consecutive outputs; thread group w (of 4) sums
-// the slices z = w, w + 4, ... in order, and the four partial sums are added
-// in the order w = 0..3, so the result does not depend on the launch.
+// C[m][n] (ld ldc; tc: C[n][m]) = sum over the slices of part[z][m][n]. A block
+// takes 64 consecutive outputs; thread group w (of 4) sums the slices z = w,
+// w + 4, ... in order, and the four partial sums are added in the order
+// w = 0..3, so the result does not depend on the launch.
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int sp, int64_t M,
-                                                          int64_t N, float* __restrict__ C, int64_t ldc,
-                                                          const float* __restrict__ mask, int64_t ldm, int tc) {
+                                                          int64_t N, float* __restrict__ C, int64_t ldc, int tc) {
     __shared__ float red[4][64];
     const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     const int w = (int)(threadIdx.x >> 6);
@@ -238,42 +226,41 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
     __syncthreads();
     if (w == 0 && i < M * N) {
         const int c = (int)threadIdx.x;
-        float v = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+        const float v = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
         const int64_t m = i / N, n = i - m * N;
-        if (mask && !(mask[m * ldm + n] > 0.0f)) v = 0.0f;
         C[tc ? n * ldc + m : m * ldc + n] = v;
     }
 }
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-bool narrow(int64_t N) { return N <= 32; }               // the 128 x 32 tile
-bool wide(int64_t M, int64_t N) { return M >= 128 && N >= 128; }  // the 128 x 128 tile
+// Only BF16 products are pairs long: FP32 ones take the 64 x 64 tile whatever their shape.
+bool narrow(int64_t N, bool bf16) { return bf16 && N <= 32; }                           // the 128 x 32 tile
+bool wide(int64_t M, int64_t N, bool bf16) { return bf16 && M >= 128 && N >= 128; }     // the 128 x 128 tile
 
-}  // namespace
-
-int gemm_split(int64_t M, int64_t N, int64_t K) {
-    const int64_t tiles = narrow(N)    ? cdiv(M, 128) * cdiv(N, 32)
-                          : wide(M, N) ? cdiv(M, 128) * cdiv(N, 128)
-                                       : cdiv(M, 64) * cdiv(N, 64);
+int gemm_split(int64_t M, int64_t N, int64_t K, bool bf16) {
+    const int64_t tiles = narrow(N, bf16)    ? cdiv(M, 128) * cdiv(N, 32)
+                          : wide(M, N, bf16) ? cdiv(M, 128) * cdiv(N, 128)
+                                             : cdiv(M, 64) * cdiv(N, 64);
     // enough blocks to cover the chip a few times, each slice at least 256 deep
     const int64_t want = cdiv(2048, tiles), deep = K / 256;
     return (int)std::max<int64_t>(1, std::min<int64_t>(256, std::min(want, deep)));
 }
 
-size_t gemm_part_floats(int64_t M, int64_t N, int64_t K) {
+}  // namespace
+
+size_t gemm_part_floats(int64_t M, int64_t N, int64_t K, bool bf16) {
     // either orientation (a product with few rows may run as its transpose)
-    const int sp = std::max(gemm_split(M, N, K), gemm_split(N, M, K));
+    const int sp = std::max(gemm_split(M, N, K, bf16), gemm_split(N, M, K, bf16));
     return sp > 1 ? (size_t)sp * (size_t)(M * N) : 0;
 }
 
 void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
-                     int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, const float* mask, int64_t ldm,
-                     bool bf16) {
+                     int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, bool bf16) {
     if (M <= 0 || N <= 0) return;
-    // a product with few rows and many columns (without a mask) runs as its transpose, C^T = op(B)^T op(A)^T,
-    // on the narrow tile, and stores the transpose back
-    const bool tc = M <= 32 && N > 32 && !mask;
+    // a product with few rows and many columns runs as its transpose, C^T = op(B)^T op(A)^T, on the narrow tile, and
+    // stores the transpose back
+    const bool tc = narrow(M, bf16) && N > 32;
     if (tc) {
         std::swap(M, N);
         std::swap(A, B);
@@ -282,21 +269,19 @@ void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const vo
         ta = !tb;
         tb = !t;
     }
-    const int sp = gemm_split(M, N, K);
+    const int sp = gemm_split(M, N, K, bf16);
     const int64_t kc = sp > 1 ? cdiv(cdiv(K, sp), kGK) * kGK : std::max<int64_t>(K, 1);
     const int slices = sp > 1 ? (int)cdiv(K, kc) : 1;  // at most sp
     GemmArgs g;
     g.A = A;
     g.B = B;
     g.C = slices > 1 ? part : C;
-    g.mask = mask;
     g.M = M;
     g.N = N;
     g.K = K;
     g.lda = lda;
     g.ldb = ldb;
     g.ldc = ldc;
-    g.ldm = ldm;
     g.kc = kc;
     // op(A) = A (M x K) is contiguous along K; op(A) = A^T (A stored K x M) along M. op(B) = B (K x N) is
     // contiguous along N, B^T (B stored N x K) along K.
@@ -305,30 +290,22 @@ void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const vo
     g.a_vec = !bf16 && lda % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
     g.b_vec = !bf16 && ldb % 4 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;
     g.tc = tc ? 1 : 0;
-    // 16-byte rows of the result: the destination of this launch (the slices' partials, or C) and the mask
-    const bool c_al = slices > 1 ? (N % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0)
-                                 : (ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0);
-    const bool m_al = !mask || (ldm % 4 == 0 && (reinterpret_cast<uintptr_t>(mask) & 15) == 0);
-    g.c_vec = c_al && m_al ? 1 : 0;
-    if (narrow(N)) {
-        const dim3 grid((unsigned)cdiv(M, 128), (unsigned)cdiv(N, 32), (unsigned)slices);
-        if (bf16)
-            gemm_f32_kernel<true, 128, 32><<<grid, 256, 0, st>>>(g);
-        else
-            gemm_f32_kernel<false, 128, 32><<<grid, 256, 0, st>>>(g);
-    } else if (bf16 && wide(M, N)) {  // the FP32 products of this library have a side below 128
-        const dim3 grid((unsigned)cdiv(M, 128), (unsigned)cdiv(N, 128), (unsigned)slices);
+    // 16-byte rows of the result: the destination of this launch (the slices' partials, or C)
+    g.c_vec = slices > 1 ? (N % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0)
+                         : (ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0);
+    const int64_t tm = narrow(N, bf16) || wide(M, N, bf16) ? 128 : 64;
+    const int64_t tn = narrow(N, bf16) ? 32 : wide(M, N, bf16) ? 128 : 64;
+    const dim3 grid((unsigned)cdiv(M, tm), (unsigned)cdiv(N, tn), (unsigned)slices);
+    if (!bf16)
+        gemm_f32_kernel<false, 64, 64><<<grid, 256, 0, st>>>(g);
+    else if (tn == 32)
+        gemm_f32_kernel<true, 128, 32><<<grid, 256, 0, st>>>(g);
+    else if (tn == 128)
         gemm_f32_kernel<true, 128, 128><<<grid, 256, 0, st>>>(g);
-    } else {
-        const dim3 grid((unsigned)cdiv(M, 64), (unsigned)cdiv(N, 64), (unsigned)slices);
-        if (bf16)
-            gemm_f32_kernel<true, 64, 64><<<grid, 256, 0, st>>>(g);
-        else
-            gemm_f32_kernel<false, 64, 64><<<grid, 256, 0, st>>>(g);
-    }
+    else
+        gemm_f32_kernel<true, 64, 64><<<grid, 256, 0, st>>>(g);
     if (slices > 1)
-        gemm_reduce_kernel<<<(unsigned)cdiv(M * N, 64), 256, 0, st>>>(part, slices, M, N, C, ldc, mask, ldm,
-                                                                      tc ? 1 : 0);
+        gemm_reduce_kernel<<<(unsigned)cdiv(M * N, 64), 256, 0, st>>>(part, slices, M, N, C, ldc, tc ? 1 : 0);
 }
 
 }  // namespace swf

@@ -298,20 +298,15 @@ struct BaseGrads {  // destinations of the 7 base-parameter gradients (device; N
 void launch_base_reduce(const float* dbase, const float* dmu_pe, const uint32_t* perm, int B, int N,
                         const BaseGrads& out, hipStream_t st);
 // gemm.hip: C = op(A) op(B) in FP32 on the matrix cores, row-major (op(A) M x K, op(B) K x N; A / B FP32, or
-// BF16 bits when bf16). mask (optional, leading dimension ldm): C *= [mask > 0]. A small C over a long K is
-// split into gemm_split(M, N, K) K-slices summed in slice order; part then holds gemm_part_floats(M, N, K)
-// floats (unused otherwise).
-int gemm_split(int64_t M, int64_t N, int64_t K);
-size_t gemm_part_floats(int64_t M, int64_t N, int64_t K);
+// BF16 bits when bf16). A small C over a long K is cut into K-slices summed in slice order; part then holds
+// gemm_part_floats(M, N, K, bf16) floats (unused otherwise).
+size_t gemm_part_floats(int64_t M, int64_t N, int64_t K, bool bf16);
 void launch_gemm_f32(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
-                     int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, const float* mask = nullptr,
-                     int64_t ldm = 0, bool bf16 = false);
-void launch_fill(float* p, float v, int64_t n, hipStream_t st);
-// out[z * out_bs + c] = sum_r A[z * bs + r * cols + c] for z < nz; part holds
-// colsum_blocks(rows) * cols * nz floats
+                     int64_t ldb, float* C, int64_t ldc, float* part, hipStream_t st, bool bf16);
+// out[c] = sum_r A[r * cols + c], cols % 4 == 0, A and part 16-byte aligned; part holds colsum_blocks(rows) * cols
+// floats
 int colsum_blocks(int64_t rows);
-void launch_colsum(const float* A, int64_t rows, int64_t cols, int nz, int64_t bs, float* part, float* out,
-                   int64_t out_bs, hipStream_t st);
+void launch_colsum(const float* A, int64_t rows, int64_t cols, float* part, float* out, hipStream_t st);
 // The arrays dz and act below are in chunk order (BF16) or piece order (FP32).
 // BF16 weights of the backward from the FP32 masters w[0 .. n_hidden]: per 256 x 256 layer 65536 values in fragment
 // order, then the output layer's 7 x 256
