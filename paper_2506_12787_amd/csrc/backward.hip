@@ -1408,7 +1408,8 @@ void launch_dz_gemm(const void* dz, const void* wf, const void* act, int64_t P, 
 // 33) with 256 rows to a block (157 blocks), 22 (28) now.
 int out_bwd_blocks(int64_t P) {
     const int64_t G = (P + kRowGroup - 1) / kRowGroup;
-    return (int)std::max<int64_t>(1, P >= 131072 ? 512 : std::min<int64_t>(256, G));
+    const int64_t cus = n_compute_units();
+    return (int)std::max<int64_t>(1, P >= 512 * cus ? 2 * cus : std::min<int64_t>(cus, G));
 }
 size_t out_bwd_floats(int64_t P) { return (size_t)out_bwd_blocks(P) * kOutSlice; }
 
@@ -1431,7 +1432,7 @@ void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act,
 static int wgrad_blocks(int64_t P, double group_us) {
     const int64_t G = (P + kRowGroup - 1) / kRowGroup;
     const auto best = (int64_t)std::ceil(std::sqrt((double)G * group_us / 0.12));
-    return (int)std::max<int64_t>(1, std::min({(int64_t)256, G, best}));
+    return (int)std::max<int64_t>(1, std::min({(int64_t)n_compute_units(), G, best}));
 }
 
 int wgrad_mfma_blocks(int64_t P) { return wgrad_blocks(P, 1.6); }

@@ -79,7 +79,6 @@ __global__ __launch_bounds__(256) void tx_features_kernel(const float* __restric
 // time (64-pair blocks, 10 rounds).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kFWaves = 4;  // waves per block, 4 output tiles each
-constexpr int kCus = 256;
 
 // Weight fragments of kAhead pieces are in flight ahead of the one in use; a layer's first ones are loaded before the
 // barriers in front of it.
@@ -450,12 +449,13 @@ void launch_mlp_fp32(const DevScene& s, const float* qs, int B, const Grid& g, b
         for (int l = 0; l < s.n_hidden && l < 8; ++l) a.act_out[l] = act_out[l];
     const size_t groups = ((size_t)s.n * B + 15) / 16;
     if (!groups) return;
-    // Whole rounds of 64-pair blocks (57 us each), then the rest: 64-pair blocks take one round more however few
-    // they are, 16-pair blocks one shorter round (24 us) per 256 groups, with four times the weight loads. One
-    // render of n Gaussians, us (16-pair / 64-pair blocks for the rest): n = 16: 48 / 83; 4,000: 69 / 103; 8,000: 94 /
-    // 112; 12,000: 117 / 117; 20,000: 142 / 174; 100,000: 414 / 446.
-    int64_t n4 = (int64_t)(groups / (4 * kCus)) * kCus, rest = (int64_t)groups - 4 * n4;
-    if (rest > 2 * kCus) {
+    // Whole rounds of 64-pair blocks over the compute units (57 us each), then the rest: 64-pair blocks take one round
+    // more however few they are, 16-pair blocks one shorter round (24 us) for as many groups as there are compute
+    // units, with four times the weight loads. One render of n Gaussians, us (16-pair / 64-pair blocks for the rest):
+    // n = 16: 48 / 83; 4,000: 69 / 103; 8,000: 94 / 112; 12,000: 117 / 117; 20,000: 142 / 174; 100,000: 414 / 446.
+    const int64_t cus = n_compute_units();
+    int64_t n4 = (int64_t)groups / (4 * cus) * cus, rest = (int64_t)groups - 4 * n4;
+    if (rest > 2 * cus) {
         n4 += (rest + 3) / 4;
         rest = 0;
     }
