@@ -729,7 +729,7 @@ def bench_beamscan(a):
                         "avg_call_ms": avg, "flop_per_call": flop,
                         "output_GBs": Bq * H * W * 4 / (avg * 1e-3) / 1e9,
                         "note": "8 K FLOP per (pixel, query): the steering-vector contraction; the per-pixel sincospi "
-                                "(shared by 8 queries) and the per-query FP64 channel are not counted"}}
+                                "(shared by 64 queries) and the per-query FP64 channel are not counted"}}
     if not a.no_cpu_baseline:
         from oracle import beamscan as Bs
         t0 = time.perf_counter()

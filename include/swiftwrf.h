@@ -171,10 +171,11 @@ swf_status swf_scene_bytes(swf_ctx *ctx, int32_t scene_id, uint64_t *bytes);
  * aux: device buffer of 8*batch*H*W bytes when SWF_KEEP_AUX, else NULL.
  * Enqueued on `stream`; the call returns after enqueueing, except that it waits
  * once for the total key count (8 bytes written to the host after the key scan),
- * unless the lists fit 2^18 entries whatever the count (batch * n * tiles). The first render of a context sizes the key buffers from that count
- * before enqueueing the rest; later ones enqueue the rest at the buffers'
- * capacity and wait for the count meanwhile, rendering again at the exact size
- * (the same call, still on `stream`) if it did not fit. A batch whose lists
+ * unless the lists fit 2^18 entries whatever the count (batch * n * tiles). The
+ * first render of a context sizes the key buffers from that count before
+ * enqueueing the rest; later ones enqueue the rest at the buffers' capacity and
+ * wait for the count meanwhile, rendering again at the exact size (the same
+ * call, still on `stream`) if it did not fit. A batch whose lists
  * would hold more entries than the context's max_list_entries (or whose
  * batch * n reaches 2^32) is rendered in chunks of queries, halving until each
  * fits (not with SWF_KEEP_AUX: SWF_E_OVERFLOW then); the outputs are those of

@@ -58,7 +58,8 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     float* R = S + (size_t)N * Hd;               // B x 256
     float* part = R + (size_t)B * Hd;            // slices (16-byte aligned)
     float* tmp = part + n_split;                 // column-sum partials
-    uint16_t* wb = (uint16_t*)(((uintptr_t)(tmp + n_cs) + 15) & ~(uintptr_t)15);  // BF16 weights (launch_pack_bwd), then dy
+    // BF16 weights (launch_pack_bwd), then dy
+    uint16_t* wb = (uint16_t*)(((uintptr_t)(tmp + n_cs) + 15) & ~(uintptr_t)15);
     float* wt = (float*)(((uintptr_t)(tmp + n_cs + n_wb) + 15) & ~(uintptr_t)15);  // FP32 W^T, 16-byte aligned
     float *ftx = (float*)w.ftx.ptr, *qs = (float*)w.qs.ptr;
     launch_tx_features(d, tx, B, qs, nullptr, st, ftx);
@@ -120,7 +121,8 @@ swf_status Ctx::mlp_backward(Workspace& w, const DevScene& d, const float* tx, i
     // dW1 [256 x 89] = [S^T gamma(mu_hat) | R^T gamma(s_hat)]; the mean part with b0 (the sum of S over Gaussians) and
     // d mu, through d gamma(mu_hat) = S W1m
     if (gr->weight[0])
-        launch_gemm_f32(true, false, Hd, kTxFeat, B, R, Hd, ftx, kTxFeat, gr->weight[0] + kMeanFeat, I, part, st, false);
+        launch_gemm_f32(true, false, Hd, kTxFeat, B, R, Hd, ftx, kTxFeat, gr->weight[0] + kMeanFeat, I, part, st,
+                        false);
     launch_mean_grad(S, d, part, gr->weight[0], gr->bias[0], (float*)w.dmu.ptr, st);
     return hip(hipGetLastError(), "mlp backward");
 }

@@ -97,7 +97,8 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals, const float4* __restrict__ geo,
     const float4* __restrict__ wm, const float2* __restrict__ oa, int H, int W, int TW, int tiles,
     const float* __restrict__ grad_out, const float* __restrict__ aux_T, const uint32_t* __restrict__ aux_last,
-    float* __restrict__ dpair, float* __restrict__ part = nullptr, const uint2* __restrict__ rect = nullptr, const uint32_t* __restrict__ det_off = nullptr) {
+    float* __restrict__ dpair, float* __restrict__ part = nullptr, const uint2* __restrict__ rect = nullptr,
+    const uint32_t* __restrict__ det_off = nullptr) {
     constexpr int kN = TILE * TILE;
     constexpr bool kCull = TILE == 16;
     constexpr int kWaves = kN / 64;
@@ -247,10 +248,9 @@ __global__ __launch_bounds__(TILE* TILE) void blend_backward_kernel(
     }
 }
 
-// Deterministic gradient sums: pair i (query b = i / N) adds, for every tile
-// of its rectangle in row-major order (a wrapped rectangle's columns from tx0
-// on), the four waves' sums of its entry in that tile's list, found by binary
-// search (a list holds its pairs in increasing order).
+// Deterministic gradient sums: pair i adds, for every tile of its rectangle in
+// row-major order (a wrapped rectangle's columns from tx0 on), the four waves'
+// sums of its entry there, which lie together from the pair's first slot on.
 __global__ void det_reduce_kernel(const uint32_t* __restrict__ count, const uint32_t* __restrict__ det_off,
                                   const float* __restrict__ part, int64_t P, float* __restrict__ dpair) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -537,7 +537,8 @@ typedef __bf16 dz_bf16x2 __attribute__((ext_vector_type(2)));
 
 // 0xffff in each half of w whose BF16 is > 0 (activations are not negative), else 0
 __device__ __forceinline__ uint32_t positive_halves(uint32_t w) {
-    const uint32_t lo = (int32_t)(w << 16) > 0 ? 0x0000ffffu : 0u, hi = (int32_t)(w & 0xffff0000u) > 0 ? 0xffff0000u : 0u;
+    const uint32_t lo = (int32_t)(w << 16) > 0 ? 0x0000ffffu : 0u;
+    const uint32_t hi = (int32_t)(w & 0xffff0000u) > 0 ? 0xffff0000u : 0u;
     return lo | hi;
 }
 
@@ -846,16 +847,19 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_mfma_kernel(const __bf16*
 #pragma unroll
         for (int b = 0; b < 8; ++b)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
+            for (int jj = 0; jj < 4; ++jj)
+                out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
 }
 
-// The same contraction after an FP32 forward (dz, act [P][256] FP32) on the FP32 matrix cores (v_mfma_f32_16x16x4_f32): part[blk][o][i] over every
-// gridDim-th listed group. Each row is read once, as 16 bytes per thread, and
-// staged row by row (padded by 16 floats: the 4 rows that one fragment read
-// touches fall in distinct banks), double-buffered, one barrier per 32 rows; the
-// next rows are loaded while the current ones are multiplied. Tiles per wave and
-// slices as above; the bias gradient is summed from the fragments. 160k pairs: 223 us per layer on the general product's 128 x 128 tiles,
-// which read each row twice; 178 here (the instructions' own time: 146).
+// The same contraction after an FP32 forward (dz, act [P][256] FP32) on the FP32
+// matrix cores (v_mfma_f32_16x16x4_f32): part[blk][o][i] over every gridDim-th
+// listed group. Each row is read once, as 16 bytes per thread, and staged row by
+// row (padded by 16 floats: the 4 rows that one fragment read touches fall in
+// distinct banks), double-buffered, one barrier per 32 rows; the next rows are
+// loaded while the current ones are multiplied. Tiles per wave and slices as
+// above; the bias gradient is summed from the fragments. 160k pairs: 223 us per
+// layer as a general product of 128 x 128 tiles, which read each row twice; 178
+// here (the instructions' own time: 146).
 constexpr int kWfRow = 256 + 16;
 
 __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* __restrict__ dz,
@@ -936,7 +940,8 @@ __global__ __launch_bounds__(64 * kWgWaves) void wgrad_f32_kernel(const float* _
 #pragma unroll
         for (int b = 0; b < 8; ++b)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
+            for (int jj = 0; jj < 4; ++jj)
+                out[(size_t)(o0 + 16 * a + 4 * g + jj) * 256 + i0 + 16 * b + n] = acc[a][b][jj];
 }
 
 // Output layer of the backward in one pass over the last hidden activations
@@ -1461,8 +1466,8 @@ void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipSt
     slice_sum(part, nb, cols, cols, 0, out, nullptr, st);
 }
 
-// Whole rounds of blocks over the compute units, the strips of 16 dealt evenly over them (at most 8 to a block): us at 8
-// queries of 2k / 10k / 20k / 50k Gaussians 21 / 31 / 42 / 55, with 8 strips to every block 49 / 51 / 49 / 57. 10k
+// Whole rounds of blocks over the compute units, the strips of 16 dealt evenly over them (at most 8 to a block): us at
+// 8 queries of 2k / 10k / 20k / 50k Gaussians 21 / 31 / 42 / 55, with 8 strips to every block 49 / 51 / 49 / 57. 10k
 // Gaussians are 625 strips, two or three to each of 256 blocks instead of eight to 79 of them.
 int layer1_grad_blocks(int N) {
     const int strips = (N + 15) / 16, cus = n_compute_units();
@@ -1492,10 +1497,13 @@ void launch_to_bf16(const float* x, int64_t n, void* y, hipStream_t st) {
     if (n > 0) to_bf16_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(x, n, (__bf16*)y);
 }
 
-int mean_grad_blocks(int64_t N) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (N + kMgRows - 1) / kMgRows)); }
+int mean_grad_blocks(int64_t N) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(512, (N + kMgRows - 1) / kMgRows));
+}
 size_t mean_grad_floats(int64_t N) { return (size_t)mean_grad_blocks(N) * kMgSlice; }
 
-void launch_mean_grad(const float* S, const DevScene& d, float* part, float* dW, float* db, float* dmu, hipStream_t st) {
+void launch_mean_grad(const float* S, const DevScene& d, float* part, float* dW, float* db, float* dmu,
+                      hipStream_t st) {
     const int nb = mean_grad_blocks(d.n);  // no Gaussians: one block writes zeros
     mean_grad_kernel<<<nb, 256, 0, st>>>(S, d.w[0], d.in_dim, d.mx, d.my, d.n, d.W, d.H, dmu, part);
     slice_sum(part, nb, kMgSlice, 256 * kMeanFeat, 256, dW, db, st, kMeanFeat, d.in_dim);

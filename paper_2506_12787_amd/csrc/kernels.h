@@ -339,14 +339,14 @@ void launch_out_bwd(bool bf16, const float* dy, const void* wo, const void* act,
                     void* dz, float* part, float* dWo, float* dbo, hipStream_t st);
 // out[c] = sum of nb slices part[j][c] of cols values (a multiple of 4), in a fixed order
 void launch_slice_sum(const float* part, int nb, int64_t cols, float* out, hipStream_t st);
-// S [N][256] = sum_b of z * [act > 0] (act BF16, chunk order; null: z is masked already) and Rpart [layer1_sums_blocks(N)][B][256]
-// partial sums over Gaussians; rows whose bit is clear (bits may be null) count zero
+// S [N][256] = sum_b of z * [act > 0] (act BF16, chunk order; null: z is masked already) and Rpart
+// [layer1_sums_blocks(N)][B][256] partial sums over Gaussians; rows whose bit is clear (bits may be null) count zero
 int layer1_sums_blocks(int N);
 void launch_layer1_sums(const float* z, const void* act, const uint32_t* bits, int B, int N, float* S, float* Rpart,
                         hipStream_t st);
 void launch_to_bf16(const float* x, int64_t n, void* y, hipStream_t st);
-// From S [N][256]: dW (rows in_dim apart) = S^T gamma(mu_hat) [256][26], db = S's column sums, dmu [N][2]; dW, db may be
-// null; part: mean_grad_floats(N)
+// From S [N][256]: dW (rows in_dim apart) = S^T gamma(mu_hat) [256][26], db = S's column sums, dmu [N][2]; dW, db may
+// be null; part: mean_grad_floats(N)
 size_t mean_grad_floats(int64_t N);
 void launch_mean_grad(const float* S, const DevScene& d, float* part, float* dW, float* db, float* dmu, hipStream_t st);
 

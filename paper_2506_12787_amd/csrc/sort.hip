@@ -651,7 +651,8 @@ __global__ __launch_bounds__(kThreads) void bin_hist_kernel(const uint2* __restr
 // launch; column prefixes, scan and count in five took 27 us per call at any
 // size below 16k tiles.
 template <int kChunk, int kGroups>
-__global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb, BinGeom G, int64_t cols, BinTotals T) {
+__global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb, BinGeom G, int64_t cols,
+                                                                      BinTotals T) {
     __shared__ uint32_t part[kGroups][kChunk];
     __shared__ uint64_t wsum[16];
     constexpr int groups = kGroups;
@@ -697,9 +698,9 @@ __global__ __launch_bounds__(kChunk* kGroups) void bin_offsets_kernel(BinBufs bb
             run += v[k];
         }
     }
-    // the columns' starts within the chunk: the first kChunk threads hold one column each. Summed in 64 bits: 64 columns
-    // of 2^26 pairs are 2^32 entries, and only a total that shows it is refused (the positions are not used then, so
-    // they may be cut to 32).
+    // the columns' starts within the chunk: the first kChunk threads hold one column each. Summed in 64 bits: 64
+    // columns of 2^26 pairs are 2^32 entries, and only a total that shows it is refused (the positions are not used
+    // then, so they may be cut to 32).
     uint64_t inc = 0;
     if (grp == 0) {
         inc = wave_inclusive_scan<uint64_t>(tot);
@@ -743,10 +744,11 @@ constexpr uint32_t kNoPair = 1023u | (1022u << 10);
 // two compactions. Finding each key's owner by binary search, ranking it by
 // masks and storing it to a scattered 4-byte address (the earlier scheme; with
 // several 512-tile segments, ranking by digit ballots) took 192 us for the 44M
-// entries of 6.4M pairs at 90 x 360, 594 us for 16M entries at 180 x 720 and
-// 2,923 us for 345M entries at 360 x 1440; this takes 109, 44 and 1,613 us,
-// bound by instruction issue (at 360 x 1440 the vector unit is busy 61% of the
-// cycles, the scalar unit 51%; HBM writes are twice the lists' bytes, 1.4 TB/s).
+// entries of 6.4M pairs at 90 x 360, 594 us for 15M entries at 180 x 720 and
+// 2,923 us for 345M entries at 360 x 1440; this takes 102, 45 and 1,650 us,
+// bound by instruction issue (at 360 x 1440 721M vector instructions, 71% of the
+// cycles, and 688M scalar ones; 2.29 GB of HBM writes, 1.7 times the lists'
+// bytes, at 1.4 TB/s).
 template <bool kMix, bool kWrap>
 __global__ __launch_bounds__(64 * kPlaceWaves) void bin_place_kernel(const uint2* __restrict__ rect,
                                                                      const uint32_t* __restrict__ count, BinGeom G,
