@@ -1,7 +1,7 @@
 """Per-tile lists by binning against the full 64-bit sort of the same records
 (bitwise): every form of grid the binning takes, around the sizes at which its
-blocks, waves and lists change (64-pair chunks, 256- to 4096-pair blocks, rows
-dealt over 1 to 8 waves, segments of 8 columns), with a periodic azimuth and
+blocks, waves and lists change (64-pair chunks, 256- to 2048-pair blocks, rows
+dealt over 1 to 12 waves, segments of 8 columns), with a periodic azimuth and
 with 8 x 8 tiles; and the culled-pair counts of both paths."""
 import numpy as np
 import pytest
