@@ -856,7 +856,10 @@ swf_status Ctx::render(Workspace& w, int sid, const float* tx, int B, int flags,
             return fail(SWF_E_INVALID, "SWF_KEEP_AUX (the backward) needs the scene's own grid");
     }
     hipSetDevice(device);
-    const uint64_t spec_cap = speculate && key_cap == 0 && w.vals.cap >= 16 + 4 * 4096 ? (w.vals.cap - 16) / 4 : 0;
+    // the list buffer is larger than what it was sized for, maybe beyond what a launch sequence takes
+    const uint64_t spec_cap = speculate && key_cap == 0 && w.vals.cap >= 16 + 4 * 4096
+                                  ? std::min<uint64_t>((w.vals.cap - 16) / 4, max_list_entries)
+                                  : 0;
     bool spec = false;
     // a render whose state the backward will need keeps its records and lists in the workspace, and the hidden
     // activations, stored by the MLP kernel (what the backward's GEMMs take)

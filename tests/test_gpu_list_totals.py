@@ -36,3 +36,29 @@ def test_more_than_2_to_the_32_entries_are_refused():
         np.testing.assert_array_equal(ctx.render(sid, None, flags=B.NO_DEFORM, batch=1).cpu().numpy(), want)
     finally:
         ctx.close()
+
+
+def test_the_list_limit_is_on_the_entries_not_on_the_buffer():
+    """A list buffer is a quarter larger than what it was sized for, so after a
+    render near the context's limit it holds more than that: the next render of
+    the same query, sized by the buffer, has as many entries as the first."""
+    from paper_2506_12787_amd import binding as B
+    n, H, W = 3000, 90, 360  # 138 tiles: past the 2^18 entries up to which no count is waited for
+    g = synth.gaussians(n, H, W, seed=8, scale_range=(0.5, 12.0))
+    free = B.Context(0)
+    sid = free.upload_scene(g, H, W)
+    want = free.render(sid, None, flags=B.NO_DEFORM, batch=1).cpu().numpy()
+    entries = free.device_status()["list_entries"]
+    free.close()
+    assert entries > 4096
+    tight = B.Context(0, max_list_entries=entries)
+    sid = tight.upload_scene(g, H, W)
+    for _ in range(3):
+        np.testing.assert_array_equal(tight.render(sid, None, flags=B.NO_DEFORM, batch=1).cpu().numpy(), want)
+    tight.close()
+    short = B.Context(0, max_list_entries=entries - 1)
+    sid = short.upload_scene(g, H, W)
+    for _ in range(2):
+        with pytest.raises(B.SwfError, match="more list entries"):
+            short.render(sid, None, flags=B.NO_DEFORM, batch=1)
+    short.close()
